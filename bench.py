@@ -10,9 +10,11 @@ projected SVD, GCV and the HKT solution (Algorithm 4).
 One step = one HKT time to solution on the plain FP64 path: problem
 creation from nodes already in HBM (assembly of the stored FP64 matrix),
 the solve from f, g in HBM to the coefficients in HBM, and the release of
-the problem.  value = GKB matvec throughput of that step: the 2 ell products
-stream the stored matrix (53.0 GB of tiles, its symmetric blocks stored
-once), so value = 2 ell x 53.0 GB / time to solution.  The roofline object
+the problem.  value = GKB matvec throughput of that step in bytes of matrix
+entries: 2 ell x 53.0 GB / time to solution, 53.0 GB being the entries of A
+with its symmetric blocks counted once and its mixed blocks whole (the unit
+of all this benchmark's values; the library streams 40.1 GB a product, one
+value per pair of nodes, so value is not an HBM rate).  The roofline object
 describes the dominant product kernel, timed with HIP events on the
 problem's stream around every product launch of the timed steps.
 
@@ -64,9 +66,15 @@ PROFILES = os.path.join(ROOT, "profiles", "hbm_traffic.json")
 
 
 def stored_bytes(n: int, n_int: int) -> int:
-    """Bytes of the stored matrix as the library keeps it: 128 x 128 FP64 tiles per class
-    (interior, boundary), the symmetric interior-interior and boundary-boundary blocks by
-    their upper tiles only."""
+    """Bytes of the stored matrix as the library keeps it and every product streams it:
+    128 x 128 FP64 tiles of one value per unordered pair of nodes (tile indices per class)."""
+    nt = -(-n_int // TILE) + (-(-(n - n_int) // TILE))
+    return nt * (nt + 1) // 2 * TILE * TILE * 8
+
+
+def entry_bytes(n: int, n_int: int) -> int:
+    """Bytes of the entries of A in the same tiles, the symmetric interior-interior and
+    boundary-boundary blocks counted once and both mixed blocks whole: the unit of value."""
     nti = -(-n_int // TILE)
     nt = nti + (-(-(n - n_int) // TILE))
     tiles = sum((nt - r) if r < nti else (nti + nt - r) for r in range(nt))
@@ -679,11 +687,10 @@ def cpu_baseline(p, target_s: float):
     entries = 2.0 * rows * p.n
     per_product_s = dt / entries * p.n * p.n
     hkt_s = 2 * p.ell * per_product_s
-    sb = stored_bytes(p.n, p.n_int)
-    return dict(value=2 * p.ell * sb / hkt_s / 1e9, unit="GB/s", cores=O.num_threads(), kind="oracle",
+    return dict(value=2 * p.ell * entry_bytes(p.n, p.n_int) / hkt_s / 1e9, unit="GB/s", cores=O.num_threads(), kind="oracle",
                 sample=f"{rows} rows of A x and {rows} columns of A^T x at the benchmark workload (entry-by-entry "
                        f"FP64, {entries:.2e} entries, {dt:.1f} s), scaled to the 2 ell products of the HKT solve; "
-                       "value = 2 ell x stored-matrix bytes / extrapolated solve time (the headline's unit)",
+                       "value = 2 ell x matrix-entry bytes / extrapolated solve time (the headline's unit)",
                 seconds=dt, hkt_solve_s_extrapolated=hkt_s, cpu_model=cpu_info(),
                 omp_num_threads=os.environ.get("OMP_NUM_THREADS", "unset"), nproc=os.cpu_count())
 
@@ -757,7 +764,7 @@ def main():
     head = run_timed(mq, torch, p, d, "stored_fp64", hkw, args.steps, args.warmup, "headline stored_fp64")
     sb = stored_bytes(n, p.n_int)
     ms = head["time_to_solution_s"] * 1000.0
-    value = 2.0 * head["ell_done"] * sb / head["time_to_solution_s"] / 1e9
+    value = 2.0 * head["ell_done"] * entry_bytes(n, p.n_int) / head["time_to_solution_s"] / 1e9
     k_at, k_a = head["kernel_ms_AT"], head["kernel_ms_A"]
     dom_at = k_at >= k_a
     dom_ms = k_at if dom_at else k_a
@@ -767,8 +774,8 @@ def main():
                 traffic=measured_traffic(kern), kernel=kern, kernel_ms=dom_ms,
                 other_kernel=("k_packed_product<0>" if dom_at else "k_packed_product<1>"),
                 other_kernel_ms=min(k_at, k_a), other_frac=sb / (min(k_at, k_a) * 1e-3) / 1e9 / HBM_PEAK_GBS,
-                bytes_per_launch=sb, bytes_note="the stored tiles (128 x 128 FP64; symmetric blocks once) one "
-                                                "product streams; per-launch partial sums (< 1%) not counted",
+                bytes_per_launch=sb, bytes_note="the stored tiles (128 x 128 FP64; one value per pair of "
+                                                "nodes) one product streams; per-launch partial sums (< 1%) not counted",
                 measured_read_peak=peaks["hbm_read_GBs"], frac_of_measured_read=achieved / peaks["hbm_read_GBs"])
 
     # context variants at the same workload: errors against the FP64 result
@@ -842,7 +849,7 @@ def main():
                             ell=p.ell, method="HKT", rule="GCV", operator="stored_fp64",
                             step="create from nodes in HBM (tile assembly) + solve from f, g in HBM to coefficients "
                                  "in HBM + release",
-                            value_def="2 ell x stored-matrix bytes (53.0 GB) / time to solution"),
+                            value_def="2 ell x matrix-entry bytes (53.0 GB) / time to solution"),
                 hkt_time_to_solution_s=head["time_to_solution_s"], create_s=head["create_s"],
                 ell_done=head["ell_done"], lam=head["lam"], rel_l2=head["rel_l2"], rel_linf=head["rel_linf"],
                 phase_ms=head["phase_ms"], product_ms=dict(AT=k_at, A=k_a), roofline=roof, peaks_measured=peaks,

@@ -239,14 +239,11 @@ struct mqh_problem {
     int32_t* sym_first = nullptr;
     double* sym_row = nullptr;
     double* sym_col = nullptr;
-    // stored matrix: kTile x kTile tiles with the symmetric blocks stored once
-    // (layout at the stored operator in op_kernels.hip), its tables, and the
-    // product partials (PR per work item, PC per stored tile)
+    // stored matrix: kTile x kTile tiles with one value per unordered pair of
+    // nodes (layout at the stored operator in stored_kernels.hip), its tables,
+    // and the product partials (PR per work item, PC per stored tile)
     double* A = nullptr;
     PackedLayout pk{};
-    int32_t pk_max_row = 0;
-    int64_t pk_tiles = 0;
-    int64_t* pk_tile_base = nullptr;
     int4* pk_items = nullptr;
     int32_t* pk_item_first = nullptr;
     double* PR = nullptr;
@@ -385,29 +382,30 @@ void sorted_layout(const std::vector<double4>& r, int64_t n, int64_t n_int, std:
 }
 
 // Tables of the tiled stored matrix: tile rows (interior tiles first), the
-// first stored tile of each, and the work items of a product (at most
-// kTileChunk consecutive tiles of one tile row).
+// number of stored tiles, and the work items of a product (consecutive tiles
+// of one tile row).  Tiles per item: as many as still leave kTileItems items
+// (four rounds of the 1024 resident workgroups), at most kTileChunk.  With 16
+// everywhere an 1 800-node product ran on 15 workgroups (57 us, now 8) and a
+// 20 000-node one on 1 150, a second round nearly empty; longer items only
+// save partials (1 KB per item against 128 KB per tile).
 struct PackedTables {
-    int32_t nti = 0, nt = 0, max_row = 0;
-    std::vector<int64_t> tile_base;
+    int32_t nti = 0, nt = 0;
+    int64_t tiles = 0;
     std::vector<int4> items;
     std::vector<int32_t> item_first;
 };
+constexpr int64_t kTileItems = 4096;
 
 void packed_tables(int64_t n, int64_t n_int, PackedTables& t) {
     t.nti = (int32_t)((n_int + kTile - 1) / kTile);
     t.nt = t.nti + (int32_t)((n - n_int + kTile - 1) / kTile);
-    t.tile_base.assign((size_t)t.nt + 1, 0);
+    t.tiles = (int64_t)t.nt * (t.nt + 1) / 2;
+    const int32_t chunk = (int32_t)std::min<int64_t>(kTileChunk, std::max<int64_t>(1, t.tiles / kTileItems));
     t.item_first.assign((size_t)t.nt + 1, 0);
     t.items.clear();
-    t.max_row = 0;
     for (int32_t R = 0; R < t.nt; ++R) {
-        const int32_t ntr = R < t.nti ? t.nt - R : t.nti + (t.nt - R);
-        t.max_row = ntr > t.max_row ? ntr : t.max_row;
-        t.tile_base[(size_t)R + 1] = t.tile_base[(size_t)R] + ntr;
         t.item_first[(size_t)R] = (int32_t)t.items.size();
-        for (int32_t p0 = 0; p0 < ntr; p0 += kTileChunk)
-            t.items.push_back(make_int4(R, p0, ntr - p0 < kTileChunk ? ntr - p0 : kTileChunk, 0));
+        for (int32_t C = R; C < t.nt; C += chunk) t.items.push_back(make_int4(R, C, std::min(chunk, t.nt - C), 0));
     }
     t.item_first[(size_t)t.nt] = (int32_t)t.items.size();
 }
@@ -424,7 +422,7 @@ int set_row_scale(mqh_problem* p, int32_t rs) {
     if (rs != 0 && rs != 1) return fail(MQH_EINVAL, "row_scale must be 0 or 1");
     p->rs = rs;
     if (p->mode == MQH_OP_STORED_FP64 && p->A_rs != rs) {
-        launch_assemble_packed(p->X64, p->pk, p->pk_max_row, op_ec(p), p->A, p->stream);
+        launch_assemble_packed(p->X64, p->pk, op_ec(p), p->A, p->stream);
         LAUNCHCHK("assembly");
         p->A_rs = rs;
     }
@@ -508,10 +506,10 @@ int op_product(mqh_problem* p, int trans, const double* x, const double* shift_p
         HIPCHK(hipEventRecord(e0, s));
     }
     if (p->mode == MQH_OP_STORED_FP64) {
-        launch_packed_product(trans, p->A, p->pk, x, p->PR, p->PC, st, s);
+        launch_packed_product(trans, p->A, p->pk, op_ec(p), x, p->PR, p->PC, st, s);
         LAUNCHCHK("stored product");
         if (timed) HIPCHK(hipEventRecord(e1, s));
-        launch_packed_reduce(trans, p->pk, p->PR, p->PC, shift_ptr, shift_val, z, y, st, s);
+        launch_packed_reduce(p->pk, p->PR, p->PC, shift_ptr, shift_val, z, y, st, s);
         LAUNCHCHK("stored product reduction");
         return MQH_OK;
     }
@@ -1836,7 +1834,6 @@ int mqh_problem_destroy(mqh_problem* p) {
     dfree(p->sym_row);
     dfree(p->sym_col);
     dfree(p->A);
-    dfree(p->pk_tile_base);
     dfree(p->pk_items);
     dfree(p->pk_item_first);
     dfree(p->PR);
@@ -2023,13 +2020,10 @@ int mqh_problem_create(const double* x_int, int64_t n_int, const double* x_bnd, 
     if (op_mode == MQH_OP_STORED_FP64) {
         PackedTables t;
         packed_tables(n, n_int, t);
-        p->pk_max_row = t.max_row;
-        p->pk_tiles = t.tile_base[(size_t)t.nt];
-        if ((rc = dalloc(&p->pk_tile_base, t.tile_base.size())) || (rc = dalloc(&p->pk_items, t.items.size())) ||
-            (rc = dalloc(&p->pk_item_first, t.item_first.size())) ||
+        if ((rc = dalloc(&p->pk_items, t.items.size())) || (rc = dalloc(&p->pk_item_first, t.item_first.size())) ||
             (rc = dalloc(&p->PR, t.items.size() * (size_t)kTile)) ||
-            (rc = dalloc(&p->PC, (size_t)p->pk_tiles * (size_t)kTile)) ||
-            (rc = dalloc(&p->A, (size_t)p->pk_tiles * (size_t)kTileElems)))
+            (rc = dalloc(&p->PC, (size_t)t.tiles * (size_t)kTile)) ||
+            (rc = dalloc(&p->A, (size_t)t.tiles * (size_t)kTileElems)))
             return bail(rc);
         p->pk.n = n;
         p->pk.n_int = n_int;
@@ -2037,17 +2031,14 @@ int mqh_problem_create(const double* x_int, int64_t n_int, const double* x_bnd, 
         p->pk.nt = t.nt;
         p->pk.nitems = (int32_t)t.items.size();
         p->pk.pad = 0;
-        p->pk.tile_base = p->pk_tile_base;
         p->pk.items = p->pk_items;
         p->pk.item_first = p->pk_item_first;
-        if ((e = hipMemcpyAsync(p->pk_tile_base, t.tile_base.data(), t.tile_base.size() * sizeof(int64_t),
-                                hipMemcpyHostToDevice, p->stream)) ||
-            (e = hipMemcpyAsync(p->pk_items, t.items.data(), t.items.size() * sizeof(int4), hipMemcpyHostToDevice,
+        if ((e = hipMemcpyAsync(p->pk_items, t.items.data(), t.items.size() * sizeof(int4), hipMemcpyHostToDevice,
                                 p->stream)) ||
             (e = hipMemcpyAsync(p->pk_item_first, t.item_first.data(), t.item_first.size() * sizeof(int32_t),
                                 hipMemcpyHostToDevice, p->stream)))
             return bail(hip_fail(e, "upload of the tile tables"));
-        launch_assemble_packed(p->X64, p->pk, p->pk_max_row, p->ec, p->A, p->stream);
+        launch_assemble_packed(p->X64, p->pk, p->ec, p->A, p->stream);
         if ((e = hipGetLastError())) return bail(hip_fail(e, "assembly launch"));
         // the tables must stay alive until the copies have run
         if ((e = hipStreamSynchronize(p->stream))) return bail(hip_fail(e, "assembly"));
@@ -2088,7 +2079,7 @@ int mqh_matrix_rows(mqh_problem* p, int64_t row0, int64_t count, double* out, ui
         double* dst = dev ? out + (r - row0) * p->n : tmp;
         hipError_t e;
         if (p->mode == MQH_OP_STORED_FP64) {
-            launch_packed_rows(p->A, p->pk, r, c, dst, p->stream);
+            launch_packed_rows(p->A, p->pk, op_ec(p), r, c, dst, p->stream);
             e = hipGetLastError();
         } else {
             launch_gen_rows(p->mode == MQH_OP_MATFREE_FP64 ? 64 : 32,

@@ -9,26 +9,25 @@
 namespace mqh {
 
 // ---------------------------------------------------------------------------
-// Stored FP64 operator in symmetric-block tiles.
+// Stored FP64 operator: one value per unordered pair of nodes, in tiles.
 //
-// The interior-interior block of A (L phi rows against interior centres) and
-// the boundary-boundary block (phi rows against boundary centres) are
-// symmetric, since their entries depend on |X_i - X_j| only.  Node indices are
-// cut into tiles of kTile per class (interior tiles 0 .. nti-1, boundary tiles
-// nti .. nt-1, each class zero-padded to whole tiles), and A is stored as
-// kTile x kTile tiles, row-major inside a tile:
-//   interior tile row R: tiles (R, C) for C = R .. nt-1   (upper part of the
-//                        interior block, then the interior-boundary block);
-//   boundary tile row R: tiles (R, C) for C = 0 .. nti-1, then C = R .. nt-1
-//                        (boundary-interior block, upper part of the
-//                        boundary block).
-// Tile rows follow each other (tile_base[R] = first tile of row R).  A tile
-// below the diagonal of a symmetric block is the transpose of a stored one.
-// A product visits every stored tile once and uses it as T x_C for y_R (row
-// use) and/or T^T x_R for y_C (column use):
-//   A x:    row use everywhere; column use for off-diagonal symmetric tiles;
-//   A^T x:  row use for symmetric tiles; column use for every tile off the
-//           diagonal (the mixed tiles enter A^T transposed).
+// A_ij and A_ji are functions of the same distance |X_i - X_j|, so one stored
+// value serves both.  Node indices are cut into tiles of kTile per class
+// (interior tiles 0 .. nti-1, boundary tiles nti .. nt-1, each class padded to
+// whole tiles), and the tiles (R, C) with C >= R are stored, kTile x kTile,
+// row-major inside a tile, tile row after tile row:
+//   both interior:  L phi (= A_ij = A_ji);
+//   both boundary:  phi   (= A_ij = A_ji);
+//   mixed (R interior, C boundary): phi = A_ji; the product forms
+//                   A_ij = L phi from it (lphi_of_phi).
+// A product visits every stored tile once, as T x_C for y_R (row use) and, off
+// the diagonal, as T^T x_R for y_C (column use).  On a mixed tile A x takes L phi
+// for the rows and phi for the columns, A^T x the other way round.
+// The product is bound by HBM, and the mixed blocks' second copy was a
+// quarter of its bytes at 20% boundary nodes: 100 000 nodes 53.0 -> 40.1 GB,
+// A^T x 8.60 -> 6.46 ms (6.2 TB/s either way); 20 000 nodes 2.27 -> 1.63 GB,
+// 375 -> 268 us.  Forming L phi costs 8 FP64 instructions and one v_rcp_f64 per
+// mixed entry, under the streaming time (about 49 FP64 issue slots per value).
 // ---------------------------------------------------------------------------
 
 // Dense row-major A (n rows, leading dimension lda, zero columns past n), for
@@ -68,63 +67,69 @@ __device__ __forceinline__ int64_t pk_start(const PackedLayout& L, int T) {
     return T < L.nti ? (int64_t)T * kTile : L.n_int + (int64_t)(T - L.nti) * kTile;
 }
 __device__ __forceinline__ int64_t pk_end(const PackedLayout& L, int T) { return T < L.nti ? L.n_int : L.n; }
-// column tile of position p in tile row R, and the position of tile (R, C)
-__device__ __forceinline__ int pk_col(const PackedLayout& L, int R, int p) {
-    return R < L.nti ? R + p : (p < L.nti ? p : R + (p - L.nti));
-}
-__device__ __forceinline__ int pk_pos(const PackedLayout& L, int R, int C) {
-    return R < L.nti ? C - R : (C < L.nti ? C : L.nti + (C - R));
+// index of stored tile (R, C), C >= R
+__device__ __forceinline__ int64_t pk_tile(const PackedLayout& L, int R, int C) {
+    return (int64_t)R * L.nt - (int64_t)R * (R - 1) / 2 + (C - R);
 }
 
-// A[tile (R, C)][i][j] = A(node R_i, node C_j): one workgroup per stored tile
-// (blockIdx.y = R, blockIdx.x = position in the row), four rows at a time,
-// two columns per lane, 16-byte non-temporal stores; padding rows and
-// columns are zero.
+// L phi from phi = sqrt(t) >= 1: s = 1 / phi from the hardware estimate e (relative
+// error below 2^-22) and one third-order step e (1 + d + d^2), d = 1 - phi e (the
+// dropped terms are below 2^-66), then the interior formula with t = phi^2.
+__device__ __forceinline__ double lphi_of_phi(double q, const EntryConst& c) {
+    const double e = __builtin_amdgcn_rcp(q);
+    const double d = fma(-q, e, 1.0);
+    const double s = fma(e, fma(d, d, d), e);
+    return fma(c.e2, s * s, fma(c.k2, q * q, c.e2x2)) * s;
+}
+
+// The stored value of pair (node R_i, node C_j) in tile (blockIdx.y = R, C = R +
+// blockIdx.x): one workgroup per stored tile, four rows at a time, two columns
+// per lane, 16-byte non-temporal stores.  Padding rows and columns hold zero,
+// in mixed tiles one (they multiply zeros of x, and lphi_of_phi stays finite).
 __global__ __launch_bounds__(kBlock) void k_assemble_packed(const double4* __restrict__ X, PackedLayout L,
                                                             EntryConst c, double* __restrict__ A) {
-    const int R = blockIdx.y, p = blockIdx.x;
-    const int ntr = R < L.nti ? L.nt - R : L.nti + (L.nt - R);
-    if (p >= ntr) return;  // whole workgroup; no barriers in this kernel
-    const int C = pk_col(L, R, p);
+    const int R = blockIdx.y, C = R + (int)blockIdx.x;
+    if (C >= L.nt) return;  // whole workgroup; no barriers in this kernel
     const int64_t r0 = pk_start(L, R), rend = pk_end(L, R);
     const int64_t c0 = pk_start(L, C), cend = pk_end(L, C);
-    const bool interior = R < L.nti;
+    const bool lphi = C < L.nti;
+    const double pad = R < L.nti && C >= L.nti ? 1.0 : 0.0;
     const int lane2 = 2 * (threadIdx.x & (kWave - 1));
     const int64_t ja = c0 + lane2, jb = ja + 1;
     const bool va = ja < cend, vb = jb < cend;
     const double4 qa = X[va ? ja : 0];
     const double4 qb = X[vb ? jb : 0];
-    double* T = A + (L.tile_base[R] + p) * kTileElems + lane2;
+    double* T = A + pk_tile(L, R, C) * kTileElems + lane2;
     for (int i = threadIdx.x / kWave; i < kTile; i += kBlock / kWave) {
         const int64_t g = r0 + i;
         v2d v;
-        v.x = 0.0;
-        v.y = 0.0;
+        v.x = pad;
+        v.y = pad;
         if (g < rend) {
             const double4 q = X[g];
             const double ta = t_of(q.x, q.y, q.z, qa.x, qa.y, qa.z);
             const double tb = t_of(q.x, q.y, q.z, qb.x, qb.y, qb.z);
-            const double ea = interior ? entry_interior(ta, c) : entry_boundary(ta, c);
-            const double eb = interior ? entry_interior(tb, c) : entry_boundary(tb, c);
-            v.x = va ? ea : 0.0;
-            v.y = vb ? eb : 0.0;
+            const double ea = lphi ? entry_interior(ta, c) : entry_boundary(ta, c);
+            const double eb = lphi ? entry_interior(tb, c) : entry_boundary(tb, c);
+            v.x = va ? ea : pad;
+            v.y = vb ? eb : pad;
         }
         store_nt(T + (int64_t)i * kTile, v);
     }
 }
 
-// One work item = up to kTileChunk consecutive tiles of one tile row R, all
-// four waves on the same tile at once (wave w: rows 32 w .. 32 w + 31, lane
-// l: columns 2l, 2l+1, 1 KB per wave load, so a workgroup reads 32 KB runs),
-// the next 8-row group's loads always in flight.  Column use: per-lane sums
-// over the wave's rows, added over the waves through LDS, one partial per
-// tile, PC[tile index][0 .. kTile).  Row use: the per-lane products of 8 rows
-// go through LDS and are summed by groups of 8 lanes (no per-row wave
-// reduction); one partial per item, PR[item][0 .. kTile).
+// One work item = consecutive tiles of one tile row R, all four waves on the
+// same tile at once (wave w: rows 32 w .. 32 w + 31, lane l: columns 2l, 2l+1,
+// 1 KB per wave load, so a workgroup reads 32 KB runs), the next 8-row group's
+// loads always in flight.  Column use: per-lane sums over the wave's rows, added
+// over the waves through LDS, one partial per tile, PC[tile index][0 .. kTile).
+// Row use: the per-lane products of 8 rows go through LDS and are summed by
+// groups of 8 lanes (no per-row wave reduction); one partial per item,
+// PR[item][0 .. kTile).
 template <int TRANS>
 __global__ __launch_bounds__(kBlock) void k_packed_product(const double* __restrict__ A, PackedLayout L,
-                                                           const double* __restrict__ x, double* __restrict__ PR,
-                                                           double* __restrict__ PC,
+                                                           EntryConst ec, const double* __restrict__ x,
+                                                           double* __restrict__ PR, double* __restrict__ PC,
                                                            const GkbState* __restrict__ st) {
     if (st != nullptr && st->stopped) return;  // uniform over the grid
     constexpr int GR = 8;
@@ -138,10 +143,11 @@ __global__ __launch_bounds__(kBlock) void k_packed_product(const double* __restr
     __shared__ double red[kWaves][kRed];
     __shared__ double csum[2][kWaves][kTile];  // double-buffered: one barrier per tile
     const int4 it = L.items[blockIdx.x];
-    const int R = it.x, p0 = it.y, cnt = it.z;
+    const int R = it.x, C0 = it.y, cnt = it.z;
     const int tid = threadIdx.x, lane = tid & (kWave - 1), w = tid / kWave;
     const int total = cnt * kGpw;
-    const double* A0 = A + (L.tile_base[R] + p0) * kTileElems + (int64_t)(w * kRows) * kTile + 2 * lane;
+    const int64_t tile0 = pk_tile(L, R, C0);
+    const double* A0 = A + tile0 * kTileElems + (int64_t)(w * kRows) * kTile + 2 * lane;
     auto gptr = [&](int G) { return A0 + (G / kGpw) * kTileElems + (int64_t)(GR * (G % kGpw)) * kTile; };
     v2d a0[GR], a1[GR];
     {
@@ -157,21 +163,16 @@ __global__ __launch_bounds__(kBlock) void k_packed_product(const double* __restr
     __syncthreads();
     double* buf = red[w];
     const int rq = lane / kLpr, qq = lane % kLpr;
-    bool use_row = false, use_col = false;
+    bool use_col = false, mixed = false;
     double xc0 = 0.0, xc1 = 0.0, cs0 = 0.0, cs1 = 0.0;
-    int64_t tix = 0;
     auto setup = [&](int q) {
-        const int p = p0 + q;
-        const int C = pk_col(L, R, p);
-        const bool sym = (R < L.nti) == (C < L.nti);
-        const bool diag = C == R;
-        use_row = TRANS ? sym : true;
-        use_col = TRANS ? !diag : (sym && !diag);
+        const int C = C0 + q;
+        use_col = C != R;
+        mixed = R < L.nti && C >= L.nti;
         const int64_t c0 = pk_start(L, C), cend = pk_end(L, C);
         const int64_t ca = c0 + 2 * lane, cb = ca + 1;
         xc0 = ca < cend ? x[ca] : 0.0;
         xc1 = cb < cend ? x[cb] : 0.0;
-        tix = L.tile_base[R] + p;
         cs0 = 0.0;
         cs1 = 0.0;
     };
@@ -189,37 +190,46 @@ __global__ __launch_bounds__(kBlock) void k_packed_product(const double* __restr
             double sm = cb[tid];
 #pragma unroll
             for (int v = 1; v < kWaves; ++v) sm += cb[v * kTile + tid];
-            PC[tix * kTile + tid] = sm;
+            PC[(tile0 + q) * kTile + tid] = sm;
         }
     };
     auto group = [&](int g, const v2d* a) {  // g: group of this wave within the tile
         const int rbase = w * kRows + GR * g;
         double rp[GR];
+        if (mixed) {
 #pragma unroll
-        for (int r = 0; r < GR; ++r) {
-            if (use_col) {
+            for (int r = 0; r < GR; ++r) {
+                const double l0 = lphi_of_phi(a[r].x, ec), l1 = lphi_of_phi(a[r].y, ec);
                 const double xi = xr[rbase + r];
-                cs0 = fma(a[r].x, xi, cs0);
-                cs1 = fma(a[r].y, xi, cs1);
+                cs0 = fma(TRANS ? l0 : a[r].x, xi, cs0);
+                cs1 = fma(TRANS ? l1 : a[r].y, xi, cs1);
+                rp[r] = TRANS ? fma(a[r].y, xc1, a[r].x * xc0) : fma(l1, xc1, l0 * xc0);
             }
-            rp[r] = fma(a[r].y, xc1, a[r].x * xc0);
+        } else {
+#pragma unroll
+            for (int r = 0; r < GR; ++r) {
+                if (use_col) {
+                    const double xi = xr[rbase + r];
+                    cs0 = fma(a[r].x, xi, cs0);
+                    cs1 = fma(a[r].y, xi, cs1);
+                }
+                rp[r] = fma(a[r].y, xc1, a[r].x * xc0);
+            }
         }
-        if (use_row) {
 #pragma unroll
-            for (int r = 0; r < GR; ++r) buf[r * (kWave + 1) + lane] = rp[r];
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
-            double sm = 0.0;
+        for (int r = 0; r < GR; ++r) buf[r * (kWave + 1) + lane] = rp[r];
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
+        double sm = 0.0;
 #pragma unroll
-            for (int k = 0; k < GR; ++k) sm += buf[rq * (kWave + 1) + qq * GR + k];
+        for (int k = 0; k < GR; ++k) sm += buf[rq * (kWave + 1) + qq * GR + k];
 #pragma unroll
-            for (int o = 1; o < kLpr; o <<= 1) sm += __shfl_xor(sm, o, kWave);
-            if (qq == 0) rsum[rbase + rq] += sm;
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
-        }
+        for (int o = 1; o < kLpr; o <<= 1) sm += __shfl_xor(sm, o, kWave);
+        if (qq == 0) rsum[rbase + rq] += sm;
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
     };
     for (int G = 0; G < total; G += 2) {  // kGpw is even: G and G + 1 in the same tile
         {
@@ -242,52 +252,36 @@ __global__ __launch_bounds__(kBlock) void k_packed_product(const double* __restr
 }
 
 // y_X = sum over the items of tile row X (row use, item order) + sum over the
-// tiles (R, X) with a column use (R ascending) - shift z; one workgroup per
-// output tile X, four groups of kTile threads taking every fourth source,
-// combined in group order.
-template <int TRANS>
-__global__ __launch_bounds__(4 * kTile) void k_packed_reduce(PackedLayout L, const double* __restrict__ PR,
-                                                             const double* __restrict__ PC,
-                                                             const double* __restrict__ shift_ptr, double shift_val,
-                                                             const double* __restrict__ z, double* __restrict__ y,
-                                                             const GkbState* __restrict__ st) {
+// tiles (R, X), R < X (column use, R ascending) - shift z; one workgroup per
+// output tile X, kRedGroups groups of kTile threads taking every
+// kRedGroups-th source, combined in group order.  Bound by the latency of the
+// strided 1 KB reads: eight groups with eight loads in flight each instead of
+// four with four (20 000 nodes 20 -> 7.6 us, 100 000 nodes 157 -> 80 us).
+constexpr int kRedGroups = 8;
+
+__global__ __launch_bounds__(kRedGroups * kTile) void k_packed_reduce(PackedLayout L, const double* __restrict__ PR,
+                                                                      const double* __restrict__ PC,
+                                                                      const double* __restrict__ shift_ptr,
+                                                                      double shift_val, const double* __restrict__ z,
+                                                                      double* __restrict__ y,
+                                                                      const GkbState* __restrict__ st) {
     if (st != nullptr && st->stopped) return;
-    __shared__ double part[4][kTile];
+    __shared__ double part[kRedGroups][kTile];
     const int X = blockIdx.x;
     const int t = threadIdx.x & (kTile - 1), grp = threadIdx.x / kTile;
     const int i0 = L.item_first[X], nrow = L.item_first[X + 1] - i0;
-    // sources of the column use: R in [a0, a1) and then [b0, b1)
-    int a0, a1, b0 = 0, b1 = 0;
-    if (X < L.nti) {
-        a0 = 0;
-        a1 = X;
-        if (TRANS) {
-            b0 = L.nti;
-            b1 = L.nt;
-        }
-    } else {
-        a0 = TRANS ? 0 : L.nti;
-        a1 = X;
-    }
-    const int na = a1 - a0;
-    const int total = nrow + na + (b1 - b0);
+    const int total = nrow + X;
     double s = 0.0;
-#pragma unroll 4
-    for (int k = grp; k < total; k += 4) {
-        const double* src;
-        if (k < nrow) {
-            src = PR + (int64_t)(i0 + k) * kTile;
-        } else {
-            const int c = k - nrow;
-            const int Rs = c < na ? a0 + c : b0 + (c - na);
-            src = PC + (L.tile_base[Rs] + pk_pos(L, Rs, X)) * kTile;
-        }
+#pragma unroll 8
+    for (int k = grp; k < total; k += kRedGroups) {
+        const double* src = k < nrow ? PR + (int64_t)(i0 + k) * kTile : PC + pk_tile(L, k - nrow, X) * kTile;
         s += src[t];
     }
     part[grp][t] = s;
     __syncthreads();
     if (grp == 0) {
-        s = (part[0][t] + part[1][t]) + (part[2][t] + part[3][t]);
+        s = ((part[0][t] + part[1][t]) + (part[2][t] + part[3][t])) +
+            ((part[4][t] + part[5][t]) + (part[6][t] + part[7][t]));
         const int64_t o = pk_start(L, X) + t;
         if (o < pk_end(L, X)) {
             if (z != nullptr) {
@@ -300,10 +294,10 @@ __global__ __launch_bounds__(4 * kTile) void k_packed_reduce(PackedLayout L, con
 }
 
 // Rows [row0, row0 + gridDim.y) of the stored tiled matrix, row-major with
-// leading dimension n (an entry below the diagonal of a symmetric block is
-// read from the transposed stored tile).
-__global__ __launch_bounds__(kBlock) void k_packed_rows(const double* __restrict__ A, PackedLayout L, int64_t row0,
-                                                        double* __restrict__ out) {
+// leading dimension n (an entry below the diagonal is read from the transposed
+// stored tile; an interior row's boundary column is formed as the products do).
+__global__ __launch_bounds__(kBlock) void k_packed_rows(const double* __restrict__ A, PackedLayout L, EntryConst ec,
+                                                        int64_t row0, double* __restrict__ out) {
     const int64_t j = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     const int64_t i = row0 + blockIdx.y;
     if (j >= L.n) return;
@@ -311,12 +305,9 @@ __global__ __launch_bounds__(kBlock) void k_packed_rows(const double* __restrict
     const int ir = (int)(i - pk_start(L, R));
     const int C = j < L.n_int ? (int)(j / kTile) : L.nti + (int)((j - L.n_int) / kTile);
     const int jc = (int)(j - pk_start(L, C));
-    const bool sym = (R < L.nti) == (C < L.nti);
-    double v;
-    if (sym && C < R)
-        v = A[(L.tile_base[C] + pk_pos(L, C, R)) * kTileElems + (int64_t)jc * kTile + ir];
-    else
-        v = A[(L.tile_base[R] + pk_pos(L, R, C)) * kTileElems + (int64_t)ir * kTile + jc];
+    double v = C < R ? A[pk_tile(L, C, R) * kTileElems + (int64_t)jc * kTile + ir]
+                     : A[pk_tile(L, R, C) * kTileElems + (int64_t)ir * kTile + jc];
+    if (R < L.nti && C >= L.nti) v = lphi_of_phi(v, ec);
     out[(int64_t)blockIdx.y * L.n + j] = v;
 }
 
@@ -327,33 +318,27 @@ void launch_assemble(const double4* X, int64_t n, int64_t n_int, int64_t lda, co
     k_assemble<RB><<<grid, kBlock, 0, s>>>(X, n, n_int, lda, c, A);
 }
 
-void launch_assemble_packed(const double4* X, const PackedLayout& L, int32_t max_row_tiles, const EntryConst& c,
-                            double* A, hipStream_t s) {
-    dim3 grid((unsigned)max_row_tiles, (unsigned)L.nt);
-    k_assemble_packed<<<grid, kBlock, 0, s>>>(X, L, c, A);
+void launch_assemble_packed(const double4* X, const PackedLayout& L, const EntryConst& c, double* A, hipStream_t s) {
+    k_assemble_packed<<<dim3((unsigned)L.nt, (unsigned)L.nt), kBlock, 0, s>>>(X, L, c, A);
 }
 
-void launch_packed_product(int trans, const double* A, const PackedLayout& L, const double* x, double* PR, double* PC,
-                           const GkbState* st, hipStream_t s) {
+void launch_packed_product(int trans, const double* A, const PackedLayout& L, const EntryConst& c, const double* x,
+                           double* PR, double* PC, const GkbState* st, hipStream_t s) {
     if (trans)
-        k_packed_product<1><<<(unsigned)L.nitems, kBlock, 0, s>>>(A, L, x, PR, PC, st);
+        k_packed_product<1><<<(unsigned)L.nitems, kBlock, 0, s>>>(A, L, c, x, PR, PC, st);
     else
-        k_packed_product<0><<<(unsigned)L.nitems, kBlock, 0, s>>>(A, L, x, PR, PC, st);
+        k_packed_product<0><<<(unsigned)L.nitems, kBlock, 0, s>>>(A, L, c, x, PR, PC, st);
 }
 
-void launch_packed_reduce(int trans, const PackedLayout& L, const double* PR, const double* PC,
-                          const double* shift_ptr, double shift_val, const double* z, double* y, const GkbState* st,
-                          hipStream_t s) {
-    if (trans)
-        k_packed_reduce<1><<<(unsigned)L.nt, 4 * kTile, 0, s>>>(L, PR, PC, shift_ptr, shift_val, z, y, st);
-    else
-        k_packed_reduce<0><<<(unsigned)L.nt, 4 * kTile, 0, s>>>(L, PR, PC, shift_ptr, shift_val, z, y, st);
+void launch_packed_reduce(const PackedLayout& L, const double* PR, const double* PC, const double* shift_ptr,
+                          double shift_val, const double* z, double* y, const GkbState* st, hipStream_t s) {
+    k_packed_reduce<<<(unsigned)L.nt, kRedGroups * kTile, 0, s>>>(L, PR, PC, shift_ptr, shift_val, z, y, st);
 }
 
-void launch_packed_rows(const double* A, const PackedLayout& L, int64_t row0, int64_t count, double* out,
-                        hipStream_t s) {
+void launch_packed_rows(const double* A, const PackedLayout& L, const EntryConst& c, int64_t row0, int64_t count,
+                        double* out, hipStream_t s) {
     dim3 grid((unsigned)((L.n + kBlock - 1) / kBlock), (unsigned)count);
-    k_packed_rows<<<grid, kBlock, 0, s>>>(A, L, row0, out);
+    k_packed_rows<<<grid, kBlock, 0, s>>>(A, L, c, row0, out);
 }
 
 }  // namespace mqh

@@ -98,6 +98,27 @@ def test_products(mq, orc, name, make, mode):
             assert np.all(np.abs(y2 - (ref - 0.75 * z)) <= tol * scale2)
 
 
+@pytest.mark.parametrize("n_int,n_bnd", [(1, 1), (127, 129), (128, 128), (257, 1), (130, 0), (0, 131), (1300, 500)])
+@pytest.mark.parametrize("row_scale", [0, 1])
+def test_stored_pair_values(mq, orc, n_int, n_bnd, row_scale):
+    """Stored tiles hold one value per pair of nodes: rows and both products at tile edges and with an
+    empty class (the interior row's mixed entries are formed from phi)."""
+    nodes = I.random_nodes_cube(n_int + n_bnd, 77)
+    xi, xb = (nodes[:n_int] if n_int else None), (nodes[n_int:] if n_bnd else None)
+    kappa, eps = 7.0, 2.5
+    A = orc.assemble(nodes, n_int, kappa, eps)
+    A[:n_int] *= 1.0 / (3 * eps * eps + kappa * kappa) if row_scale else 1.0
+    x, z = I.random_vector(n_int + n_bnd, 3), I.random_vector(n_int + n_bnd, 4)
+    with mq.Problem(xi, xb, kappa, eps, "stored_fp64") as pr:
+        say("stored pairs", n_int, n_bnd, row_scale)
+        R = pr.matrix_rows(0, pr.n, row_scale=row_scale)
+        ys = [pr.apply(x, trans=t, shift=0.5, z=z, row_scale=row_scale) for t in (False, True)]
+    # the interior row's mixed entry adds the rounding of phi and of its reciprocal: about 8 eps
+    assert np.all(np.abs(R - A) <= 4e-15 * np.abs(A))
+    for y, M in zip(ys, (A, A.T)):
+        assert np.all(np.abs(y - (M @ x - 0.5 * z)) <= 1e-13 * (np.abs(M) @ np.abs(x) + np.abs(z)))
+
+
 def test_products_device_pointers(mq, orc):
     import torch
 
