@@ -222,15 +222,13 @@ struct mqh_problem {
     double4* X64 = nullptr;
     float4* X32 = nullptr;
     // FP32-evaluated products: nodes in Morton order within each class (FP32
-    // records), perm[q] = original index of sorted node q, one frame centre
-    // per block of kMfmFixed sorted nodes, and the weight-folded coefficients
-    // of the current product in the sorted order
+    // records, the product's weights in .w), perm[q] = original index of sorted
+    // node q, and one frame centre per block of kMfmFixed sorted nodes
     float4* XS = nullptr;
     double4* XS64 = nullptr;  // FP64 pair products: sorted coordinates, the product's weights in .w
     int32_t* perm = nullptr;
     int32_t* iperm = nullptr;  // iperm[perm[q]] = q
     float4* frames = nullptr;
-    float4* cf = nullptr;
     double blk_tmax = 1.0;  // bound on t = 1 + |P - Q|^2 over node pairs (the block products' entry scale)
     // the single-vector FP32 products over unordered node pairs: work items,
     // their tables, and the row / column partials of a product
@@ -438,36 +436,52 @@ int scale_rhs(mqh_problem* p, double* x, int nz, int64_t stride) {
     return MQH_OK;
 }
 
-// One product y = op(A) x - shift z on device vectors (x, z of length ldn,
-// zero-padded).  shift from *shift_ptr when non-null.
-// Work items of the pair products (SymLayout): blocks of kMfmFixed sorted
-// nodes per class; super-rows of F fixed blocks and segments of Lb loop
-// blocks, the largest (F, Lb) that still gives enough items to fill the GPU;
-// first[k] indexes the items in (super-row, segment) order, the list itself
-// is in launch order.
-void sym_tables(int64_t n, int64_t n_int, SymLayout& L, std::vector<int2>& items, std::vector<int32_t>& first) {
-    L = SymLayout{};
-    L.n = n;
-    L.n_int = n_int;
-    L.nb_int = (int32_t)((n_int + kMfmFixed - 1) / kMfmFixed);
-    L.nb = L.nb_int + (int32_t)((n - n_int + kMfmFixed - 1) / kMfmFixed);
-    static const int shapes[][2] = {{8, 14}, {4, 8}, {2, 4}, {1, 2}};
-    for (const auto& sh : shapes) {
+// Blocks of column partials of a pair product: one per block and super-row up
+// to its own.
+int64_t sym_col_blocks(const SymLayout& L) {
+    const int64_t k = L.nb / L.F;  // whole super-rows before the last, partial one
+    return (int64_t)L.F * (k * (k + 1) / 2) + (L.nb - k * L.F) * (k + 1);
+}
+
+// Work items of the pair products (SymLayout): blocks of blk sorted nodes per
+// class; super-rows of F fixed blocks and segments of Lb loop blocks; first[k]
+// indexes the items in (super-row, segment) order, the list itself is in
+// launch order.  A larger item writes fewer partials and sets up fewer fixed
+// blocks; too few items leave a round of resident workgroups nearly empty.
+// FP32 form: the largest shape with 1200 items (its FP32 sums follow the shape).
+// FP64 form (768 workgroups of 128-node blocks resident): the largest shape with
+// 3000 items; below that 1 x 2 blocks of 128 nodes, and with fewer of those
+// than CUs blocks of 64.  Whole products, us: 20 000 nodes 174 with (1, 4), 178
+// (2, 4), 230 (4, 8), 462 (8, 14); 70 000 nodes 1645 (4, 8), 1659 (1, 4), 1769
+// (8, 14); 1 800 nodes 32 with blocks of 64, 37 with 128.
+void sym_tables(int64_t n, int64_t n_int, bool fp64, SymLayout& L, std::vector<int2>& items,
+                std::vector<int32_t>& first) {
+    struct Shape {
+        int blk, F, Lb, want;
+    };
+    static const Shape shapes32[] = {{128, 8, 14, 1200}, {128, 4, 8, 1200}, {128, 2, 4, 1200}, {128, 1, 2, 0}};
+    static const Shape shapes64[] = {{128, 8, 14, 3000}, {128, 4, 8, 3000}, {128, 2, 8, 3000}, {128, 2, 4, 3000},
+                                     {128, 1, 4, 3000},  {128, 1, 2, 256},  {64, 1, 2, 0}};
+    for (const Shape* sh = fp64 ? shapes64 : shapes32;; ++sh) {
+        L = SymLayout{};
+        L.n = n;
+        L.n_int = n_int;
+        L.blk = sh->blk;
+        L.F = sh->F;
+        L.Lb = sh->Lb;
+        L.nb_int = (int32_t)((n_int + L.blk - 1) / L.blk);
+        L.nb = L.nb_int + (int32_t)((n - n_int + L.blk - 1) / L.blk);
         items.clear();
         first.clear();
-        const int F = sh[0], Lb = sh[1];
-        const int nsr = (L.nb + F - 1) / F;
-        for (int k = 0; k < nsr; ++k) {
+        L.nsr = (L.nb + L.F - 1) / L.F;
+        for (int k = 0; k < L.nsr; ++k) {
             first.push_back((int32_t)items.size());
-            const int nseg = (L.nb - k * F + Lb - 1) / Lb;
+            const int nseg = (L.nb - k * L.F + L.Lb - 1) / L.Lb;
             for (int sg = 0; sg < nseg; ++sg) items.push_back(make_int2(k, sg));
         }
         first.push_back((int32_t)items.size());
-        L.F = F;
-        L.Lb = Lb;
-        L.nsr = nsr;
         L.nitems = (int32_t)items.size();
-        if (L.nitems >= 1200) break;
+        if (L.nitems >= sh->want) break;
     }
     // launch order: items by their number of block pairs, largest first
     // (stable), so the last workgroups to start are the short ones
@@ -481,13 +495,17 @@ void sym_tables(int64_t n, int64_t n_int, SymLayout& L, std::vector<int2>& items
     std::stable_sort(items.begin(), items.end(), [&](const int2& a, const int2& b) { return pairs(a) > pairs(b); });
 }
 
+// One product y = op(A) x - shift z on device vectors (x, z of length ldn,
+// zero-padded).  shift from *shift_ptr when non-null.  staged: the sorted
+// records already hold x as their weights (written by the normalisation that
+// produced x).
 int op_product(mqh_problem* p, int trans, const double* x, const double* shift_ptr, double shift_val, const double* z,
-               double* y, const GkbState* st, bool timed) {
+               double* y, const GkbState* st, bool timed, bool staged = false) {
     hipStream_t s = p->stream;
-    if (p->mode == MQH_OP_MATFREE_FP32) {
-        // x into the sorted node order, folded into the entry coefficients
-        // (outside the timed span)
-        launch_gather_coef(x, p->perm, p->n, op_ec(p), p->cf, st, s);
+    if (staged) {
+    } else if (p->mode == MQH_OP_MATFREE_FP32) {
+        // x into the sorted node order (outside the timed span)
+        launch_gather_w32(x, p->perm, p->n, p->XS, st, s);
         LAUNCHCHK("gather");
     } else if (p->mode == MQH_OP_MATFREE_FP64) {
         launch_gather_w64(x, p->perm, p->n, p->XS64, st, s);
@@ -514,7 +532,7 @@ int op_product(mqh_problem* p, int trans, const double* x, const double* shift_p
         return MQH_OK;
     }
     if (p->mode == MQH_OP_MATFREE_FP32) {
-        launch_mfs_product(trans, p->XS, p->frames, p->cf, p->sym, op_ec(p), p->sym_row, p->sym_col, st, s);
+        launch_mfs_product(trans, p->XS, p->frames, p->sym, op_ec(p), p->sym_row, p->sym_col, st, s);
         LAUNCHCHK("pair product");
         if (timed) HIPCHK(hipEventRecord(e1, s));
         launch_mfs_reduce(p->sym, p->sym_row, p->sym_col, p->perm, shift_ptr, shift_val, z, y, st, s);
@@ -571,32 +589,27 @@ int run_gkb(mqh_problem* p, int32_t ell, int32_t reorth, bool timed, int32_t j0 
     hipStream_t s = p->stream;
     const int64_t n = p->n, ldn = p->ldn;
     const int nbq = sumsq_blocks(n);
-    const int nbu = update_blocks(n);
     if (j1 < 0) j1 = ell;
+    // every normalised vector is the next product's operand: the matrix-free
+    // forms get it in their sorted records with the normalisation
+    const SortedOut so{p->iperm, nullptr, p->XS, p->XS64};
+    const bool staged = p->mode != MQH_OP_STORED_FP64;
     if (j0 == 0) {
         launch_init_state(p->st, ell, p->alpha, p->beta, s);
         LAUNCHCHK("init state");
         launch_sumsq_partial(p->vx, n, p->npart, nbq, p->st, s);
-        launch_finalize_scale(p->npart, nbq, 0, 0, n, p->alpha, p->beta, p->st, p->vx, p->W, s);
+        launch_finalize_scale_b(p->npart, nbq, 0, 0, n, p->alpha, p->beta, p->st, p->vx, p->W, so, 1, Bz{}, s);
         LAUNCHCHK("initial normalisation");
     }
     auto orthonormalize = [&](double* v, const double* V, int32_t m, int kind, int32_t j, double* dst) -> int {
         int nparts;
         if (reorth && m > 0) {
-            launch_gemvt(V, ldn, n, m, v, p->gpart, p->cvec, p->st, s);
-            if (m <= kFusedCgsMaxCols) {
-                launch_update_gemvt(V, ldn, n, m, p->cvec, v, p->gpart, p->st, s);
-            } else {
-                launch_update(V, ldn, n, m, p->cvec, v, nullptr, p->st, s);
-                launch_gemvt(V, ldn, n, m, v, p->gpart, p->cvec, p->st, s);
-            }
-            launch_update(V, ldn, n, m, p->cvec, v, p->npart, p->st, s);
-            nparts = nbu;
+            nparts = launch_cgs2(V, ldn, n, m, v, p->gpart, p->cvec, p->npart, p->st, 1, CgsStrides{}, s);
         } else {
             launch_sumsq_partial(v, n, p->npart, nbq, p->st, s);
             nparts = nbq;
         }
-        launch_finalize_scale(p->npart, nparts, kind, j, n, p->alpha, p->beta, p->st, v, dst, s);
+        launch_finalize_scale_b(p->npart, nparts, kind, j, n, p->alpha, p->beta, p->st, v, dst, so, 1, Bz{}, s);
         LAUNCHCHK("reorthogonalisation / normalisation");
         return MQH_OK;
     };
@@ -606,11 +619,11 @@ int run_gkb(mqh_problem* p, int32_t ell, int32_t reorth, bool timed, int32_t j0 
         double* Zj = p->Z + (int64_t)j * ldn;
         // r = A^T w_j - beta_j z_{j-1}
         if ((rc = op_product(p, 1, Wj, p->beta + j, 0.0, j > 0 ? p->Z + (int64_t)(j - 1) * ldn : nullptr, p->vy,
-                             p->st, timed)))
+                             p->st, timed, staged)))
             return rc;
         if ((rc = orthonormalize(p->vy, p->Z, j, 1, j, Zj))) return rc;
         // p = A z_j - alpha_j w_j
-        if ((rc = op_product(p, 0, Zj, p->alpha + j, 0.0, Wj, p->vy, p->st, timed))) return rc;
+        if ((rc = op_product(p, 0, Zj, p->alpha + j, 0.0, Wj, p->vy, p->st, timed, staged))) return rc;
         if ((rc = orthonormalize(p->vy, p->W, j + 1, 2, j, p->W + (int64_t)(j + 1) * ldn))) return rc;
     }
     return MQH_OK;
@@ -758,7 +771,7 @@ int ensure_multi(mqh_problem* p, int nz, int32_t ell) {
     w.vstr = (int64_t)lc + 2;
     w.bstr = cols * ldn;
     w.gstr = cgs_partial_doubles(n, cols);
-    w.nstr = update_blocks(n) > 1024 ? update_blocks(n) : 1024;
+    w.nstr = std::max(fused_cgs_blocks(n), 1024);
     const size_t Z = (size_t)zc;
     int rc;
     if ((rc = dalloc(&w.W, Z * (size_t)w.bstr)) || (rc = dalloc(&w.Z, Z * (size_t)w.bstr)) ||
@@ -871,37 +884,27 @@ int run_gkb_multi(mqh_problem* p, int nz, int32_t ell, int32_t reorth, bool time
     hipStream_t s = p->stream;
     const int64_t n = p->n, ldn = p->ldn;
     const int nbq = sumsq_blocks(n);
-    const int nbu = update_blocks(n);
     launch_init_state_b(w.st, ell, w.alpha, w.beta, nz, Bz{w.vstr, w.vstr}, s);
     LAUNCHCHK("init state");
     // block products read their operand from w.Vg, which the normalisation
     // writes (columns past nz stay zero)
     const bool blk = p->mode == MQH_OP_MATFREE_FP32 && nz >= 2;
-    const int32_t* ip = blk ? p->iperm : nullptr;
-    float* vg = blk ? w.Vg : nullptr;
+    const SortedOut so{p->iperm, blk ? w.Vg : nullptr, nullptr, nullptr};
     if (blk) launch_fill_f32(w.Vg, n * kBlkRhs, 0.f, s);
     launch_sumsq_partial_b(w.X, n, w.npart, nbq, w.st, nz, Bz{ldn, w.nstr}, s);
-    launch_finalize_scale_b(w.npart, nbq, 0, 0, n, w.alpha, w.beta, w.st, w.X, w.W, ip, vg, nz,
+    launch_finalize_scale_b(w.npart, nbq, 0, 0, n, w.alpha, w.beta, w.st, w.X, w.W, so, nz,
                             Bz{w.nstr, w.vstr, ldn, w.bstr}, s);
     LAUNCHCHK("initial normalisation");
     auto orthonormalize = [&](const double* V, int32_t m, int kind, int32_t j, double* dst) -> int {
         int nparts;
         if (reorth && m > 0) {
-            const Bz ub{w.bstr, w.vstr, ldn, w.nstr};
-            launch_gemvt_b(V, ldn, n, m, w.Y, w.gpart, w.cvec, w.st, nz, w.bstr, ldn, w.gstr, w.vstr, s);
-            if (m <= kFusedCgsMaxCols) {
-                launch_update_gemvt_b(V, ldn, n, m, w.cvec, w.Y, w.gpart, w.st, nz, w.bstr, w.vstr, ldn, w.gstr, s);
-            } else {
-                launch_update_b(V, ldn, n, m, w.cvec, w.Y, nullptr, w.st, nz, ub, s);
-                launch_gemvt_b(V, ldn, n, m, w.Y, w.gpart, w.cvec, w.st, nz, w.bstr, ldn, w.gstr, w.vstr, s);
-            }
-            launch_update_b(V, ldn, n, m, w.cvec, w.Y, w.npart, w.st, nz, ub, s);
-            nparts = nbu;
+            nparts = launch_cgs2(V, ldn, n, m, w.Y, w.gpart, w.cvec, w.npart, w.st, nz,
+                                 CgsStrides{w.bstr, ldn, w.gstr, w.vstr, w.nstr}, s);
         } else {
             launch_sumsq_partial_b(w.Y, n, w.npart, nbq, w.st, nz, Bz{ldn, w.nstr}, s);
             nparts = nbq;
         }
-        launch_finalize_scale_b(w.npart, nparts, kind, j, n, w.alpha, w.beta, w.st, w.Y, dst, ip, vg, nz,
+        launch_finalize_scale_b(w.npart, nparts, kind, j, n, w.alpha, w.beta, w.st, w.Y, dst, so, nz,
                                 Bz{w.nstr, w.vstr, ldn, w.bstr}, s);
         LAUNCHCHK("reorthogonalisation / normalisation");
         return MQH_OK;
@@ -1828,7 +1831,6 @@ int mqh_problem_destroy(mqh_problem* p) {
     dfree(p->perm);
     dfree(p->iperm);
     dfree(p->frames);
-    dfree(p->cf);
     dfree(p->sym_items);
     dfree(p->sym_first);
     dfree(p->sym_row);
@@ -1947,7 +1949,7 @@ int mqh_problem_create(const double* x_int, int64_t n_int, const double* x_bnd, 
     if ((rc = dalloc(&p->vy, (size_t)p->ldn))) return bail(rc);
     if ((rc = dalloc(&p->vz, (size_t)p->ldn))) return bail(rc);
     if ((rc = dalloc(&p->st, 1))) return bail(rc);
-    if ((rc = dalloc(&p->npart, (size_t)(update_blocks(n) > 1024 ? update_blocks(n) : 1024)))) return bail(rc);
+    if ((rc = dalloc(&p->npart, (size_t)std::max(fused_cgs_blocks(n), 1024)))) return bail(rc);
     if ((rc = dalloc(&p->pout, 1))) return bail(rc);
     if ((rc = dalloc(&p->svd_status, 1))) return bail(rc);
     if ((rc = dalloc(&p->coef, (size_t)p->ldn))) return bail(rc);
@@ -1986,9 +1988,7 @@ int mqh_problem_create(const double* x_int, int64_t n_int, const double* x_bnd, 
                 m2 = r2 > m2 ? r2 : m2;
             }
             p->blk_tmax = (1.0 + 4.0 * m2) * (1.0 + 1e-3);
-            if ((rc = dalloc(&p->XS, (size_t)n)) || (rc = dalloc(&p->frames, frames.size())) ||
-                (rc = dalloc(&p->cf, (size_t)n)))
-                return bail(rc);
+            if ((rc = dalloc(&p->XS, (size_t)n)) || (rc = dalloc(&p->frames, frames.size()))) return bail(rc);
             if ((e = hipMemcpyAsync(p->XS, rs.data(), (size_t)n * sizeof(float4), hipMemcpyHostToDevice,
                                     p->stream)) ||
                 (e = hipMemcpyAsync(p->frames, frames.data(), frames.size() * sizeof(float4), hipMemcpyHostToDevice,
@@ -2003,10 +2003,10 @@ int mqh_problem_create(const double* x_int, int64_t n_int, const double* x_bnd, 
         if ((e = hipStreamSynchronize(p->stream))) return bail(hip_fail(e, "upload of the sorted layout"));
         std::vector<int2> items;
         std::vector<int32_t> first;
-        sym_tables(n, n_int, p->sym, items, first);
+        sym_tables(n, n_int, op_mode == MQH_OP_MATFREE_FP64, p->sym, items, first);
         if ((rc = dalloc(&p->sym_items, items.size())) || (rc = dalloc(&p->sym_first, first.size())) ||
-            (rc = dalloc(&p->sym_row, items.size() * (size_t)p->sym.F * kMfmFixed)) ||
-            (rc = dalloc(&p->sym_col, items.size() * (size_t)p->sym.Lb * kMfmFixed)))
+            (rc = dalloc(&p->sym_row, items.size() * (size_t)(p->sym.F * p->sym.blk))) ||
+            (rc = dalloc(&p->sym_col, (size_t)sym_col_blocks(p->sym) * (size_t)p->sym.blk)))
             return bail(rc);
         if ((e = hipMemcpyAsync(p->sym_items, items.data(), items.size() * sizeof(int2), hipMemcpyHostToDevice,
                                 p->stream)) ||

@@ -86,15 +86,16 @@ __global__ __launch_bounds__(kBlock) void k_sumsq_partial(const double* __restri
 // reduction), so all blocks hold the same norm and take the same decision
 // from the same state: the snapshot (snap_stopped, snap_scale) that the
 // kernel producing the partials wrote, which no block of this launch writes;
-// block 0 records the decision in stopped, scale and the scalars.  With Vg, the
-// normalised vector also goes, in FP32, to column z of the sorted
-// block-product operand, Vg[iperm[i]][z] (zeros for a stopped run).
+// block 0 records the decision in stopped, scale and the scalars.  The
+// normalised vector also goes to the products' sorted operands that so names:
+// in FP32 to column z of the block products' Vg[iperm[i]][z] (zeros for a
+// stopped run), to the weights xs32[iperm[i]].w or xs64[iperm[i]].w of the pair
+// products (one run), which saves the gather launch before each product.
 __global__ __launch_bounds__(kBlock) void k_finalize_scale(const double* __restrict__ partial, int nparts, int kind,
                                                            int32_t j, int64_t n, double* __restrict__ alpha,
                                                            double* __restrict__ beta, GkbState* __restrict__ st,
                                                            const double* __restrict__ x, double* __restrict__ dst,
-                                                           const int32_t* __restrict__ iperm, float* __restrict__ Vg,
-                                                           Bz bz) {
+                                                           SortedOut so, Bz bz) {
     __shared__ double lds[kBlock / kWave];
     __shared__ int s_stopped;
     const int64_t z = blockIdx.y;  // batch: partial + z bz.a, alpha, beta + z bz.b, x + z bz.c, dst + z bz.d, state z
@@ -108,7 +109,7 @@ __global__ __launch_bounds__(kBlock) void k_finalize_scale(const double* __restr
     if (threadIdx.x == 0) s_stopped = st->snap_stopped;
     __syncthreads();
     if (s_stopped) {  // block-uniform
-        if (Vg != nullptr && i < n) Vg[(int64_t)iperm[i] * kBlkRhs + z] = 0.f;
+        if (so.Vg != nullptr && i < n) so.Vg[(int64_t)so.iperm[i] * kBlkRhs + z] = 0.f;
         return;
     }
     double s = 0.0;
@@ -152,12 +153,14 @@ __global__ __launch_bounds__(kBlock) void k_finalize_scale(const double* __restr
     }
     if (i >= n) return;
     if (!ok) {
-        if (Vg != nullptr) Vg[(int64_t)iperm[i] * kBlkRhs + z] = 0.f;
+        if (so.Vg != nullptr) so.Vg[(int64_t)so.iperm[i] * kBlkRhs + z] = 0.f;
         return;
     }
     const double d = x[i] / nrm;
     dst[i] = d;
-    if (Vg != nullptr) Vg[(int64_t)iperm[i] * kBlkRhs + z] = (float)d;
+    if (so.Vg != nullptr) so.Vg[(int64_t)so.iperm[i] * kBlkRhs + z] = (float)d;
+    if (so.xs32 != nullptr) so.xs32[so.iperm[i]].w = (float)d;
+    if (so.xs64 != nullptr) so.xs64[so.iperm[i]].w = d;
 }
 
 // ---------------------------------------------------------------------------
@@ -256,6 +259,59 @@ __global__ __launch_bounds__(kBlock) void k_gemvt_reduce(const double* __restric
     if (lane == 0) c[k] = s;
 }
 
+// The coefficients c_k = sum_b p[b m + k], b < nb, k < m <= kFusedCgsMaxCols, by
+// kBlock threads: thread t takes column t % m and the blocks b = t / m,
+// t / m + G, ..., G = kBlock / m groups but at most 16 (coef_group_sum), whose
+// sums are added in group order (coef_of_groups).  A consumer's workgroups form them from the
+// partials in place of a k_gemvt_reduce launch (a launch costs 2.5 us at least).
+static_assert(kFusedCgsMaxCols <= kBlock, "one thread per column at least");
+
+__device__ __forceinline__ int coef_groups(int32_t m) { return kBlock / m < 16 ? kBlock / m : 16; }
+__device__ __forceinline__ void coef_group_sum(const double* __restrict__ p, int nb, int32_t m, int t,
+                                               double* __restrict__ sums) {
+    const int groups = coef_groups(m);
+    const int k = t % m, g = t / m;
+    if (g >= groups) return;
+    double s = 0.0;
+#pragma unroll 8
+    for (int b = g; b < nb; b += groups) s += p[(int64_t)b * m + k];
+    sums[t] = s;
+}
+__device__ __forceinline__ double coef_of_groups(const double* __restrict__ sums, int32_t m, int k) {
+    const int groups = coef_groups(m);
+    double s = sums[k];
+    for (int q = 1; q < groups; ++q) s += sums[q * m + k];
+    return s;
+}
+
+// The same coefficients, sums in the same order, by a launch of its own where
+// the consumer has too many workgroups for each to form them: kCoefCols columns
+// per workgroup, one thread per column and group.
+constexpr int kCoefCols = kBlock / 16;
+
+__global__ __launch_bounds__(kBlock) void k_coef(const double* __restrict__ partial, int nb, int32_t m,
+                                                 double* __restrict__ c, const GkbState* __restrict__ st, Bz bz) {
+    __shared__ double sums[16][kCoefCols];
+    const int64_t z = blockIdx.y;  // batch: partial + z bz.a, c + z bz.b, state z
+    partial += z * bz.a;
+    c += z * bz.b;
+    if (st != nullptr && st[z].stopped) return;
+    const int q = threadIdx.x % kCoefCols, g = threadIdx.x / kCoefCols;
+    const int k = (int)blockIdx.x * kCoefCols + q, groups = coef_groups(m);
+    if (g < groups && k < m) {
+        double s = 0.0;
+#pragma unroll 8
+        for (int b = g; b < nb; b += groups) s += partial[(int64_t)b * m + k];
+        sums[g][q] = s;
+    }
+    __syncthreads();
+    if (g == 0 && k < m) {
+        double s = sums[0][q];
+        for (int h = 1; h < groups; ++h) s += sums[h][q];
+        c[k] = s;
+    }
+}
+
 // x_i -= sum_k V[k][i] c_k for the kUpdRows rows of block b; optionally
 // partial[b] = sum over the block of the updated x_i^2.  Lane l of every wave
 // owns the block's rows 2l, 2l + 1 (16-byte loads, 1 KB per wave load); wave
@@ -323,7 +379,8 @@ __global__ __launch_bounds__(kBlock) void k_update(const double* __restrict__ V,
 // The middle of classical Gram-Schmidt applied twice in one pass over V:
 // x -= V c (the first pass's update), then partial[k * nb + b] = sum over the
 // kFuRows rows of block b of V[k][i] x_i for the updated x (the second
-// pass's projection coefficients, reduced by k_gemvt_reduce).  The block's
+// pass's projection coefficients, reduced by k_gemvt_reduce).  RED: c from the
+// nb1 partials p1 of the first projection.  The block's
 // rows of V[:, 0:m] come from HBM once and stay in LDS (m x kFuLd doubles of
 // dynamic shared memory) between the two, so CGS2 reads the basis three
 // times instead of four.  Thread t takes the row pair 2 (t % 16), + 1 and
@@ -340,18 +397,25 @@ constexpr int kFuLd = kFuRows + 1;             // padded LDS row of the tile
 constexpr int kFuPairs = kFuRows / 2;
 constexpr int kFuGroups = kBlock / kFuPairs;   // 16
 static_assert(kFuGroups * kFuPairs == kBlock, "fused CGS2 tile layout");
-static_assert(kFusedCgsMaxCols * kFuLd * 8 + (kFuGroups + 1) * kFuRows * 8 <= 65536, "fused CGS2 LDS within 64 KB");
+static_assert(kFusedCgsMaxCols * kFuLd * 8 + (kFuGroups + 1) * kFuRows * 8 + kFusedCgsMaxCols * 8 <= 65536,
+              "fused CGS2 LDS within 64 KB");
+static_assert(kFuGroups * kFuRows >= kBlock, "the coefficient sums fit the row sums' LDS");
 
+template <bool RED>
 __global__ __launch_bounds__(kBlock) void k_update_gemvt(const double* __restrict__ V, int64_t ldn, int64_t n,
                                                          int32_t m, const double* __restrict__ c,
-                                                         double* __restrict__ x, double* __restrict__ partial,
-                                                         int nb, const GkbState* __restrict__ st, Bz bz) {
+                                                         const double* __restrict__ p1, int nb1,
+                                                         double* __restrict__ x, double* __restrict__ partial, int nb,
+                                                         const GkbState* __restrict__ st, Bz bz) {
     extern __shared__ double tile[];  // [m][kFuLd]
     __shared__ double part[kFuGroups][kFuRows];
     __shared__ double xs[kFuRows];
-    const int64_t z = blockIdx.z;  // batch: V + z bz.a, c + z bz.b, x + z bz.c, partial + z bz.d, state z
+    __shared__ double cs[RED ? kFusedCgsMaxCols : 1];
+    // batch: V + z bz.a, c + z bz.b, x + z bz.c, partial and p1 + z bz.d, state z
+    const int64_t z = blockIdx.z;
     V += z * bz.a;
     c += z * bz.b;
+    p1 += z * bz.d;
     x += z * bz.c;
     partial += z * bz.d;
     if (st != nullptr) st += z;
@@ -359,6 +423,13 @@ __global__ __launch_bounds__(kBlock) void k_update_gemvt(const double* __restric
     const int per = (nb + 7) / 8;
     const int b = (int)(blockIdx.x % 8) * per + (int)(blockIdx.x / 8);
     if (b >= nb) return;  // uniform over the workgroup
+    if (RED) {
+        coef_group_sum(p1, nb1, m, threadIdx.x, &part[0][0]);
+        __syncthreads();
+        if ((int)threadIdx.x < m) cs[threadIdx.x] = coef_of_groups(&part[0][0], m, threadIdx.x);
+        __syncthreads();
+        c = cs;
+    }
     const int t = threadIdx.x, rp = t % kFuPairs, cg = t / kFuPairs;
     const int64_t i0 = (int64_t)b * kFuRows + 2 * rp;
     const double* v = V + (i0 < n ? i0 : 0);
@@ -410,6 +481,105 @@ __global__ __launch_bounds__(kBlock) void k_update_gemvt(const double* __restric
 #pragma unroll
         for (int i = 0; i < kFuRows; ++i) acc = fma(r[i], xs[i], acc);
         partial[(int64_t)kk * nb + b] = acc;
+    }
+}
+
+// The fused kernels of small problems (launch_cgs2's rule): one workgroup of
+// 512 threads per kFuRows rows.  Half the threads bring the rows of V[:, 0:m]
+// into LDS while the other half sums the projection coefficients from the nb1
+// partials p1 (layout b m + k), so the two latencies overlap and no reduction
+// is launched (RED; else it takes them from c); then x -= V c.  NORM false (first pass): out[b m + k] = the second
+// projection's partials; true (second pass): out[b] = the block's sum of
+// squares, and the state's snapshot for the normalisation.  These kernels are
+// bound by their launch and one memory latency: at 1 800 nodes and up to 60
+// columns 4.4 + 5.0 us, against 3.8 + 4.3 + two reductions of 2.5.
+constexpr int kSmThreads = 512;
+constexpr int kSmGroups = kSmThreads / kFuPairs;  // 32
+constexpr int kSmMaxCols = 192;
+static_assert(kSmMaxCols * kFuLd * 8 + (kSmGroups + 1) * kFuRows * 8 + kSmMaxCols * 8 <= 65536, "LDS within 64 KB");
+static_assert(kSmThreads == 2 * kBlock && kSmGroups * kFuRows >= kBlock, "two halves; sums fit the row sums' LDS");
+
+template <bool NORM, bool RED>
+__global__ __launch_bounds__(kSmThreads) void k_cgs_small(const double* __restrict__ V, int64_t ldn, int64_t n,
+                                                          int32_t m, const double* __restrict__ c, int64_t cstr,
+                                                          const double* __restrict__ p1, int nb1,
+                                                          double* __restrict__ x, double* __restrict__ out,
+                                                          GkbState* __restrict__ st, Bz bz) {
+    extern __shared__ double tile[];  // [m][kFuLd]
+    __shared__ double part[kSmGroups][kFuRows];
+    __shared__ double xs[kFuRows];
+    __shared__ double cs[kSmMaxCols];
+    // batch: V + z bz.a, p1 + z bz.b, x + z bz.c, out + z bz.d, c + z cstr, state z
+    const int64_t z = blockIdx.z;
+    V += z * bz.a;
+    p1 += z * bz.b;
+    c += z * cstr;
+    x += z * bz.c;
+    out += z * bz.d;
+    st += z;
+    const int b = blockIdx.x, t = threadIdx.x;
+    if (NORM && b == 0 && t == 0) {
+        st->snap_stopped = st->stopped;
+        st->snap_scale = st->scale;
+    }
+    if (st->stopped) return;  // uniform over the grid
+    const int rp = t % kFuPairs;
+    if (t < kBlock) {
+        const int64_t i0 = (int64_t)b * kFuRows + 2 * rp;
+        const double* v = V + (i0 < n ? i0 : 0);  // a pair past n reads rows 0, 1; one that straddles n the zero padding
+        double* tr = tile + 2 * rp;
+#pragma unroll 4
+        for (int k = t / kFuPairs; k < m; k += kBlock / kFuPairs) {
+            const v2d a = load2(v + (int64_t)k * ldn);
+            tr[k * kFuLd] = a.x;
+            tr[k * kFuLd + 1] = a.y;
+        }
+    } else if (RED) {
+        coef_group_sum(p1, nb1, m, t - kBlock, &part[0][0]);
+    } else if (t - kBlock < m) {
+        cs[t - kBlock] = c[t - kBlock];
+    }
+    __syncthreads();
+    if (RED) {
+        if (t < m) cs[t] = coef_of_groups(&part[0][0], m, t);
+        __syncthreads();
+    }
+    double s0 = 0.0, s1 = 0.0;
+    for (int k = t / kFuPairs; k < m; k += kSmGroups) {
+        const double ck = cs[k];
+        s0 = fma(tile[k * kFuLd + 2 * rp], ck, s0);
+        s1 = fma(tile[k * kFuLd + 2 * rp + 1], ck, s1);
+    }
+    part[t / kFuPairs][2 * rp] = s0;
+    part[t / kFuPairs][2 * rp + 1] = s1;
+    __syncthreads();
+    if (t < kWave) {  // one wave: lanes l and l + 32 take half the groups of row l
+        const int row = t % kFuRows, h = t / kFuRows;
+        double sum = 0.0;
+#pragma unroll
+        for (int g = 0; g < kSmGroups / 2; ++g) sum += part[h * (kSmGroups / 2) + g][row];
+        sum += __shfl_xor(sum, kFuRows, kWave);
+        const int64_t i = (int64_t)b * kFuRows + row;
+        double xi = 0.0;
+        if (i < n) {
+            xi = x[i] - sum;
+            if (h == 0) x[i] = xi;
+        }
+        if (NORM) {
+            const double q = wave_sum(h == 0 ? xi * xi : 0.0);
+            if (t == 0) out[b] = q;
+        } else if (h == 0) {
+            xs[row] = xi;
+        }
+    }
+    if (NORM) return;
+    __syncthreads();
+    if (t < m) {
+        const double* r = tile + t * kFuLd;
+        double acc = 0.0;
+#pragma unroll
+        for (int i = 0; i < kFuRows; ++i) acc = fma(r[i], xs[i], acc);
+        out[(int64_t)b * m + t] = acc;
     }
 }
 
@@ -489,60 +659,90 @@ void launch_sumsq_partial_b(const double* x, int64_t n, double* partial, int nb,
     k_sumsq_partial<<<dim3(nb, 1, nz), kBlock, 0, s>>>(x, n, partial, st, bz);
 }
 
-void launch_finalize_scale(const double* partial, int nparts, int kind, int32_t j, int64_t n, double* alpha,
-                           double* beta, GkbState* st, const double* x, double* dst, hipStream_t s) {
-    launch_finalize_scale_b(partial, nparts, kind, j, n, alpha, beta, st, x, dst, nullptr, nullptr, 1, Bz{}, s);
-}
-
 void launch_finalize_scale_b(const double* partial, int nparts, int kind, int32_t j, int64_t n, double* alpha,
-                             double* beta, GkbState* st, const double* x, double* dst, const int32_t* iperm,
-                             float* Vg, int nz, Bz bz, hipStream_t s) {
+                             double* beta, GkbState* st, const double* x, double* dst, const SortedOut& so, int nz,
+                             Bz bz, hipStream_t s) {
     k_finalize_scale<<<dim3((unsigned)((n + kBlock - 1) / kBlock), nz), kBlock, 0, s>>>(
-        partial, nparts, kind, j, n, alpha, beta, st, x, dst, iperm, Vg, bz);
+        partial, nparts, kind, j, n, alpha, beta, st, x, dst, so, bz);
 }
 
 int gemvt_blocks(int64_t n) { return (int)((n + kGtRows - 1) / kGtRows); }
-
-void launch_gemvt(const double* V, int64_t ldn, int64_t n, int32_t m, const double* x, double* partial, double* c,
-                  const GkbState* st, hipStream_t s) {
-    launch_gemvt_b(V, ldn, n, m, x, partial, c, st, 1, 0, 0, 0, 0, s);
-}
-
-void launch_gemvt_b(const double* V, int64_t ldn, int64_t n, int32_t m, const double* x, double* partial, double* c,
-                    const GkbState* st, int nz, int64_t sV, int64_t sx, int64_t sp, int64_t sc, hipStream_t s) {
-    const int nb = gemvt_blocks(n);
-    k_gemvt_partial<<<dim3(nb, (m + kGtCols - 1) / kGtCols, nz), kBlock, 0, s>>>(V, ldn, n, m, x, partial, st,
-                                                                                 Bz{sV, sx, sp, 0});
-    k_gemvt_reduce<<<dim3((m + kBlock / kWave - 1) / (kBlock / kWave), nz), kBlock, 0, s>>>(
-        partial, nb, m, m, 1, c, st, Bz{sp, sc, 0, 0});
-}
-
 int fused_cgs_blocks(int64_t n) { return (int)((n + kFuRows - 1) / kFuRows); }
 
-void launch_update_gemvt_b(const double* V, int64_t ldn, int64_t n, int32_t m, double* c, double* x,
-                           double* partial, const GkbState* st, int nz, int64_t sV, int64_t sc, int64_t sx,
-                           int64_t sp, hipStream_t s) {
-    const int nb = fused_cgs_blocks(n);
+// The small form (k_cgs_small) up to kCgsSmallBlocks row blocks whose second
+// projection leaves at most kCgsSmallParts partials (32 loads a thread to sum
+// them).  The rule looks at n and m only, so a run's sums do not depend on the
+// runs beside it; summing in the consumer or by k_coef gives the same bits.
+constexpr int64_t kCgsSmallParts = 8192, kCgsSmallBlocks = 64;
+// A consumer's workgroups sum the partials themselves while one round of them
+// fits the GPU; with 16 runs of 20 000 nodes (10 300 workgroups) that took 39.5 us
+// against 26.4 + 5.1.  More than kCoefParts partials go through k_gemvt_reduce.
+constexpr int64_t kCoefParts = 8192, kCoefGrid = 1024;
+
+bool cgs_small(int64_t n, int32_t m) {
+    const int64_t nbf = fused_cgs_blocks(n);
+    return m <= kSmMaxCols && nbf <= kCgsSmallBlocks && nbf * m <= kCgsSmallParts;
+}
+
+// x -= V (V^T x) twice, and npart = the block sums of squares of the result;
+// returns their number.  Passes over V: the projection (k_gemvt_partial), the
+// update with the second projection (k_update_gemvt or k_cgs_small; two kernels
+// beyond kFusedCgsMaxCols columns), the second update.
+int launch_cgs2(const double* V, int64_t ldn, int64_t n, int32_t m, double* x, double* part, double* c, double* npart,
+                GkbState* st, int nz, const CgsStrides& b, hipStream_t s) {
+    const int nbg = gemvt_blocks(n), nbf = fused_cgs_blocks(n), nbu = update_blocks(n);
+    const dim3 ggrid((unsigned)nbg, (unsigned)((m + kGtCols - 1) / kGtCols), (unsigned)nz);
+    const dim3 rgrid((unsigned)((m + kBlock / kWave - 1) / (kBlock / kWave)), (unsigned)nz);
+    const dim3 ugrid((unsigned)nbu, 1, (unsigned)nz);
+    const Bz gb{b.V, b.x, b.part, 0}, rb{b.part, b.c, 0, 0}, ub{b.V, b.c, b.x, b.npart};
     const size_t lds = (size_t)m * kFuLd * sizeof(double);
-    k_update_gemvt<<<dim3(8 * ((nb + 7) / 8), 1, nz), kBlock, lds, s>>>(V, ldn, n, m, c, x, partial, nb, st,
-                                                                       Bz{sV, sc, sx, sp});
-    k_gemvt_reduce<<<dim3((m + kBlock / kWave - 1) / (kBlock / kWave), nz), kBlock, 0, s>>>(
-        partial, nb, m, 1, nb, c, st, Bz{sp, sc, 0, 0});
-}
-
-void launch_update_gemvt(const double* V, int64_t ldn, int64_t n, int32_t m, double* c, double* x,
-                         double* partial, const GkbState* st, hipStream_t s) {
-    launch_update_gemvt_b(V, ldn, n, m, c, x, partial, st, 1, 0, 0, 0, 0, s);
-}
-
-void launch_update(const double* V, int64_t ldn, int64_t n, int32_t m, const double* c, double* x,
-                   double* sumsq_partial, GkbState* st, hipStream_t s) {
-    launch_update_b(V, ldn, n, m, c, x, sumsq_partial, st, 1, Bz{}, s);
-}
-
-void launch_update_b(const double* V, int64_t ldn, int64_t n, int32_t m, const double* c, double* x,
-                     double* sumsq_partial, GkbState* st, int nz, Bz bz, hipStream_t s) {
-    k_update<<<dim3((unsigned)update_blocks(n), 1, nz), kBlock, 0, s>>>(V, ldn, n, m, c, x, sumsq_partial, st, bz);
+    // the second projection's partials follow the first's, which workgroups of
+    // a fused kernel may still be reading
+    double* part2 = part + (int64_t)nbg * m;
+    auto project = [&]() { k_gemvt_partial<<<ggrid, kBlock, 0, s>>>(V, ldn, n, m, x, part, st, gb); };
+    auto coef = [&](const double* p, int nb) {
+        k_coef<<<dim3((unsigned)((m + kCoefCols - 1) / kCoefCols), (unsigned)nz), kBlock, 0, s>>>(p, nb, m, c, st, rb);
+    };
+    const bool few = (int64_t)nbf * nz <= kCoefGrid;
+    project();
+    if (cgs_small(n, m)) {
+        const dim3 grid((unsigned)nbf, 1, (unsigned)nz);
+        const Bz b1{b.V, b.part, b.x, b.part}, b2{b.V, b.part, b.x, b.npart};
+        if (few) {
+            k_cgs_small<false, true><<<grid, kSmThreads, lds, s>>>(V, ldn, n, m, c, b.c, part, nbg, x, part2, st, b1);
+            k_cgs_small<true, true><<<grid, kSmThreads, lds, s>>>(V, ldn, n, m, c, b.c, part2, nbf, x, npart, st, b2);
+        } else {
+            coef(part, nbg);
+            k_cgs_small<false, false><<<grid, kSmThreads, lds, s>>>(V, ldn, n, m, c, b.c, part, nbg, x, part2, st, b1);
+            coef(part2, nbf);
+            k_cgs_small<true, false><<<grid, kSmThreads, lds, s>>>(V, ldn, n, m, c, b.c, part2, nbf, x, npart, st, b2);
+        }
+        return nbf;
+    }
+    auto reduce = [&]() {
+        if (m <= kFusedCgsMaxCols && (int64_t)nbg * m <= kCoefParts)
+            coef(part, nbg);
+        else
+            k_gemvt_reduce<<<rgrid, kBlock, 0, s>>>(part, nbg, m, m, 1, c, st, rb);
+    };
+    if (m > kFusedCgsMaxCols) {
+        reduce();
+        k_update<<<ugrid, kBlock, 0, s>>>(V, ldn, n, m, c, x, nullptr, st, ub);
+        project();
+        reduce();
+    } else {
+        const dim3 fgrid((unsigned)(8 * ((nbf + 7) / 8)), 1, (unsigned)nz);
+        const Bz fb{b.V, b.c, b.x, b.part};
+        if ((int64_t)nbg * m <= kCoefParts && few) {
+            k_update_gemvt<true><<<fgrid, kBlock, lds, s>>>(V, ldn, n, m, c, part, nbg, x, part2, nbf, st, fb);
+        } else {
+            reduce();
+            k_update_gemvt<false><<<fgrid, kBlock, lds, s>>>(V, ldn, n, m, c, part, nbg, x, part2, nbf, st, fb);
+        }
+        k_gemvt_reduce<<<rgrid, kBlock, 0, s>>>(part2, nbf, m, 1, nbf, c, st, rb);
+    }
+    k_update<<<ugrid, kBlock, 0, s>>>(V, ldn, n, m, c, x, npart, st, ub);
+    return nbu;
 }
 
 int update_blocks(int64_t n) { return (int)((n + kUpdRows - 1) / kUpdRows); }

@@ -47,14 +47,16 @@ struct PackedLayout {
 // blocks nb_int .. nb-1).  Work item (k, s): fixed blocks [kF, kF + F) (a
 // super-row) against loop blocks [kF + s Lb, kF + (s+1) Lb) (a segment),
 // only pairs of blocks b <= c (b == c: the block's own square, row sums
-// only).  Each item writes F x kMfmFixed row partials and Lb x kMfmFixed
-// column partials; a node's output adds the row partials of its super-row's
-// items and the column partials of the items whose segment holds it.
+// only).  Each item writes F x blk row partials and the column partials of its
+// loop blocks (for each block one from every super-row up to its own); a
+// node's output adds the row partials of its super-row's items and its block's
+// column partials.
 constexpr int kSymMaxF = 8;    // fixed blocks per super-row (at most)
 constexpr int kSymMaxLb = 14;  // loop blocks per segment (at most; the LDS of four workgroups per CU)
 struct SymLayout {
     int64_t n, n_int;
-    int32_t nb_int, nb;         // blocks of kMfmFixed nodes per class, all blocks
+    int32_t nb_int, nb;         // blocks of blk nodes per class, all blocks
+    int32_t blk, pad;           // 128 (FP32 form), 64 or 128 (FP64 form)
     int32_t F, Lb;              // fixed blocks per super-row, loop blocks per segment
     int32_t nsr, nitems;        // super-rows, work items
     const int2* items;          // (super-row, segment) of every item, in launch order (largest first)
@@ -73,12 +75,12 @@ struct ParamOut {
 
 // operator (op_kernels.hip)
 int64_t mfm_blocks(int64_t n, int64_t n_int);
-void launch_gather_coef(const double* x, const int32_t* perm, int64_t n, const EntryConst& c, float4* CF,
-                        const GkbState* st, hipStream_t s);
-void launch_mfs_product(int trans, const float4* XS, const float4* frames, const float4* CF, const SymLayout& L,
-                        const EntryConst& c, double* RowP, double* ColP, const GkbState* st, hipStream_t s);
-// FP64 products over unordered node pairs (same work items and partials as
-// the FP32 form; XS64 sorted coordinates, weights written into .w by the gather)
+// XS / XS64: sorted coordinates, the product's weights in .w (written by the
+// gathers, or by the normalisation that produced the vector)
+void launch_gather_w32(const double* x, const int32_t* perm, int64_t n, float4* XS, const GkbState* st,
+                       hipStream_t s);
+void launch_mfs_product(int trans, const float4* XS, const float4* frames, const SymLayout& L, const EntryConst& c,
+                        double* RowP, double* ColP, const GkbState* st, hipStream_t s);
 void launch_gather_w64(const double* x, const int32_t* perm, int64_t n, double4* XS64, const GkbState* st,
                        hipStream_t s);
 void launch_mfs64_product(int trans, const double4* XS64, const SymLayout& L, const EntryConst& c, double* RowP,
@@ -150,26 +152,23 @@ void launch_fill(double* x, int64_t n, double v, hipStream_t s);
 void launch_scale(double* x, int64_t n, double a, int nz, int64_t stride, hipStream_t s);
 int sumsq_blocks(int64_t n);
 void launch_sumsq_partial(const double* x, int64_t n, double* partial, int nb, GkbState* st, hipStream_t s);
-// norm of x from partial sums of squares, breakdown test, dst = x / norm
-void launch_finalize_scale(const double* partial, int nparts, int kind, int32_t j, int64_t n, double* alpha,
-                           double* beta, GkbState* st, const double* x, double* dst, hipStream_t s);
 int gemvt_blocks(int64_t n);
-// c = V^T x through block partials (gemvt_blocks(n) x m); x -= V c
-void launch_gemvt(const double* V, int64_t ldn, int64_t n, int32_t m, const double* x, double* partial, double* c,
-                  const GkbState* st, hipStream_t s);
 int update_blocks(int64_t n);
-void launch_update(const double* V, int64_t ldn, int64_t n, int32_t m, const double* c, double* x,
-                   double* sumsq_partial, GkbState* st, hipStream_t s);
-// x -= V c, then c = V^T x for the updated x, reading V once (partials:
-// fused_cgs_blocks(n) x m); for m <= kFusedCgsMaxCols (the LDS tile within 64 KB)
-constexpr int kFusedCgsMaxCols = 224;
+constexpr int kFusedCgsMaxCols = 224;  // columns of the fused update and projection (its LDS tile within 64 KB)
 int fused_cgs_blocks(int64_t n);
-void launch_update_gemvt(const double* V, int64_t ldn, int64_t n, int32_t m, double* c, double* x,
-                         double* partial, const GkbState* st, hipStream_t s);
+// Batch strides of launch_cgs2's arguments (nz slices).
+struct CgsStrides {
+    int64_t V = 0, x = 0, part = 0, c = 0, npart = 0;
+};
+// x -= V (V^T x) twice (classical Gram-Schmidt against m orthonormal columns),
+// npart = block sums of squares of the result, whose number is returned (at
+// most fused_cgs_blocks(n)).  part: cgs_partial_doubles(n, m) per slice, c: m
+// per slice.
+int launch_cgs2(const double* V, int64_t ldn, int64_t n, int32_t m, double* x, double* part, double* c, double* npart,
+                GkbState* st, int nz, const CgsStrides& b, hipStream_t s);
 // partial buffers of the reorthogonalisation for n rows and up to cols columns
 inline int64_t cgs_partial_doubles(int64_t n, int64_t cols) {
-    const int64_t b = fused_cgs_blocks(n) > gemvt_blocks(n) ? fused_cgs_blocks(n) : gemvt_blocks(n);
-    return b * cols;
+    return ((int64_t)fused_cgs_blocks(n) + gemvt_blocks(n)) * cols;
 }
 void launch_lift(const double* Z, int64_t ldz, int64_t n, int32_t ell, const int32_t* ell_ptr, const double* y,
                  double* coef, hipStream_t s, int nz = 1, Bz bz = Bz{});
@@ -177,18 +176,18 @@ void launch_lift(const double* Z, int64_t ldz, int64_t n, int32_t ell, const int
 void launch_init_state_b(GkbState* st, int32_t ell, double* alpha, double* beta, int nz, Bz bz, hipStream_t s);
 void launch_sumsq_partial_b(const double* x, int64_t n, double* partial, int nb, GkbState* st, int nz, Bz bz,
                             hipStream_t s);
-// iperm / Vg: also write the normalised vectors into the sorted FP32
-// block-product operand (both NULL: not)
+// Where a normalised vector also goes in the sorted node order (NULL: nowhere):
+// column z of the block products' FP32 operand, the pair products' weights.
+struct SortedOut {
+    const int32_t* iperm;
+    float* Vg;
+    float4* xs32;
+    double4* xs64;
+};
+// norm of x from partial sums of squares, breakdown test, dst = x / norm
 void launch_finalize_scale_b(const double* partial, int nparts, int kind, int32_t j, int64_t n, double* alpha,
-                             double* beta, GkbState* st, const double* x, double* dst, const int32_t* iperm,
-                             float* Vg, int nz, Bz bz, hipStream_t s);
-void launch_gemvt_b(const double* V, int64_t ldn, int64_t n, int32_t m, const double* x, double* partial, double* c,
-                    const GkbState* st, int nz, int64_t sV, int64_t sx, int64_t sp, int64_t sc, hipStream_t s);
-void launch_update_b(const double* V, int64_t ldn, int64_t n, int32_t m, const double* c, double* x,
-                     double* sumsq_partial, GkbState* st, int nz, Bz bz, hipStream_t s);
-void launch_update_gemvt_b(const double* V, int64_t ldn, int64_t n, int32_t m, double* c, double* x,
-                           double* partial, const GkbState* st, int nz, int64_t sV, int64_t sc, int64_t sx,
-                           int64_t sp, hipStream_t s);
+                             double* beta, GkbState* st, const double* x, double* dst, const SortedOut& so, int nz,
+                             Bz bz, hipStream_t s);
 void launch_fill_f32(float* x, int64_t n, float v, hipStream_t s);
 
 // projected SVD (svd_kernels.hip; the QR iteration in proj_kernels.hip).

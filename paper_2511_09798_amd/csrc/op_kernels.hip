@@ -165,17 +165,36 @@ __device__ __forceinline__ v4u loop_terms(float b) {
 // lane groups by a swizzle and stored to LDS, and after the chunk the 8
 // partials of each loop node are added in FP64 and collected in LDS over the
 // item's fixed blocks.  Weights come
-// from CF[q].w (w = x[perm[q]] in FP32).  Work items are launched largest
+// from XS[q].w (w = x[perm[q]] in FP32).  Work items are launched largest
 // first and write their partials at their place in (super-row, segment) order.
 // ---------------------------------------------------------------------------
 
+// B: nodes per block of the layout.
+template <int B = kMfmFixed>
 __device__ __forceinline__ int64_t sym_blk_start(int b, const SymLayout& L) {
-    return b < L.nb_int ? (int64_t)b * kMfmFixed : L.n_int + (int64_t)(b - L.nb_int) * kMfmFixed;
+    return b < L.nb_int ? (int64_t)b * B : L.n_int + (int64_t)(b - L.nb_int) * B;
 }
+template <int B = kMfmFixed>
 __device__ __forceinline__ int64_t sym_blk_end(int b, const SymLayout& L) {
-    const int64_t e = sym_blk_start(b, L) + kMfmFixed;
+    const int64_t e = sym_blk_start<B>(b, L) + B;
     const int64_t lim = b < L.nb_int ? L.n_int : L.n;
     return e < lim ? e : lim;
+}
+
+// Place of block beta's column partials in ColP (in blocks): one from each
+// super-row k <= beta / F, in order of k, block after block.
+__device__ __forceinline__ int64_t sym_col_base(int beta, int F) {
+    const int64_t k = beta / F;
+    return (int64_t)F * (k * (k + 1) / 2) + (beta - k * F) * (k + 1);
+}
+
+// Sum of a row's 16 lane partials by four neighbouring lanes (part p takes 4p ..
+// 4p + 3), in a fixed order; every lane gets the sum.
+__device__ __forceinline__ double row_sum16(const double* __restrict__ row, int p) {
+    double s = (row[4 * p] + row[4 * p + 1]) + (row[4 * p + 2] + row[4 * p + 3]);
+    s += __shfl_xor(s, 1, kWave);
+    s += __shfl_xor(s, 2, kWave);
+    return s;
 }
 
 // NT staged tiles of 16 loop nodes against the lane's fixed rows.  RI / CI:
@@ -278,10 +297,10 @@ __device__ __forceinline__ void mfs_dispatch(bool ri, bool ci, const v4u* lds_b,
 }
 
 // One work item (blockIdx.x) of the SymLayout.  TRANS: y = A^T x.
-// RowP[item][(fb - kF) kMfmFixed + row], ColP[item][(c - c0) kMfmFixed + node].
+// RowP[item][(fb - kF) kMfmFixed + row], ColP[sym_col_base(c) + k][node].
 template <bool TRANS>
-__global__ __launch_bounds__(kBlock) void k_mfs(const float4* __restrict__ XS, const float4* __restrict__ CF,
-                                                SymLayout L, const float4* __restrict__ frames, EntryConst c,
+__global__ __launch_bounds__(kBlock) void k_mfs(const float4* __restrict__ XS, SymLayout L,
+                                                const float4* __restrict__ frames, EntryConst c,
                                                 double* __restrict__ RowP, double* __restrict__ ColP,
                                                 const GkbState* __restrict__ st) {
     __shared__ v4u lds_b[4 * kMfmChunk];
@@ -296,7 +315,7 @@ __global__ __launch_bounds__(kBlock) void k_mfs(const float4* __restrict__ XS, c
     const int c0 = b0 + item.y * L.Lb;
     const int c1 = c0 + L.Lb < L.nb ? c0 + L.Lb : L.nb;
     const int tid = threadIdx.x, lane = tid & (kWave - 1), g = lane >> 4, jj = lane & 15, wv = tid / kWave;
-    for (int i = tid; i < kSymMaxLb * kMfmFixed; i += kBlock) colacc[i] = 0.0;
+    for (int i = tid; i < L.Lb * kMfmFixed; i += kBlock) colacc[i] = 0.0;
     // the entry constants in vector registers: an FP32 instruction with a
     // scalar operand does not pair with another in one issue cycle
     float k2 = c.k2f, e2x2 = c.e2x2f, e2 = c.e2f;
@@ -338,7 +357,7 @@ __global__ __launch_bounds__(kBlock) void k_mfs(const float4* __restrict__ XS, c
                     const float4 q = XS[i2];
                     const float ex = q.x - fr.x, ey = q.y - fr.y, ez = q.z - fr.z;
                     d2 = fmaf(ez, ez, fmaf(ey, ey, ex * ex));
-                    w = CF[i2].w;
+                    w = q.w;
                 }
                 C[f][r] = d2;
                 xi[f][r] = w;
@@ -358,7 +377,7 @@ __global__ __launch_bounds__(kBlock) void k_mfs(const float4* __restrict__ XS, c
             float dx = 0.f, dy = 0.f, dz = 0.f, w = 0.f;
             if (j < j1) {
                 const float4 q = XS[j];
-                w = CF[j].w;
+                w = q.w;
                 dx = q.x - fr.x;
                 dy = q.y - fr.y;
                 dz = q.z - fr.z;
@@ -412,18 +431,15 @@ __global__ __launch_bounds__(kBlock) void k_mfs(const float4* __restrict__ XS, c
 #pragma unroll
             for (int r = 0; r < 4; ++r) red[(wv * 16 + 4 * g + r) * 17 + jj] = acc[f][r];
             __syncthreads();
-            if (tid < 64) {
-                const int node = tid;
-                double sum = 0.0;
-                for (int q = 0; q < 16; ++q) sum += red[node * 17 + q];
-                const int row = ((node >> 4) * kMfmFt + f) * 16 + (node & 15);
-                rp[row] = fs + row < fe ? sum : 0.0;
-            }
+            const int node = tid >> 2;
+            const double sum = row_sum16(red + node * 17, tid & 3);
+            const int row = ((node >> 4) * kMfmFt + f) * 16 + (node & 15);
+            if ((tid & 3) == 0) rp[row] = fs + row < fe ? sum : 0.0;
         }
     }
     __syncthreads();
-    double* cpo = ColP + slot * L.Lb * kMfmFixed;
-    for (int i = tid; i < L.Lb * kMfmFixed; i += kBlock) cpo[i] = colacc[i];
+    for (int i = tid; i < (c1 - c0) * kMfmFixed; i += kBlock)
+        ColP[(sym_col_base(c0 + i / kMfmFixed, L.F) + item.x) * kMfmFixed + i % kMfmFixed] = colacc[i];
 }
 
 // ---------------------------------------------------------------------------
@@ -447,17 +463,18 @@ __device__ __forceinline__ double swizzle_xor16(double v) {
     return __hiloint2double(hi, lo);
 }
 
-template <bool RI, bool CI, bool SYM, int NT>
-__device__ __forceinline__ void mfs64_tiles(const double4* __restrict__ lds_p, const double (&px)[kMfmFt][4],
-                                            const double (&py)[kMfmFt][4], const double (&pz)[kMfmFt][4],
-                                            const double (&xi)[kMfmFt][4], double k2, double e2x2, double e2,
-                                            double (&acc)[kMfmFt][4], double* __restrict__ colw) {
+// nt tiles of 16 staged loop nodes against the lane's 4 FT fixed rows.
+template <bool RI, bool CI, bool SYM, int FT>
+__device__ __forceinline__ void mfs64_tiles(const double4* __restrict__ lds_p, int nt, const double (&px)[FT][4],
+                                            const double (&py)[FT][4], const double (&pz)[FT][4],
+                                            const double (&xi)[FT][4], double k2, double e2x2, double e2,
+                                            double (&acc)[FT][4], double* __restrict__ colw) {
     const int lane = threadIdx.x & (kWave - 1), jj = lane & 15;
-    for (int u = 0; u < NT; ++u) {
+    for (int u = 0; u < nt; ++u) {
         const double4 q = lds_p[u * 16 + jj];
         double cp = 0.0;
 #pragma unroll
-        for (int f = 0; f < kMfmFt; ++f) {
+        for (int f = 0; f < FT; ++f) {
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 const double dx = px[f][r] - q.x, dy = py[f][r] - q.y, dz = pz[f][r] - q.z;
@@ -482,7 +499,7 @@ __device__ __forceinline__ void mfs64_tiles(const double4* __restrict__ lds_p, c
         // keep the row sums at their tile (left to itself the compiler sinks
         // them past the loop and holds every tile's entries live)
 #pragma unroll
-        for (int f = 0; f < kMfmFt; ++f)
+        for (int f = 0; f < FT; ++f)
             asm volatile("" : "+v"(acc[f][0]), "+v"(acc[f][1]), "+v"(acc[f][2]), "+v"(acc[f][3]));
         if (SYM) {
             // lanes l and l ^ 16 hold the same loop node: add them and let the lower lane store
@@ -492,28 +509,15 @@ __device__ __forceinline__ void mfs64_tiles(const double4* __restrict__ lds_p, c
     }
 }
 
-template <int NT>
-__device__ __forceinline__ void mfs64_dispatch(bool ri, bool ci, const double4* lds_p, const double (&px)[kMfmFt][4],
-                                               const double (&py)[kMfmFt][4], const double (&pz)[kMfmFt][4],
-                                               const double (&xi)[kMfmFt][4], double k2, double e2x2, double e2,
-                                               double (&acc)[kMfmFt][4], double* colw) {
-    if (ri && ci)
-        mfs64_tiles<true, true, true, NT>(lds_p, px, py, pz, xi, k2, e2x2, e2, acc, colw);
-    else if (!ri && !ci)
-        mfs64_tiles<false, false, true, NT>(lds_p, px, py, pz, xi, k2, e2x2, e2, acc, colw);
-    else if (ri)
-        mfs64_tiles<true, false, true, NT>(lds_p, px, py, pz, xi, k2, e2x2, e2, acc, colw);
-    else
-        mfs64_tiles<false, true, true, NT>(lds_p, px, py, pz, xi, k2, e2x2, e2, acc, colw);
-}
-
-template <bool TRANS>
+// One work item of the layout, blocks of B = 64 FT nodes.
+template <bool TRANS, int FT>
 __global__ __launch_bounds__(kBlock) void k_mfs64(const double4* __restrict__ XS64, SymLayout L, EntryConst c,
                                                   double* __restrict__ RowP, double* __restrict__ ColP,
                                                   const GkbState* __restrict__ st) {
+    constexpr int B = 64 * FT;
     __shared__ double4 lds_p[kMfmChunk];
     __shared__ double lds_col[2 * (kBlock / kWave)][kMfmChunk];  // per (wave, lane-group pair)
-    __shared__ double colacc[kSymMaxLb * kMfmFixed];
+    __shared__ double colacc[kSymMaxLb * B];
     double* red = &lds_col[0][0];  // 64 rows x 17 (padded), between chunks (four workgroups fit a CU's LDS)
     if (st != nullptr && st->stopped) return;
     const int2 item = L.items[blockIdx.x];
@@ -523,15 +527,15 @@ __global__ __launch_bounds__(kBlock) void k_mfs64(const double4* __restrict__ XS
     const int c0 = b0 + item.y * L.Lb;
     const int c1 = c0 + L.Lb < L.nb ? c0 + L.Lb : L.nb;
     const int tid = threadIdx.x, lane = tid & (kWave - 1), g = lane >> 4, jj = lane & 15, wv = tid / kWave;
-    for (int i = tid; i < kSymMaxLb * kMfmFixed; i += kBlock) colacc[i] = 0.0;
+    for (int i = tid; i < L.Lb * B; i += kBlock) colacc[i] = 0.0;
     const double k2 = c.k2, e2x2 = c.e2x2, e2 = c.e2;
     for (int fb = b0; fb < b1; ++fb) {
-        const int64_t fs = sym_blk_start(fb, L), fe = sym_blk_end(fb, L);
+        const int64_t fs = sym_blk_start<B>(fb, L), fe = sym_blk_end<B>(fb, L);
         const bool fint = fb < L.nb_int;
-        double px[kMfmFt][4], py[kMfmFt][4], pz[kMfmFt][4], xi[kMfmFt][4], acc[kMfmFt][4];
+        double px[FT][4], py[FT][4], pz[FT][4], xi[FT][4], acc[FT][4];
 #pragma unroll
-        for (int f = 0; f < kMfmFt; ++f) {
-            const int64_t base = fs + (int64_t)(wv * kMfmFt + f) * 16;
+        for (int f = 0; f < FT; ++f) {
+            const int64_t base = fs + (int64_t)(wv * FT + f) * 16;
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 const int64_t i2 = base + 4 * g + r;
@@ -547,10 +551,11 @@ __global__ __launch_bounds__(kBlock) void k_mfs64(const double4* __restrict__ XS
         for (int cb = c0 > fb ? c0 : fb; cb < c1;) {
             const bool diag = cb == fb;
             const bool cint = cb < L.nb_int;
+            // a chunk: as many whole blocks of one class as the staging holds (the own square alone)
             int ce = cb + 1;
-            if (!diag && ce < c1 && (ce < L.nb_int) == cint && sym_blk_end(cb, L) - sym_blk_start(cb, L) == kMfmFixed)
-                ce = cb + 2;
-            const int64_t j0 = sym_blk_start(cb, L), j1 = sym_blk_end(ce - 1, L);
+            while (!diag && ce < c1 && (ce - cb) < kMfmChunk / B && (ce < L.nb_int) == cint) ++ce;
+            const int64_t j0 = sym_blk_start<B>(cb, L), j1 = sym_blk_end<B>(ce - 1, L);
+            const int nt = (int)((j1 - j0 + 15) / 16);
             // stage the chunk's loop nodes (coordinates and weight); past j1 the
             // first node with weight 0 (its column sums are not collected)
             const int64_t j = j0 + tid;
@@ -563,46 +568,46 @@ __global__ __launch_bounds__(kBlock) void k_mfs64(const double4* __restrict__ XS
             double* colw = &lds_col[2 * wv + (g >> 1)][jj];
             if (diag) {
                 if (fint)
-                    mfs64_tiles<true, true, false, 8>(lds_p, px, py, pz, xi, k2, e2x2, e2, acc, colw);
+                    mfs64_tiles<true, true, false, FT>(lds_p, nt, px, py, pz, xi, k2, e2x2, e2, acc, colw);
                 else
-                    mfs64_tiles<false, false, false, 8>(lds_p, px, py, pz, xi, k2, e2x2, e2, acc, colw);
-            } else if (ce == cb + 2) {
-                mfs64_dispatch<16>(ri, ci, lds_p, px, py, pz, xi, k2, e2x2, e2, acc, colw);
+                    mfs64_tiles<false, false, false, FT>(lds_p, nt, px, py, pz, xi, k2, e2x2, e2, acc, colw);
             } else {
-                mfs64_dispatch<8>(ri, ci, lds_p, px, py, pz, xi, k2, e2x2, e2, acc, colw);
-            }
-            if (!diag) {
+                if (ri && ci)
+                    mfs64_tiles<true, true, true, FT>(lds_p, nt, px, py, pz, xi, k2, e2x2, e2, acc, colw);
+                else if (!ri && !ci)
+                    mfs64_tiles<false, false, true, FT>(lds_p, nt, px, py, pz, xi, k2, e2x2, e2, acc, colw);
+                else if (ri)
+                    mfs64_tiles<true, false, true, FT>(lds_p, nt, px, py, pz, xi, k2, e2x2, e2, acc, colw);
+                else
+                    mfs64_tiles<false, true, true, FT>(lds_p, nt, px, py, pz, xi, k2, e2x2, e2, acc, colw);
                 // the chunk's column sums: the 8 (wave, lane-group pair) partials of each loop node
                 __syncthreads();
                 if (tid < (int)(j1 - j0)) {
                     double v = 0.0;
 #pragma unroll
                     for (int qq = 0; qq < 2 * (kBlock / kWave); ++qq) v += lds_col[qq][tid];
-                    colacc[(cb - c0) * kMfmFixed + tid] += v;
+                    colacc[(cb - c0) * B + tid] += v;
                 }
             }
             cb = ce;
         }
         // the fixed block's row sums: each row's 16 lane partials in a fixed order
-        double* rp = RowP + slot * L.F * kMfmFixed + (int64_t)(fb - b0) * kMfmFixed;
+        double* rp = RowP + slot * L.F * B + (int64_t)(fb - b0) * B;
 #pragma unroll
-        for (int f = 0; f < kMfmFt; ++f) {
+        for (int f = 0; f < FT; ++f) {
             __syncthreads();
 #pragma unroll
             for (int r = 0; r < 4; ++r) red[(wv * 16 + 4 * g + r) * 17 + jj] = acc[f][r];
             __syncthreads();
-            if (tid < 64) {
-                const int node = tid;
-                double sum = 0.0;
-                for (int qq = 0; qq < 16; ++qq) sum += red[node * 17 + qq];
-                const int row = ((node >> 4) * kMfmFt + f) * 16 + (node & 15);
-                rp[row] = fs + row < fe ? sum : 0.0;
-            }
+            const int node = tid >> 2;
+            const double sum = row_sum16(red + node * 17, tid & 3);
+            const int row = ((node >> 4) * FT + f) * 16 + (node & 15);
+            if ((tid & 3) == 0) rp[row] = fs + row < fe ? sum : 0.0;
         }
     }
     __syncthreads();
-    double* cpo = ColP + slot * L.Lb * kMfmFixed;
-    for (int i = tid; i < L.Lb * kMfmFixed; i += kBlock) cpo[i] = colacc[i];
+    for (int i = tid; i < (c1 - c0) * B; i += kBlock)
+        ColP[(sym_col_base(c0 + i / B, L.F) + item.x) * B + i % B] = colacc[i];
 }
 
 // XS64[q].w = x[perm[q]]: the weights of a FP64 pair product in the sorted order.
@@ -616,47 +621,45 @@ __global__ __launch_bounds__(kBlock) void k_gather_w64(const double* __restrict_
 }
 
 // y_o = (row partials of the items of q's super-row + column partials of
-// the items whose segment holds q's block) - shift z_o, o = perm[q]; the
-// partials are added in item order, four running sums combined at the end.
-__global__ __launch_bounds__(kBlock) void k_mfs_reduce(SymLayout L, const double* __restrict__ RowP,
-                                                       const double* __restrict__ ColP,
-                                                       const int32_t* __restrict__ perm,
-                                                       const double* __restrict__ shift_ptr, double shift_val,
-                                                       const double* __restrict__ z, double* __restrict__ y,
-                                                       const GkbState* __restrict__ st) {
+// the items whose segment holds q's block) - shift z_o, o = perm[q].  One
+// workgroup per block of B nodes, kSymRedThreads / B groups of B threads taking
+// every so-many-th row partial (item order) and column partial (super-row
+// order), the groups' sums added in group order.  Bound by the latency of the
+// strided reads: with a thread per node taking them all one product's
+// reduction took 7.1 us at 4 000 nodes and 15 us at 20 000.
+constexpr int kSymRedThreads = 1024;
+
+template <int B>
+__global__ __launch_bounds__(kSymRedThreads) void k_mfs_reduce(SymLayout L, const double* __restrict__ RowP,
+                                                               const double* __restrict__ ColP,
+                                                               const int32_t* __restrict__ perm,
+                                                               const double* __restrict__ shift_ptr, double shift_val,
+                                                               const double* __restrict__ z, double* __restrict__ y,
+                                                               const GkbState* __restrict__ st) {
+    constexpr int kGroups = kSymRedThreads / B;
+    __shared__ double part[kGroups][B];
     if (st != nullptr && st->stopped) return;
-    const int64_t q = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (q >= L.n) return;
-    const int beta = q < L.n_int ? (int)(q / kMfmFixed) : L.nb_int + (int)((q - L.n_int) / kMfmFixed);
-    const int64_t off = q - sym_blk_start(beta, L);
+    const int beta = blockIdx.x;
+    const int off = threadIdx.x % B, grp = threadIdx.x / B;
     const int k = beta / L.F;
-    const int64_t rs = (int64_t)L.F * kMfmFixed, cs = (int64_t)L.Lb * kMfmFixed;
-    const int64_t roff = (int64_t)(beta - k * L.F) * kMfmFixed + off;
-    double a0 = 0.0, a1 = 0.0, a2 = 0.0, a3 = 0.0;
-    const int i0 = L.item_first[k], i1 = L.item_first[k + 1];
-    int it = i0;
-    for (; it + 3 < i1; it += 4) {
-        a0 += RowP[(int64_t)it * rs + roff];
-        a1 += RowP[(int64_t)(it + 1) * rs + roff];
-        a2 += RowP[(int64_t)(it + 2) * rs + roff];
-        a3 += RowP[(int64_t)(it + 3) * rs + roff];
-    }
-    for (; it < i1; ++it) a0 += RowP[(int64_t)it * rs + roff];
-    double b0 = 0.0, b1 = 0.0, b2 = 0.0, b3 = 0.0;
-    auto col = [&](int kk) {
-        const int sg = (beta - kk * L.F) / L.Lb;
-        const int cst = kk * L.F + sg * L.Lb;
-        return ColP[(int64_t)(L.item_first[kk] + sg) * cs + (int64_t)(beta - cst) * kMfmFixed + off];
-    };
-    int kk = 0;
-    for (; kk + 3 <= k; kk += 4) {
-        b0 += col(kk);
-        b1 += col(kk + 1);
-        b2 += col(kk + 2);
-        b3 += col(kk + 3);
-    }
-    for (; kk <= k; ++kk) b0 += col(kk);
-    double s = ((a0 + a1) + (a2 + a3)) + ((b0 + b1) + (b2 + b3));
+    const int64_t rs = (int64_t)L.F * B;
+    const int i0 = L.item_first[k], nrow = (L.nb - k * L.F + L.Lb - 1) / L.Lb;
+    const double* rp = RowP + i0 * rs + (int64_t)(beta - k * L.F) * B + off;
+    const double* cp = ColP + sym_col_base(beta, L.F) * B + off;
+    double s = 0.0, sc = 0.0;
+#pragma unroll 4
+    for (int e = grp; e <= k; e += kGroups) sc += cp[(int64_t)e * B];
+#pragma unroll 4
+    for (int e = grp; e < nrow; e += kGroups) s += rp[e * rs];
+    s += sc;
+    part[grp][off] = s;
+    __syncthreads();
+    if (grp != 0) return;
+    s = 0.0;
+#pragma unroll
+    for (int g = 0; g < kGroups; ++g) s += part[g][off];
+    const int64_t q = sym_blk_start<B>(beta, L) + off;
+    if (q >= sym_blk_end<B>(beta, L)) return;
     const int64_t o = perm[q];
     if (z != nullptr) {
         const double sh = shift_ptr != nullptr ? *shift_ptr : shift_val;
@@ -665,16 +668,14 @@ __global__ __launch_bounds__(kBlock) void k_mfs_reduce(SymLayout L, const double
     y[o] = s;
 }
 
-// CF[q] = (w kappa^2, 2 w eps^2, w eps^2, w) with w = x[perm[q]]: the
-// weight-folded entry coefficients of the sorted nodes for one product.
-__global__ __launch_bounds__(kBlock) void k_gather_coef(const double* __restrict__ x,
-                                                        const int32_t* __restrict__ perm, int64_t n, EntryConst c,
-                                                        float4* __restrict__ CF, const GkbState* __restrict__ st) {
+// XS[q].w = x[perm[q]] in FP32: the weights of a FP32 pair product in the sorted order.
+__global__ __launch_bounds__(kBlock) void k_gather_w32(const double* __restrict__ x, const int32_t* __restrict__ perm,
+                                                       int64_t n, float4* __restrict__ XS,
+                                                       const GkbState* __restrict__ st) {
     if (st != nullptr && st->stopped) return;
     const int64_t q = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     if (q >= n) return;
-    const double w = x[perm[q]];
-    CF[q] = make_float4((float)(w * c.k2), (float)(w * c.e2x2), (float)(w * c.e2), (float)w);
+    XS[q].w = (float)x[perm[q]];
 }
 
 // ---------------------------------------------------------------------------
@@ -1084,18 +1085,18 @@ int64_t mfm_blocks(int64_t n, int64_t n_int) {
     return (n_int + kMfmFixed - 1) / kMfmFixed + (n - n_int + kMfmFixed - 1) / kMfmFixed;
 }
 
-void launch_gather_coef(const double* x, const int32_t* perm, int64_t n, const EntryConst& c, float4* CF,
-                        const GkbState* st, hipStream_t s) {
-    k_gather_coef<<<(unsigned)((n + kBlock - 1) / kBlock), kBlock, 0, s>>>(x, perm, n, c, CF, st);
+void launch_gather_w32(const double* x, const int32_t* perm, int64_t n, float4* XS, const GkbState* st,
+                       hipStream_t s) {
+    k_gather_w32<<<(unsigned)((n + kBlock - 1) / kBlock), kBlock, 0, s>>>(x, perm, n, XS, st);
 }
 
-void launch_mfs_product(int trans, const float4* XS, const float4* frames, const float4* CF, const SymLayout& L,
-                        const EntryConst& c, double* RowP, double* ColP, const GkbState* st, hipStream_t s) {
+void launch_mfs_product(int trans, const float4* XS, const float4* frames, const SymLayout& L, const EntryConst& c,
+                        double* RowP, double* ColP, const GkbState* st, hipStream_t s) {
     if (L.nitems <= 0) return;
     if (trans)
-        k_mfs<true><<<(unsigned)L.nitems, kBlock, 0, s>>>(XS, CF, L, frames, c, RowP, ColP, st);
+        k_mfs<true><<<(unsigned)L.nitems, kBlock, 0, s>>>(XS, L, frames, c, RowP, ColP, st);
     else
-        k_mfs<false><<<(unsigned)L.nitems, kBlock, 0, s>>>(XS, CF, L, frames, c, RowP, ColP, st);
+        k_mfs<false><<<(unsigned)L.nitems, kBlock, 0, s>>>(XS, L, frames, c, RowP, ColP, st);
 }
 
 void launch_gather_w64(const double* x, const int32_t* perm, int64_t n, double4* XS64, const GkbState* st,
@@ -1106,18 +1107,29 @@ void launch_gather_w64(const double* x, const int32_t* perm, int64_t n, double4*
 void launch_mfs64_product(int trans, const double4* XS64, const SymLayout& L, const EntryConst& c, double* RowP,
                           double* ColP, const GkbState* st, hipStream_t s) {
     if (L.nitems <= 0) return;
-    if (trans)
-        k_mfs64<true><<<(unsigned)L.nitems, kBlock, 0, s>>>(XS64, L, c, RowP, ColP, st);
-    else
-        k_mfs64<false><<<(unsigned)L.nitems, kBlock, 0, s>>>(XS64, L, c, RowP, ColP, st);
+    const unsigned g = (unsigned)L.nitems;
+    if (L.blk == 64) {
+        if (trans)
+            k_mfs64<true, 1><<<g, kBlock, 0, s>>>(XS64, L, c, RowP, ColP, st);
+        else
+            k_mfs64<false, 1><<<g, kBlock, 0, s>>>(XS64, L, c, RowP, ColP, st);
+    } else {
+        if (trans)
+            k_mfs64<true, 2><<<g, kBlock, 0, s>>>(XS64, L, c, RowP, ColP, st);
+        else
+            k_mfs64<false, 2><<<g, kBlock, 0, s>>>(XS64, L, c, RowP, ColP, st);
+    }
 }
 
 void launch_mfs_reduce(const SymLayout& L, const double* RowP, const double* ColP, const int32_t* perm,
                        const double* shift_ptr, double shift_val, const double* z, double* y, const GkbState* st,
                        hipStream_t s) {
-    if (L.n <= 0) return;
-    k_mfs_reduce<<<(unsigned)((L.n + kBlock - 1) / kBlock), kBlock, 0, s>>>(L, RowP, ColP, perm, shift_ptr, shift_val,
-                                                                          z, y, st);
+    if (L.nb <= 0) return;
+    if (L.blk == 64)
+        k_mfs_reduce<64><<<(unsigned)L.nb, kSymRedThreads, 0, s>>>(L, RowP, ColP, perm, shift_ptr, shift_val, z, y, st);
+    else
+        k_mfs_reduce<128><<<(unsigned)L.nb, kSymRedThreads, 0, s>>>(L, RowP, ColP, perm, shift_ptr, shift_val, z, y,
+                                                                  st);
 }
 
 int64_t mfh_block_blocks(int64_t n, int64_t n_int, int ft) {

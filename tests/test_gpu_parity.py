@@ -119,6 +119,42 @@ def test_stored_pair_values(mq, orc, n_int, n_bnd, row_scale):
         assert np.all(np.abs(y - (M @ x - 0.5 * z)) <= 1e-13 * (np.abs(M) @ np.abs(x) + np.abs(z)))
 
 
+@pytest.mark.parametrize("n_int,n_bnd", [(63, 1), (64, 65), (3300, 900), (15361, 4740)])
+def test_fp64_pair_product_shapes(mq, n_int, n_bnd):
+    """The FP64 pair products' work shapes (blocks of 64 nodes; 1 x 2 and 1 x 4 blocks of 128) with ragged
+    classes against the stored products; all entries are positive, so |A||x| = A|x|."""
+    nodes = I.random_nodes_cube(n_int + n_bnd, 78)
+    x = I.random_vector(n_int + n_bnd, 5)
+    ys = {}
+    for mode in ("stored_fp64", "matfree_fp64"):
+        with mq.Problem(nodes[:n_int], nodes[n_int:], 9.0, 3.0, mode) as pr:
+            say("pair product shapes", mode, n_int, n_bnd)
+            ys[mode] = [(pr.apply(x, trans=t), pr.apply(np.abs(x), trans=t)) for t in (False, True)]
+    for (y, sc), (ref, _) in zip(ys["matfree_fp64"], ys["stored_fp64"]):
+        assert np.all(np.abs(y - ref) <= 2e-13 * sc)  # 1e-13 for each side
+
+
+@pytest.mark.parametrize("n,ell", [(70, 60), (2047, 140), (2049, 40)])
+def test_reorthogonalisation_forms(mq, orc, n, ell):
+    """Runs across the small form's limits (64 blocks of 32 rows, 8192 partials): Golub-Kahan relations and
+    orthonormal bases, and lockstep runs equal to single ones bit for bit."""
+    n_int = int(0.8 * n)
+    p = I.cube_scaled(n_int, n - n_int, kappa=12.0, eps=3.4, ell=ell)
+    A = orc.assemble(p.nodes, p.n_int, p.kappa, p.eps)
+    F = np.stack([p.rhs, I.random_vector(n, 6)])
+    with _problem(mq, p, "matfree_fp64") as pr:
+        say("gkb", n, ell)
+        g = [pr.gkb(f, ell) for f in F]
+        m = pr.gkb_multi(F, ell)
+    for k in range(2):
+        W, Z, C = g[k]["W"].T, g[k]["Z"].T, orc.bidiag_matrix(g[k]["alpha"], g[k]["beta"])
+        assert g[k]["ell_done"] == ell
+        assert np.linalg.norm(A @ Z - W @ C) / np.linalg.norm(C, 2) < 1e-12
+        assert np.max(np.abs(W.T @ W - np.eye(ell + 1))) < 1e-12 and np.max(np.abs(Z.T @ Z - np.eye(ell))) < 1e-12
+        for key in ("W", "Z", "alpha", "beta"):
+            assert np.array_equal(g[k][key], m[key][k]), key
+
+
 def test_products_device_pointers(mq, orc):
     import torch
 
