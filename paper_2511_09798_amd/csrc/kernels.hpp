@@ -134,7 +134,6 @@ void launch_eval_partial(const double4* X, const double* coef, int64_t n, const 
                          int64_t slice_len, const EntryConst& c, double* P, int64_t ldp, hipStream_t s);
 
 // predictor network (mlp_kernels.hip)
-int64_t mlp_param_offset(int layer);
 void launch_mlp_forward(const float* params, const float* x, int B, float* y, float* hidden, hipStream_t s);
 void launch_mlp_backward(const float* params, const float* x, const float* hidden, const float* dy, int B,
                          float* grad, float* work, hipStream_t s);

@@ -10,99 +10,267 @@
 
 namespace mqh {
 
-constexpr int kMlpSizes[kMlpLayers + 1] = {kMlpIn, kMlpWidth, kMlpWidth, kMlpWidth, kMlpOut};
+static_assert(kMlpLayers == 4 && kMlpWidth == 128 && kMlpOut == 2 && kMlpIn <= 32, "layout of the fused kernels");
+
+// Offset of layer l's weights in the parameters (its biases follow the weights).
+__host__ __device__ constexpr int64_t mlp_off(int l) {
+    int64_t off = 0;
+    for (int q = 0; q < l; ++q) {
+        const int in = q == 0 ? kMlpIn : kMlpWidth, out = q == kMlpLayers - 1 ? kMlpOut : kMlpWidth;
+        off += (int64_t)out * in + out;
+    }
+    return off;
+}
 
 // ---------------------------------------------------------------------------
-// FP32 GEMM, C (M x N) = op(A) op(B), 64 x 64 tiles, K in chunks of 16,
-// 256 threads with a 4 x 4 block of C each.
-//   op(A)(m, k) = TA ? A[k * lda + m] : A[m * lda + k]
-//   op(B)(k, n) = TB ? B[n * ldb + k] : B[k * ldb + n]
-// Epilogues: 0 plain; 1 tanh(acc + bias[n]); 2 acc + bias[n];
-// 3 acc * (1 - H[m][n]^2) (the tanh derivative from the layer's output H).
+// The network is 73 KFLOP a sample: a batch's step is bound by launches and
+// memory latencies, so each direction is one or two launches.  All
+// contractions run on the FP32 matrix cores (v_mfma_f32_16x16x4_f32: lane l
+// supplies A[l%16][l/16] and B[l/16][l%16] and receives D[4(l/16) + r][l%16]).
+// As one 64 x 64-tile GEMM per layer and direction and serial column sums (17
+// launches of 4 .. 50 us on 2 .. 8 workgroups) a training step took 532 us on
+// 256 samples and 3.18 ms on 2 048; in these 5 launches 29 and 79 us.
 // ---------------------------------------------------------------------------
-constexpr int kGT = 64, kGK = 16;
 
-template <bool TA, bool TB, int EPI>
-__global__ __launch_bounds__(256) void k_gemm32(int M, int N, int K, const float* __restrict__ A, int lda,
-                                                const float* __restrict__ B, int ldb, float* __restrict__ C, int ldc,
-                                                const float* __restrict__ bias, const float* __restrict__ H,
-                                                int ldh) {
-    __shared__ float As[kGK][kGT + 4];
-    __shared__ float Bs[kGK][kGT + 4];
-    const int tid = threadIdx.x;
-    const int tx = tid & 15, ty = tid >> 4;
-    const int m0 = blockIdx.y * kGT, n0 = blockIdx.x * kGT;
-    float acc[4][4];
+typedef float v4f __attribute__((ext_vector_type(4)));
+constexpr int kMlpRows = 16;             // samples per workgroup of the fused kernels
+constexpr int kMlpLd = kMlpWidth + 4;    // padded LDS row
+
+// Four consecutive parameters (VEC: 16-byte aligned).
+template <bool VEC>
+__device__ __forceinline__ v4f load4(const float* __restrict__ p) {
+    if (VEC) return *reinterpret_cast<const v4f*>(p);
+    v4f v;
+    v[0] = p[0];
+    v[1] = p[1];
+    v[2] = p[2];
+    v[3] = p[3];
+    return v;
+}
+
+// y and the tanh outputs of 16 samples through all four layers.  Wave w of eight
+// forms columns 16 w .. + 15 of a hidden layer; contraction step s takes k =
+// 16 s + 4 (l/16) + j in its j-th product, so a lane reads four consecutive
+// weights of an output row.  Every weight a lane needs is loaded before the
+// first layer starts (18 float4), which leaves one memory latency instead of
+// four.
+constexpr int kMlpThreads = 512;
+static_assert(kMlpThreads / kWave * 16 == kMlpWidth, "one 16-column tile per wave");
+
+template <int STEPS>
+__device__ __forceinline__ void mlp_layer(const float (*in)[kMlpLd], float (*out)[kMlpLd], const v4f (&wt)[STEPS],
+                                          float bias, int B, int64_t b0, float* __restrict__ hid) {
+    const int lane = threadIdx.x & (kWave - 1), li = lane & 15, lk = lane >> 4;
+    const int n = 16 * (threadIdx.x / kWave) + li;
+    v4f acc = v4f{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int s = 0; s < STEPS; ++s) {
+        const v4f h = *reinterpret_cast<const v4f*>(&in[li][16 * s + 4 * lk]);
 #pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = 0.f;
-    for (int k0 = 0; k0 < K; k0 += kGK) {
-        // 64 x 16 of op(A) and 16 x 64 of op(B): four elements per thread each
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int e = tid + q * 256;
-            const int kk = e & 15, mm = e >> 4;  // A tile: As[kk][mm]
-            const int m = m0 + mm, k = k0 + kk;
-            float va = 0.f;
-            if (m < M && k < K) va = TA ? A[(int64_t)k * lda + m] : A[(int64_t)m * lda + k];
-            As[kk][mm] = va;
-            const int nn = e & 63, kb = e >> 6;  // B tile: Bs[kb][nn]
-            const int n = n0 + nn, k2 = k0 + kb;
-            float vb = 0.f;
-            if (n < N && k2 < K) vb = TB ? B[(int64_t)n * ldb + k2] : B[(int64_t)k2 * ldb + n];
-            Bs[kb][nn] = vb;
-        }
-        __syncthreads();
-#pragma unroll
-        for (int kk = 0; kk < kGK; ++kk) {
-            float a[4], b[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) a[i] = As[kk][ty * 4 + i];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) b[j] = Bs[kk][tx * 4 + j];
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(a[i], b[j], acc[i][j]);
-        }
-        __syncthreads();
+        for (int j = 0; j < 4; ++j) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(h[j], wt[s][j], acc, 0, 0, 0);
     }
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int m = m0 + ty * 4 + i;
-        if (m >= M) continue;
+    for (int r = 0; r < 4; ++r) {
+        const int row = 4 * lk + r;
+        const float v = tanhf(acc[r] + bias);
+        out[row][n] = v;
+        if (b0 + row < B) hid[(b0 + row) * kMlpWidth + n] = v;
+    }
+    __syncthreads();
+}
+
+template <bool VEC>
+__global__ __launch_bounds__(kMlpThreads) void k_mlp_forward(const float* __restrict__ params,
+                                                             const float* __restrict__ x, int B,
+                                                             float* __restrict__ y, float* __restrict__ hidden) {
+    __shared__ float H[2][kMlpRows][kMlpLd];
+    const int tid = threadIdx.x, lane = tid & (kWave - 1);
+    const int li = lane & 15, lk = lane >> 4;
+    const int n = 16 * (tid / kWave) + li;
+    const int64_t b0 = (int64_t)blockIdx.x * kMlpRows;
+    const int64_t hs = (int64_t)B * kMlpWidth;  // a layer's block of activations
+    v4f w0[2], w1[8], w2[8];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int n = n0 + tx * 4 + j;
-            if (n >= N) continue;
-            float v = acc[i][j];
-            if (EPI == 1) v = tanhf(v + bias[n]);
-            if (EPI == 2) v = v + bias[n];
-            if (EPI == 3) {
-                const float h = H[(int64_t)m * ldh + n];
-                v = v * (1.f - h * h);
+    for (int s = 0; s < 2; ++s) {
+        const int k = 16 * s + 4 * lk;
+        w0[s] = k < kMlpIn ? load4<VEC>(params + (int64_t)n * kMlpIn + k) : v4f{0.f, 0.f, 0.f, 0.f};
+    }
+#pragma unroll
+    for (int s = 0; s < 8; ++s) {
+        w1[s] = load4<VEC>(params + mlp_off(1) + (int64_t)n * kMlpWidth + 16 * s + 4 * lk);
+        w2[s] = load4<VEC>(params + mlp_off(2) + (int64_t)n * kMlpWidth + 16 * s + 4 * lk);
+    }
+    const float c0 = params[mlp_off(0) + kMlpWidth * kMlpIn + n];
+    const float c1 = params[mlp_off(1) + kMlpWidth * kMlpWidth + n];
+    const float c2 = params[mlp_off(2) + kMlpWidth * kMlpWidth + n];
+    if (tid < kMlpRows * 32) {
+        const int r = tid / 32, k = tid % 32;
+        H[0][r][k] = k < kMlpIn && b0 + r < B ? x[(b0 + r) * kMlpIn + k] : 0.f;
+    }
+    __syncthreads();
+    mlp_layer<2>(H[0], H[1], w0, c0, B, b0, hidden);
+    mlp_layer<8>(H[1], H[0], w1, c1, B, b0, hidden + hs);
+    mlp_layer<8>(H[0], H[1], w2, c2, B, b0, hidden + 2 * hs);
+    // 32 outputs, sixteen lanes each
+    const int o = tid >> 4, q = tid & 15, row = o >> 1, k = o & 1;
+    const float* w3 = params + mlp_off(3) + k * kMlpWidth + 8 * q;
+    float v = 0.f;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v = fmaf(H[1][row][8 * q + e], w3[e], v);
+    v += __shfl_xor(v, 1, kWave);
+    v += __shfl_xor(v, 2, kWave);
+    v += __shfl_xor(v, 4, kWave);
+    v += __shfl_xor(v, 8, kWave);
+    if (q == 0 && b0 + row < B) y[(b0 + row) * kMlpOut + k] = v + params[mlp_off(3) + kMlpOut * kMlpWidth + k];
+}
+
+// dL/dz of layer 2 for one sample and column (rank two in dy): (dy W_3) (1 - h^2).
+__device__ __forceinline__ float dz_out(float d0, float d1, float wa, float wb, float h) {
+    return fmaf(d0, wa, d1 * wb) * (1.f - h * h);
+}
+
+// dL/dz of layers 1 and 0 for 16 samples (dz1, dz0: batch x 128 each); layer
+// 2's follows from dy and is not stored.  Lanes and columns as in the forward
+// kernel; the weights are read transposed (B[k][n] = W[k][n]), both layers'
+// before the first product.
+__global__ __launch_bounds__(kMlpThreads) void k_mlp_data_grad(const float* __restrict__ params,
+                                                               const float* __restrict__ hidden,
+                                                               const float* __restrict__ dy, int B,
+                                                               float* __restrict__ dz1, float* __restrict__ dz0) {
+    __shared__ float D[2][kMlpRows][kMlpLd];
+    const int tid = threadIdx.x, lane = tid & (kWave - 1);
+    const int li = lane & 15, lk = lane >> 4;
+    const int n = 16 * (tid / kWave) + li;
+    const int64_t b0 = (int64_t)blockIdx.x * kMlpRows;
+    const int64_t hs = (int64_t)B * kMlpWidth;
+    float wt[2][kMlpWidth / 4];
+#pragma unroll
+    for (int l = 1; l >= 0; --l) {
+        const float* W = params + mlp_off(l + 1) + n;
+#pragma unroll
+        for (int e = 0; e < kMlpWidth / 4; ++e) wt[l][e] = W[(16 * (e / 4) + 4 * lk + e % 4) * kMlpWidth];
+    }
+    const float* w3 = params + mlp_off(3);
+#pragma unroll
+    for (int e = tid; e < kMlpRows * kMlpWidth; e += kMlpThreads) {
+        const int r = e / kMlpWidth, i = e % kMlpWidth;
+        const int64_t b = b0 + r < B ? b0 + r : B - 1;
+        const float v = dz_out(dy[b * kMlpOut], dy[b * kMlpOut + 1], w3[i], w3[kMlpWidth + i],
+                               hidden[2 * hs + b * kMlpWidth + i]);
+        D[0][r][i] = b0 + r < B ? v : 0.f;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int l = 1; l >= 0; --l) {  // dz of layer l from that of layer l + 1
+        const float(*in)[kMlpLd] = D[1 - l];
+        float* dz = l == 1 ? dz1 : dz0;
+        v4f acc = v4f{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int s = 0; s < kMlpWidth / 16; ++s) {
+            const v4f d = *reinterpret_cast<const v4f*>(&in[li][16 * s + 4 * lk]);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(d[j], wt[l][4 * s + j], acc, 0, 0, 0);
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int row = 4 * lk + r;
+            const int64_t b = b0 + row;
+            float v = 0.f;
+            if (b < B) {
+                const float h = hidden[l * hs + b * kMlpWidth + n];
+                v = acc[r] * (1.f - h * h);
+                dz[b * kMlpWidth + n] = v;
             }
-            C[(int64_t)m * ldc + n] = v;
+            if (l == 1) D[1][row][n] = v;
         }
+        __syncthreads();
     }
 }
 
-template <bool TA, bool TB, int EPI>
-void gemm32(int M, int N, int K, const float* A, int lda, const float* B, int ldb, float* C, int ldc,
-            const float* bias, const float* H, int ldh, hipStream_t s) {
-    dim3 grid((unsigned)((N + kGT - 1) / kGT), (unsigned)((M + kGT - 1) / kGT));
-    k_gemm32<TA, TB, EPI><<<grid, 256, 0, s>>>(M, N, K, A, lda, B, ldb, C, ldc, bias, H, ldh);
+// Weight and bias gradients, one workgroup per 16 x 16 tile of a layer's
+// dW = dz^T h_in (contraction over the batch): blockIdx.x 0 .. 63 layer 2, 64 ..
+// 127 layer 1, 128 .. 143 layer 0, 144 .. 151 layer 3.  Wave w of eight takes
+// samples 4 (w + 8 q) .. + 3, its sums are added in wave order; the tile of a
+// layer's first columns also sums dz itself (the products with ones) into db.
+// Samples past the batch read its last one with weight zero, so that a wave's
+// loads carry no branch.
+constexpr int kMlpGradTiles = 64 + 64 + 16 + 8;
+
+template <int L>
+__device__ __forceinline__ void mlp_grad_sums(const float* __restrict__ params, const float* __restrict__ hin,
+                                              const float* __restrict__ h2, const float* __restrict__ dy,
+                                              const float* __restrict__ dz, int B, int i, int jc, v4f& acc,
+                                              v4f& bacc) {
+    constexpr int in = L == 0 ? kMlpIn : kMlpWidth, out = L == 3 ? kMlpOut : kMlpWidth;
+    const int lane = threadIdx.x & (kWave - 1), lk = lane >> 4;
+    const bool iok = i < out, jok = jc < in;
+    const int ic = iok ? i : 0, jr = jok ? jc : 0;
+    const float wa = L == 2 ? params[mlp_off(3) + ic] : 0.f, wb = L == 2 ? params[mlp_off(3) + kMlpWidth + ic] : 0.f;
+    // A[i][k] = dz of sample b + k, B[k][j] = h_in of sample b + k
+#pragma unroll 8
+    for (int64_t b = 4 * (threadIdx.x / kWave); b < B; b += 4 * (kMlpThreads / kWave)) {
+        const bool ok = b + lk < B;
+        const int64_t q = ok ? b + lk : B - 1;
+        float a;
+        if (L == 2)
+            a = dz_out(dy[q * kMlpOut], dy[q * kMlpOut + 1], wa, wb, h2[q * kMlpWidth + ic]);
+        else
+            a = L == 3 ? dy[q * kMlpOut + ic] : dz[q * kMlpWidth + ic];
+        a = ok && iok ? a : 0.f;
+        const float h = ok && jok ? hin[q * in + jr] : 0.f;
+        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a, h, acc, 0, 0, 0);
+        bacc = __builtin_amdgcn_mfma_f32_16x16x4f32(a, 1.f, bacc, 0, 0, 0);
+    }
 }
 
-// db[n] = sum over the batch of dZ[b][n], one thread per column, in order.
-__global__ __launch_bounds__(kBlock) void k_colsum(const float* __restrict__ dZ, int B, int N,
-                                                   float* __restrict__ db) {
-    const int n = blockIdx.x * kBlock + threadIdx.x;
-    if (n >= N) return;
-    float s = 0.f;
-    for (int b = 0; b < B; ++b) s += dZ[(int64_t)b * N + n];
-    db[n] = s;
+__global__ __launch_bounds__(kMlpThreads) void k_mlp_weight_grad(const float* __restrict__ params,
+                                                                 const float* __restrict__ x,
+                                                                 const float* __restrict__ hidden,
+                                                                 const float* __restrict__ dy,
+                                                                 const float* __restrict__ dz1,
+                                                                 const float* __restrict__ dz0, int B,
+                                                                 float* __restrict__ grad) {
+    constexpr int kWaves = kMlpThreads / kWave;
+    __shared__ float part[kWaves][16 * 16], bpart[kWaves][16];
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), w = tid / kWave;
+    const int li = lane & 15, lk = lane >> 4;
+    const int q = blockIdx.x;
+    const int l = q < 64 ? 2 : q < 128 ? 1 : q < 144 ? 0 : 3;
+    const int e = l == 2 ? q : l == 1 ? q - 64 : l == 0 ? q - 128 : q - 144;
+    const int ncol = l == 0 ? 2 : 8;  // 16-column tiles of the layer's input
+    const int i0 = 16 * (e / ncol), j0 = 16 * (e % ncol);
+    const int in = l == 0 ? kMlpIn : kMlpWidth, out = l == 3 ? kMlpOut : kMlpWidth;
+    const int64_t hs = (int64_t)B * kMlpWidth;
+    const float* h2 = hidden + 2 * hs;
+    v4f acc = v4f{0.f, 0.f, 0.f, 0.f}, bacc = acc;
+    if (l == 2)
+        mlp_grad_sums<2>(params, hidden + hs, h2, dy, nullptr, B, i0 + li, j0 + li, acc, bacc);
+    else if (l == 1)
+        mlp_grad_sums<1>(params, hidden, h2, dy, dz1, B, i0 + li, j0 + li, acc, bacc);
+    else if (l == 0)
+        mlp_grad_sums<0>(params, x, h2, dy, dz0, B, i0 + li, j0 + li, acc, bacc);
+    else
+        mlp_grad_sums<3>(params, h2, h2, dy, nullptr, B, i0 + li, j0 + li, acc, bacc);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        part[w][(4 * lk + r) * 16 + li] = acc[r];
+        if (li == 0) bpart[w][4 * lk + r] = bacc[r];
+    }
+    __syncthreads();
+    float* gW = grad + mlp_off(l);
+    if (tid < 16 * 16) {
+        const int r = tid / 16, c = tid % 16;
+        float v = part[0][tid];
+#pragma unroll
+        for (int u = 1; u < kWaves; ++u) v += part[u][tid];
+        if (i0 + r < out && j0 + c < in) gW[(int64_t)(i0 + r) * in + j0 + c] = v;
+    } else if (j0 == 0 && tid < 16 * 16 + 16 && i0 + tid - 16 * 16 < out) {
+        const int r = tid - 16 * 16;
+        float s = bpart[0][r];
+#pragma unroll
+        for (int u = 1; u < kWaves; ++u) s += bpart[u][r];
+        gW[(int64_t)out * in + i0 + r] = s;
+    }
 }
 
 // Weighted MSE: dY = 2 w_k (Y - T) / B and loss = sum w_k (Y - T)^2 / B
@@ -161,53 +329,24 @@ __global__ void k_mlp_features(const double* __restrict__ alpha, const double* _
 // Host launchers
 // ---------------------------------------------------------------------------
 
-int64_t mlp_param_offset(int layer) {
-    int64_t off = 0;
-    for (int l = 0; l < layer; ++l) off += (int64_t)kMlpSizes[l + 1] * kMlpSizes[l] + kMlpSizes[l + 1];
-    return off;
-}
-
 // hidden: batch x (kMlpLayers - 1) x kMlpWidth, layer-major blocks of
-// batch x kMlpWidth (the tanh outputs, kept for the backward pass).
+// batch x kMlpWidth (the tanh outputs, kept for the backward pass).  Parameters
+// that do not start on 16 bytes are read one at a time.
 void launch_mlp_forward(const float* params, const float* x, int B, float* y, float* hidden, hipStream_t s) {
-    const float* in = x;
-    int in_dim = kMlpIn;
-    for (int l = 0; l < kMlpLayers; ++l) {
-        const int out_dim = kMlpSizes[l + 1];
-        const float* W = params + mlp_param_offset(l);
-        const float* b = W + (int64_t)out_dim * in_dim;
-        if (l < kMlpLayers - 1) {
-            float* h = hidden + (int64_t)l * B * kMlpWidth;
-            gemm32<false, true, 1>(B, out_dim, in_dim, in, in_dim, W, in_dim, h, out_dim, b, nullptr, 0, s);
-            in = h;
-        } else {
-            gemm32<false, true, 2>(B, out_dim, in_dim, in, in_dim, W, in_dim, y, out_dim, b, nullptr, 0, s);
-        }
-        in_dim = out_dim;
-    }
+    const unsigned g = (unsigned)((B + kMlpRows - 1) / kMlpRows);
+    if (reinterpret_cast<uintptr_t>(params) % 16 == 0)
+        k_mlp_forward<true><<<g, kMlpThreads, 0, s>>>(params, x, B, y, hidden);
+    else
+        k_mlp_forward<false><<<g, kMlpThreads, 0, s>>>(params, x, B, y, hidden);
 }
 
-// work: 2 x batch x kMlpWidth floats (dZ of the current and next layer).
+// work: 2 x batch x kMlpWidth floats (dL/dz of layers 1 and 0).
 void launch_mlp_backward(const float* params, const float* x, const float* hidden, const float* dy, int B,
                          float* grad, float* work, hipStream_t s) {
-    const float* dz = dy;  // dL/dz of the output layer
-    float* bufs[2] = {work, work + (int64_t)B * kMlpWidth};
-    for (int l = kMlpLayers - 1; l >= 0; --l) {
-        const int out_dim = kMlpSizes[l + 1], in_dim = kMlpSizes[l];
-        const float* W = params + mlp_param_offset(l);
-        float* gW = grad + mlp_param_offset(l);
-        float* gb = gW + (int64_t)out_dim * in_dim;
-        const float* hin = l == 0 ? x : hidden + (int64_t)(l - 1) * B * kMlpWidth;
-        // dW = dz^T h_in (out x in), db = column sums of dz
-        gemm32<true, false, 0>(out_dim, in_dim, B, dz, out_dim, hin, in_dim, gW, in_dim, nullptr, nullptr, 0, s);
-        k_colsum<<<(unsigned)((out_dim + kBlock - 1) / kBlock), kBlock, 0, s>>>(dz, B, out_dim, gb);
-        if (l > 0) {
-            // dz_{l-1} = (dz W) * (1 - h_in^2)
-            float* nd = bufs[l & 1];
-            gemm32<false, false, 3>(B, in_dim, out_dim, dz, out_dim, W, in_dim, nd, in_dim, nullptr, hin, in_dim, s);
-            dz = nd;
-        }
-    }
+    float* dz1 = work;
+    float* dz0 = work + (int64_t)B * kMlpWidth;
+    k_mlp_data_grad<<<(unsigned)((B + kMlpRows - 1) / kMlpRows), kMlpThreads, 0, s>>>(params, hidden, dy, B, dz1, dz0);
+    k_mlp_weight_grad<<<kMlpGradTiles, kMlpThreads, 0, s>>>(params, x, hidden, dy, dz1, dz0, B, grad);
 }
 
 void launch_mse(const float* y, const float* t, const float* w, int B, float* loss, float* dy, hipStream_t s) {

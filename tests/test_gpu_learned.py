@@ -77,6 +77,43 @@ def test_mlp_forward_backward_loss(env, batch):
         off += o * i + o
 
 
+@pytest.mark.parametrize("batch,shift", [(15, 0), (16, 1), (17, 3), (1030, 2)])
+def test_mlp_fused_edges(env, batch, shift):
+    """The fused kernels at the edges of their 16-sample blocks, with parameters off 16-byte alignment
+    (shift floats), to the tolerances above; arrays past the batch stay as they were."""
+    mq, torch, dev = env
+    rng = np.random.default_rng(100 + batch)
+    P = M.n_params()
+    params = (rng.normal(scale=0.15, size=P)).astype(np.float32)
+    X = rng.normal(size=(batch, 24)).astype(np.float32)
+    dY = rng.normal(size=(batch, 2)).astype(np.float32)
+    buf = torch.empty(P + 4, dtype=torch.float32, device=dev)
+    p_d = buf[shift:shift + P]
+    p_d.copy_(_f32(torch, dev, params))
+    x_d, dy_d = _f32(torch, dev, X), _f32(torch, dev, dY)
+    guard = lambda n: torch.full((n + 64,), 7.0, dtype=torch.float32, device=dev)  # noqa: E731
+    y_d, hid, g_d, work = guard(2 * batch), guard(3 * batch * 128), guard(P), guard(2 * batch * 128)
+    say("mlp edges", batch, shift)
+    mq.mqh_mlp_forward(p_d, x_d, y_d, hid)
+    mq.mqh_mlp_backward(p_d, x_d, hid, dy_d, g_d, work)
+    for a in (y_d, hid, g_d, work):
+        assert torch.all(a[-64:] == 7.0)
+    Y, H = M.forward(params.astype(np.float64), X.astype(np.float64))
+    y = y_d[:-64].cpu().numpy().reshape(batch, 2).astype(np.float64)
+    assert np.max(np.abs(y - Y)) <= 2e-5 * np.max(np.abs(Y))
+    h = hid[:-64].cpu().numpy().reshape(3, batch, 128).astype(np.float64)
+    for l in range(3):
+        assert np.max(np.abs(h[l] - H[l + 1])) <= 2e-5
+    G = M.backward(params.astype(np.float64), H, dY.astype(np.float64))
+    g = g_d[:-64].cpu().numpy().astype(np.float64)
+    off = 0
+    for l in range(4):
+        o, i = M.SIZES[l + 1], M.SIZES[l]
+        sl = slice(off, off + o * i + o)
+        assert np.max(np.abs(g[sl] - G[sl])) <= 1e-4 * np.max(np.abs(G[sl])), l
+        off += o * i + o
+
+
 def test_mlp_adam(env):
     mq, torch, dev = env
     rng = np.random.default_rng(3)
