@@ -373,13 +373,14 @@ __global__ __launch_bounds__(kBandThreads) void k_band_data(const double* __rest
     }
     __syncthreads();
     const SvdWs w = svd_ws(ws, N);
-    double emax = 0.0, bad = 0.0;
+    double bnd = 0.0, bad = 0.0;
     for (int i = tid; i < N; i += kBandThreads) {
         const double di = du[i], ei = i + 1 < N ? eu[i] : 0.0;
         w.d[i] = di;
         w.e[i] = ei;
         w.g[i] = 0.0;
-        emax = ei * ei > emax ? ei * ei : emax;
+        const double bi = msvd::eig_bound_row(du, eu, N, i);
+        bnd = bi > bnd ? bi : bnd;
         bad = (!(di > 0.0) || !isfinite(di) || !isfinite(ei)) ? 1.0 : bad;
     }
     for (int idx = tid; idx < N * kBlkRhs; idx += kBandThreads) {
@@ -390,20 +391,20 @@ __global__ __launch_bounds__(kBandThreads) void k_band_data(const double* __rest
     }
     // maxima over the workgroup
     {
-        double m1 = emax, m2 = bad;
+        double m1 = bnd, m2 = bad;
 #pragma unroll
         for (int o = 32; o > 0; o >>= 1) {
             const double x1 = __shfl_xor(m1, o, kWave), x2 = __shfl_xor(m2, o, kWave);
             m1 = x1 > m1 ? x1 : m1;
             m2 = x2 > m2 ? x2 : m2;
         }
-        __syncthreads();  // the stage's du / eu are still read below by thread 0 only
+        __syncthreads();
         if (lane == 0) red[wv] = m1;
         __syncthreads();
         if (tid == 0) {
             double mm = 0.0;
             for (int q = 0; q < kBandWaves; ++q) mm = red[q] > mm ? red[q] : mm;
-            w.misc[1] = DBL_MIN * (mm > 1.0 ? mm : 1.0);
+            w.misc[0] = msvd::eig_bound_of(mm);
         }
         __syncthreads();
         if (lane == 0) red[wv] = m2;
@@ -411,8 +412,6 @@ __global__ __launch_bounds__(kBandThreads) void k_band_data(const double* __rest
         if (tid == 0) {
             double mm = 0.0;
             for (int q = 0; q < kBandWaves; ++q) mm = red[q] > mm ? red[q] : mm;
-            eu[N - 1] = 0.0;
-            w.misc[0] = msvd::eig_bound(du, eu, N);
             w.flag[0] = mm > 0.0 ? 1 : 0;
             w.flag[1] = 0;
         }

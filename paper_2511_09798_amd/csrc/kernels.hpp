@@ -206,11 +206,11 @@ struct SvdWs {
     double* d;      // L: diagonal of B
     double* e;      // L: superdiagonal of B (L - 1 used)
     double* g;      // L: beta_1 e_1 after the left rotations
-    double* lam;    // L: s_j^2
+    double* lam;    // L: s_j^2, then U h
     double* h;      // L: u_j^T g
     double* res;    // L: residual of triple j over its bound
     double* tmax;   // 2 * kSvdTiles: tile maxima of |V^T V - I| and |U^T U - I|
-    double* misc;   // [0] eigenvalue bound, [1] pivot floor
+    double* misc;   // [0] eigenvalue bound
     int32_t* flag;  // [0] setup or values unresolved, [1] fallback needed
 };
 

@@ -20,9 +20,10 @@
 //    lambda; gamma_k = s_k + p_k + lambda is the pivot of the factorisation
 //    twisted at k, and the k of least |gamma_k| gives the eigenvector by one
 //    step of inverse iteration (twisted_solve) with z_k = 1.
-// Pivots below pivmin in magnitude are replaced by -pivmin (a perturbation
-// of x within the rounding of the data), so no recurrence divides by zero;
-// in the count a quotient that comes out NaN is taken as 1.
+// Zero pivots (in the quotient form pivots below pivmin in magnitude) are
+// replaced by tiny negative ones (a perturbation of x within the rounding of
+// the data), so no recurrence divides by zero; in the quotient form of the
+// count a quotient that comes out NaN is taken as 1.
 #pragma once
 
 #include <math.h>
@@ -37,10 +38,80 @@
 namespace mqh {
 namespace msvd {
 
+// The transforms below carry s_i + x as a quotient w_i / c_i (and p_i + x alike),
+// which leaves two dependent FMAs on a step's serial chain where the quotient
+// itself puts a division there:
+//     a = w - x c (s_i = a / c),  c' = a + u c (the pivot is c' / c),  w' = v a,
+// u = d_i^2, v = e_i^2 from the top, u = e_i^2, v = d_i^2 from the bottom.  The
+// roundings are relative perturbations of s_i, of the pivot and of v, one fewer
+// than in the quotient form.  The pair is brought back near exponent zero every
+// kRescale steps (exact); callers keep u, v and x at most about one, so no step
+// in between overflows.
+constexpr int kRescale = 4;
+// Exponent fields (of 2^-300 and 2^300) beyond which a pair may lose range between
+// two rescalings: seen halfway through a group and applied at its end, the scale
+// lags by up to six steps, over which the pair then shrinks by no more than
+// 2^-600 (and grows by 3^6); with x >= kCountFloor the product x c stays a normal
+// number.
+constexpr uint32_t kPairMin = (1023u - 300u) << 20, kPairMax = (1023u + 300u) << 20;
+constexpr double kCountFloor = 0x1p-360;
+constexpr double kZeroPivot = 0x1p-300;
+
+MQH_HD inline uint32_t high_word(double x) {
+#ifdef __HIP_DEVICE_COMPILE__
+    return (uint32_t)__double2hiint(x);
+#else
+    uint64_t b;
+    __builtin_memcpy(&b, &x, 8);
+    return (uint32_t)(b >> 32);
+#endif
+}
+// Keeps a value loaded ahead of its use where it was loaded: without it the
+// compiler folds the load of the next group back to the start of that group,
+// and its latency returns to the chain.
+MQH_HD inline double kept(double x) {
+#ifdef __HIP_DEVICE_COMPILE__
+    asm volatile("" : "+v"(x));
+#endif
+    return x;
+}
+// The larger exponent field of a and b, and the power of two that takes
+// max(|a|, |b|) into [1, 2) (a multiplication by it is exact).
+MQH_HD inline uint32_t pair_exponent(double a, double b) {
+    const uint32_t ea = high_word(a) & 0x7ff00000u, eb = high_word(b) & 0x7ff00000u;
+    return ea > eb ? ea : eb;
+}
+MQH_HD inline double scale_of(uint32_t ex) {
+    const uint32_t s = 0x7fe00000u - ex;
+#ifdef __HIP_DEVICE_COMPILE__
+    return __hiloint2double((int)s, 0);
+#else
+    const uint64_t v = (uint64_t)s << 32;
+    double r;
+    __builtin_memcpy(&r, &v, 8);
+    return r;
+#endif
+}
+MQH_HD inline double pair_scale(double a, double b) { return scale_of(pair_exponent(a, b)); }
+
+// acc with the sign of c shifted in, and the sign changes among its last m + 1 bits.
+MQH_HD inline uint32_t push_sign(uint32_t acc, double c) {
+#ifdef __HIP_DEVICE_COMPILE__
+    return __builtin_amdgcn_alignbit(acc, high_word(c), 31);
+#else
+    return (acc << 1) | (high_word(c) >> 31);
+#endif
+}
+MQH_HD inline uint32_t sign_changes(uint32_t acc, int m) {
+    return (uint32_t)__builtin_popcount((acc ^ (acc >> 1)) & ((1u << m) - 1u));
+}
+
 // Number of eigenvalues of L D L^T below x, from d2 = d^2 (n) and e2 = e^2
-// (n - 1).  Elements are read at d2[i * ds], e2[i * es] (ds, es = +1 or -1 on
-// suitably placed pointers give the reversed sequences).
-MQH_HD inline int negcount(const double* d2, int ds, const double* e2, int es, int n, double x, double pivmin) {
+// (n - 1), by the quotients s_i themselves (pivots below pivmin replaced).
+// Elements are read at d2[i * ds], e2[i * es] (ds, es = +1 or -1 on suitably
+// placed pointers give the reversed sequences).
+MQH_HD inline int negcount_quotient(const double* d2, int ds, const double* e2, int es, int n, double x,
+                                    double pivmin) {
     double s = -x;
     int neg = 0;
     for (int i = 0; i < n - 1; ++i) {
@@ -56,22 +127,209 @@ MQH_HD inline int negcount(const double* d2, int ds, const double* e2, int es, i
     return neg + (dp < 0.0 ? 1 : 0);
 }
 
+// A chain of the count: the pair, the signs of its last c's, the extreme exponents
+// of its pairs, and the scale of the current group.
+struct CountChain {
+    double w, c, sc;
+    uint32_t acc, lo, hi;
+};
+MQH_HD inline void count_step(CountChain& t, double u, double v, double x) {
+    const double a = fma(-x, t.c, t.w);
+    t.c = fma(u, t.c, a);
+    t.w = v * a;
+    t.acc = push_sign(t.acc, t.c);
+}
+MQH_HD inline void count_exponent(CountChain& t) {
+    const uint32_t ex = pair_exponent(t.w, t.c);
+    t.lo = ex < t.lo ? ex : t.lo;
+    t.hi = ex > t.hi ? ex : t.hi;
+    t.sc = scale_of(ex);
+}
+struct CountOperands {  // of kRescale steps of both chains
+    double u[kRescale], v[kRescale], p[kRescale], r[kRescale];
+};
+MQH_HD inline void count_load(CountOperands& o, const double* d2, int ds, const double* e2, int es, const double* db,
+                              const double* eb, int i) {
+    for (int q = 0; q < kRescale; ++q) {
+        o.u[q] = d2[(i + q) * ds];
+        o.v[q] = e2[(i + q) * es];
+        o.p[q] = eb[-(i + q) * es];
+        o.r[q] = db[-(i + q) * ds];
+    }
+}
+MQH_HD inline void count_keep(CountOperands& o) {
+    for (int q = 0; q < kRescale; ++q) {
+        o.u[q] = kept(o.u[q]);
+        o.v[q] = kept(o.v[q]);
+        o.p[q] = kept(o.p[q]);
+        o.r[q] = kept(o.r[q]);
+    }
+}
+// kRescale steps of both chains; the scale is formed halfway, off the chain.
+MQH_HD inline void count_group(CountChain& t, CountChain& b, const CountOperands& o, double x) {
+    for (int q = 0; q < kRescale; ++q) {
+        count_step(t, o.u[q], o.v[q], x);
+        count_step(b, o.p[q], o.r[q], x);
+        if (q == kRescale / 2 - 1) {
+            count_exponent(t);
+            count_exponent(b);
+        }
+    }
+    t.w *= t.sc;
+    t.c *= t.sc;
+    b.w *= b.sc;
+    b.c *= b.sc;
+}
+
+// The same count from the pairs (a pivot is negative where c changes sign), by the
+// factorisation twisted at the middle k: the pivots of the top-down transform
+// above it, those of the bottom-up one below it, and gamma_k = s_k + (p_k + x).
+// Two chains of half the length, independent of each other.  The c's are a Sturm
+// sequence, so a zero among them counts rightly with either sign: its neighbours
+// differ in sign.  An x below kCountFloor, a pair that left its range or one that
+// vanished sends the count to the quotients.
+MQH_HD inline int negcount(const double* d2, int ds, const double* e2, int es, int n, double x, double pivmin) {
+    const int k = n / 2, nb = n - 1 - k;  // steps from the top (nb or nb + 1) and from the bottom
+    const double* db = d2 + (n - 2) * ds;
+    const double* eb = e2 + (n - 2) * es;
+    CountChain t{0.0, 1.0, 1.0, 0u, kPairMax, kPairMin}, b{d2[(n - 1) * ds], 1.0, 1.0, 0u, kPairMax, kPairMin};
+    uint32_t neg = 0;
+    constexpr int kTwo = 2 * kRescale;
+    const int full = nb / kTwo * kTwo;
+    if (full > 0) {
+        CountOperands A, B;
+        count_load(A, d2, ds, e2, es, db, eb, 0);
+        for (int i = 0; i < full; i += kTwo) {  // the other group's operands in flight during one
+            count_load(B, d2, ds, e2, es, db, eb, i + kRescale);
+            count_group(t, b, A, x);
+            count_keep(B);
+            count_load(A, d2, ds, e2, es, db, eb, i + kTwo < full ? i + kTwo : 0);
+            count_group(t, b, B, x);
+            count_keep(A);
+            neg += sign_changes(t.acc, kTwo);
+            neg += sign_changes(b.acc, kTwo);
+        }
+    }
+    int i = full;
+    if (nb - i >= kRescale) {
+        CountOperands A;
+        count_load(A, d2, ds, e2, es, db, eb, i);
+        count_group(t, b, A, x);
+        neg += sign_changes(t.acc, kRescale);
+        neg += sign_changes(b.acc, kRescale);
+        i += kRescale;
+    }
+    if (const int rem = nb - i) {
+        double u[kRescale], v[kRescale], p[kRescale], r[kRescale];
+        for (int q = 0; q < kRescale - 1; ++q) {
+            const int j = q < rem ? i + q : i;
+            u[q] = d2[j * ds];
+            v[q] = e2[j * es];
+            p[q] = eb[-j * es];
+            r[q] = db[-j * ds];
+        }
+        for (int q = 0; q < kRescale - 1; ++q) {
+            if (q < rem) {
+                count_step(t, u[q], v[q], x);
+                count_step(b, p[q], r[q], x);
+            }
+        }
+        neg += sign_changes(t.acc, rem);
+        neg += sign_changes(b.acc, rem);
+    }
+    if (k > nb) {
+        count_step(t, d2[nb * ds], e2[nb * es], x);
+        neg += sign_changes(t.acc, 1);
+    }
+    count_exponent(t);
+    count_exponent(b);
+    const double ct = t.c * t.sc;
+    const double at = fma(-x, ct, t.w * t.sc);
+    const double g = fma(at, b.c * b.sc, (b.w * b.sc) * ct);  // gamma_k times both c
+    neg += (high_word(g) ^ high_word(t.c) ^ high_word(b.c)) >> 31;
+    const uint32_t lo = t.lo < b.lo ? t.lo : b.lo, hi = t.hi > b.hi ? t.hi : b.hi;
+    const bool ok = x >= kCountFloor && lo > kPairMin && hi < kPairMax && fabs(g) > 0.0;
+    return ok ? (int)neg : negcount_quotient(d2, ds, e2, es, n, x, pivmin);
+}
+
+// One step of a transform's pair; s_i = a / (c before the step).
+MQH_HD inline double pair_step(double& w, double& c, double u, double v, double lam) {
+    const double a = fma(-lam, c, w);
+    w = v * a;
+    c = fma(u, c, a);
+    return a;
+}
+// s_i of a stored pair; a zero c (a zero pivot before it) as a tiny negative pivot.
+MQH_HD inline double pair_pivot(double c) { return c == 0.0 ? -kZeroPivot : c; }
+MQH_HD inline double pair_quotient(double a, double b) { return a / pair_pivot(b); }
+
+// The pairs of a transform, in place: uv holds (u_k, v_k), k < n - 1, and receives
+// (a_k, c_k), s_k = a_k / c_k, k < n.  The top-down (stationary) transform has
+// (u, v) = (d^2, e^2) from the top and w0 = 0; the bottom-up one (e^2, d^2) from
+// the bottom and w0 = d_{n-1}^2 (then s_k is p_{n-1-k}).
+MQH_HD inline void pair_chain(double* uv, int n, double w0, double lam) {
+    double w = w0, c = 1.0;
+    double u[kRescale], v[kRescale];
+    const int full = (n - 1) / kRescale * kRescale;
+    for (int q = 0; q < kRescale && full > 0; ++q) {
+        u[q] = uv[2 * q];
+        v[q] = uv[2 * q + 1];
+    }
+    for (int k0 = 0; k0 < full; k0 += kRescale) {
+        double un[kRescale], vn[kRescale];  // the next group's
+        const double* nx = uv + (k0 + kRescale < full ? 2 * kRescale : 0);
+        for (int q = 0; q < kRescale; ++q) {
+            un[q] = nx[2 * q];
+            vn[q] = nx[2 * q + 1];
+        }
+        double sc = 1.0;
+        for (int q = 0; q < kRescale; ++q) {
+            uv[2 * q + 1] = c;
+            uv[2 * q] = pair_step(w, c, u[q], v[q], lam);
+            if (q == kRescale / 2 - 1) sc = pair_scale(w, c);
+        }
+        w *= sc;
+        c *= sc;
+        uv += 2 * kRescale;
+        for (int q = 0; q < kRescale; ++q) {
+            u[q] = kept(un[q]);
+            v[q] = kept(vn[q]);
+        }
+    }
+    for (int k = full; k < n - 1; ++k) {
+        const double uk = uv[0], vk = uv[1];
+        uv[1] = c;
+        uv[0] = pair_step(w, c, uk, vk, lam);
+        uv += 2;
+    }
+    uv[0] = fma(-lam, c, w);
+    uv[1] = c;
+}
+
+// d e / D for the pivot D = s + u of the pair (a, b): L+_i of the top-down
+// transform (u = d^2) and U-_i of the bottom-up one (u = e^2).
+MQH_HD inline double pair_multiplier(double a, double b, double u, double de) {
+    const double c = pair_pivot(b);
+    return de * c / pair_pivot(fma(u, c, a));
+}
+
 // Top-down transform at lambda: s_0 = -lambda; for i < n - 1,
 // D+_i = s_i + d_i^2, L+_i = d_i e_i / D+_i, s_{i+1} = e_i^2 s_i / D+_i - lambda.
 // Writes s[0..n-1] and lp[0..n-2].
-MQH_HD inline void stationary(const double* d, int ds, const double* e, int es, int n, double lam, double pivmin,
+MQH_HD inline void stationary(const double* d, int ds, const double* e, int es, int n, double lam, double,
                               double* lp, double* s) {
-    double si = -lam;
-    for (int i = 0; i < n - 1; ++i) {
-        const double di = d[i * ds], ei = e[i * es];
-        s[i] = si;
-        double dp = si + di * di;
-        dp = fabs(dp) < pivmin ? -pivmin : dp;
-        const double r = 1.0 / dp;
-        lp[i] = (di * ei) * r;
-        si = (ei * ei) * (si * r) - lam;
+    double w = 0.0, c = 1.0;
+    for (int i = 0; i < n; ++i) {
+        const double di = d[i * ds], ei = i + 1 < n ? e[i * es] : 0.0, b = c;
+        const double a = pair_step(w, c, di * di, ei * ei, lam);
+        if (i + 1 < n) lp[i] = pair_multiplier(a, b, di * di, di * ei);
+        s[i] = pair_quotient(a, b);
+        if (i % kRescale == kRescale - 1) {
+            const double sc = pair_scale(w, c);
+            w *= sc;
+            c *= sc;
+        }
     }
-    s[n - 1] = si;
 }
 
 // Bottom-up transform at lambda: p_{n-1} = d_{n-1}^2 - lambda; for
@@ -79,19 +337,22 @@ MQH_HD inline void stationary(const double* d, int ds, const double* e, int es, 
 // p_i = p_{i+1} d_i^2 / D-_{i+1} - lambda; with gamma_k = s_k + p_k + lambda
 // on the way.  Returns the twist index r = argmin |gamma_k| (the smallest k
 // on ties) and its gamma; U-_i replaces s_i in su (s_i is read first).
-MQH_HD inline int progressive_twist(const double* d, int ds, const double* e, int es, int n, double lam,
-                                    double pivmin, double* su, double* gamma_r) {
-    double p = d[(n - 1) * ds] * d[(n - 1) * ds] - lam;
-    double gbest = su[n - 1] + p + lam;
+MQH_HD inline int progressive_twist(const double* d, int ds, const double* e, int es, int n, double lam, double,
+                                    double* su, double* gamma_r) {
+    const double dn = d[(n - 1) * ds];
+    double w = dn * dn, b = 1.0;
+    double gbest = su[n - 1] + pair_quotient(fma(-lam, b, w), b) + lam;
     int r = n - 1;
     for (int i = n - 2; i >= 0; --i) {
         const double di = d[i * ds], ei = e[i * es];
-        double dm = ei * ei + p;
-        dm = fabs(dm) < pivmin ? -pivmin : dm;
-        const double q = 1.0 / dm;
-        const double um = (di * ei) * q;
-        p = p * (di * di) * q - lam;
-        const double g = su[i] + p + lam;
+        const double b0 = b;
+        const double um = pair_multiplier(pair_step(w, b, ei * ei, di * di, lam), b0, ei * ei, di * ei);
+        if ((n - 1 - i) % kRescale == 0) {
+            const double sc = pair_scale(w, b);
+            w *= sc;
+            b *= sc;
+        }
+        const double g = su[i] + pair_quotient(fma(-lam, b, w), b) + lam;
         if (fabs(g) <= fabs(gbest)) {  // ties to the smaller index
             gbest = g;
             r = i;
@@ -122,6 +383,38 @@ MQH_HD inline void twisted_solve(double* lp_z, const double* um, int n, int r, i
     }
 }
 
+// One direction of the twisted solve from z_r = 1 (z_r included, so that both may run
+// at once): dir < 0 takes mul[k st] = L+_k, dir > 0 U-_k.
+MQH_HD inline void twisted_from(const double* mul, int st, int n, int r, int dir, double* zout) {
+    constexpr int kAhead = 8;  // multipliers in flight ahead of the chain
+    double z = 1.0;
+    zout[r] = 1.0;
+    const int steps = dir < 0 ? r : n - 1 - r;
+    const int full = steps / kAhead * kAhead, sd = st * dir;
+    const double* m = mul + st * (dir < 0 ? r - 1 : r);
+    double* out = zout + r;
+    double q[kAhead];
+    for (int k = 0; k < kAhead && full > 0; ++k) q[k] = m[sd * k];
+    for (int k0 = 0; k0 < full; k0 += kAhead) {
+        double qn[kAhead];
+        if (k0 + kAhead < full) m += sd * kAhead;
+        for (int k = 0; k < kAhead; ++k) qn[k] = m[sd * k];
+        for (int k = 0; k < kAhead; ++k) {
+            z = -q[k] * z;
+            out += dir;
+            out[0] = z;
+        }
+        for (int k = 0; k < kAhead; ++k) q[k] = kept(qn[k]);
+    }
+    if (full > 0) m += sd * kAhead;
+    for (int k = full; k < steps; ++k) {
+        z = -m[0] * z;
+        m += sd;
+        out += dir;
+        out[0] = z;
+    }
+}
+
 // d x + e y - s w for one row of B v - s u (or B^T u - s v) with the
 // rounding error of e y added back (two-product by fma): near a singular
 // triple d x + e y nearly cancels against s w, and without the correction
@@ -136,11 +429,12 @@ MQH_HD inline double resid_row(double d, double x, double e, double y, double s,
 
 // Multisection points: P points strictly inside (lo, hi), equally spaced in
 // log2 while the bracket spans more than a factor of two (from
-// max(lo, hi 2^-1000) when lo = 0), equally spaced otherwise.
+// max(lo, hi 2^-350); a value below that is looked for from the next round's hi
+// on), equally spaced otherwise.
 MQH_HD inline double section_point(double lo, double hi, int t, int P) {
     const double f = (double)(t + 1) / (double)(P + 1);
     if (lo == 0.0 || hi > 2.0 * lo) {
-        const double a = log2(lo > hi * 0x1p-1000 ? lo : hi * 0x1p-1000);
+        const double a = log2(lo > hi * 0x1p-350 ? lo : hi * 0x1p-350);
         const double b = log2(hi);
         return exp2(a + (b - a) * f);
     }
@@ -149,16 +443,27 @@ MQH_HD inline double section_point(double lo, double hi, int t, int P) {
 
 // Upper bound of the eigenvalues of B^T B: the square of max_i (|d_i| + |e_i|, |d_i| + |e_{i-1}|),
 // which bounds ||B||_2 by the geometric mean of the 1- and infinity-norms.
+MQH_HD inline double eig_bound_row(const double* d, const double* e, int n, int i) {
+    const double a = fabs(d[i]);
+    const double r = a + (i < n - 1 ? fabs(e[i]) : 0.0);
+    const double c = a + (i > 0 ? fabs(e[i - 1]) : 0.0);
+    return r > c ? r : c;
+}
+MQH_HD inline double eig_bound_of(double m) { return m * m * (1.0 + 64.0 * 2.220446049250313e-16); }
 MQH_HD inline double eig_bound(const double* d, const double* e, int n) {
     double m = 0.0;
     for (int i = 0; i < n; ++i) {
-        const double a = fabs(d[i]);
-        const double r = a + (i < n - 1 ? fabs(e[i]) : 0.0);
-        const double c = a + (i > 0 ? fabs(e[i - 1]) : 0.0);
+        const double r = eig_bound_row(d, e, n, i);
         m = r > m ? r : m;
-        m = c > m ? c : m;
     }
-    return m * m * (1.0 + 64.0 * 2.220446049250313e-16);
+    return eig_bound_of(m);
+}
+// Half the power of two that brings B^T B's bound below one: d 2^-h, e 2^-h,
+// lambda 2^-2h are the scaled operands of the pair recurrences (exact).
+MQH_HD inline int pair_shift(double bound) {
+    int ex;
+    (void)frexp(bound, &ex);
+    return (ex + 2) / 2;
 }
 
 // Thresholds of the fast path's acceptance test: the Gram matrices of the
@@ -171,7 +476,7 @@ constexpr double kResTol = 1e-9;
 MQH_HD inline double resid_bound(double s, double s1, int n) {
     return kResTol * s + 64.0 * (double)n * 2.220446049250313e-16 * s1;
 }
-constexpr int kSections = 256;  // multisection points per round
+constexpr int kSections = 256;  // multisection points per round (the device takes 64 to 256)
 
 }  // namespace msvd
 }  // namespace mqh

@@ -116,74 +116,96 @@ __global__ __launch_bounds__(kSvdThreads) void k_bidiag_svd(const double* __rest
 // Parameter choice
 // ---------------------------------------------------------------------------
 
-// GCV numerator and trace sum for one lambda, evaluated by one thread.
-__device__ inline void gcv_terms(const double* sv, const double* ft, int l, double lam, double& num, double& tr) {
-    const double l2 = lam * lam;
-    double a = 0.0, t = 0.0;
-    for (int i = 0; i < l; ++i) {
-        const double s2 = sv[i] * sv[i];
-        const double den = s2 + l2;
-        const double psi = l2 / den;
-        const double x = psi * ft[i];
-        a = fma(x, x, a);
-        t += s2 / den;
-    }
-    num = fma(ft[l], ft[l], a);
-    tr = t;
+// The sums over the spectrum are taken by groups of lanes over values staged in
+// LDS, one reciprocal a term (two divisions of global operands before).
+constexpr int kParThreads = 1024;
+static_assert(kMaxEll <= kParThreads, "one singular value per thread in the sums over the workgroup");
+constexpr int kParLanes = 4;  // lanes per point of the grid: 256 points (the default grid has 200) in one pass
+
+__device__ __forceinline__ double par_lanes_sum(double v) {
+#pragma unroll
+    for (int o = kParLanes / 2; o > 0; o >>= 1) v += __shfl_xor(v, o, kWave);
+    return v;
+}
+
+// GCV numerator (without f~_{l+1}) and trace terms of one singular value.
+__device__ __forceinline__ void gcv_term(double s, double f, double l2, double& num, double& tr) {
+    const double s2 = s * s;
+    const double q = 1.0 / (s2 + l2);
+    const double x = (l2 * q) * f;
+    num = fma(x, x, num);
+    tr = fma(s2, q, tr);
 }
 
 // rho_l^2 / ((l+1) - omega sum_i phi_i)^2: eq. (30) for omega = 1, the
 // weighted GCV otherwise.
-__device__ inline double gcv_value(const double* sv, const double* ft, int l, double lam, double omega) {
-    double num, tr;
-    gcv_terms(sv, ft, l, lam, num, tr);
+__device__ __forceinline__ double gcv_of(double num, double tr, double flast, int l, double omega) {
     const double den = (double)(l + 1) - omega * tr;
-    return num / (den * den);
+    return fma(flast, flast, num) / (den * den);
+}
+
+// The same at one lambda by kParLanes lanes (the value in each of them).
+__device__ inline double gcv_lanes(const double* sv, const double* ft, int l, double lam, double omega) {
+    const double l2 = lam * lam;
+    double a = 0.0, t = 0.0;
+    for (int i = threadIdx.x % kParLanes; i < l; i += kParLanes) gcv_term(sv[i], ft[i], l2, a, t);
+    return gcv_of(par_lanes_sum(a), par_lanes_sum(t), ft[l], l, omega);
 }
 
 // Signed curvature of (log rho, log eta) in t = log lambda (analytic derivatives,
-// d phi_i / dt = -2 phi_i psi_i).
-__device__ inline double lcurve_kappa(const double* sv, const double* ft, int l, double lam) {
+// d phi_i / dt = -2 phi_i psi_i) by kParLanes lanes.
+__device__ inline double lcurve_lanes(const double* sv, const double* ft, int l, double lam) {
     const double l2 = lam * lam;
-    double R = ft[l] * ft[l], R1 = 0.0, R2 = 0.0, E = 0.0, E1 = 0.0, E2 = 0.0;
-    for (int i = 0; i < l; ++i) {
-        const double s2 = sv[i] * sv[i];
-        const double den = s2 + l2;
-        const double ph = s2 / den, ps = l2 / den;
-        const double f2 = ft[i] * ft[i];
-        const double g2 = f2 / s2;
-        R += ps * ps * f2;
-        R1 += 4.0 * ph * ps * ps * f2;
-        R2 += 8.0 * f2 * ph * ps * ps * (2.0 * ph - ps);
-        E += ph * ph * g2;
-        E1 += -4.0 * ph * ph * ps * g2;
-        E2 += 8.0 * g2 * ph * ph * ps * (2.0 * ps - ph);
+    double R = 0.0, R1 = 0.0, R2 = 0.0, E = 0.0, E1 = 0.0, E2 = 0.0;
+    for (int i = threadIdx.x % kParLanes; i < l; i += kParLanes) {
+        const double s2 = sv[i] * sv[i], f2 = ft[i] * ft[i];
+        const double q = 1.0 / (s2 + l2);
+        const double ph = s2 * q, ps = l2 * q;
+        const double r = ps * ps * f2, r1 = ph * r;
+        const double e = ph * q * f2, e1 = ps * e;  // phi^2 f2 / s2 = phi f2 / (s2 + l2)
+        R += r;
+        R1 += r1;
+        R2 = fma(r1, fma(2.0, ph, -ps), R2);
+        E += e;
+        E1 += e1;
+        E2 = fma(e1, fma(2.0, ps, -ph), E2);
     }
+    R = fma(ft[l], ft[l], par_lanes_sum(R));
+    R1 = 4.0 * par_lanes_sum(R1);
+    R2 = 8.0 * par_lanes_sum(R2);
+    E = par_lanes_sum(E);
+    E1 = -4.0 * par_lanes_sum(E1);
+    E2 = 8.0 * par_lanes_sum(E2);
     const double x1 = R1 / (2.0 * R), x2 = (R2 * R - R1 * R1) / (2.0 * R * R);
     const double y1 = E1 / (2.0 * E), y2 = (E2 * E - E1 * E1) / (2.0 * E * E);
     const double q = x1 * x1 + y1 * y1;
     return (x1 * y2 - x2 * y1) / (q * sqrt(q));
 }
 
-// Block-parallel (weighted) GCV for the refinement loop.
-__device__ inline double gcv_block(const double* sv, const double* ft, int l, double lam, double omega, double* lds) {
-    const double l2 = lam * lam;
-    double a = 0.0, t = 0.0;
-    for (int i = threadIdx.x; i < l; i += kProjThreads) {
-        const double s2 = sv[i] * sv[i];
-        const double den = s2 + l2;
-        const double x = (l2 / den) * ft[i];
-        a = fma(x, x, a);
-        t += s2 / den;
+// Sums of a and b over the workgroup where only the first nw waves hold any;
+// consecutive calls alternate buf, so one barrier each is enough.
+__device__ inline void par_block_sum2(double& a, double& b, int nw, double (*buf)[2]) {
+    const int wv = threadIdx.x / kWave;
+    if (wv < nw) {
+        a = wave_sum(a);
+        b = wave_sum(b);
+        if ((threadIdx.x & (kWave - 1)) == 0) {
+            buf[wv][0] = a;
+            buf[wv][1] = b;
+        }
     }
-    a = block_sum<kProjThreads>(a, lds);
-    t = block_sum<kProjThreads>(t, lds);
-    const double num = fma(ft[l], ft[l], a);
-    const double den = (double)(l + 1) - omega * t;
-    return num / (den * den);
+    __syncthreads();
+    a = 0.0;
+    b = 0.0;
+    for (int q = 0; q < nw; ++q) {
+        a += buf[q][0];
+        b += buf[q][1];
+    }
 }
 
-__global__ __launch_bounds__(kProjThreads) void k_param_choice(const double* __restrict__ sv,
+// One workgroup per problem; bound by the J l terms of the grid on one compute
+// unit: 29 us for 200 points at l = 300 (73 with a thread per point).
+__global__ __launch_bounds__(kParThreads) void k_param_choice(const double* __restrict__ sv,
                                                                const double* __restrict__ ft, int32_t l_arg,
                                                                const int32_t* __restrict__ l_ptr, int32_t method,
                                                                int32_t rule, int32_t J, double lambda_fixed,
@@ -199,8 +221,8 @@ __global__ __launch_bounds__(kProjThreads) void k_param_choice(const double* __r
         out += z;
     }
     __shared__ double vals[kMaxGrid];
-    __shared__ double lds[kProjThreads / kWave];
-    __shared__ double s_lo, s_hi;
+    __shared__ double s_sv[kMaxEll], s_ft[kMaxEll + 1];
+    __shared__ double buf[2][kParThreads / kWave][2];
     const int tid = threadIdx.x;
     const int l = l_ptr != nullptr ? *l_ptr : l_arg;
     // rule 3: weighted GCV (rule 0 with the trace term scaled by omega)
@@ -217,6 +239,19 @@ __global__ __launch_bounds__(kProjThreads) void k_param_choice(const double* __r
         }
         return;
     }
+    for (int i = tid; i < l; i += kParThreads) s_sv[i] = sv[i];
+    for (int i = tid; i <= l; i += kParThreads) s_ft[i] = ft[i];
+    __syncthreads();
+    sv = s_sv;
+    ft = s_ft;
+    const int nw = (l + kWave - 1) / kWave;  // waves with a term of a workgroup-wide sum
+    int nsum = 0;
+    auto gcv_block = [&](double at) {
+        double a = 0.0, t = 0.0;
+        if (tid < l) gcv_term(sv[tid], ft[tid], at * at, a, t);
+        par_block_sum2(a, t, nw, buf[nsum++ & 1]);
+        return gcv_of(a, t, ft[l], l, omega);
+    };
     if (method == 0) {  // Ine-TSVD
         if (tid == 0) {
             int k;
@@ -265,38 +300,47 @@ __global__ __launch_bounds__(kProjThreads) void k_param_choice(const double* __r
     double lam = lambda_fixed, crit = 0.0;
     uint32_t flags = 0;
     if (rule != 2) {
-        if (tid == 0) {
-            const double hi = sv[0];
-            double lo = sv[l - 1] > 16.0 * DBL_EPSILON * hi ? sv[l - 1] : 16.0 * DBL_EPSILON * hi;
-            if (!(lo < hi)) lo = 16.0 * DBL_EPSILON * hi;
-            s_lo = log(lo);
-            s_hi = log(hi);
-        }
-        __syncthreads();
-        const double t0 = s_lo, t1 = s_hi;
+        const double hi = sv[0];
+        double lo = sv[l - 1] > 16.0 * DBL_EPSILON * hi ? sv[l - 1] : 16.0 * DBL_EPSILON * hi;
+        if (!(lo < hi)) lo = 16.0 * DBL_EPSILON * hi;
+        const double t0 = log(lo), t1 = log(hi);
         const double step = (t1 - t0) / (double)(J - 1);
-        for (int j = tid; j < J; j += kProjThreads) {
+        for (int j = tid / kParLanes; j < J; j += kParThreads / kParLanes) {
             const double lj = j == J - 1 ? exp(t1) : exp(t0 + step * (double)j);
-            const double v = rule == 0 ? gcv_value(sv, ft, l, lj, omega) : lcurve_kappa(sv, ft, l, lj);
-            vals[j] = v;
-            if (curve != nullptr) curve[j] = v;
+            const double v = rule == 0 ? gcv_lanes(sv, ft, l, lj, omega) : lcurve_lanes(sv, ft, l, lj);
+            if (tid % kParLanes == 0) {
+                vals[j] = v;
+                if (curve != nullptr) curve[j] = v;
+            }
         }
         __syncthreads();
         __shared__ int s_k;
-        if (tid == 0) {
-            int kb;
-            if (rule == 0) {  // argmin, ties -> larger lambda
-                kb = 0;
-                for (int j = 1; j < J; ++j)
-                    if (vals[j] <= vals[kb]) kb = j;
-                if (kb == 0 || kb == J - 1) flags |= 2u;
-            } else {  // argmax over inner points, ties -> larger lambda
-                kb = 1;
-                for (int j = 2; j < J - 1; ++j)
-                    if (vals[j] >= vals[kb]) kb = j;
-                if (kb == 1 || kb == J - 2) flags |= 4u;
+        if (tid < kWave) {
+            // rule 0: argmin, rule 1: argmax over the inner points, ties -> larger
+            // lambda; a point that is not a number is passed over, but for the first
+            const int jf = rule == 0 ? 0 : 1, jl = rule == 0 ? J - 1 : J - 2;
+            const double sgn = rule == 0 ? 1.0 : -1.0;
+            double best = sgn * vals[jf];
+            int kb = jf;
+            const bool scan = best == best;
+            for (int j = jf + 1 + tid; j <= jl; j += kWave) {
+                const double v = sgn * vals[j];
+                if (scan && v <= best) {
+                    best = v;
+                    kb = j;
+                }
             }
-            s_k = kb;
+#pragma unroll
+            for (int o = 32; o > 0; o >>= 1) {
+                const double ob = __shfl_xor(best, o, kWave);
+                const int ok = __shfl_xor(kb, o, kWave);
+                if (ob < best || (ob == best && ok > kb)) {
+                    best = ob;
+                    kb = ok;
+                }
+            }
+            if (kb == jf || kb == jl) flags |= rule == 0 ? 2u : 4u;
+            if (tid == 0) s_k = kb;
         }
         __syncthreads();
         const int kb = s_k;
@@ -309,7 +353,7 @@ __global__ __launch_bounds__(kProjThreads) void k_param_choice(const double* __r
             double a = t0 + step * (double)(kb - 1);
             double b = kb + 1 == J - 1 ? t1 : t0 + step * (double)(kb + 1);
             double c = b - gr * (b - a), dd = a + gr * (b - a);
-            double fc = gcv_block(sv, ft, l, exp(c), omega, lds), fd = gcv_block(sv, ft, l, exp(dd), omega, lds);
+            double fc = gcv_block(exp(c)), fd = gcv_block(exp(dd));
             int it = 0;
             while (fabs(b - a) > 1e-10 && it < 200) {
                 if (fc < fd) {
@@ -317,18 +361,18 @@ __global__ __launch_bounds__(kProjThreads) void k_param_choice(const double* __r
                     dd = c;
                     fd = fc;
                     c = b - gr * (b - a);
-                    fc = gcv_block(sv, ft, l, exp(c), omega, lds);
+                    fc = gcv_block(exp(c));
                 } else {
                     a = c;
                     c = dd;
                     fc = fd;
                     dd = a + gr * (b - a);
-                    fd = gcv_block(sv, ft, l, exp(dd), omega, lds);
+                    fd = gcv_block(exp(dd));
                 }
                 ++it;
             }
             const double lr = exp(0.5 * (a + b));
-            const double gv = gcv_block(sv, ft, l, lr, omega, lds);
+            const double gv = gcv_block(lr);
             if (!(gv > crit)) {
                 lam = lr;
                 crit = gv;
@@ -339,20 +383,25 @@ __global__ __launch_bounds__(kProjThreads) void k_param_choice(const double* __r
     {
         const double l2 = lam * lam;
         double r = 0.0, e = 0.0;
-        for (int i = tid; i < l; i += kProjThreads) {
-            const double s2 = sv[i] * sv[i];
-            const double den = s2 + l2;
-            const double x = (l2 / den) * ft[i];
-            const double q = (sv[i] / den) * ft[i];
-            r = fma(x, x, r);
-            e = fma(q, q, e);
+        if (tid < l) {
+            const double den = sv[tid] * sv[tid] + l2;
+            const double x = (l2 / den) * ft[tid];
+            const double q = (sv[tid] / den) * ft[tid];
+            r = x * x;
+            e = q * q;
         }
-        r = block_sum<kProjThreads>(r, lds);
-        e = block_sum<kProjThreads>(e, lds);
+        par_block_sum2(r, e, nw, buf[nsum++ & 1]);
+        double gfix = 0.0;
+        if (rule == 2) {  // the criterion at a given lambda: unweighted
+            double a = 0.0, t = 0.0;
+            if (tid < l) gcv_term(sv[tid], ft[tid], l2, a, t);
+            par_block_sum2(a, t, nw, buf[nsum++ & 1]);
+            gfix = gcv_of(a, t, ft[l], l, 1.0);
+        }
         if (tid == 0) {
             out->lambda = lam;
             out->k = 0;
-            out->crit = rule == 2 ? gcv_value(sv, ft, l, lam, 1.0) : crit;
+            out->crit = rule == 2 ? gfix : crit;
             out->flags = flags;
             out->rho = sqrt(fma(ft[l], ft[l], r));
             out->eta = sqrt(e);
@@ -362,12 +411,16 @@ __global__ __launch_bounds__(kProjThreads) void k_param_choice(const double* __r
 
 // y_r = sum_i V[i][r] w_i with w_i = s_i/(s_i^2+lambda^2) f~_i (HKT) or
 // f~_i/s_i for i < k (Ine-TSVD); lambda and k from *po when given.
-__global__ __launch_bounds__(kBlock) void k_proj_solution(const double* __restrict__ sv,
-                                                          const double* __restrict__ ft,
-                                                          const double* __restrict__ V, int64_t ldv, int32_t l_arg,
-                                                          const int32_t* __restrict__ l_ptr, int32_t method,
-                                                          double lambda, int32_t k, const ParamOut* __restrict__ po,
-                                                          double* __restrict__ y, ProjBatch pb) {
+// 64 rows per workgroup, the columns dealt to 16 waves and their sums added in
+// LDS; the weights are formed once per workgroup.  Bound by the latency of the
+// loads of V: 6 us at l = 300, a thread per row with every weight's division in
+// its own chain 76.
+constexpr int kSolRows = 64, kSolGroups = 16;
+
+__global__ __launch_bounds__(kSolRows * kSolGroups) void k_proj_solution(
+    const double* __restrict__ sv, const double* __restrict__ ft, const double* __restrict__ V, int64_t ldv,
+    int32_t l_arg, const int32_t* __restrict__ l_ptr, int32_t method, double lambda, int32_t k,
+    const ParamOut* __restrict__ po, double* __restrict__ y, ProjBatch pb) {
     {
         const int64_t z = blockIdx.y;  // batch: problem z
         sv += z * pb.vec;
@@ -377,22 +430,32 @@ __global__ __launch_bounds__(kBlock) void k_proj_solution(const double* __restri
         if (po != nullptr) po += z;
         y += z * pb.vec;
     }
+    __shared__ double wt[kMaxEll];
+    __shared__ double part[kSolGroups][kSolRows];
     const int l = l_ptr != nullptr ? *l_ptr : l_arg;
-    const int r = blockIdx.x * kBlock + threadIdx.x;
-    if (r >= l) return;
+    if ((int)blockIdx.x * kSolRows >= l) return;
+    const int tid = threadIdx.x, rl = tid % kSolRows, g = tid / kSolRows;
+    const int r = blockIdx.x * kSolRows + rl;
     const double lam = po != nullptr ? po->lambda : lambda;
     const int kk = po != nullptr ? po->k : k;
     const double l2 = lam * lam;
+    const int m = method == 1 ? l : (kk < l ? kk : l);
+    for (int i = tid; i < m; i += kSolRows * kSolGroups)
+        wt[i] = method == 1 ? sv[i] / (sv[i] * sv[i] + l2) * ft[i] : ft[i] / sv[i];
+    __syncthreads();
     double s = 0.0;
-    if (method == 1) {
-        for (int i = 0; i < l; ++i) {
-            const double w = sv[i] / (sv[i] * sv[i] + l2) * ft[i];
-            s = fma(V[(int64_t)i * ldv + r], w, s);
-        }
-    } else {
-        for (int i = 0; i < kk && i < l; ++i) s = fma(V[(int64_t)i * ldv + r], ft[i] / sv[i], s);
+    if (r < l) {
+        const double* Vr = V + r;
+#pragma unroll 8
+        for (int i = g; i < m; i += kSolGroups) s = fma(Vr[(int64_t)i * ldv], wt[i], s);
     }
-    y[r] = s;
+    part[g][rl] = s;
+    __syncthreads();
+    if (g == 0 && r < l) {
+#pragma unroll
+        for (int q = 1; q < kSolGroups; ++q) s += part[q][rl];
+        y[r] = s;
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -576,7 +639,7 @@ void launch_bidiag_qr(const double* alpha, const double* beta, int32_t l, const 
 void launch_param_choice(const double* sv, const double* ft, int32_t l, const int32_t* l_ptr, int32_t method,
                          int32_t rule, int32_t J, double lambda_fixed, int32_t k_fixed, double omega, double* curve,
                          ParamOut* out, hipStream_t s, int nz, ProjBatch pb) {
-    k_param_choice<<<nz, kProjThreads, 0, s>>>(sv, ft, l, l_ptr, method, rule, J, lambda_fixed, k_fixed, omega, curve,
+    k_param_choice<<<nz, kParThreads, 0, s>>>(sv, ft, l, l_ptr, method, rule, J, lambda_fixed, k_fixed, omega, curve,
                                                out, pb);
 }
 
@@ -589,8 +652,8 @@ void launch_lsqr(const double* alpha, const double* beta, int32_t l, const int32
 void launch_proj_solution(const double* sv, const double* ft, const double* V, int64_t ldv, int32_t l,
                           const int32_t* l_ptr, int32_t method, double lambda, int32_t k, const ParamOut* po,
                           double* y, int32_t l_max, hipStream_t s, int nz, ProjBatch pb) {
-    k_proj_solution<<<dim3((l_max + kBlock - 1) / kBlock, nz), kBlock, 0, s>>>(sv, ft, V, ldv, l, l_ptr, method,
-                                                                               lambda, k, po, y, pb);
+    k_proj_solution<<<dim3((l_max + kSolRows - 1) / kSolRows, nz), kSolRows * kSolGroups, 0, s>>>(
+        sv, ft, V, ldv, l, l_ptr, method, lambda, k, po, y, pb);
 }
 
 }  // namespace mqh

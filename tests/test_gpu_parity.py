@@ -279,6 +279,43 @@ def test_proj_svd_small(mq, orc, ell):
     assert np.max(np.abs(np.abs(ftg) - np.abs(ft))) < 1e-13
 
 
+@pytest.mark.parametrize("kind", ["positive", "signed", "steep"])
+@pytest.mark.parametrize("ell", [1, 2, 8, 9, 17, 63, 65, 128, 256, 257, 512, 513, 1000])
+def test_projected_problem_shapes(mq, orc, kind, ell):
+    """Lengths around the kernels' groups, strips and thread rules, with the coefficients that the scan of
+    the rotations takes (positive), leaves to the rotations (signed), or gives back to them from about
+    80 steps on (steep: rhobar falls by 30 a step).  LAPACK's backward error, l eps s_1, is the bound of a value."""
+    rng = np.random.default_rng(ell)
+    a = np.exp(0.3 * rng.standard_normal(ell)) * (rng.choice([-1.0, 1.0], ell) if kind == "signed" else 1.0)
+    b = np.concatenate([[2.0], np.exp(0.3 * rng.standard_normal(ell)) * (30.0 if kind == "steep" else 0.6)])
+    C = orc.bidiag_matrix(a, b)
+    rhs = np.zeros(ell + 1)
+    rhs[0] = b[0]
+    U, s, Vt = np.linalg.svd(C)
+    say("projected shapes", kind, ell)
+    sv, ft, V = mq.mqh_proj_svd(a, b)
+    assert np.max(np.abs(sv - s)) <= 8 * ell * EPS * s[0]
+    assert np.max(np.abs(V @ V.T - np.eye(ell))) <= 64 * ell * EPS
+    assert np.max(np.abs(np.linalg.norm(C @ V.T, axis=0) - sv)) <= 64 * ell * EPS * s[0]  # ||C v_i|| = s_i
+    # the Tikhonov solution at s_1 / 10: a condition of 101 on a backward error of l eps
+    lam = 0.1 * s[0]
+    f = U.T @ rhs
+    y0 = Vt.T @ (s / (s ** 2 + lam ** 2) * f[:ell])
+    y = mq.mqh_proj_solution(sv, ft, V, mq.MQH_METHOD_HKT, lam)
+    assert np.linalg.norm(y - y0) <= 101 * 8 * ell * EPS * np.linalg.norm(y0)
+    # the GCV curve over grids below, at and past one pass: sums of positive terms, then (l + 1) - tr, from
+    # which at least 1 is left of l
+    for J in (3, 256, 259):
+        ch = mq.mqh_param_choice(sv, ft, mq.MQH_METHOD_HKT, mq.MQH_RULE_GCV, n_grid=J, want_curve=True)
+        lo = max(sv[-1], 16 * EPS * sv[0])
+        lo = lo if lo < sv[0] else 16 * EPS * sv[0]
+        lams = np.exp(np.linspace(np.log(lo), np.log(sv[0]), J))[:, None]
+        psi, phi = lams ** 2 / (sv ** 2 + lams ** 2), sv ** 2 / (sv ** 2 + lams ** 2)
+        ref = (np.sum((psi * ft[:-1]) ** 2, axis=1) + ft[-1] ** 2) / (ell + 1 - np.sum(phi, axis=1)) ** 2
+        # exp of a logarithm of up to 40 in size: 40 eps of lambda, four times that of the squared terms
+        assert np.max(np.abs(ch["curve"] - ref) / ref) <= (8 * ell * ell + 1024) * EPS
+
+
 def _decaying(l, seed):
     # a spectrum like that of a Golub-Kahan run on an ill-posed operator
     rng = np.random.default_rng(seed)
