@@ -147,7 +147,7 @@ struct HostResults {
     GkbState st;
     ParamOut po;
     int32_t svd_status;
-    int32_t pad;
+    int32_t eval_bad;  // the number of an evaluation whose points were not finite
 };
 
 }  // namespace
@@ -276,6 +276,10 @@ struct mqh_problem {
     double* EP = nullptr;
     int64_t EP_cap = 0;
     double* u = nullptr;
+    double* Exyz = nullptr;  // coordinates of the points when they come from elsewhere
+    int64_t Exyz_cap = 0;
+    int32_t* eval_flag = nullptr;
+    int32_t eval_call = 0;
     // learned predictor: features (kMlpIn), outputs (kMlpOut), hidden
     // activations (3 x kMlpWidth), standardisation (2 kMlpIn), FP32
     float* mlp = nullptr;
@@ -1336,6 +1340,16 @@ int stage_in(double* dst, const double* src, int64_t count, uint32_t flags, hipS
     return MQH_OK;
 }
 
+// p points to memory of the device itself, which its kernels may read and write.
+bool on_device(const void* ptr, int device) {
+    hipPointerAttribute_t a;
+    if (hipPointerGetAttributes(&a, ptr) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return a.type == hipMemoryTypeDevice && a.device == device;
+}
+
 int check_problem(const mqh_problem* p) {
     if (p == nullptr) return fail(MQH_EINVAL, "NULL problem");
     return MQH_OK;
@@ -1864,6 +1878,8 @@ int mqh_problem_destroy(mqh_problem* p) {
     dfree(p->u);
     multi_free(p->mw);
     block_cache_free(p->bc);
+    dfree(p->Exyz);
+    dfree(p->eval_flag);
     if (p->hres) (void)hipHostFree(p->hres);
     for (auto& e : p->ev)
         if (e) (void)hipEventDestroy(e);
@@ -2767,20 +2783,7 @@ int mqh_eval(mqh_problem* p, const double* coef, const double* x_eval, int64_t m
     if (coef == nullptr || x_eval == nullptr || u == nullptr || m < 1) return fail(MQH_EINVAL, "bad eval arguments");
     HIPCHK(hipSetDevice(p->device));
     hipStream_t s = p->stream;
-    std::vector<double> xyz((size_t)(3 * m));
-    if (flags & MQH_FLAG_DEVICE_PTRS)
-        HIPCHK(hipMemcpy(xyz.data(), x_eval, (size_t)(3 * m) * sizeof(double), hipMemcpyDeviceToHost));
-    else
-        memcpy(xyz.data(), x_eval, (size_t)(3 * m) * sizeof(double));
-    if (!all_finite(xyz.data(), 3 * m)) return fail(MQH_EINVAL, "non-finite evaluation point");
-    std::vector<double4> rec((size_t)m);
-    to_records(p, xyz.data(), m, rec.data(), nullptr);
-    const int64_t mb = (m + kBlock - 1) / kBlock;
-    int64_t S = (4096 + mb - 1) / mb;
-    if (S > 256) S = 256;
-    int64_t len = (p->n + S - 1) / S;
-    len = round_up(len < 64 ? 64 : len, 2);
-    S = (p->n + len - 1) / len;
+    const EvalShape g = eval_shape(p->n, m);
     const int64_t ldm = round_up(m, 64);
     if (m > p->E_cap) {
         dfree(p->E);
@@ -2790,20 +2793,50 @@ int mqh_eval(mqh_problem* p, const double* coef, const double* x_eval, int64_t m
         if ((rc = dalloc(&p->u, (size_t)ldm))) return rc;
         p->E_cap = m;
     }
-    if (S * ldm > p->EP_cap) {
+    if (g.S * ldm > p->EP_cap) {
         dfree(p->EP);
         p->EP_cap = 0;
-        if ((rc = dalloc(&p->EP, (size_t)(S * ldm)))) return rc;
-        p->EP_cap = S * ldm;
+        if ((rc = dalloc(&p->EP, (size_t)(g.S * ldm)))) return rc;
+        p->EP_cap = g.S * ldm;
     }
-    if ((rc = stage_in(p->vx, coef, p->n, flags, s))) return rc;
-    HIPCHK(hipMemcpyAsync(p->E, rec.data(), (size_t)m * sizeof(double4), hipMemcpyHostToDevice, s));
-    launch_eval_partial(p->X64, p->vx, p->n, p->E, m, (int)S, len, p->ec, p->EP, ldm, s);
+    if (p->eval_flag == nullptr) {
+        if ((rc = dalloc(&p->eval_flag, 1))) return rc;
+        HIPCHK(hipMemsetAsync(p->eval_flag, 0, sizeof(int32_t), s));
+    }
+    // Arrays on the problem's device are read and written where they are; the
+    // rest is staged.  Device arrays may still be in the making on the null stream (it is
+    // seldom busy: waiting for it here costs nothing measurable, an event on it 20 us).
+    const bool dev = (flags & MQH_FLAG_DEVICE_PTRS) != 0;
+    if (dev && s != nullptr) HIPCHK(hipStreamSynchronize(nullptr));
+    const double* xyz = x_eval;
+    const double* cf = coef;
+    double* out = u;
+    if (!dev && !all_finite(x_eval, 3 * m)) return fail(MQH_EINVAL, "non-finite evaluation point");
+    if (!dev || !on_device(coef, p->device)) {
+        if ((rc = stage_in(p->vx, coef, p->n, flags, s))) return rc;
+        cf = p->vx;
+    }
+    if (!dev || !on_device(x_eval, p->device)) {
+        if (3 * m > p->Exyz_cap) {
+            dfree(p->Exyz);
+            p->Exyz_cap = 0;
+            if ((rc = dalloc(&p->Exyz, (size_t)(3 * m)))) return rc;
+            p->Exyz_cap = 3 * m;
+        }
+        HIPCHK(hipMemcpyAsync(p->Exyz, x_eval, (size_t)(3 * m) * sizeof(double), kind_in(flags), s));
+        xyz = p->Exyz;
+    }
+    if (!dev || !on_device(u, p->device)) out = p->u;
+    p->eval_call = p->eval_call == INT32_MAX ? 1 : p->eval_call + 1;
+    launch_eval_records(xyz, m, p->eps, p->center, p->eval_call, p->E, p->eval_flag, s);
+    launch_eval(p->X64, cf, p->n, p->E, m, g, p->EP, ldm, p->eval_call, p->eval_flag, out, &p->hres->eval_bad, s);
     LAUNCHCHK("evaluation");
-    launch_reduce_slices(p->EP, ldm, (int)S, m, nullptr, nullptr, 0.0, nullptr, p->u, nullptr, s);
-    LAUNCHCHK("evaluation reduction");
-    HIPCHK(hipMemcpyAsync(u, p->u, (size_t)m * sizeof(double), kind_out(flags), s));
     HIPCHK(hipStreamSynchronize(s));
+    if (p->hres->eval_bad != 0) return fail(MQH_EINVAL, "non-finite evaluation point");
+    if (out != u) {
+        HIPCHK(hipMemcpyAsync(u, out, (size_t)m * sizeof(double), kind_out(flags), s));
+        HIPCHK(hipStreamSynchronize(s));
+    }
     return MQH_OK;
 }
 

@@ -112,9 +112,6 @@ void launch_gather_block(const double* X, int64_t ldx, int nrhs, const int32_t* 
 void launch_reduce_block(const double* P, int64_t ldp, int S, int64_t n, int nrhs, const int32_t* perm,
                          const double* shift, int64_t sstride, const double* z, int64_t ldz, double* y, int64_t ldy,
                          const GkbState* st, hipStream_t s);
-void launch_reduce_slices(const double* P, int64_t ldp, int S, int64_t n, const int32_t* perm,
-                          const double* shift_ptr, double shift_val, const double* z, double* y,
-                          const GkbState* st, hipStream_t s);
 // dense row-major A (lda >= n, zero columns past n): the full SVD's work matrix
 void launch_assemble(const double4* X, int64_t n, int64_t n_int, int64_t lda, const EntryConst& c, double* A,
                      hipStream_t s);
@@ -130,8 +127,25 @@ void launch_packed_rows(const double* A, const PackedLayout& L, const EntryConst
                         double* out, hipStream_t s);
 void launch_gen_rows(int prec, const void* X, int64_t n, int64_t n_int, int64_t row0, int64_t count,
                      const EntryConst& c, double* out, hipStream_t s);
-void launch_eval_partial(const double4* X, const double* coef, int64_t n, const double4* E, int64_t m, int S,
-                         int64_t slice_len, const EntryConst& c, double* P, int64_t ldp, hipStream_t s);
+// evaluation at m points: their records, then the slices of the sum over the centres
+// (P: S x ldp) and u, unless flag bears the call's number (to *hflag, host memory)
+// Centres per wave: so few that a launch holds 32 waves per SIMD, whose ends even out
+// (602 us at 20 000 points and 60 000 centres, 710 with 8 waves), but at least 48, below
+// which the partial sums take what the waves gain (2000 points, 20 000 centres: 54 us
+// with 16, 49 to 50 with 32 to 79).
+constexpr int kEvalWaves = 8;           // slices of the centres per workgroup
+constexpr int64_t kEvalTarget = 32768;  // waves of a launch
+constexpr int64_t kEvalMinLen = 48;
+struct EvalShape {
+    int S;
+    int64_t blocks, len;
+};
+EvalShape eval_shape(int64_t n, int64_t m);
+void launch_eval_records(const double* xyz, int64_t m, double eps, const double* center, int32_t call, double4* E,
+                         int32_t* flag, hipStream_t s);
+void launch_eval(const double4* X, const double* coef, int64_t n, const double4* E, int64_t m, const EvalShape& g,
+                 double* P, int64_t ldp, int32_t call, const int32_t* flag, double* u, int32_t* hflag,
+                 hipStream_t s);
 
 // predictor network (mlp_kernels.hip)
 void launch_mlp_forward(const float* params, const float* x, int B, float* y, float* hidden, hipStream_t s);

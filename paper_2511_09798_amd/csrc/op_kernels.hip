@@ -12,67 +12,6 @@
 namespace mqh {
 
 // ---------------------------------------------------------------------------
-// A span of loop nodes against one output position (the evaluation of the
-// RBF expansion): the loop index is wave-uniform, so the loop node's record
-// and weight are scalar loads and each term costs only VALU work.  Split
-// over the loop range, the partial sums go to P[slice * ldp + out] and
-// k_reduce_slices adds them in slice order.
-// ---------------------------------------------------------------------------
-
-template <typename R, int KIND>
-__device__ __forceinline__ void mf_span(const typename NodeOf<R>::type* __restrict__ X,
-                                        const double* __restrict__ w, int64_t j0, int64_t j1, R px, R py,
-                                        R pz, const EntryConst& c, double& acc0, double& acc1) {
-    int64_t j = j0;
-    for (; j + 1 < j1; j += 2) {
-        const auto q0 = X[j];
-        const auto q1 = X[j + 1];
-        const double w0 = w[j], w1 = w[j + 1];
-        const R t0 = t_of(px, py, pz, q0.x, q0.y, q0.z);
-        const R t1 = t_of(px, py, pz, q1.x, q1.y, q1.z);
-        const R e0 = KIND == 0 ? entry_interior(t0, c) : entry_boundary(t0, c);
-        const R e1 = KIND == 0 ? entry_interior(t1, c) : entry_boundary(t1, c);
-        acc0 = fma((double)e0, w0, acc0);
-        acc1 = fma((double)e1, w1, acc1);
-    }
-    if (j < j1) {
-        const auto q0 = X[j];
-        const R t0 = t_of(px, py, pz, q0.x, q0.y, q0.z);
-        const R e0 = KIND == 0 ? entry_interior(t0, c) : entry_boundary(t0, c);
-        acc0 = fma((double)e0, w[j], acc0);
-    }
-}
-
-// y_o = sum_s P[s][i] - shift * z_o with o = perm[i] (o = i when perm is
-// null; shift from *shift_ptr when given); the slices are summed in four
-// interleaved groups combined in a fixed order.
-__global__ __launch_bounds__(kBlock) void k_reduce_slices(const double* __restrict__ P, int64_t ldp, int S,
-                                                          int64_t n, const int32_t* __restrict__ perm,
-                                                          const double* __restrict__ shift_ptr, double shift_val,
-                                                          const double* __restrict__ z, double* __restrict__ y,
-                                                          const GkbState* __restrict__ st) {
-    if (st != nullptr && st->stopped) return;
-    const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (i >= n) return;
-    double a0 = 0.0, a1 = 0.0, a2 = 0.0, a3 = 0.0;
-    int k = 0;
-    for (; k + 3 < S; k += 4) {
-        a0 += P[(int64_t)k * ldp + i];
-        a1 += P[(int64_t)(k + 1) * ldp + i];
-        a2 += P[(int64_t)(k + 2) * ldp + i];
-        a3 += P[(int64_t)(k + 3) * ldp + i];
-    }
-    for (; k < S; ++k) a0 += P[(int64_t)k * ldp + i];
-    double s = (a0 + a1) + (a2 + a3);
-    const int64_t o = perm != nullptr ? (int64_t)perm[i] : i;
-    if (z != nullptr) {
-        const double sh = shift_ptr != nullptr ? *shift_ptr : shift_val;
-        s -= sh * z[o];
-    }
-    y[o] = s;
-}
-
-// ---------------------------------------------------------------------------
 // FP32-evaluated matrix-free products: the squared distances on the matrix
 // cores.
 //
@@ -1059,22 +998,82 @@ __global__ __launch_bounds__(kBlock) void k_gen_rows(const typename NodeOf<R>::t
 }
 
 // ---------------------------------------------------------------------------
-// Evaluation u(P_e) = sum_j coef_j phi(|P_e - X_j|), FP64, split over centres.
+// Evaluation u(P_e) = sum_j coef_j phi(|P_e - X_j|), FP64.  A wave takes 64 points
+// against a slice of the centres; the centre index is wave-uniform, so records and
+// coefficients are scalar loads.  The kEvalWaves slices of a workgroup are added in
+// LDS in wave order, the workgroups' sums by k_eval_reduce.  Bound by the FP64 units:
+// six operations for the squared distance, the estimate of the root, five to
+// refine it and one for the sum, about 80 cycles a wave: 610 us for 20 000 points and
+// 60 000 centres, 598 measured for the call (842 with slices of a workgroup's
+// width, six refining operations and 256 partial sums a point).
 // ---------------------------------------------------------------------------
 
-__global__ __launch_bounds__(kBlock) void k_eval_partial(const double4* __restrict__ X,
-                                                         const double* __restrict__ coef, int64_t n,
-                                                         const double4* __restrict__ E, int64_t m,
-                                                         int64_t slice_len, EntryConst c,
-                                                         double* __restrict__ P, int64_t ldp) {
+// Points as records (centred, times eps); a point that is not finite leaves the
+// call's number in *flag.
+__global__ __launch_bounds__(kBlock) void k_eval_records(const double* __restrict__ xyz, int64_t m, double eps,
+                                                         double3 center, int32_t call, double4* __restrict__ E,
+                                                         int32_t* __restrict__ flag) {
     const int64_t e = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    const bool valid = e < m;
-    const double4 p = E[valid ? e : 0];
-    const int64_t j0 = (int64_t)blockIdx.y * slice_len;
+    if (e >= m) return;
+    const double a = xyz[3 * e], b = xyz[3 * e + 1], d = xyz[3 * e + 2];
+    if (!(isfinite(a) && isfinite(b) && isfinite(d))) *flag = call;
+    E[e] = make_double4(eps * (a - center.x), eps * (b - center.y), eps * (d - center.z), 0.0);
+}
+
+// sqrt(t) for t >= 1: with s the estimate of 1/sqrt(t), h = fl(t s) and r = 1 -
+// h s, sqrt(t) = h (1 + r/2 + 3 r^2/8 + ..) up to half of h's rounding.
+__device__ __forceinline__ double sqrt_f64(double t) {
+    const double s = __builtin_amdgcn_rsq(t);
+    const double h = t * s;
+    const double r = fma(-h, s, 1.0);
+    const double p = fma(0.375, r, 0.5);
+    return fma(h * r, p, h);
+}
+
+__global__ __launch_bounds__(kEvalWaves* kWave) void k_eval_partial(const double4* __restrict__ X,
+                                                                    const double* __restrict__ coef, int64_t n,
+                                                                    const double4* __restrict__ E, int64_t m,
+                                                                    int64_t slice_len, double* __restrict__ P,
+                                                                    int64_t ldp) {
+    __shared__ double part[kEvalWaves][kWave];
+    const int lane = threadIdx.x & (kWave - 1), wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave);
+    const int64_t e = (int64_t)blockIdx.x * kWave + lane;
+    const double4 p = E[e < m ? e : 0];
+    const int64_t j0 = ((int64_t)blockIdx.y * kEvalWaves + wv) * slice_len;
     const int64_t j1 = j0 + slice_len < n ? j0 + slice_len : n;
-    double a0 = 0.0, a1 = 0.0;
-    mf_span<double, 1>(X, coef, j0, j1, p.x, p.y, p.z, c, a0, a1);
-    if (valid) P[(int64_t)blockIdx.y * ldp + e] = a0 + a1;
+    double a = 0.0;
+#pragma unroll 4
+    for (int64_t j = j0; j < j1; ++j) {
+        const double4 q = X[j];
+        a = fma(sqrt_f64(t_of(p.x, p.y, p.z, q.x, q.y, q.z)), coef[j], a);
+    }
+    part[wv][lane] = a;
+    __syncthreads();
+    if (wv == 0 && e < m) {
+#pragma unroll
+        for (int g = 1; g < kEvalWaves; ++g) a += part[g][lane];
+        P[(int64_t)blockIdx.y * ldp + e] = a;
+    }
+}
+
+// u_e = sum over the S slices, four interleaved groups combined in a fixed order;
+// nothing is written when the points' flag bears the call's number, which goes to
+// the host (pinned memory) with it.
+__global__ __launch_bounds__(kWave) void k_eval_reduce(const double* __restrict__ P, int64_t ldp, int S, int64_t m,
+                                                       int32_t call, const int32_t* __restrict__ flag,
+                                                       double* __restrict__ u, int32_t* __restrict__ hflag) {
+    const bool bad = *flag == call;
+    if (blockIdx.x == 0 && threadIdx.x == 0) *hflag = bad ? call : 0;
+    const int64_t i = (int64_t)blockIdx.x * kWave + threadIdx.x;
+    if (bad || i >= m) return;
+    double a[4] = {};
+    int k = 0;
+    for (; k + 3 < S; k += 4) {
+#pragma unroll
+        for (int g = 0; g < 4; ++g) a[g] += P[(int64_t)(k + g) * ldp + i];
+    }
+    for (; k < S; ++k) a[0] += P[(int64_t)k * ldp + i];
+    u[i] = (a[0] + a[1]) + (a[2] + a[3]);
 }
 
 // ---------------------------------------------------------------------------
@@ -1203,13 +1202,6 @@ void launch_reduce_block(const double* P, int64_t ldp, int S, int64_t n, int nrh
                                                                                        sstride, z, ldz, y, ldy, st);
 }
 
-void launch_reduce_slices(const double* P, int64_t ldp, int S, int64_t n, const int32_t* perm,
-                          const double* shift_ptr, double shift_val, const double* z, double* y,
-                          const GkbState* st, hipStream_t s) {
-    k_reduce_slices<<<(unsigned)((n + kBlock - 1) / kBlock), kBlock, 0, s>>>(P, ldp, S, n, perm, shift_ptr,
-                                                                            shift_val, z, y, st);
-}
-
 void launch_gen_rows(int prec, const void* X, int64_t n, int64_t n_int, int64_t row0, int64_t count,
                      const EntryConst& c, double* out, hipStream_t s) {
     dim3 grid((unsigned)((n + kBlock - 1) / kBlock), (unsigned)count);
@@ -1219,10 +1211,28 @@ void launch_gen_rows(int prec, const void* X, int64_t n, int64_t n_int, int64_t 
         k_gen_rows<float><<<grid, kBlock, 0, s>>>((const float4*)X, n, n_int, row0, c, out);
 }
 
-void launch_eval_partial(const double4* X, const double* coef, int64_t n, const double4* E, int64_t m, int S,
-                         int64_t slice_len, const EntryConst& c, double* P, int64_t ldp, hipStream_t s) {
-    dim3 grid((unsigned)((m + kBlock - 1) / kBlock), (unsigned)S);
-    k_eval_partial<<<grid, kBlock, 0, s>>>(X, coef, n, E, m, slice_len, c, P, ldp);
+void launch_eval_records(const double* xyz, int64_t m, double eps, const double* center, int32_t call, double4* E,
+                         int32_t* flag, hipStream_t s) {
+    k_eval_records<<<(unsigned)((m + kBlock - 1) / kBlock), kBlock, 0, s>>>(
+        xyz, m, eps, make_double3(center[0], center[1], center[2]), call, E, flag);
+}
+
+EvalShape eval_shape(int64_t n, int64_t m) {
+    EvalShape g;
+    g.blocks = (m + kWave - 1) / kWave;
+    const int64_t waves = (kEvalTarget + g.blocks - 1) / g.blocks;
+    g.len = (n + waves - 1) / waves;
+    g.len = g.len < kEvalMinLen ? kEvalMinLen : g.len;
+    g.S = (int)((n + g.len * kEvalWaves - 1) / (g.len * kEvalWaves));
+    return g;
+}
+
+void launch_eval(const double4* X, const double* coef, int64_t n, const double4* E, int64_t m, const EvalShape& g,
+                 double* P, int64_t ldp, int32_t call, const int32_t* flag, double* u, int32_t* hflag,
+                 hipStream_t s) {
+    const dim3 grid((unsigned)g.blocks, (unsigned)g.S);
+    k_eval_partial<<<grid, kEvalWaves * kWave, 0, s>>>(X, coef, n, E, m, g.len, P, ldp);
+    k_eval_reduce<<<(unsigned)((m + kWave - 1) / kWave), kWave, 0, s>>>(P, ldp, g.S, m, call, flag, u, hflag);
 }
 
 }  // namespace mqh

@@ -155,6 +155,35 @@ def test_reorthogonalisation_forms(mq, orc, n, ell):
             assert np.array_equal(g[k][key], m[key][k]), key
 
 
+@pytest.mark.parametrize("m", [1, 63, 64, 65, 1025])
+@pytest.mark.parametrize("n", [1, 48, 49, 385, 2100])
+def test_evaluation_shapes(mq, orc, n, m):
+    """Points and centres around a wave and a slice, from host and device arrays (equal
+    bit for bit), and a point that is not finite: refused, u left as it was."""
+    import torch
+
+    n_int = n // 2
+    nodes, pts, coef = I.random_nodes_cube(n, 3), I.random_nodes_cube(m, 4), I.random_vector(n, 5)
+    r2 = np.sum((pts[:, None, :] - nodes[None, :, :]) ** 2, axis=2)
+    phi = np.sqrt(1.0 + 9.0 * r2)
+    with mq.Problem(nodes[:n_int], nodes[n_int:], 9.0, 3.0, "matfree_fp64") as pr:
+        say("evaluation shapes", n, m)
+        u = pr.eval(coef, pts)
+        cd, xd, ud = torch.from_numpy(coef).cuda(), torch.from_numpy(pts).cuda(), torch.full((m,), 7.0).cuda().double()
+        torch.cuda.synchronize()
+        pr.eval(cd, xd, ud)
+        assert np.array_equal(ud.cpu().numpy(), u)
+        xd[m - 1, 2] = float("nan")
+        ud.fill_(7.0)
+        with pytest.raises(mq.MQHError):
+            pr.eval(cd, xd, ud)
+        assert bool((ud == 7.0).all())
+        xd.copy_(torch.from_numpy(pts))
+        assert np.array_equal(pr.eval(cd, xd).cpu().numpy(), u)
+    # n roundings of the sum, about eight of a term
+    assert np.all(np.abs(u - phi @ coef) <= (n + 8) * EPS * (phi @ np.abs(coef)))
+
+
 def test_products_device_pointers(mq, orc):
     import torch
 
