@@ -36,147 +36,149 @@ namespace {
 
 constexpr int kBandThreads = 1024;  // the replay kernels
 constexpr int kBandWaves = kBandThreads / kWave;
-constexpr int kChaseThreads = 512;  // the chase: two tasks per wave, 16 per pass (LDS holds the band)
+constexpr int kChaseThreads = 1024;  // the chase: one task per wave, 16 per pass (LDS holds the band)
 constexpr int kChaseWaves = kChaseThreads / kWave;
 constexpr int kStageDoubles = 8192;  // reflectors staged per chunk in the replay kernels (64 KiB)
 constexpr int kMmRows = 16;          // output rows per workgroup of k_band_mm
 
-// Orders a wave's LDS accesses across its lanes: what one lane wrote before
-// this point is seen by every lane's reads after it.
-__device__ __forceinline__ void wave_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+// Sums and maxima over the four lanes of a quad (data-parallel moves, no LDS).
+template <int CTRL>
+__device__ __forceinline__ double quad_move(double v) {
+    const int2 b = __builtin_bit_cast(int2, v);
+    return __builtin_bit_cast(double, make_int2(__builtin_amdgcn_mov_dpp(b.x, CTRL, 0xF, 0xF, true),
+                                                __builtin_amdgcn_mov_dpp(b.y, CTRL, 0xF, 0xF, true)));
+}
+__device__ __forceinline__ double quad_sum(double v) {
+    v += quad_move<0xB1>(v);  // lanes 1 0 3 2
+    v += quad_move<0x4E>(v);  // lanes 2 3 0 1
+    return v;
+}
+__device__ __forceinline__ double quad_max(double v) {
+    v = fmax(v, quad_move<0xB1>(v));
+    return fmax(v, quad_move<0x4E>(v));
 }
 
-// Tree sum and maximum of |a| over 16 values (short dependency chains).
-__device__ __forceinline__ double tree_sum16(const double (&a)[band::kMaxB]) {
-    double t[8];
-#pragma unroll
-    for (int k = 0; k < 8; ++k) t[k] = a[2 * k] + a[2 * k + 1];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) t[k] = t[2 * k] + t[2 * k + 1];
-    return (t[0] + t[1]) + (t[2] + t[3]);
-}
-__device__ __forceinline__ double tree_absmax16(const double (&a)[band::kMaxB], int k_from) {
-    double t[8];
-#pragma unroll
-    for (int k = 0; k < 8; ++k)
-        t[k] = fmax(2 * k >= k_from ? fabs(a[2 * k]) : 0.0, 2 * k + 1 >= k_from ? fabs(a[2 * k + 1]) : 0.0);
-#pragma unroll
-    for (int k = 0; k < 4; ++k) t[k] = fmax(t[2 * k], t[2 * k + 1]);
-    return fmax(fmax(t[0], t[1]), fmax(t[2], t[3]));
-}
-
-// The reflector of band.hpp for x_0 .. x_15 (0 past the reflector's length),
-// computed alike in every lane: tau, beta and sc (v_k = x_k sc for k >= 1,
-// v_0 = 1; sc = 0 when tau = 0).  NaN data make tau NaN, which the
-// acceptance test downstream rejects.
-__device__ __forceinline__ double local_reflector(const double (&x)[band::kMaxB], double* beta, double* sc) {
-    const double amax = tree_absmax16(x, 0), tmax = tree_absmax16(x, 1);
+// The reflector of band.hpp for x_0 .. x_15 (0 past the reflector's length), lane
+// q of a quad holding x_{4q} .. x_{4q+3}, computed alike in every quad: tau and
+// beta, v_k over x_k (v_0 = 1).  x is scaled by a power of two, not by its
+// largest entry.  NaN data make tau NaN, which the acceptance test
+// downstream rejects.
+__device__ __forceinline__ double quad_reflector(const double (&x)[4], int q, double (&v)[4], double* beta) {
+    const double x0 = __builtin_bit_cast(double, make_int2(
+        __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int2, x[0]).x, 0x00, 0xF, 0xF, true),
+        __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int2, x[0]).y, 0x00, 0xF, 0xF, true)));
+    double t = fmax(fmax(q == 0 ? 0.0 : fabs(x[0]), fabs(x[1])), fmax(fabs(x[2]), fabs(x[3])));
+    const double tmax = quad_max(t);
     if (!(tmax > 0.0)) {
-        *beta = x[0];
-        *sc = 0.0;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) v[k] = (q == 0 && k == 0) ? 1.0 : 0.0;
+        *beta = x0;
         return 0.0;
     }
-    const double inv = 1.0 / amax;
-    double a[band::kMaxB];
+    const int ex = __builtin_amdgcn_frexp_exp(fmax(fabs(x0), tmax));
+    double ss = 0.0;
 #pragma unroll
-    for (int k = 0; k < band::kMaxB; ++k) {
-        const double y = x[k] * inv;
-        a[k] = y * y;
+    for (int k = 0; k < 4; ++k) {
+        const double y = __builtin_amdgcn_ldexp(x[k], -ex);
+        ss = fma(y, y, ss);
     }
-    const double nrm = amax * sqrt(tree_sum16(a));
-    const double bt = x[0] >= 0.0 ? -nrm : nrm;
-    *sc = 1.0 / (x[0] - bt);
+    ss = quad_sum(ss);
+    const double rs = rsqrt_f64(ss);  // 1/4 <= ss < 16
+    const double nrm = __builtin_amdgcn_ldexp(ss * rs, ex);
+    const double bt = x0 >= 0.0 ? -nrm : nrm;
+    const double sc = 1.0 / (x0 - bt);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) v[k] = x[k] * sc;
+    if (q == 0) v[0] = 1.0;
     *beta = bt;
-    return (bt - x[0]) / bt;
+    const double ib = __builtin_amdgcn_ldexp(rs, -ex);  // 1 / |bt|
+    return (bt - x0) * (x0 >= 0.0 ? -ib : ib);
 }
 
-// y <- (I - tau v v^T) y on n <= 16 entries at y[k * ys], v_k = x_k sc
-// (v_0 = 1, v_k = 0 for k >= n); tree dot product.  No branch per entry:
-// entries k >= n are read at y[(n - 1) ys] (their v_k is 0) and written to
-// the scratch slot sink.
-__device__ __forceinline__ void local_apply(const double (&x)[band::kMaxB], double sc, double tau, int n, double* y,
-                                            int64_t ys, double* sink) {
-    double yv[band::kMaxB], pr[band::kMaxB];
+// Vectors j = 0 .. nv - 1 (at most 32) of n <= 16 entries, entry k of vector j at
+// y[j js + k ks]: vector 0 becomes (beta, 0, ..), the others lose tau v (v^T y).
+// Quad l / 4 takes vectors l / 4 and l / 4 + 16, lane q its entries 4 q .. + 3 (v_k =
+// 0 for k >= n; those are read at entry n - 1 and written to the sink).
+__device__ __forceinline__ void quad_apply(const double (&v)[4], double tau, double beta, int n, int nv, double* y,
+                                           int js, int ks, int lane, double* sink) {
+    const int q = lane & 3;
 #pragma unroll
-    for (int k = 0; k < band::kMaxB; ++k) {
-        yv[k] = y[(k < n ? k : n - 1) * ys];
-        pr[k] = (k == 0 ? 1.0 : x[k] * sc) * yv[k];
-    }
-    const double tw = tau * tree_sum16(pr);
+    for (int h = 0; h < 2; ++h) {
+        const int j = (lane >> 2) + 16 * h;
+        if (16 * h >= nv) break;  // uniform
+        double* yj = y + (j < nv ? j : 0) * js;
+        double a[4];
 #pragma unroll
-    for (int k = 0; k < band::kMaxB; ++k) {
-        double* dst = k < n ? y + k * ys : sink;
-        *dst = fma(-tw, k == 0 ? 1.0 : x[k] * sc, yv[k]);
-    }
-}
-
-// y[0] = beta, y[k * ys] = 0 for 0 < k < n (entries k >= n to sink).
-__device__ __forceinline__ void local_set(double beta, int n, double* y, int64_t ys, double* sink) {
+        for (int k = 0; k < 4; ++k) a[k] = yj[(4 * q + k < n ? 4 * q + k : n - 1) * ks];
+        const double tw = tau * quad_sum(fma(v[0], a[0], v[1] * a[1]) + fma(v[2], a[2], v[3] * a[3]));
 #pragma unroll
-    for (int k = 0; k < band::kMaxB; ++k) {
-        double* dst = k < n ? y + k * ys : sink;
-        *dst = k == 0 ? beta : 0.0;
+        for (int k = 0; k < 4; ++k) {
+            const double set = (q == 0 && k == 0) ? beta : 0.0;
+            double* dst = (j < nv && 4 * q + k < n) ? yj + (4 * q + k) * ks : sink;
+            *dst = j == 0 ? set : fma(-tw, v[k], a[k]);
+        }
     }
 }
 
-// Up to two tasks of the chase per wave, one per half-wave (hl = lane % 32):
-// task (i, t) when on, its reflectors to rr and ll (b + 1 doubles each:
-// v_0 .. v_{b-1}, tau); vsh: the half-wave's 16 doubles of LDS, through
-// which its lanes get the reflector's data.  One lane per row (right
-// reflector) or column (left reflector), at most 2 b <= 32 of them.
-__device__ void chase_task(double* B, int N, int Mc, int b, bool on, int i, int t, double* __restrict__ rr,
-                           double* __restrict__ ll, double* vsh, double* sink, int hl) {
-    int r0 = 0, c0 = 0, c1 = 0;
-    if (on) band::task_cols(i, t, b, Mc, r0, c0, c1);
-    const int nj = on ? c1 - c0 + 1 : 0, r1 = c1 < N - 1 ? c1 : N - 1;
-    const int64_t cs = band::width(b) - 1;  // from (r, c) to (r + 1, c)
-    double x[band::kMaxB], beta, sc;
+// Task (i, t) of the chase on one wave, its reflectors to rr and ll (b + 1 doubles
+// each: v_0 .. v_{b-1}, tau).  Four lanes share a row (right reflector) or column
+// (left reflector) of at most 2 b <= 32.  A step's time is the issue and the latency of
+// one task, so its instructions count: 655 us for the 340 steps of N = 112, b = 16,
+// against 1010 with a lane per row, whose 16 entries it walked through.
+__device__ void chase_task(double* B, int N, int Mc, int b, int i, int t, double* __restrict__ rr,
+                           double* __restrict__ ll, double* sink, int lane) {
+    int r0, c0, c1;
+    band::task_cols(i, t, b, Mc, r0, c0, c1);
+    const int nj = c1 - c0 + 1, r1 = c1 < N - 1 ? c1 : N - 1;
+    const int W = band::width(b), cs = W - 1;  // from (r, c) to (r + 1, c)
+    const int q = lane & 3;
+    double x[4], v[4], beta;
     // right reflector from row r0
-    double xk = 0.0;
-    if (hl < band::kMaxB) {
-        xk = hl < nj ? B[band::at(r0, c0 + hl, b)] : 0.0;
-        vsh[hl] = xk;
-    }
-    wave_sync();
+    {
+        double* row = B + band::at(r0, c0, b);
 #pragma unroll
-    for (int k = 0; k < band::kMaxB; ++k) x[k] = vsh[k];
-    const double tau = local_reflector(x, &beta, &sc);
-    if (on) {
-        if (hl < b) rr[hl] = hl == 0 ? 1.0 : xk * sc;
-        if (hl == b) rr[b] = tau;
-    }
-    if (on && tau != 0.0 && hl <= r1 - r0) {
-        if (hl == 0)
-            local_set(beta, nj, B + band::at(r0, c0, b), 1, sink);
-        else
-            local_apply(x, sc, tau, nj, B + band::at(r0 + hl, c0, b), 1, sink);
+        for (int k = 0; k < 4; ++k) {
+            const double a = row[4 * q + k < nj ? 4 * q + k : 0];
+            x[k] = 4 * q + k < nj ? a : 0.0;
+        }
+        const double tau = quad_reflector(x, q, v, &beta);
+        if (lane < 4) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                if (4 * q + k < b) rr[4 * q + k] = v[k];
+            if (q == 0) rr[b] = tau;
+        }
+        wave_sync();  // row r0 has been read
+        if (tau != 0.0) {
+            // vector j is row r0 for j = 0 and rows r0 + 1 .. r1 after it
+            quad_apply(v, tau, beta, nj, r1 - r0 + 1, row, cs, 1, lane, sink);
+        }
     }
     wave_sync();
     // left reflector from column c0, rows c0 .. r1
-    const int ni = on ? r1 - c0 + 1 : 0;
-    xk = 0.0;
-    if (hl < band::kMaxB) {
-        xk = hl < ni ? B[band::at(c0 + hl, c0, b)] : 0.0;
-        vsh[hl] = xk;
-    }
-    wave_sync();
+    const int ni = r1 - c0 + 1;
+    double* col = B + band::at(c0, c0, b);
 #pragma unroll
-    for (int k = 0; k < band::kMaxB; ++k) x[k] = vsh[k];
-    const double tau2 = ni >= 2 ? local_reflector(x, &beta, &sc) : 0.0;
-    if (on) {
-        if (hl < b) ll[hl] = hl == 0 ? 1.0 : (ni >= 2 ? xk * sc : 0.0);
-        if (hl == b) ll[b] = tau2;
+    for (int k = 0; k < 4; ++k) {
+        const double a = col[(4 * q + k < ni ? 4 * q + k : 0) * cs];
+        x[k] = 4 * q + k < ni ? a : 0.0;
+    }
+    double tau2 = 0.0;
+    if (ni >= 2) {
+        tau2 = quad_reflector(x, q, v, &beta);
+    } else {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) v[k] = (q == 0 && k == 0) ? 1.0 : 0.0;
+    }
+    if (lane < 4) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            if (4 * q + k < b) ll[4 * q + k] = v[k];
+        if (q == 0) ll[b] = tau2;
     }
     const int ce = c1 + b < Mc - 1 ? c1 + b : Mc - 1;
-    if (on && tau2 != 0.0 && hl <= ce - c0) {
-        if (hl == 0)
-            local_set(beta, ni, B + band::at(c0, c0, b), cs, sink);
-        else
-            local_apply(x, sc, tau2, ni, B + band::at(c0, c0 + hl, b), cs, sink);
-    }
+    wave_sync();
+    if (tau2 != 0.0) quad_apply(v, tau2, beta, ni, ce - c0 + 1, col, 1, cs, lane, sink);
     wave_sync();
 }
 
@@ -242,40 +244,31 @@ __global__ __launch_bounds__(kChaseThreads) void k_band_chase(const double* __re
                                                              double* __restrict__ d, double* __restrict__ e) {
     __shared__ double B[kBandLdsDoubles];
     __shared__ int32_t cntw[2][kChaseWaves];
-    __shared__ double vsh[kChaseWaves][2][band::kMaxB];
+    __shared__ int16_t ntask[kMaxEll];    // tasks of every sweep
     __shared__ double sink[kChaseWaves];  // written, never read
-    const int tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
-    const int half = lane >> 5, hl = lane & 31;
+    const int tid = threadIdx.x, lane = tid & (kWave - 1);
+    const int wv = __builtin_amdgcn_readfirstlane(tid / kWave);
     const int W = band::width(b);
     for (int64_t idx = tid; idx < (int64_t)N * W; idx += kChaseThreads) {
         const int r = (int)(idx / W), o = (int)(idx - (int64_t)r * W);
         const int c = r + o - (b - 1);
         B[idx] = (c >= r && c <= r + b && c < Mc) ? C[(int64_t)c * ldc + r] : 0.0;
     }
+    for (int i = tid; i < N; i += kChaseThreads) ntask[i] = (int16_t)band::ntasks(i, N, Mc, b);
     __syncthreads();
     int q0 = 0;
     for (int s = 0; s < T; ++s) {
         // the step's sweeps are ihi, ihi - 1, ... while they have a task at
         // this step (a contiguous range of ranks q = ihi - i); wave wv takes
-        // ranks 2 wv, 2 wv + 1, then 2 kChaseWaves further on, one per half-wave
+        // ranks wv, wv + kChaseWaves, ..
         const int ihi = band::step_top(s, N, Mc);
         int mine = 0;
-        for (int p = wv;; p += kChaseWaves) {
-            bool on[2];
-            int ii[2], tt[2];
-#pragma unroll
-            for (int e = 0; e < 2; ++e) {
-                const int q = 2 * p + e;
-                ii[e] = ihi - q;
-                tt[e] = s - band::kLag * ii[e];
-                on[e] = ii[e] >= 0 && tt[e] < band::ntasks(ii[e], N, Mc, b);
-            }
-            if (!on[0]) break;
-            const int q = 2 * p + half;
-            chase_task(B, N, Mc, b, on[half], ii[half], tt[half], RR + (int64_t)(q0 + q) * (b + 1),
-                       LL + (int64_t)(q0 + q) * (b + 1), vsh[wv][half], &sink[wv], hl);
-            mine += on[1] ? 2 : 1;
-            if (!on[1]) break;
+        for (int q = wv; q <= ihi; q += kChaseWaves) {
+            const int i = ihi - q, t = s - band::kLag * i;
+            if (t >= ntask[i]) break;
+            chase_task(B, N, Mc, b, i, t, RR + (int64_t)(q0 + q) * (b + 1), LL + (int64_t)(q0 + q) * (b + 1),
+                       &sink[wv], lane);
+            ++mine;
         }
         if (lane == 0) cntw[s & 1][wv] = mine;
         if (tid == 0) toff[s] = q0;

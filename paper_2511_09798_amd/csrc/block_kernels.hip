@@ -5,13 +5,13 @@
 // Two tall-skinny contractions carry the reorthogonalisation against a
 // shared basis of m columns (m = s j at step j) and the block QR:
 //   c = V^T P   (m x s, K = n rows)        -- k_blk_gemvt + k_blk_reduce
-//   P -= V c, or P = V c                   -- k_blk_update
+//   P -= V c, or P = V c                   -- k_blk_update (with P^T P on request)
 // both on the FP64 matrix cores (v_mfma_f64_16x16x4f64: lane l supplies
 // A[l%16][l/16] and B[l/16][l%16] and receives D[4r + l/16][l%16]).  The
 // block QR is shifted Cholesky QR applied three times (the shift in the
 // first pass keeps the Cholesky factorisation defined for nearly dependent
 // columns; the two unshifted passes restore orthogonality to rounding):
-// k_blk_chol factors one 16 x 16 Gram matrix on one workgroup.
+// k_blk_chol adds the parts of one 16 x 16 Gram matrix and factors it.
 
 #include <float.h>
 #include <math.h>
@@ -91,171 +91,247 @@ __global__ __launch_bounds__(kBlock) void k_blk_reduce(const double* __restrict_
     if (lane == 0) c[e] = v;
 }
 
-// Rows [16 (4 x + w), + 16) of the s output columns, per wave:
+// Rows of the s output columns, 16 per wave and turn:
 //   sub = 1: P[k][i] -= sum_col V[col][i] c[col cs + k ks]
 //   sub = 0: P[k][i]  = sum_col V[col][i] c[col cs + k ks]
 // (V may be P itself for sub = 0: a wave reads all its rows before it
-// writes them, and no two waves share a row).  No barrier: waves past n
-// return at once.
-__global__ __launch_bounds__(kBlock) void k_blk_update(const double* V, int64_t ldv, int64_t n, int32_t m,
+// writes them, and no two waves share a row).  Workgroup x takes rows
+// [x chunk, (x + 1) chunk), chunk a multiple of the rows of a turn.  With GRAM it also leaves its part
+// of the Gram matrix of the columns it writes, in the layout of k_blk_gemvt for m =
+// s: the new values are the operands of the products as the lanes hold them, so
+// the pass of k_blk_gemvt over P and its launch are saved (6.3 + 5.6 -> 6.5 us
+// at 20 000 rows, m = s = 16).
+constexpr int kGramThreads = 512;
+constexpr int64_t kGramRowsPer = 16 * (kGramThreads / kWave);  // rows of a workgroup in one turn
+
+template <bool GRAM, int NT>
+__global__ __launch_bounds__(NT) void k_blk_update(const double* V, int64_t ldv, int64_t n, int32_t m,
                                                        const double* __restrict__ c, int64_t cs, int64_t ks,
-                                                       double* P, int64_t ldp, int32_t s, int32_t sub) {
+                                                       double* P, int64_t ldp, int32_t s, int32_t sub, int64_t chunk,
+                                                       double* __restrict__ part) {
     const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
     const int li = lane & 15, lk = lane >> 4;
-    const int64_t row0 = ((int64_t)blockIdx.x * (kBlock / kWave) + w) * 16;
-    if (row0 >= n) return;
-    const int64_t row = row0 + li;
-    const bool rok = row < n;
-    v4d acc = v4d{0.0, 0.0, 0.0, 0.0};
-    for (int kk = 0; kk < m; kk += 4) {
-        const int col = kk + lk;
-        const bool cok = col < m;
-        // A[i][k'] = V[col kk + k'][row0 + i], B[k'][j] = c[col kk + k'][j]
-        const double a = (rok && cok) ? V[(int64_t)col * ldv + row] : 0.0;
-        const double b = (cok && li < s) ? c[(int64_t)col * cs + (int64_t)li * ks] : 0.0;
-        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, acc, 0, 0, 0);
+    const int64_t r0 = (int64_t)blockIdx.x * chunk;
+    const int64_t r1 = r0 + chunk < n ? r0 + chunk : n;
+    v4d gram = v4d{0.0, 0.0, 0.0, 0.0};
+    for (int64_t row0 = r0 + 16 * w; row0 < r1; row0 += 16 * (NT / kWave)) {
+        const int64_t row = row0 + li;
+        const bool rok = row < n;
+        v4d acc = v4d{0.0, 0.0, 0.0, 0.0};
+        for (int kk = 0; kk < m; kk += 4) {
+            const int col = kk + lk;
+            const bool cok = col < m;
+            // A[i][k'] = V[col kk + k'][row0 + i], B[k'][j] = c[col kk + k'][j]
+            const double a = (rok && cok) ? V[(int64_t)col * ldv + row] : 0.0;
+            const double b = (cok && li < s) ? c[(int64_t)col * cs + (int64_t)li * ks] : 0.0;
+            acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, acc, 0, 0, 0);
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int64_t rr = row0 + 4 * r + lk;
+            const bool in = li < s && rr < n;
+            double* dst = P + (int64_t)(in ? li : 0) * ldp + (in ? rr : row0);
+            const double v = sub ? *dst - acc[r] : acc[r];
+            if (in) *dst = v;
+            acc[r] = in ? v : 0.0;
+        }
+        if (GRAM) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) gram = __builtin_amdgcn_mfma_f64_16x16x4f64(acc[r], acc[r], gram, 0, 0, 0);
+        }
     }
-    if (li >= s) return;
+    if (GRAM) {
+        __shared__ double g[NT / kWave][kBlkRhs][kBlkRhs + 1];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) g[w][4 * r + lk][li] = gram[r];
+        __syncthreads();
+        const int i = threadIdx.x / kBlkRhs, k = threadIdx.x % kBlkRhs;
+        if (i >= s) return;
+        double v = g[0][i][k];
+#pragma unroll
+        for (int q = 1; q < NT / kWave; ++q) v += g[q][i][k];
+        part[((int64_t)blockIdx.x * s + i) * kBlkRhs + k] = v;
+    }
+}
+static_assert(kGramThreads >= kBlkRhs * kBlkRhs, "one entry of the Gram matrix per thread");
+
+// What the block QR's last pass does with the factor (no host round trip per step).
+// kind 0: E_1 (the data's factor, kept in E1; a diagonal entry at most tau
+// times its largest, or a failed factorisation, marks the sources invalid);
+// kind 1: D_j = R^T of step j; kind 2: E_{j+1} = R.  For kinds 1 and 2 the
+// running scale is the largest diagonal entry of the D and E blocks so far; a
+// failed factorisation or a diagonal entry at most tau times the scale stops
+// the run (ell_done = j - 1 at a D block, j at an E block, flag = kind).
+// Otherwise the block goes into C (row-major, ld ldc) and its transpose (16 x
+// 16, the update kernel's coefficient layout) into mat, the coefficients of
+// the next shift.  Once stopped, nothing is written.  One wave; R: the factor in LDS.
+__device__ void blk_check(const double (*R)[kBlkRhs + 1], bool bad, int32_t s, const BlkCheck& ck) {
+    const int lane = threadIdx.x, j = ck.j;
+    BlkState* bs = ck.bs;
+    const double d = fabs(R[lane & 15][lane & 15]);
+    double mn = (lane & 15) < s ? d : HUGE_VAL, mx = (lane & 15) < s ? d : 0.0;
+    // NaN loses every comparison, as in a scan of the diagonal
+    mn = mn < HUGE_VAL ? mn : HUGE_VAL;
+    mx = mx > 0.0 ? mx : 0.0;
+#pragma unroll
+    for (int o = 8; o > 0; o >>= 1) {
+        const double a = __shfl_xor(mn, o, kWave), b = __shfl_xor(mx, o, kWave);
+        mn = a < mn ? a : mn;
+        mx = b > mx ? b : mx;
+    }
+    const double scale = bs->scale;
+    bool ok = bs->stopped == 0;
+    if (!ok) return;
+    if (ck.kind == 0) {
+        ok = !bad && mn > ck.tau * mx;
+        if (!ok && lane == 0) {
+            bs->invalid = 1;
+            bs->stopped = 1;
+            bs->ell_done = 0;
+        }
+    } else {
+        const double sc = mx > scale ? mx : scale;
+        ok = !bad && mn > ck.tau * sc;
+        if (lane == 0) {
+            if (!ok) {
+                bs->stopped = 1;
+                bs->ell_done = ck.kind == 1 ? j - 1 : j;
+                bs->flag = ck.kind;
+            } else {
+                bs->scale = sc;
+            }
+        }
+    }
+    if (!ok) return;
+    for (int q = lane; q < kBlkRhs * kBlkRhs; q += kWave) {
+        const int r = q / kBlkRhs, c = q % kBlkRhs;
+        const double v = R[r][c];
+        const bool in = r < s && c < s;
+        ck.mat[c * kBlkRhs + r] = in ? v : 0.0;
+        if (!in) continue;
+        if (ck.kind == 0)
+            ck.E1[r * s + c] = v;
+        else if (ck.kind == 1)
+            ck.C[(int64_t)((j - 1) * s + c) * ck.ldc + (j - 1) * s + r] = v;  // D_j = R^T
+        else
+            ck.C[(int64_t)(j * s + r) * ck.ldc + (j - 1) * s + c] = v;  // E_{j+1} = R
+    }
+}
+
+// One pass (0, 1, 2) of (shifted) Cholesky QR on one workgroup.  All threads add the
+// chunks' parts of G (c layout, G[i 16 + j] = P_i . P_j, i, j < s), thread group
+// q the chunks q, q + kCholGroups, ..; one wave does the rest.  G plus, in pass 0,
+// 11 (n s + s (s + 1)) eps trace(G) on the diagonal is factored as R^T R by row
+// elimination, lane (j, g) = (l % 16, l / 16) with rows 4 g .. + 3 of column j; the
+// same operations take the identity to R^{-T}, so no substitution follows.
+// Rinv = R^{-1} in the c layout of k_blk_update (Rinv[col 16 + k]); Racc <- R Racc
+// (row-major 16 x 16, the accumulated triangular factor, from the identity in pass
+// 0).  status (0 at pass 0) <- 1 if a pivot is not positive and finite; Racc and Rinv
+// are then left as they were.  Pass 2 ends with blk_check.
+// 12.5 us with 157 parts, most of it their way to one compute unit and the columns'
+// chain, in place of a reduction of 4.7, a factorisation of 13.3 (three barriers
+// a column, a serial substitution) and a third of the launches for the identity
+// (4.3) and the breakdown test (4.4).
+constexpr int kCholGroups = 4;
+
+__global__ __launch_bounds__(kCholGroups* kBlkRhs* kBlkRhs) void k_blk_chol(
+    const double* __restrict__ part, int chunks, int32_t s, int64_t n, int32_t pass, double* __restrict__ Rinv,
+    double* __restrict__ Racc, int32_t* __restrict__ status, BlkCheck ck) {
+    __shared__ double G[kCholGroups][kBlkRhs * kBlkRhs];
+    __shared__ double R[kBlkRhs][kBlkRhs + 1], Q[kBlkRhs][kBlkRhs + 1];
+    {
+        const int e = threadIdx.x % (kBlkRhs * kBlkRhs), q = threadIdx.x / (kBlkRhs * kBlkRhs);
+        double v = 0.0;
+        if (e < s * kBlkRhs) {
+            const double* pe = part + e;
+#pragma unroll 8
+            for (int c = q; c < chunks; c += kCholGroups) v += pe[(int64_t)c * s * kBlkRhs];
+        }
+        G[q][e] = v;
+    }
+    __syncthreads();
+    if (threadIdx.x >= kWave) return;
+    const int lane = threadIdx.x, j = lane & 15, g = lane >> 4;
+    double m[4], y[4];  // entries (4 g + r, j)
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-        const int64_t rr = row0 + 4 * r + lk;
-        if (rr < n) {
-            double* dst = P + (int64_t)li * ldp + rr;
-            *dst = sub ? *dst - acc[r] : acc[r];
-        }
+        const int i = 4 * g + r, e = i * kBlkRhs + j;
+        double v = G[0][e];
+#pragma unroll
+        for (int q = 1; q < kCholGroups; ++q) v += G[q][e];
+        m[r] = (i < s && j < s) ? v : 0.0;
+        y[r] = i == j ? 1.0 : 0.0;
+        Q[i][j] = pass == 0 ? y[r] : Racc[e];
     }
-}
-
-// One pass of (shifted) Cholesky QR on one workgroup of 256 threads, thread
-// (i, j) = (t / 16, t % 16) owning entry (i, j) of the 16 x 16 tiles in LDS:
-// G (c layout, G[i 16 + j] = P_i . P_j, i, j < s) plus, if shifted,
-// 11 (n s + s (s + 1)) eps trace(G) on the diagonal is factored as R^T R
-// (R upper triangular, right-looking: per column a pivot, a row of R, a
-// rank-one update of the trailing block); Rinv = R^{-1} (back substitution,
-// column j by thread j) in the c layout of k_blk_update (Rinv[col 16 + k]);
-// Racc <- R Racc (row-major 16 x 16, the accumulated triangular factor).
-// status <- 1 if a pivot is not positive and finite (Racc and Rinv are then
-// left as they were).
-__global__ __launch_bounds__(kBlock) void k_blk_chol(const double* __restrict__ G, int32_t s, int64_t n,
-                                                     int32_t shifted, double* __restrict__ Rinv,
-                                                     double* __restrict__ Racc, int32_t* __restrict__ status) {
-    __shared__ double M[kBlkRhs][kBlkRhs];  // the trailing matrix, then R
-    __shared__ double X[kBlkRhs][kBlkRhs];  // R^{-1}
-    __shared__ double red[kBlock / kWave];
-    __shared__ int bad;
-    const int i = threadIdx.x / kBlkRhs, j = threadIdx.x % kBlkRhs;
-    const bool in = i < s && j < s;
-    const double g = in ? G[i * kBlkRhs + j] : 0.0;
-    double tr = (in && i == j) ? g : 0.0;
-    tr = block_sum<kBlock>(tr, red);
-    const double shift = shifted ? 11.0 * ((double)n * s + (double)s * (s + 1)) * DBL_EPSILON * tr : 0.0;
-    M[i][j] = in ? g + (i == j ? shift : 0.0) : 0.0;
-    X[i][j] = 0.0;
-    if (threadIdx.x == 0) bad = 0;
-    __syncthreads();
+    bool bad = pass != 0 && *status != 0;
+    if (pass == 0) {
+        double tr = 0.0;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) tr += 4 * g + r == j ? m[r] : 0.0;
+        tr = wave_sum(tr);
+        const double shift = 11.0 * ((double)n * s + (double)s * (s + 1)) * DBL_EPSILON * tr;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) m[r] += (4 * g + r == j && j < s) ? shift : 0.0;
+    }
+    bool fail = false;
+    // a rolled loop: the code is fetched once, and cold
+#pragma unroll 1
     for (int c = 0; c < s; ++c) {
-        if (threadIdx.x == 0) {
-            const double d = M[c][c];
-            if (!(d > 0.0) || !isfinite(d)) bad = 1;
-            M[c][c] = (d > 0.0 && isfinite(d)) ? sqrt(d) : 1.0;
+        const int rc = c & 3;
+        if (g == c >> 2) {  // row c to every lane
+            R[0][j] = rc == 0 ? m[0] : rc == 1 ? m[1] : rc == 2 ? m[2] : m[3];
+            R[1][j] = rc == 0 ? y[0] : rc == 1 ? y[1] : rc == 2 ? y[2] : y[3];
         }
-        __syncthreads();
-        if (i == c && j > c && j < s) M[c][j] /= M[c][c];  // row c of R
-        __syncthreads();
-        if (i > c && j >= i && j < s) M[i][j] -= M[c][i] * M[c][j];  // trailing upper triangle
-        __syncthreads();
+        wave_sync();
+        const double d = R[0][c];
+        double rj = R[0][j], yj = R[1][j], ri[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) ri[r] = R[0][4 * g + r];
+        const bool pos = d > 0.0 && isfinite(d);
+        fail = fail || !pos;
+        const double inv = pos ? rsqrt_f64(d) : 1.0;
+        rj *= inv;
+        yj *= inv;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int i = 4 * g + r;
+            const double f = i > c ? -ri[r] * inv : 0.0;
+            m[r] = i == c ? rj : fma(f, rj, m[r]);
+            y[r] = i == c ? yj : fma(f, yj, y[r]);
+        }
+        wave_sync();
     }
-    if (bad) {
-        if (threadIdx.x == 0) *status = 1;
-        return;
-    }
-    // R = upper triangle of M; R^{-1} column by column (thread j < s)
-    if (threadIdx.x < s) {
-        const int cj = threadIdx.x;
-        for (int r = cj; r >= 0; --r) {
-            double v = (r == cj) ? 1.0 : 0.0;
-            for (int k = r + 1; k <= cj; ++k) v -= M[r][k] * X[k][cj];
-            X[r][cj] = v / M[r][r];
+    if (!fail) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int i = 4 * g + r;
+            R[i][j] = i <= j ? m[r] : 0.0;
+            // row i of R^{-T} is column i of R^{-1}
+            Rinv[j * kBlkRhs + i] = (j <= i && i < s) ? y[r] : 0.0;
+        }
+        wave_sync();
+        v4d acc = v4d{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int k = 0; k < kBlkRhs; k += 4)
+            acc = __builtin_amdgcn_mfma_f64_16x16x4f64(R[j][k + g], Q[k + g][j], acc, 0, 0, 0);
+        wave_sync();
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int i = 4 * r + g;
+            if (i < s && j < s) Q[i][j] = j >= i ? acc[r] : 0.0;
         }
     }
-    __syncthreads();
-    Rinv[i * kBlkRhs + j] = X[i][j];
-    // Racc <- R Racc (upper triangular), entry (i, j) by thread (i, j)
-    double v = 0.0;
-    if (in && j >= i)
-        for (int k = i; k <= j; ++k) v += M[i][k] * Racc[k * kBlkRhs + j];
-    __syncthreads();  // every thread has read Racc
-    if (in) Racc[i * kBlkRhs + j] = j >= i ? v : 0.0;
-}
-
-// Racc <- identity (row-major 16 x 16), status <- 0.
-__global__ void k_blk_eye(double* __restrict__ Racc, int32_t* __restrict__ status) {
-    const int e = threadIdx.x;
-    if (e < kBlkRhs * kBlkRhs) Racc[e] = (e / kBlkRhs == e % kBlkRhs) ? 1.0 : 0.0;
-    if (e == 0) *status = 0;
-}
-
-// The breakdown test of a block QR on the device (no host round trip per
-// step).  kind 0: E_1 (the data's factor, kept in E1; a diagonal entry at
-// most tau times its largest, or a failed factorisation, marks the sources
-// invalid); kind 1: D_j = R^T of step j; kind 2: E_{j+1} = R.  For kinds 1
-// and 2 the running scale is the largest diagonal entry of the D and E blocks
-// so far; a failed factorisation or a diagonal entry at most tau times the
-// scale stops the run (ell_done = j - 1 at a D block, j at an E block, flag =
-// kind).  Otherwise the block goes into C (row-major, ld ldc) and its
-// transpose (16 x 16, the update kernel's coefficient layout) into mat, the
-// coefficients of the next shift.  Once stopped, nothing is written.
-__global__ __launch_bounds__(kBlkRhs * kBlkRhs) void k_blk_check(const double* __restrict__ Racc,
-                                                                 const int32_t* __restrict__ status, int32_t s,
-                                                                 int32_t kind, int32_t j, double tau,
-                                                                 BlkState* __restrict__ bs, double* __restrict__ C,
-                                                                 int64_t ldc, double* __restrict__ E1,
-                                                                 double* __restrict__ mat) {
-    __shared__ int s_ok;
-    if (threadIdx.x == 0) {
-        int ok = bs->stopped ? 0 : 1;
-        if (ok) {
-            double mn = HUGE_VAL, mx = 0.0;
-            for (int i = 0; i < s; ++i) {
-                const double d = fabs(Racc[i * kBlkRhs + i]);
-                mn = d < mn ? d : mn;
-                mx = d > mx ? d : mx;
-            }
-            const bool bad = *status != 0;
-            if (kind == 0) {
-                if (bad || !(mn > tau * mx)) {
-                    bs->invalid = 1;
-                    bs->stopped = 1;
-                    bs->ell_done = 0;
-                    ok = 0;
-                }
-            } else {
-                const double sc = mx > bs->scale ? mx : bs->scale;
-                if (bad || !(mn > tau * sc)) {
-                    bs->stopped = 1;
-                    bs->ell_done = kind == 1 ? j - 1 : j;
-                    bs->flag = kind;
-                    ok = 0;
-                } else {
-                    bs->scale = sc;
-                }
-            }
+    wave_sync();
+    if (!fail || pass == 0) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int i = 4 * g + r;
+            Racc[i * kBlkRhs + j] = Q[i][j];
         }
-        s_ok = ok;
     }
-    __syncthreads();
-    if (!s_ok) return;
-    const int r = threadIdx.x / kBlkRhs, c = threadIdx.x % kBlkRhs;
-    const double v = Racc[r * kBlkRhs + c];
-    const bool in = r < s && c < s;
-    mat[c * kBlkRhs + r] = in ? v : 0.0;
-    if (!in) return;
-    if (kind == 0)
-        E1[r * s + c] = v;
-    else if (kind == 1)
-        C[(int64_t)((j - 1) * s + c) * ldc + (j - 1) * s + r] = v;  // D_j = R^T
-    else
-        C[(int64_t)(j * s + r) * ldc + (j - 1) * s + c] = v;  // E_{j+1} = R
+    bad = bad || fail;
+    if (lane == 0 && (pass == 0 || fail)) *status = bad ? 1 : 0;
+    if (pass == 2) blk_check(Q, bad, s, ck);
 }
 
 }  // namespace
@@ -285,18 +361,38 @@ void launch_blk_gemvt(const double* V, int64_t ldv, int64_t n, int32_t m, const 
 void launch_blk_update(const double* V, int64_t ldv, int64_t n, int32_t m, const double* c, int64_t cs, int64_t ks,
                        double* P, int64_t ldp, int32_t s, int32_t sub, hipStream_t st) {
     const int64_t rows_per_block = 16 * (kBlock / kWave);
-    k_blk_update<<<(unsigned)((n + rows_per_block - 1) / rows_per_block), kBlock, 0, st>>>(V, ldv, n, m, c, cs, ks, P,
-                                                                                         ldp, s, sub);
+    k_blk_update<false, kBlock><<<(unsigned)((n + rows_per_block - 1) / rows_per_block), kBlock, 0, st>>>(
+        V, ldv, n, m, c, cs, ks, P, ldp, s, sub, rows_per_block, nullptr);
 }
 
-void launch_blk_chol(const double* G, int32_t s, int64_t n, int32_t shifted, double* Rinv, double* Racc,
-                     int32_t* status, hipStream_t st) {
-    k_blk_chol<<<1, kBlock, 0, st>>>(G, s, n, shifted, Rinv, Racc, status);
+// Workgroups (and rows of each) of an update that leaves the Gram matrix: at most
+// 256 parts for the next k_blk_chol to add.
+static int gram_chunks(int64_t n, int64_t* chunk) {
+    int64_t ch = (n + 255) / 256;
+    ch = (ch + kGramRowsPer - 1) / kGramRowsPer * kGramRowsPer;
+    *chunk = ch;
+    return (int)((n + ch - 1) / ch);
 }
 
-void launch_blk_check(const double* Racc, const int32_t* status, int32_t s, int32_t kind, int32_t j, double tau,
-                      BlkState* bs, double* C, int64_t ldc, double* E1, double* mat, hipStream_t st) {
-    k_blk_check<<<1, kBlkRhs * kBlkRhs, 0, st>>>(Racc, status, s, kind, j, tau, bs, C, ldc, E1, mat);
+int launch_blk_update_gram(const double* V, int64_t ldv, int64_t n, int32_t m, const double* c, int64_t cs, int64_t ks,
+                           double* P, int64_t ldp, int32_t s, int32_t sub, double* part, hipStream_t st) {
+    int64_t chunk;
+    const int chunks = gram_chunks(n, &chunk);
+    k_blk_update<true, kGramThreads>
+        <<<(unsigned)chunks, kGramThreads, 0, st>>>(V, ldv, n, m, c, cs, ks, P, ldp, s, sub, chunk, part);
+    return chunks;
+}
+
+int launch_blk_gram(const double* P, int64_t ldp, int64_t n, int32_t s, double* part, hipStream_t st) {
+    int64_t chunk;
+    const int chunks = blk_chunks(n, s, &chunk);
+    k_blk_gemvt<<<dim3((unsigned)chunks, 1), kBlock, 0, st>>>(P, ldp, n, s, P, ldp, s, chunk, part);
+    return chunks;
+}
+
+void launch_blk_chol(const double* part, int chunks, int32_t s, int64_t n, int32_t pass, double* Rinv, double* Racc,
+                     int32_t* status, const BlkCheck& ck, hipStream_t st) {
+    k_blk_chol<<<1, kCholGroups * kBlkRhs * kBlkRhs, 0, st>>>(part, chunks, s, n, pass, Rinv, Racc, status, ck);
 }
 
 // The Jacobi route's work matrix of the projected problem from the device
@@ -317,10 +413,6 @@ void launch_blk_fill_g(const double* C, int64_t ldc, int64_t m, int64_t ls, cons
                        int64_t ldg, hipStream_t st) {
     const unsigned gx = (unsigned)((ls + kBlock - 1) / kBlock);
     k_blk_fill_g<<<dim3(gx, (unsigned)m), kBlock, 0, st>>>(C, ldc, m, ls, E1, s, G, ldg);
-}
-
-void launch_blk_eye(double* Racc, int32_t* status, hipStream_t st) {
-    k_blk_eye<<<1, kBlkRhs * kBlkRhs, 0, st>>>(Racc, status);
 }
 
 }  // namespace mqh

@@ -1394,7 +1394,6 @@ struct BlockWs {
     double* P = nullptr;     // ldn x 16 work block
     double* part = nullptr;  // split-K partials of V^T P
     double* c = nullptr;     // m x 16 coefficients
-    double* G = nullptr;     // 16 x 16 Gram matrix
     double* Rinv = nullptr;  // 16 x 16
     double* Racc = nullptr;  // 16 x 16 accumulated R
     double* mat = nullptr;   // two 16 x 16 shift blocks (c layout), written by the QR checks
@@ -1411,7 +1410,6 @@ struct BlockWs {
         dfree(P);
         dfree(part);
         dfree(c);
-        dfree(G);
         dfree(Rinv);
         dfree(Racc);
         dfree(mat);
@@ -1431,7 +1429,7 @@ int block_alloc(mqh_problem* p, BlockWs& b, int32_t s, int32_t ell) {
     int rc;
     if ((rc = dalloc(&b.W, (size_t)((int64_t)mmax * ldn))) || (rc = dalloc(&b.Z, (size_t)((int64_t)ell * s * ldn))) ||
         (rc = dalloc(&b.P, (size_t)(kBlkRhs * ldn))) || (rc = dalloc(&b.part, (size_t)(most * kBlkRhs))) ||
-        (rc = dalloc(&b.c, (size_t)mmax * kBlkRhs)) || (rc = dalloc(&b.G, kBlkRhs * kBlkRhs)) ||
+        (rc = dalloc(&b.c, (size_t)mmax * kBlkRhs)) ||
         (rc = dalloc(&b.Rinv, kBlkRhs * kBlkRhs)) || (rc = dalloc(&b.Racc, kBlkRhs * kBlkRhs)) ||
         (rc = dalloc(&b.mat, 2 * kBlkRhs * kBlkRhs)) || (rc = dalloc(&b.status, 1)) ||
         (rc = dalloc(&b.Cd, (size_t)mmax * (size_t)ell * s)) || (rc = dalloc(&b.E1d, kBlkRhs * kBlkRhs)) ||
@@ -1550,40 +1548,42 @@ int block_ws(mqh_problem* p, int32_t s, int32_t ell, BlockWs** out) {
     return MQH_OK;
 }
 
-// Q R = X in place (X: n x s, leading dimension ldn) by shifted Cholesky QR
-// three times; R (s x s, row-major, upper triangular) to the host.  *bad is
-// set when a Cholesky factorisation fails (X numerically zero or not finite).
-// Cholesky QR of the s columns of X in place (three passes, the first
-// shifted), then the breakdown test and the bookkeeping of the factor on
-// the device (k_blk_check: kind 0 for E_1, 1 for D_j, 2 for E_{j+1}); the
-// factor's transpose goes to shift slot `slot` of b.mat.
-void block_qr(mqh_problem* p, BlockWs& b, double* X, int32_t s, int32_t kind, int32_t j, int32_t ell, int slot) {
+// Cholesky QR of the s columns of X, Q to `to` (X itself, or other columns): three
+// passes, the first shifted, then the breakdown test and the bookkeeping of
+// the factor on the device (kind 0 for E_1, 1 for D_j, 2 for E_{j+1}); the
+// factor's transpose goes to shift slot `slot` of b.mat.  chunks: the parts of X's
+// Gram matrix that the update that formed X left in b.part (0: none).
+void block_qr(mqh_problem* p, BlockWs& b, double* X, double* to, int32_t s, int32_t kind, int32_t j, int32_t ell,
+              int slot, int chunks) {
     hipStream_t st = p->stream;
     const int64_t n = p->n, ldn = p->ldn;
-    launch_blk_eye(b.Racc, b.status, st);
+    const BlkCheck ck{kind, j, (double)n * DBL_EPSILON, b.bs, b.Cd, (int64_t)ell * s, b.E1d,
+                      b.mat + slot * kBlkRhs * kBlkRhs};
+    if (chunks == 0) chunks = launch_blk_gram(X, ldn, n, s, b.part, st);
     for (int pass = 0; pass < 3; ++pass) {
-        launch_blk_gemvt(X, ldn, n, s, X, ldn, s, b.part, b.G, st);
-        launch_blk_chol(b.G, s, n, pass == 0 ? 1 : 0, b.Rinv, b.Racc, b.status, st);
-        launch_blk_update(X, ldn, n, s, b.Rinv, kBlkRhs, 1, X, ldn, s, 0, st);
+        launch_blk_chol(b.part, chunks, s, n, pass, b.Rinv, b.Racc, b.status, ck, st);
+        if (pass < 2)
+            chunks = launch_blk_update_gram(X, ldn, n, s, b.Rinv, kBlkRhs, 1, X, ldn, s, 0, b.part, st);
+        else
+            launch_blk_update(X, ldn, n, s, b.Rinv, kBlkRhs, 1, to, ldn, s, 0, st);
     }
-    launch_blk_check(b.Racc, b.status, s, kind, j, (double)n * DBL_EPSILON, b.bs, b.Cd, (int64_t)ell * s, b.E1d,
-                     b.mat + slot * kBlkRhs * kBlkRhs, st);
 }
 
 // X -= V M with M the device coefficients in shift slot `slot` of b.mat (the
-// transpose of the QR factor k_blk_check left there).
+// transpose of the QR factor that its last pass left there).
 void block_shift_dev(mqh_problem* p, BlockWs& b, const double* V, int32_t s, double* X, int slot) {
     launch_blk_update(V, p->ldn, p->n, s, b.mat + slot * kBlkRhs * kBlkRhs, kBlkRhs, 1, X, p->ldn, s, 1, p->stream);
 }
 
-// X -= V (V^T X) twice, V the first m columns of a basis.
-void block_cgs2(mqh_problem* p, BlockWs& b, const double* V, int32_t m, int32_t s, double* X) {
-    if (m <= 0) return;
+// X -= V (V^T X) twice, V the first m columns of a basis; the Gram matrix of the
+// result to b.part.  Returns its parts (0 for m = 0).
+int block_cgs2(mqh_problem* p, BlockWs& b, const double* V, int32_t m, int32_t s, double* X) {
+    if (m <= 0) return 0;
     hipStream_t st = p->stream;
-    for (int pass = 0; pass < 2; ++pass) {
-        launch_blk_gemvt(V, p->ldn, p->n, m, X, p->ldn, s, b.part, b.c, st);
-        launch_blk_update(V, p->ldn, p->n, m, b.c, kBlkRhs, 1, X, p->ldn, s, 1, st);
-    }
+    launch_blk_gemvt(V, p->ldn, p->n, m, X, p->ldn, s, b.part, b.c, st);
+    launch_blk_update(V, p->ldn, p->n, m, b.c, kBlkRhs, 1, X, p->ldn, s, 1, st);
+    launch_blk_gemvt(V, p->ldn, p->n, m, X, p->ldn, s, b.part, b.c, st);
+    return launch_blk_update_gram(V, p->ldn, p->n, m, b.c, kBlkRhs, 1, X, p->ldn, s, 1, b.part, st);
 }
 
 // The block recurrence from the block already in W's first s columns:
@@ -1608,7 +1608,7 @@ int run_gkb_block(mqh_problem* p, BlockWs& b, int32_t s, int32_t ell, std::vecto
     C.assign(host_c ? csize : 0, 0.0);
     HIPCHK(hipMemsetAsync(b.Cd, 0, csize * sizeof(double), st));
     HIPCHK(hipMemsetAsync(b.bs, 0, sizeof(BlkState), st));
-    block_qr(p, b, b.W, s, 0, 0, ell, 0);
+    block_qr(p, b, b.W, b.W, s, 0, 0, ell, 0, 0);
     for (int32_t j = 1; j <= ell; ++j) {
         double* Wj = b.W + (int64_t)(j - 1) * s * ldn;
         double* Zj = b.Z + (int64_t)(j - 1) * s * ldn;
@@ -1616,16 +1616,13 @@ int run_gkb_block(mqh_problem* p, BlockWs& b, int32_t s, int32_t ell, std::vecto
         int rc;
         if ((rc = block_product(p, s, 1, Wj, ldn, nullptr, 0, nullptr, 0, b.P, nullptr, false))) return rc;
         if (j > 1) block_shift_dev(p, b, Zj - (int64_t)s * ldn, s, b.P, 0);
-        block_cgs2(p, b, b.Z, (j - 1) * s, s, b.P);
-        block_qr(p, b, b.P, s, 1, j, ell, 1);  // D_j = R^T into C; the shift below reads slot 1
-        HIPCHK(hipMemcpyAsync(Zj, b.P, (size_t)s * ldn * sizeof(double), hipMemcpyDeviceToDevice, st));
+        int parts = block_cgs2(p, b, b.Z, (j - 1) * s, s, b.P);
+        block_qr(p, b, b.P, Zj, s, 1, j, ell, 1, parts);  // D_j = R^T into C; the shift below reads slot 1
         // Q = A Z_j - W_j D_j, reorthogonalised against W_1 .. W_j
         if ((rc = block_product(p, s, 0, Zj, ldn, nullptr, 0, nullptr, 0, b.P, nullptr, false))) return rc;
         block_shift_dev(p, b, Wj, s, b.P, 1);
-        block_cgs2(p, b, b.W, j * s, s, b.P);
-        block_qr(p, b, b.P, s, 2, j, ell, 0);  // E_{j+1} = R, the next step's shift
-        HIPCHK(hipMemcpyAsync(Wj + (int64_t)s * ldn, b.P, (size_t)s * ldn * sizeof(double), hipMemcpyDeviceToDevice,
-                              st));
+        parts = block_cgs2(p, b, b.W, j * s, s, b.P);
+        block_qr(p, b, b.P, Wj + (int64_t)s * ldn, s, 2, j, ell, 0, parts);  // E_{j+1} = R, the next step's shift
     }
     LAUNCHCHK("block Golub-Kahan");
     BlkState h{};

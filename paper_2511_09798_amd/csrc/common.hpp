@@ -57,6 +57,14 @@ __device__ __forceinline__ void store_nt(double* p, v2d v) {
 }
 __device__ __forceinline__ v2d load2(const double* p) { return *reinterpret_cast<const v2d*>(p); }
 
+// Orders a wave's LDS accesses across its lanes: what one lane wrote before
+// this point is seen by every lane's reads after it.
+__device__ __forceinline__ void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // ---------------------------------------------------------------------------
 // Deterministic reductions (fixed butterfly / fixed order, no atomics)
 // ---------------------------------------------------------------------------

@@ -348,17 +348,28 @@ void launch_blk_gemvt(const double* V, int64_t ldv, int64_t n, int32_t m, const 
                       double* part, double* c, hipStream_t st);
 void launch_blk_update(const double* V, int64_t ldv, int64_t n, int32_t m, const double* c, int64_t cs, int64_t ks,
                        double* P, int64_t ldp, int32_t s, int32_t sub, hipStream_t st);
-void launch_blk_chol(const double* G, int32_t s, int64_t n, int32_t shifted, double* Rinv, double* Racc,
-                     int32_t* status, hipStream_t st);
-void launch_blk_eye(double* Racc, int32_t* status, hipStream_t st);
+// P^T P in parts (chunks x s x 16), alone or of the columns an update writes; both
+// return the chunks, at most blk_chunks(n, s)
+int launch_blk_gram(const double* P, int64_t ldp, int64_t n, int32_t s, double* part, hipStream_t st);
+int launch_blk_update_gram(const double* V, int64_t ldv, int64_t n, int32_t m, const double* c, int64_t cs, int64_t ks,
+                           double* P, int64_t ldp, int32_t s, int32_t sub, double* part, hipStream_t st);
 // Device state of a block Golub-Kahan run: the breakdown test of every QR
 // without a host round trip.
 struct BlkState {
     int32_t stopped, ell_done, flag, invalid;
     double scale;
 };
-void launch_blk_check(const double* Racc, const int32_t* status, int32_t s, int32_t kind, int32_t j, double tau,
-                      BlkState* bs, double* C, int64_t ldc, double* E1, double* mat, hipStream_t st);
+// What the last pass of a block QR does with the factor.
+struct BlkCheck {
+    int32_t kind, j;
+    double tau;
+    BlkState* bs;
+    double* C;
+    int64_t ldc;
+    double *E1, *mat;
+};
+void launch_blk_chol(const double* part, int chunks, int32_t s, int64_t n, int32_t pass, double* Rinv, double* Racc,
+                     int32_t* status, const BlkCheck& ck, hipStream_t st);
 // G (zero) <- [C | (E1; 0)]: the Jacobi route's work matrix from the device copies of C and E1
 void launch_blk_fill_g(const double* C, int64_t ldc, int64_t m, int64_t ls, const double* E1, int32_t s, double* G,
                        int64_t ldg, hipStream_t st);

@@ -966,13 +966,26 @@ __global__ __launch_bounds__(kBlock) void k_reduce_block(const double* __restric
     if (st != nullptr && st[k].stopped) return;
     const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     if (i >= n) return;
+    // eight slices in flight, added evens and odds apart
+    const double* Pk = P + (int64_t)k * ldp + i;
+    const int64_t ss = (int64_t)kBlkRhs * ldp;
     double a0 = 0.0, a1 = 0.0;
     int sl = 0;
-    for (; sl + 1 < S; sl += 2) {
-        a0 += P[((int64_t)sl * kBlkRhs + k) * ldp + i];
-        a1 += P[((int64_t)(sl + 1) * kBlkRhs + k) * ldp + i];
+    for (; sl + 8 <= S; sl += 8) {
+        double v[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) v[q] = Pk[(sl + q) * ss];
+#pragma unroll
+        for (int q = 0; q < 8; q += 2) {
+            a0 += v[q];
+            a1 += v[q + 1];
+        }
     }
-    if (sl < S) a0 += P[((int64_t)sl * kBlkRhs + k) * ldp + i];
+    for (; sl + 1 < S; sl += 2) {
+        a0 += Pk[sl * ss];
+        a1 += Pk[(sl + 1) * ss];
+    }
+    if (sl < S) a0 += Pk[sl * ss];
     double v = a0 + a1;
     const int64_t o = perm[i];
     if (z != nullptr) v -= shift[k * sstride] * z[k * ldz + o];

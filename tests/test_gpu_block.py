@@ -103,6 +103,30 @@ def test_block_gkb_against_oracle(mq, blk, case, mode):
     assert np.max(np.abs(g["E1"] - o.E1)) <= 1e-13 * np.abs(o.E1).max()
 
 
+@pytest.mark.parametrize("n,s,ell", [(130, 1, 3), (129, 16, 3), (1025, 15, 4), (257, 2, 40), (33100, 3, 2)])
+def test_block_shapes(mq, n, s, ell):
+    """Rows around and past a workgroup's share of the Gram matrix, one source to sixteen: the block relations
+    and orthonormal bases, and the band path's singular values against LAPACK's of the same C."""
+    n_int = int(0.8 * n)
+    p = I.cube_scaled(n_int, n - n_int, kappa=12.0, eps=3.4, ell=ell)
+    F = np.stack([I.random_vector(n, 40 + k) for k in range(s)])
+    with mq.Problem(p.x_int, p.x_bnd, p.kappa, p.eps, "matfree_fp64") as pr:
+        say("block shapes", n, s, ell)
+        g = pr.gkb_block(F, ell, want_bases=True)
+        AZ = np.stack([pr.apply(z) for z in np.ascontiguousarray(g["Z"])], axis=1)
+        out = pr.solve_block(F, ell, want_sv=True)
+    C, W, Z = g["C"], g["W"].T, g["Z"].T
+    nc = np.linalg.norm(C, 2)
+    assert g["status"] == 0 and g["ell_done"] == ell
+    assert np.linalg.norm(AZ - W @ C) <= 1e-12 * nc
+    assert np.linalg.norm(W[:, :s] @ g["E1"] - F.T) <= 1e-13 * np.linalg.norm(F)
+    assert np.max(np.abs(W.T @ W - np.eye(W.shape[1]))) <= 1e-12
+    assert np.max(np.abs(Z.T @ Z - np.eye(Z.shape[1]))) <= 1e-12
+    assert not np.any(out.flags & mq.MQH_INFO_BLOCK_JACOBI)
+    sv = np.linalg.svd(C, compute_uv=False)
+    assert np.max(np.abs(out.sv[: ell * s] - sv)) <= 64 * (ell + 1) * s * EPS * sv[0]
+
+
 @pytest.fixture(scope="module")
 def blobs(case):
     # five Gaussian-blob sources (the sweep's kind) with 1e-3 seeded noise: at 16 block steps
