@@ -184,6 +184,35 @@ def test_evaluation_shapes(mq, orc, n, m):
     assert np.all(np.abs(u - phi @ coef) <= (n + 8) * EPS * (phi @ np.abs(coef)))
 
 
+@pytest.mark.parametrize("mode", ["stored_fp64", "matfree_fp64", "matfree_fp32"])
+@pytest.mark.parametrize("trans", [False, True])
+def test_products_in_place_vectors(mq, mode, trans):
+    """Device vectors read and written where they are: at an odd element, z the output itself, z one element off
+    it, and x the output; the bits of the staged product of host arrays every time."""
+    import torch
+
+    n = 1003
+    nodes, x, z = I.random_nodes_cube(n, 8), I.random_vector(n, 5), I.random_vector(n, 6)
+    with mq.Problem(nodes[:700], nodes[700:], 9.0, 3.0, mode) as pr:
+        say("products in place", mode, trans)
+        ref = pr.apply(x, trans=trans, shift=0.7, z=z)
+        buf = torch.zeros(4 * n, dtype=torch.float64, device="cuda:0")
+        xd, zd = buf[1:n + 1], buf[n + 2:2 * n + 2]
+        yd = buf[2 * n + 5:3 * n + 5]
+
+        def run(xv, zv, yv):
+            xv.copy_(torch.from_numpy(x))
+            zv.copy_(torch.from_numpy(z))
+            torch.cuda.synchronize()
+            mq.mqh_apply(pr.h, trans, xv, 0.7, zv, yv)
+            return yv.cpu().numpy()
+
+        assert np.array_equal(run(xd, zd, yd), ref)
+        assert np.array_equal(run(xd, yd, yd), ref)
+        assert np.array_equal(run(xd, zd, buf[n + 3:2 * n + 3]), ref)
+        assert np.array_equal(run(xd, zd, xd), ref)
+
+
 def test_products_device_pointers(mq, orc):
     import torch
 
