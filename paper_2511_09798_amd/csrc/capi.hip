@@ -233,7 +233,7 @@ struct mqh_problem {
     // the single-vector FP32 products over unordered node pairs: work items,
     // their tables, and the row / column partials of a product
     SymLayout sym{};
-    int2* sym_items = nullptr;
+    int4* sym_items = nullptr;
     int32_t* sym_first = nullptr;
     double* sym_row = nullptr;
     double* sym_col = nullptr;
@@ -458,7 +458,7 @@ int64_t sym_col_blocks(const SymLayout& L) {
 // than CUs blocks of 64.  Whole products, us: 20 000 nodes 174 with (1, 4), 178
 // (2, 4), 230 (4, 8), 462 (8, 14); 70 000 nodes 1645 (4, 8), 1659 (1, 4), 1769
 // (8, 14); 1 800 nodes 32 with blocks of 64, 37 with 128.
-void sym_tables(int64_t n, int64_t n_int, bool fp64, SymLayout& L, std::vector<int2>& items,
+void sym_tables(int64_t n, int64_t n_int, bool fp64, SymLayout& L, std::vector<int4>& items,
                 std::vector<int32_t>& first) {
     struct Shape {
         int blk, F, Lb, want;
@@ -481,7 +481,7 @@ void sym_tables(int64_t n, int64_t n_int, bool fp64, SymLayout& L, std::vector<i
         for (int k = 0; k < L.nsr; ++k) {
             first.push_back((int32_t)items.size());
             const int nseg = (L.nb - k * L.F + L.Lb - 1) / L.Lb;
-            for (int sg = 0; sg < nseg; ++sg) items.push_back(make_int2(k, sg));
+            for (int sg = 0; sg < nseg; ++sg) items.push_back(make_int4(k, sg, (int32_t)items.size(), 0));
         }
         first.push_back((int32_t)items.size());
         L.nitems = (int32_t)items.size();
@@ -489,14 +489,14 @@ void sym_tables(int64_t n, int64_t n_int, bool fp64, SymLayout& L, std::vector<i
     }
     // launch order: items by their number of block pairs, largest first
     // (stable), so the last workgroups to start are the short ones
-    auto pairs = [&](const int2& it) {
+    auto pairs = [&](const int4& it) {
         const int b0 = it.x * L.F, b1 = std::min(b0 + L.F, L.nb);
         const int c0 = b0 + it.y * L.Lb, c1 = std::min(c0 + L.Lb, L.nb);
         int64_t cnt = 0;
         for (int b = b0; b < b1; ++b) cnt += std::max(0, c1 - std::max(c0, b));
         return cnt;
     };
-    std::stable_sort(items.begin(), items.end(), [&](const int2& a, const int2& b) { return pairs(a) > pairs(b); });
+    std::stable_sort(items.begin(), items.end(), [&](const int4& a, const int4& b) { return pairs(a) > pairs(b); });
 }
 
 // One product y = op(A) x - shift z on device vectors (x, z of length ldn,
@@ -2014,14 +2014,14 @@ int mqh_problem_create(const double* x_int, int64_t n_int, const double* x_bnd, 
                 return bail(hip_fail(e, "upload of the sorted layout"));
         }
         if ((e = hipStreamSynchronize(p->stream))) return bail(hip_fail(e, "upload of the sorted layout"));
-        std::vector<int2> items;
+        std::vector<int4> items;
         std::vector<int32_t> first;
         sym_tables(n, n_int, op_mode == MQH_OP_MATFREE_FP64, p->sym, items, first);
         if ((rc = dalloc(&p->sym_items, items.size())) || (rc = dalloc(&p->sym_first, first.size())) ||
             (rc = dalloc(&p->sym_row, items.size() * (size_t)(p->sym.F * p->sym.blk))) ||
             (rc = dalloc(&p->sym_col, (size_t)sym_col_blocks(p->sym) * (size_t)p->sym.blk)))
             return bail(rc);
-        if ((e = hipMemcpyAsync(p->sym_items, items.data(), items.size() * sizeof(int2), hipMemcpyHostToDevice,
+        if ((e = hipMemcpyAsync(p->sym_items, items.data(), items.size() * sizeof(int4), hipMemcpyHostToDevice,
                                 p->stream)) ||
             (e = hipMemcpyAsync(p->sym_first, first.data(), first.size() * sizeof(int32_t), hipMemcpyHostToDevice,
                                 p->stream)) ||

@@ -57,6 +57,14 @@ __device__ __forceinline__ void store_nt(double* p, v2d v) {
 }
 __device__ __forceinline__ v2d load2(const double* p) { return *reinterpret_cast<const v2d*>(p); }
 
+// A value that later code needs from a load: waits for it where this stands.  The
+// kernels of a run load what they need together with the run's state and branch on
+// the state behind it, so that one memory latency covers both; without this
+// the compiler moves such loads behind the branch.
+__device__ __forceinline__ void arrived(double& v) { asm volatile("" : "+v"(v)); }
+__device__ __forceinline__ void arrived(int& v) { asm volatile("" : "+v"(v)); }
+__device__ __forceinline__ void arrived_uniform(int& v) { asm volatile("" : "+s"(v)); }
+
 // Orders a wave's LDS accesses across its lanes: what one lane wrote before
 // this point is seen by every lane's reads after it.
 __device__ __forceinline__ void wave_sync() {

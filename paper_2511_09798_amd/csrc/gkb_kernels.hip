@@ -97,7 +97,6 @@ __global__ __launch_bounds__(kBlock) void k_finalize_scale(const double* __restr
                                                            const double* __restrict__ x, double* __restrict__ dst,
                                                            SortedOut so, Bz bz) {
     __shared__ double lds[kBlock / kWave];
-    __shared__ int s_stopped;
     const int64_t z = blockIdx.y;  // batch: partial + z bz.a, alpha, beta + z bz.b, x + z bz.c, dst + z bz.d, state z
     partial += z * bz.a;
     alpha += z * bz.b;
@@ -106,21 +105,30 @@ __global__ __launch_bounds__(kBlock) void k_finalize_scale(const double* __restr
     dst += z * bz.d;
     st += z;
     const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (threadIdx.x == 0) s_stopped = st->snap_stopped;
-    __syncthreads();
-    if (s_stopped) {  // block-uniform
-        if (so.Vg != nullptr && i < n) so.Vg[(int64_t)so.iperm[i] * kBlkRhs + z] = 0.f;
+    // all loads of the kernel together
+    int stop = st->snap_stopped, ip = 0;
+    double scale = st->snap_scale, xi = 0.0, s = 0.0;
+    if (i < n) {
+        xi = x[i];
+        if (so.iperm != nullptr) ip = so.iperm[i];
+    }
+    for (int q = threadIdx.x; q < nparts; q += kBlock) s += partial[q];
+    arrived(s);
+    arrived(scale);
+    arrived(xi);
+    arrived(ip);
+    arrived(stop);
+    if (stop) {  // block-uniform
+        if (so.Vg != nullptr && i < n) so.Vg[(int64_t)ip * kBlkRhs + z] = 0.f;
         return;
     }
-    double s = 0.0;
-    for (int q = threadIdx.x; q < nparts; q += kBlock) s += partial[q];
     s = block_sum<kBlock>(s, lds);
     const double nrm = sqrt(s);
     bool ok;
     if (kind == 0) {
         ok = nrm > 0.0;
     } else {
-        const double tau = (double)n * DBL_EPSILON * st->snap_scale;
+        const double tau = (double)n * DBL_EPSILON * scale;
         ok = nrm > tau;
     }
     if (blockIdx.x == 0 && threadIdx.x == 0) {
@@ -149,18 +157,18 @@ __global__ __launch_bounds__(kBlock) void k_finalize_scale(const double* __restr
                 beta[j + 1] = nrm;
             }
         }
-        if (ok && kind != 0 && nrm > st->snap_scale) st->scale = nrm;
+        if (ok && kind != 0 && nrm > scale) st->scale = nrm;
     }
     if (i >= n) return;
     if (!ok) {
-        if (so.Vg != nullptr) so.Vg[(int64_t)so.iperm[i] * kBlkRhs + z] = 0.f;
+        if (so.Vg != nullptr) so.Vg[(int64_t)ip * kBlkRhs + z] = 0.f;
         return;
     }
-    const double d = x[i] / nrm;
+    const double d = xi / nrm;
     dst[i] = d;
-    if (so.Vg != nullptr) so.Vg[(int64_t)so.iperm[i] * kBlkRhs + z] = (float)d;
-    if (so.xs32 != nullptr) so.xs32[so.iperm[i]].w = (float)d;
-    if (so.xs64 != nullptr) so.xs64[so.iperm[i]].w = d;
+    if (so.Vg != nullptr) so.Vg[(int64_t)ip * kBlkRhs + z] = (float)d;
+    if (so.xs32 != nullptr) so.xs32[ip].w = (float)d;
+    if (so.xs64 != nullptr) so.xs64[ip].w = d;
 }
 
 // ---------------------------------------------------------------------------
@@ -196,7 +204,7 @@ __global__ __launch_bounds__(kBlock) void k_gemvt_partial(const double* __restri
     x += z * bz.b;
     partial += z * bz.c;
     if (st != nullptr) st += z;
-    if (st != nullptr && st->stopped) return;  // uniform over the grid
+    int stop = st != nullptr ? st->stopped : 0;
     const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
     const int64_t ib = (int64_t)blockIdx.x * kGtRows + w * (2 * kWave) + 2 * lane;
     const int k0 = blockIdx.y * kGtCols;
@@ -226,7 +234,10 @@ __global__ __launch_bounds__(kBlock) void k_gemvt_partial(const double* __restri
             const v2d a = load2(v + off[q]);
             acc[cc] = fma(a.y, x1[q], fma(a.x, x0[q], acc[cc]));
         }
+        arrived(acc[cc]);
     }
+    arrived_uniform(stop);
+    if (stop) return;  // uniform over the grid
 #pragma unroll
     for (int cc = 0; cc < kGtCols; ++cc) {
         const double sc = wave_sum(acc[cc]);
@@ -249,12 +260,15 @@ __global__ __launch_bounds__(kBlock) void k_gemvt_reduce(const double* __restric
     partial += z * bz.a;
     c += z * bz.b;
     if (st != nullptr) st += z;
-    if (st != nullptr && st->stopped) return;
+    int stop = st != nullptr ? st->stopped : 0;
     const int lane = threadIdx.x & (kWave - 1);
     const int k = blockIdx.x * (kBlock / kWave) + threadIdx.x / kWave;
     if (k >= m) return;  // wave-uniform; no barriers
     double s = 0.0;
     for (int b = lane; b < nb; b += kWave) s += partial[(int64_t)b * sb + (int64_t)k * sk];
+    arrived(s);
+    arrived_uniform(stop);
+    if (stop) return;
     s = wave_sum(s);
     if (lane == 0) c[k] = s;
 }
@@ -295,7 +309,7 @@ __global__ __launch_bounds__(kBlock) void k_coef(const double* __restrict__ part
     const int64_t z = blockIdx.y;  // batch: partial + z bz.a, c + z bz.b, state z
     partial += z * bz.a;
     c += z * bz.b;
-    if (st != nullptr && st[z].stopped) return;
+    int stop = st != nullptr ? st[z].stopped : 0;
     const int q = threadIdx.x % kCoefCols, g = threadIdx.x / kCoefCols;
     const int k = (int)blockIdx.x * kCoefCols + q, groups = coef_groups(m);
     if (g < groups && k < m) {
@@ -304,6 +318,8 @@ __global__ __launch_bounds__(kBlock) void k_coef(const double* __restrict__ part
         for (int b = g; b < nb; b += groups) s += partial[(int64_t)b * m + k];
         sums[g][q] = s;
     }
+    arrived_uniform(stop);
+    if (stop) return;
     __syncthreads();
     if (g == 0 && k < m) {
         double s = sums[0][q];
@@ -337,7 +353,7 @@ __global__ __launch_bounds__(kBlock) void k_update(const double* __restrict__ V,
         st->snap_stopped = st->stopped;
         st->snap_scale = st->scale;
     }
-    if (st != nullptr && st->stopped) return;  // uniform over the grid
+    int stop = st != nullptr ? st->stopped : 0;
     const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
     const int64_t i0 = (int64_t)blockIdx.x * kUpdRows + 2 * lane;  // i0 even, so i0 + 1 < ldn when i0 < n
     double s0 = 0.0, s1 = 0.0, t0 = 0.0, t1 = 0.0;
@@ -362,12 +378,16 @@ __global__ __launch_bounds__(kBlock) void k_update(const double* __restrict__ V,
     }
     part[w][2 * lane] = s0 + t0;
     part[w][2 * lane + 1] = s1 + t1;
-    __syncthreads();
-    double xi = 0.0;
     const int64_t i = (int64_t)blockIdx.x * kUpdRows + threadIdx.x;
+    double xi = 0.0;
+    if (threadIdx.x < kUpdRows && i < n) xi = x[i];
+    arrived(xi);
+    arrived_uniform(stop);
+    if (stop) return;  // uniform over the grid
+    __syncthreads();
     if (threadIdx.x < kUpdRows && i < n) {
         const int t = threadIdx.x;
-        xi = x[i] - (((part[0][t] + part[1][t]) + part[2][t]) + part[3][t]);
+        xi = xi - (((part[0][t] + part[1][t]) + part[2][t]) + part[3][t]);
         x[i] = xi;
     }
     if (sumsq_partial != nullptr) {
@@ -522,8 +542,13 @@ __global__ __launch_bounds__(kSmThreads) void k_cgs_small(const double* __restri
         st->snap_stopped = st->stopped;
         st->snap_scale = st->scale;
     }
-    if (st->stopped) return;  // uniform over the grid
+    int stop = st->stopped;
     const int rp = t % kFuPairs;
+    double xr = 0.0;  // the first wave's rows of x, each in two lanes
+    if (t < kWave) {
+        const int64_t i = (int64_t)b * kFuRows + t % kFuRows;
+        if (i < n) xr = x[i];
+    }
     if (t < kBlock) {
         const int64_t i0 = (int64_t)b * kFuRows + 2 * rp;
         const double* v = V + (i0 < n ? i0 : 0);  // a pair past n reads rows 0, 1; one that straddles n the zero padding
@@ -539,6 +564,9 @@ __global__ __launch_bounds__(kSmThreads) void k_cgs_small(const double* __restri
     } else if (t - kBlock < m) {
         cs[t - kBlock] = c[t - kBlock];
     }
+    arrived(xr);
+    arrived(stop);
+    if (stop) return;  // uniform over the grid
     __syncthreads();
     if (RED) {
         if (t < m) cs[t] = coef_of_groups(&part[0][0], m, t);
@@ -562,7 +590,7 @@ __global__ __launch_bounds__(kSmThreads) void k_cgs_small(const double* __restri
         const int64_t i = (int64_t)b * kFuRows + row;
         double xi = 0.0;
         if (i < n) {
-            xi = x[i] - sum;
+            xi = xr - sum;
             if (h == 0) x[i] = xi;
         }
         if (NORM) {

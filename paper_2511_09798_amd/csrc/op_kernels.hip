@@ -246,9 +246,12 @@ __global__ __launch_bounds__(kBlock) void k_mfs(const float4* __restrict__ XS, S
     __shared__ float lds_w[kMfmChunk];
     __shared__ float lds_col[2 * (kBlock / kWave)][kMfmChunk];  // per (wave, lane-group pair)
     __shared__ double colacc[kSymMaxLb * kMfmFixed];
-    if (st != nullptr && st->stopped) return;
-    const int2 item = L.items[blockIdx.x];  // launch order: the largest items first
-    const int64_t slot = (int64_t)L.item_first[item.x] + item.y;  // the item's place in the partials
+    int4 item = L.items[blockIdx.x];  // launch order: the largest items first
+    int stop = st != nullptr ? st->stopped : 0;
+    arrived_uniform(item.x);
+    arrived_uniform(stop);
+    if (stop) return;
+    const int64_t slot = item.z;
     const int b0 = item.x * L.F;
     const int b1 = b0 + L.F < L.nb ? b0 + L.F : L.nb;
     const int c0 = b0 + item.y * L.Lb;
@@ -260,10 +263,22 @@ __global__ __launch_bounds__(kBlock) void k_mfs(const float4* __restrict__ XS, S
     float k2 = c.k2f, e2x2 = c.e2x2f, e2 = c.e2f;
     asm volatile("" : "+v"(k2), "+v"(e2x2), "+v"(e2));
     double* red = reinterpret_cast<double*>(lds_b);  // 64 rows x 17 (padded) doubles, between chunks
+    // a chunk: two whole blocks of one class, or one (the own square, a short block)
+    auto chunk_end = [&](int cb, int fb) {
+        const bool two = cb != fb && cb + 1 < c1 && (cb + 1 < L.nb_int) == (cb < L.nb_int) &&
+                         sym_blk_end(cb, L) - sym_blk_start(cb, L) == kMfmFixed;
+        return cb + (two ? 2 : 1);
+    };
     for (int fb = b0; fb < b1; ++fb) {
         const int64_t fs = sym_blk_start(fb, L), fe = sym_blk_end(fb, L);
         const bool fint = fb < L.nb_int;
         const float4 fr = frames[fb];
+        int cb = c0 > fb ? c0 : fb;
+        float4 qn;  // this thread's node of the next chunk
+        {
+            const int64_t k = sym_blk_start(cb < c1 ? cb : fb, L) + tid;
+            qn = XS[k < L.n ? k : L.n - 1];
+        }
         v4u a[kMfmFt];
         v4f C[kMfmFt];
         float xi[kMfmFt][4];
@@ -303,19 +318,20 @@ __global__ __launch_bounds__(kBlock) void k_mfs(const float4* __restrict__ XS, S
                 acc[f][r] = 0.0;
             }
         }
-        for (int cb = c0 > fb ? c0 : fb; cb < c1;) {
+        while (cb < c1) {
             const bool diag = cb == fb;
             const bool cint = cb < L.nb_int;
-            int ce = cb + 1;
-            if (!diag && ce < c1 && (ce < L.nb_int) == cint && sym_blk_end(cb, L) - sym_blk_start(cb, L) == kMfmFixed)
-                ce = cb + 2;
+            const int ce = chunk_end(cb, fb);
             const int64_t j0 = sym_blk_start(cb, L), j1 = sym_blk_end(ce - 1, L);
             // stage the chunk's loop nodes in the fixed block's frame: B
             // operand (4 lane groups x 8 bf16) and weight; past j1: d = 0, w = 0
-            const int64_t j = j0 + tid;
+            const float4 q = qn;
+            if (ce < c1) {  // the next chunk's nodes, in flight during this one
+                const int64_t k = sym_blk_start(ce, L) + tid;
+                qn = XS[k < L.n ? k : L.n - 1];
+            }
             float dx = 0.f, dy = 0.f, dz = 0.f, w = 0.f;
-            if (j < j1) {
-                const float4 q = XS[j];
+            if (j0 + tid < j1) {
                 w = q.w;
                 dx = q.x - fr.x;
                 dy = q.y - fr.y;
@@ -458,9 +474,12 @@ __global__ __launch_bounds__(kBlock) void k_mfs64(const double4* __restrict__ XS
     __shared__ double lds_col[2 * (kBlock / kWave)][kMfmChunk];  // per (wave, lane-group pair)
     __shared__ double colacc[kSymMaxLb * B];
     double* red = &lds_col[0][0];  // 64 rows x 17 (padded), between chunks (four workgroups fit a CU's LDS)
-    if (st != nullptr && st->stopped) return;
-    const int2 item = L.items[blockIdx.x];
-    const int64_t slot = (int64_t)L.item_first[item.x] + item.y;
+    int4 item = L.items[blockIdx.x];
+    int stop = st != nullptr ? st->stopped : 0;
+    arrived_uniform(item.x);
+    arrived_uniform(stop);
+    if (stop) return;
+    const int64_t slot = item.z;
     const int b0 = item.x * L.F;
     const int b1 = b0 + L.F < L.nb ? b0 + L.F : L.nb;
     const int c0 = b0 + item.y * L.Lb;
@@ -472,6 +491,7 @@ __global__ __launch_bounds__(kBlock) void k_mfs64(const double4* __restrict__ XS
         const int64_t fs = sym_blk_start<B>(fb, L), fe = sym_blk_end<B>(fb, L);
         const bool fint = fb < L.nb_int;
         double px[FT][4], py[FT][4], pz[FT][4], xi[FT][4], acc[FT][4];
+        int cb = c0 > fb ? c0 : fb;
 #pragma unroll
         for (int f = 0; f < FT; ++f) {
             const int64_t base = fs + (int64_t)(wv * FT + f) * 16;
@@ -487,7 +507,7 @@ __global__ __launch_bounds__(kBlock) void k_mfs64(const double4* __restrict__ XS
                 acc[f][r] = 0.0;
             }
         }
-        for (int cb = c0 > fb ? c0 : fb; cb < c1;) {
+        while (cb < c1) {
             const bool diag = cb == fb;
             const bool cint = cb < L.nb_int;
             // a chunk: as many whole blocks of one class as the staging holds (the own square alone)
@@ -577,33 +597,41 @@ __global__ __launch_bounds__(kSymRedThreads) void k_mfs_reduce(SymLayout L, cons
                                                                const GkbState* __restrict__ st) {
     constexpr int kGroups = kSymRedThreads / B;
     __shared__ double part[kGroups][B];
-    if (st != nullptr && st->stopped) return;
+    int stop = st != nullptr ? st->stopped : 0;
     const int beta = blockIdx.x;
     const int off = threadIdx.x % B, grp = threadIdx.x / B;
     const int k = beta / L.F;
     const int64_t rs = (int64_t)L.F * B;
-    const int i0 = L.item_first[k], nrow = (L.nb - k * L.F + L.Lb - 1) / L.Lb;
+    int i0 = L.item_first[k];
+    arrived_uniform(i0);
+    arrived_uniform(stop);
+    if (stop) return;
+    const int nrow = (L.nb - k * L.F + L.Lb - 1) / L.Lb;
     const double* rp = RowP + i0 * rs + (int64_t)(beta - k * L.F) * B + off;
     const double* cp = ColP + sym_col_base(beta, L.F) * B + off;
+    // the output's place and its shift term, while the partials are on their way
+    const int64_t q = sym_blk_start<B>(beta, L) + off;
+    const bool out = grp == 0 && q < sym_blk_end<B>(beta, L);
+    int o = 0;
+    if (out) o = perm[q];
     double s = 0.0, sc = 0.0;
 #pragma unroll 4
     for (int e = grp; e <= k; e += kGroups) sc += cp[(int64_t)e * B];
+    double zo = 0.0, sh = 0.0;
+    if (out && z != nullptr) {
+        sh = shift_ptr != nullptr ? *shift_ptr : shift_val;
+        zo = z[o];
+    }
 #pragma unroll 4
     for (int e = grp; e < nrow; e += kGroups) s += rp[e * rs];
     s += sc;
     part[grp][off] = s;
     __syncthreads();
-    if (grp != 0) return;
+    if (!out) return;
     s = 0.0;
 #pragma unroll
     for (int g = 0; g < kGroups; ++g) s += part[g][off];
-    const int64_t q = sym_blk_start<B>(beta, L) + off;
-    if (q >= sym_blk_end<B>(beta, L)) return;
-    const int64_t o = perm[q];
-    if (z != nullptr) {
-        const double sh = shift_ptr != nullptr ? *shift_ptr : shift_val;
-        s -= sh * z[o];
-    }
+    if (z != nullptr) s -= sh * zo;
     y[o] = s;
 }
 

@@ -131,7 +131,7 @@ __global__ __launch_bounds__(kBlock) void k_packed_product(const double* __restr
                                                            EntryConst ec, const double* __restrict__ x,
                                                            double* __restrict__ PR, double* __restrict__ PC,
                                                            const GkbState* __restrict__ st) {
-    if (st != nullptr && st->stopped) return;  // uniform over the grid
+    int stop = st != nullptr ? st->stopped : 0;
     constexpr int GR = 8;
     constexpr int kWaves = kBlock / kWave;
     constexpr int kRows = kTile / kWaves;   // rows of a tile per wave (32)
@@ -142,7 +142,10 @@ __global__ __launch_bounds__(kBlock) void k_packed_product(const double* __restr
     __shared__ double rsum[kTile];
     __shared__ double red[kWaves][kRed];
     __shared__ double csum[2][kWaves][kTile];  // double-buffered: one barrier per tile
-    const int4 it = L.items[blockIdx.x];
+    int4 it = L.items[blockIdx.x];
+    arrived_uniform(it.x);
+    arrived_uniform(stop);
+    if (stop) return;  // uniform over the grid
     const int R = it.x, C0 = it.y, cnt = it.z;
     const int tid = threadIdx.x, lane = tid & (kWave - 1), w = tid / kWave;
     const int total = cnt * kGpw;
@@ -265,13 +268,22 @@ __global__ __launch_bounds__(kRedGroups * kTile) void k_packed_reduce(PackedLayo
                                                                       double shift_val, const double* __restrict__ z,
                                                                       double* __restrict__ y,
                                                                       const GkbState* __restrict__ st) {
-    if (st != nullptr && st->stopped) return;
     __shared__ double part[kRedGroups][kTile];
+    int stop = st != nullptr ? st->stopped : 0;
     const int X = blockIdx.x;
     const int t = threadIdx.x & (kTile - 1), grp = threadIdx.x / kTile;
-    const int i0 = L.item_first[X], nrow = L.item_first[X + 1] - i0;
-    const int total = nrow + X;
-    double s = 0.0;
+    int i0 = L.item_first[X], i1 = L.item_first[X + 1];
+    arrived_uniform(i0);
+    arrived_uniform(i1);
+    arrived_uniform(stop);
+    if (stop) return;
+    const int nrow = i1 - i0, total = nrow + X;
+    const int64_t o = pk_start(L, X) + t;
+    double s = 0.0, zo = 0.0, sh = 0.0;
+    if (grp == 0 && z != nullptr && o < pk_end(L, X)) {  // the shift term, while the partials are on their way
+        zo = z[o];
+        sh = shift_ptr != nullptr ? *shift_ptr : shift_val;
+    }
 #pragma unroll 8
     for (int k = grp; k < total; k += kRedGroups) {
         const double* src = k < nrow ? PR + (int64_t)(i0 + k) * kTile : PC + pk_tile(L, k - nrow, X) * kTile;
@@ -282,12 +294,8 @@ __global__ __launch_bounds__(kRedGroups * kTile) void k_packed_reduce(PackedLayo
     if (grp == 0) {
         s = ((part[0][t] + part[1][t]) + (part[2][t] + part[3][t])) +
             ((part[4][t] + part[5][t]) + (part[6][t] + part[7][t]));
-        const int64_t o = pk_start(L, X) + t;
         if (o < pk_end(L, X)) {
-            if (z != nullptr) {
-                const double sh = shift_ptr != nullptr ? *shift_ptr : shift_val;
-                s -= sh * z[o];
-            }
+            if (z != nullptr) s -= sh * zo;
             y[o] = s;
         }
     }
