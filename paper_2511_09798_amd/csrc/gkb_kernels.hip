@@ -264,8 +264,7 @@ __global__ __launch_bounds__(kBlock) void k_gemvt_reduce(const double* __restric
     const int lane = threadIdx.x & (kWave - 1);
     const int k = blockIdx.x * (kBlock / kWave) + threadIdx.x / kWave;
     if (k >= m) return;  // wave-uniform; no barriers
-    double s = 0.0;
-    for (int b = lane; b < nb; b += kWave) s += partial[(int64_t)b * sb + (int64_t)k * sk];
+    double s = batched_sum<4>(0.0, partial + (int64_t)k * sk, lane, nb, kWave, sb);
     arrived(s);
     arrived_uniform(stop);
     if (stop) return;

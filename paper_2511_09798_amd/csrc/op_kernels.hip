@@ -614,16 +614,13 @@ __global__ __launch_bounds__(kSymRedThreads) void k_mfs_reduce(SymLayout L, cons
     const bool out = grp == 0 && q < sym_blk_end<B>(beta, L);
     int o = 0;
     if (out) o = perm[q];
-    double s = 0.0, sc = 0.0;
-#pragma unroll 4
-    for (int e = grp; e <= k; e += kGroups) sc += cp[(int64_t)e * B];
+    double sc = batched_sum<4>(0.0, cp, grp, k + 1, kGroups, B);
     double zo = 0.0, sh = 0.0;
     if (out && z != nullptr) {
         sh = shift_ptr != nullptr ? *shift_ptr : shift_val;
         zo = z[o];
     }
-#pragma unroll 4
-    for (int e = grp; e < nrow; e += kGroups) s += rp[e * rs];
+    double s = batched_sum<4>(0.0, rp, grp, nrow, kGroups, rs);
     s += sc;
     part[grp][off] = s;
     __syncthreads();
