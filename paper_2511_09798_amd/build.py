@@ -34,6 +34,12 @@ FLAGS = [
     # result with VALU instructions; the accumulator-register form would add
     # one move per value)
     "-mllvm", "-amdgpu-mfma-vgpr-form",
+    # the leading kernel arguments (up to 14 dwords) in SGPRs when a wave
+    # starts: reading them is one of the latencies that bound the kernels of a
+    # Golub-Kahan half-step, whose signatures therefore begin with what the
+    # first loads need (half-step 32.9 -> 30.3 us at 4 000 nodes, 28.1 -> 26.3
+    # at 1 800)
+    "-mllvm", "-amdgpu-kernarg-preload-count=16",
     "-I", INCLUDE,
     "-I", CSRC,
 ]

@@ -33,9 +33,9 @@ constexpr int kPLd = kBlkRhs + 1;
 // V[col][i] P[k][i], for col < m and all 16 k (zero for k >= s).  V: column
 // col at V + col ldv; P: column k at P + k ldp.  Grid (chunks, ceil(m / 64)),
 // chunk a multiple of 64; wave w forms columns 64 y + 16 w .. + 15.
-__global__ __launch_bounds__(kBlock) void k_blk_gemvt(const double* __restrict__ V, int64_t ldv, int64_t n,
-                                                      int32_t m, const double* __restrict__ P, int64_t ldp,
-                                                      int32_t s, int64_t chunk, double* __restrict__ part) {
+__global__ __launch_bounds__(kBlock) void k_blk_gemvt(const double* __restrict__ V, const double* __restrict__ P,
+                                                      int64_t n, int64_t chunk, int64_t ldv, int64_t ldp, int32_t m,
+                                                      int32_t s, double* __restrict__ part) {
     __shared__ double tV[kBt * kBtLd];
     __shared__ double tP[kBt * kPLd];
     const int64_t r0 = (int64_t)blockIdx.x * chunk;
@@ -352,8 +352,7 @@ void launch_blk_gemvt(const double* V, int64_t ldv, int64_t n, int32_t m, const 
                       double* part, double* c, hipStream_t st) {
     int64_t chunk;
     const int chunks = blk_chunks(n, m, &chunk);
-    k_blk_gemvt<<<dim3((unsigned)chunks, (unsigned)((m + kBt - 1) / kBt)), kBlock, 0, st>>>(V, ldv, n, m, P, ldp, s,
-                                                                                           chunk, part);
+    k_blk_gemvt<<<dim3((unsigned)chunks, (unsigned)((m + kBt - 1) / kBt)), kBlock, 0, st>>>(V, P, n, chunk, ldv, ldp, m, s, part);
     const int64_t waves = (int64_t)m * kBlkRhs, per = kBlock / kWave;
     k_blk_reduce<<<(unsigned)((waves + per - 1) / per), kBlock, 0, st>>>(part, chunks, m, c);
 }
@@ -386,7 +385,7 @@ int launch_blk_update_gram(const double* V, int64_t ldv, int64_t n, int32_t m, c
 int launch_blk_gram(const double* P, int64_t ldp, int64_t n, int32_t s, double* part, hipStream_t st) {
     int64_t chunk;
     const int chunks = blk_chunks(n, s, &chunk);
-    k_blk_gemvt<<<dim3((unsigned)chunks, 1), kBlock, 0, st>>>(P, ldp, n, s, P, ldp, s, chunk, part);
+    k_blk_gemvt<<<dim3((unsigned)chunks, 1), kBlock, 0, st>>>(P, P, n, chunk, ldp, ldp, s, s, part);
     return chunks;
 }
 

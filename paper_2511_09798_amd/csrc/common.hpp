@@ -31,7 +31,8 @@ struct GkbState {
 // Per-batch-slice strides of a kernel's pointer arguments (in elements):
 // slice z of a batched launch uses pointer + z * stride; which argument
 // takes which stride is stated at each kernel.  Zero strides with one slice
-// are the unbatched call.
+// are the unbatched call.  Problem 0 does not read the strides: they lie past the
+// arguments a wave starts with.
 struct Bz {
     int64_t a = 0, b = 0, c = 0, d = 0;
 };

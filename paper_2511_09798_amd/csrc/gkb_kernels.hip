@@ -91,26 +91,29 @@ __global__ __launch_bounds__(kBlock) void k_sumsq_partial(const double* __restri
 // in FP32 to column z of the block products' Vg[iperm[i]][z] (zeros for a
 // stopped run), to the weights xs32[iperm[i]].w or xs64[iperm[i]].w of the pair
 // products (one run), which saves the gather launch before each product.
-__global__ __launch_bounds__(kBlock) void k_finalize_scale(const double* __restrict__ partial, int nparts, int kind,
-                                                           int32_t j, int64_t n, double* __restrict__ alpha,
-                                                           double* __restrict__ beta, GkbState* __restrict__ st,
-                                                           const double* __restrict__ x, double* __restrict__ dst,
-                                                           SortedOut so, Bz bz) {
+__global__ __launch_bounds__(kBlock) void k_finalize_scale(const double* __restrict__ partial,
+                                                           GkbState* __restrict__ st, const double* __restrict__ x,
+                                                           const int32_t* __restrict__ iperm, int64_t n, int nparts,
+                                                           int kind, double* __restrict__ dst,
+                                                           double* __restrict__ alpha, double* __restrict__ beta,
+                                                           int32_t j, SortedOut so, Bz bz) {
     __shared__ double lds[kBlock / kWave];
     const int64_t z = blockIdx.y;  // batch: partial + z bz.a, alpha, beta + z bz.b, x + z bz.c, dst + z bz.d, state z
-    partial += z * bz.a;
-    alpha += z * bz.b;
-    beta += z * bz.b;
-    x += z * bz.c;
-    dst += z * bz.d;
-    st += z;
+    if (z != 0) {
+        partial += z * bz.a;
+        alpha += z * bz.b;
+        beta += z * bz.b;
+        x += z * bz.c;
+        dst += z * bz.d;
+        st += z;
+    }
     const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     // all loads of the kernel together
     int stop = st->snap_stopped, ip = 0;
     double scale = st->snap_scale, xi = 0.0, s = 0.0;
     if (i < n) {
         xi = x[i];
-        if (so.iperm != nullptr) ip = so.iperm[i];
+        if (iperm != nullptr) ip = iperm[i];
     }
     for (int q = threadIdx.x; q < nparts; q += kBlock) s += partial[q];
     arrived(s);
@@ -194,16 +197,17 @@ constexpr int kGtCols = 2;
 // of the same launch needs a device-scope release in every block, which on
 // this GPU writes back the L2 of the block's XCD; measured 1.25 ms per call
 // against 30 us for the two launches.)
-__global__ __launch_bounds__(kBlock) void k_gemvt_partial(const double* __restrict__ V, int64_t ldn, int64_t n,
-                                                          int32_t m, const double* __restrict__ x,
-                                                          double* __restrict__ partial,
-                                                          const GkbState* __restrict__ st, Bz bz) {
+__global__ __launch_bounds__(kBlock) void k_gemvt_partial(const double* __restrict__ V, const double* __restrict__ x,
+                                                          const GkbState* __restrict__ st, int64_t n, int64_t ldn,
+                                                          int32_t m, double* __restrict__ partial, Bz bz) {
     __shared__ double lds[kBlock / kWave][kGtCols];
     const int64_t z = blockIdx.z;  // batch: V + z bz.a, x + z bz.b, partial + z bz.c, state z
-    V += z * bz.a;
-    x += z * bz.b;
-    partial += z * bz.c;
-    if (st != nullptr) st += z;
+    if (z != 0) {
+        V += z * bz.a;
+        x += z * bz.b;
+        partial += z * bz.c;
+        if (st != nullptr) st += z;
+    }
     int stop = st != nullptr ? st->stopped : 0;
     const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
     const int64_t ib = (int64_t)blockIdx.x * kGtRows + w * (2 * kWave) + 2 * lane;
@@ -253,13 +257,15 @@ __global__ __launch_bounds__(kBlock) void k_gemvt_partial(const double* __restri
 // c[k] = sum_b partial[b * sb + k * sk] (k_gemvt_partial: sb = m, sk = 1;
 // k_update_gemvt: sb = 1, sk = nb): one wave per column, lanes take b = lane,
 // lane + 64, ... and the wave reduction combines them in a fixed order.
-__global__ __launch_bounds__(kBlock) void k_gemvt_reduce(const double* __restrict__ partial, int nb, int32_t m,
-                                                         int64_t sb, int64_t sk, double* __restrict__ c,
-                                                         const GkbState* __restrict__ st, Bz bz) {
+__global__ __launch_bounds__(kBlock) void k_gemvt_reduce(const double* __restrict__ partial,
+                                                         const GkbState* __restrict__ st, int64_t sb, int64_t sk,
+                                                         int nb, int32_t m, double* __restrict__ c, Bz bz) {
     const int64_t z = blockIdx.y;  // batch: partial + z bz.a, c + z bz.b, state z
-    partial += z * bz.a;
-    c += z * bz.b;
-    if (st != nullptr) st += z;
+    if (z != 0) {
+        partial += z * bz.a;
+        c += z * bz.b;
+        if (st != nullptr) st += z;
+    }
     int stop = st != nullptr ? st->stopped : 0;
     const int lane = threadIdx.x & (kWave - 1);
     const int k = blockIdx.x * (kBlock / kWave) + threadIdx.x / kWave;
@@ -302,12 +308,15 @@ __device__ __forceinline__ double coef_of_groups(const double* __restrict__ sums
 // per workgroup, one thread per column and group.
 constexpr int kCoefCols = kBlock / 16;
 
-__global__ __launch_bounds__(kBlock) void k_coef(const double* __restrict__ partial, int nb, int32_t m,
-                                                 double* __restrict__ c, const GkbState* __restrict__ st, Bz bz) {
+__global__ __launch_bounds__(kBlock) void k_coef(const double* __restrict__ partial,
+                                                 const GkbState* __restrict__ st, double* __restrict__ c, int nb,
+                                                 int32_t m, Bz bz) {
     __shared__ double sums[16][kCoefCols];
     const int64_t z = blockIdx.y;  // batch: partial + z bz.a, c + z bz.b, state z
-    partial += z * bz.a;
-    c += z * bz.b;
+    if (z != 0) {
+        partial += z * bz.a;
+        c += z * bz.b;
+    }
     int stop = st != nullptr ? st[z].stopped : 0;
     const int q = threadIdx.x % kCoefCols, g = threadIdx.x / kCoefCols;
     const int k = (int)blockIdx.x * kCoefCols + q, groups = coef_groups(m);
@@ -334,23 +343,19 @@ __global__ __launch_bounds__(kBlock) void k_coef(const double* __restrict__ part
 // four waves' sums are added in wave order through LDS.
 constexpr int kUpdRows = 2 * kWave;
 
-__global__ __launch_bounds__(kBlock) void k_update(const double* __restrict__ V, int64_t ldn, int64_t n, int32_t m,
-                                                   const double* __restrict__ c, double* __restrict__ x,
-                                                   double* __restrict__ sumsq_partial, GkbState* __restrict__ st,
+__global__ __launch_bounds__(kBlock) void k_update(const double* __restrict__ V, const double* __restrict__ c,
+                                                   GkbState* __restrict__ st, double* __restrict__ x, int64_t n,
+                                                   int64_t ldn, int32_t m, double* __restrict__ sumsq_partial,
                                                    Bz bz) {
     constexpr int kW = kBlock / kWave;
     __shared__ double part[kW][kUpdRows];
     __shared__ double lds[kW];
     const int64_t z = blockIdx.z;  // batch: V + z bz.a, c + z bz.b, x + z bz.c, sumsq + z bz.d, state z
-    V += z * bz.a;
-    c += z * bz.b;
-    x += z * bz.c;
-    if (sumsq_partial != nullptr) sumsq_partial += z * bz.d;
-    if (st != nullptr) st += z;
-    if (st != nullptr && sumsq_partial != nullptr && blockIdx.x == 0 && threadIdx.x == 0) {
-        // the state the normalisation that consumes these partials decides from
-        st->snap_stopped = st->stopped;
-        st->snap_scale = st->scale;
+    if (z != 0) {
+        V += z * bz.a;
+        c += z * bz.b;
+        x += z * bz.c;
+        if (st != nullptr) st += z;
     }
     int stop = st != nullptr ? st->stopped : 0;
     const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
@@ -382,6 +387,11 @@ __global__ __launch_bounds__(kBlock) void k_update(const double* __restrict__ V,
     if (threadIdx.x < kUpdRows && i < n) xi = x[i];
     arrived(xi);
     arrived_uniform(stop);
+    if (st != nullptr && sumsq_partial != nullptr && blockIdx.x == 0 && threadIdx.x == 0) {
+        // the state the normalisation that consumes these partials decides from
+        st->snap_stopped = st->stopped;
+        st->snap_scale = st->scale;
+    }
     if (stop) return;  // uniform over the grid
     __syncthreads();
     if (threadIdx.x < kUpdRows && i < n) {
@@ -391,7 +401,7 @@ __global__ __launch_bounds__(kBlock) void k_update(const double* __restrict__ V,
     }
     if (sumsq_partial != nullptr) {
         const double s = block_sum<kBlock>(xi * xi, lds);
-        if (threadIdx.x == 0) sumsq_partial[blockIdx.x] = s;
+        if (threadIdx.x == 0) sumsq_partial[(z != 0 ? z * bz.d : 0) + blockIdx.x] = s;
     }
 }
 
@@ -421,29 +431,34 @@ static_assert(kFusedCgsMaxCols * kFuLd * 8 + (kFuGroups + 1) * kFuRows * 8 + kFu
 static_assert(kFuGroups * kFuRows >= kBlock, "the coefficient sums fit the row sums' LDS");
 
 template <bool RED>
-__global__ __launch_bounds__(kBlock) void k_update_gemvt(const double* __restrict__ V, int64_t ldn, int64_t n,
-                                                         int32_t m, const double* __restrict__ c,
-                                                         const double* __restrict__ p1, int nb1,
-                                                         double* __restrict__ x, double* __restrict__ partial, int nb,
-                                                         const GkbState* __restrict__ st, Bz bz) {
+__global__ __launch_bounds__(kBlock) void k_update_gemvt(const double* __restrict__ V, const double* __restrict__ p1,
+                                                         const GkbState* __restrict__ st, double* __restrict__ x,
+                                                         int64_t n, int64_t ldn, int32_t m, int nb1,
+                                                         const double* __restrict__ c, double* __restrict__ partial,
+                                                         Bz bz) {
     extern __shared__ double tile[];  // [m][kFuLd]
     __shared__ double part[kFuGroups][kFuRows];
     __shared__ double xs[kFuRows];
     __shared__ double cs[RED ? kFusedCgsMaxCols : 1];
     // batch: V + z bz.a, c + z bz.b, x + z bz.c, partial and p1 + z bz.d, state z
     const int64_t z = blockIdx.z;
-    V += z * bz.a;
-    c += z * bz.b;
-    p1 += z * bz.d;
-    x += z * bz.c;
-    partial += z * bz.d;
-    if (st != nullptr) st += z;
-    if (st != nullptr && st->stopped) return;  // uniform over the grid
+    if (z != 0) {
+        V += z * bz.a;
+        c += z * bz.b;
+        p1 += z * bz.d;
+        x += z * bz.c;
+        partial += z * bz.d;
+        if (st != nullptr) st += z;
+    }
+    int stop = st != nullptr ? st->stopped : 0;
+    const int nb = (int)((n + kFuRows - 1) / kFuRows);
     const int per = (nb + 7) / 8;
     const int b = (int)(blockIdx.x % 8) * per + (int)(blockIdx.x / 8);
     if (b >= nb) return;  // uniform over the workgroup
     if (RED) {
         coef_group_sum(p1, nb1, m, threadIdx.x, &part[0][0]);
+        arrived_uniform(stop);
+        if (stop) return;  // uniform over the grid
         __syncthreads();
         if ((int)threadIdx.x < m) cs[threadIdx.x] = coef_of_groups(&part[0][0], m, threadIdx.x);
         __syncthreads();
@@ -480,6 +495,10 @@ __global__ __launch_bounds__(kBlock) void k_update_gemvt(const double* __restric
     }
     part[cg][2 * rp] = s0;
     part[cg][2 * rp + 1] = s1;
+    if (!RED) {
+        arrived_uniform(stop);
+        if (stop) return;  // uniform over the grid
+    }
     __syncthreads();
     if (t < kFuRows) {
         double sum = 0.0;
@@ -519,23 +538,24 @@ static_assert(kSmMaxCols * kFuLd * 8 + (kSmGroups + 1) * kFuRows * 8 + kSmMaxCol
 static_assert(kSmThreads == 2 * kBlock && kSmGroups * kFuRows >= kBlock, "two halves; sums fit the row sums' LDS");
 
 template <bool NORM, bool RED>
-__global__ __launch_bounds__(kSmThreads) void k_cgs_small(const double* __restrict__ V, int64_t ldn, int64_t n,
-                                                          int32_t m, const double* __restrict__ c, int64_t cstr,
-                                                          const double* __restrict__ p1, int nb1,
-                                                          double* __restrict__ x, double* __restrict__ out,
-                                                          GkbState* __restrict__ st, Bz bz) {
+__global__ __launch_bounds__(kSmThreads) void k_cgs_small(const double* __restrict__ V, const double* __restrict__ p1,
+                                                          GkbState* __restrict__ st, double* __restrict__ x, int64_t n,
+                                                          int64_t ldn, int32_t m, int nb1, double* __restrict__ out,
+                                                          const double* __restrict__ c, int64_t cstr, Bz bz) {
     extern __shared__ double tile[];  // [m][kFuLd]
     __shared__ double part[kSmGroups][kFuRows];
     __shared__ double xs[kFuRows];
     __shared__ double cs[kSmMaxCols];
     // batch: V + z bz.a, p1 + z bz.b, x + z bz.c, out + z bz.d, c + z cstr, state z
     const int64_t z = blockIdx.z;
-    V += z * bz.a;
-    p1 += z * bz.b;
-    c += z * cstr;
-    x += z * bz.c;
-    out += z * bz.d;
-    st += z;
+    if (z != 0) {
+        V += z * bz.a;
+        p1 += z * bz.b;
+        c += z * cstr;
+        x += z * bz.c;
+        out += z * bz.d;
+        st += z;
+    }
     const int b = blockIdx.x, t = threadIdx.x;
     if (NORM && b == 0 && t == 0) {
         st->snap_stopped = st->stopped;
@@ -690,7 +710,7 @@ void launch_finalize_scale_b(const double* partial, int nparts, int kind, int32_
                              double* beta, GkbState* st, const double* x, double* dst, const SortedOut& so, int nz,
                              Bz bz, hipStream_t s) {
     k_finalize_scale<<<dim3((unsigned)((n + kBlock - 1) / kBlock), nz), kBlock, 0, s>>>(
-        partial, nparts, kind, j, n, alpha, beta, st, x, dst, so, bz);
+        partial, st, x, so.iperm, n, nparts, kind, dst, alpha, beta, j, so, bz);
 }
 
 int gemvt_blocks(int64_t n) { return (int)((n + kGtRows - 1) / kGtRows); }
@@ -726,9 +746,9 @@ int launch_cgs2(const double* V, int64_t ldn, int64_t n, int32_t m, double* x, d
     // the second projection's partials follow the first's, which workgroups of
     // a fused kernel may still be reading
     double* part2 = part + (int64_t)nbg * m;
-    auto project = [&]() { k_gemvt_partial<<<ggrid, kBlock, 0, s>>>(V, ldn, n, m, x, part, st, gb); };
+    auto project = [&]() { k_gemvt_partial<<<ggrid, kBlock, 0, s>>>(V, x, st, n, ldn, m, part, gb); };
     auto coef = [&](const double* p, int nb) {
-        k_coef<<<dim3((unsigned)((m + kCoefCols - 1) / kCoefCols), (unsigned)nz), kBlock, 0, s>>>(p, nb, m, c, st, rb);
+        k_coef<<<dim3((unsigned)((m + kCoefCols - 1) / kCoefCols), (unsigned)nz), kBlock, 0, s>>>(p, st, c, nb, m, rb);
     };
     const bool few = (int64_t)nbf * nz <= kCoefGrid;
     project();
@@ -736,13 +756,13 @@ int launch_cgs2(const double* V, int64_t ldn, int64_t n, int32_t m, double* x, d
         const dim3 grid((unsigned)nbf, 1, (unsigned)nz);
         const Bz b1{b.V, b.part, b.x, b.part}, b2{b.V, b.part, b.x, b.npart};
         if (few) {
-            k_cgs_small<false, true><<<grid, kSmThreads, lds, s>>>(V, ldn, n, m, c, b.c, part, nbg, x, part2, st, b1);
-            k_cgs_small<true, true><<<grid, kSmThreads, lds, s>>>(V, ldn, n, m, c, b.c, part2, nbf, x, npart, st, b2);
+            k_cgs_small<false, true><<<grid, kSmThreads, lds, s>>>(V, part, st, x, n, ldn, m, nbg, part2, c, b.c, b1);
+            k_cgs_small<true, true><<<grid, kSmThreads, lds, s>>>(V, part2, st, x, n, ldn, m, nbf, npart, c, b.c, b2);
         } else {
             coef(part, nbg);
-            k_cgs_small<false, false><<<grid, kSmThreads, lds, s>>>(V, ldn, n, m, c, b.c, part, nbg, x, part2, st, b1);
+            k_cgs_small<false, false><<<grid, kSmThreads, lds, s>>>(V, part, st, x, n, ldn, m, nbg, part2, c, b.c, b1);
             coef(part2, nbf);
-            k_cgs_small<true, false><<<grid, kSmThreads, lds, s>>>(V, ldn, n, m, c, b.c, part2, nbf, x, npart, st, b2);
+            k_cgs_small<true, false><<<grid, kSmThreads, lds, s>>>(V, part2, st, x, n, ldn, m, nbf, npart, c, b.c, b2);
         }
         return nbf;
     }
@@ -750,25 +770,25 @@ int launch_cgs2(const double* V, int64_t ldn, int64_t n, int32_t m, double* x, d
         if (m <= kFusedCgsMaxCols && (int64_t)nbg * m <= kCoefParts)
             coef(part, nbg);
         else
-            k_gemvt_reduce<<<rgrid, kBlock, 0, s>>>(part, nbg, m, m, 1, c, st, rb);
+            k_gemvt_reduce<<<rgrid, kBlock, 0, s>>>(part, st, m, 1, nbg, m, c, rb);
     };
     if (m > kFusedCgsMaxCols) {
         reduce();
-        k_update<<<ugrid, kBlock, 0, s>>>(V, ldn, n, m, c, x, nullptr, st, ub);
+        k_update<<<ugrid, kBlock, 0, s>>>(V, c, st, x, n, ldn, m, nullptr, ub);
         project();
         reduce();
     } else {
         const dim3 fgrid((unsigned)(8 * ((nbf + 7) / 8)), 1, (unsigned)nz);
         const Bz fb{b.V, b.c, b.x, b.part};
         if ((int64_t)nbg * m <= kCoefParts && few) {
-            k_update_gemvt<true><<<fgrid, kBlock, lds, s>>>(V, ldn, n, m, c, part, nbg, x, part2, nbf, st, fb);
+            k_update_gemvt<true><<<fgrid, kBlock, lds, s>>>(V, part, st, x, n, ldn, m, nbg, c, part2, fb);
         } else {
             reduce();
-            k_update_gemvt<false><<<fgrid, kBlock, lds, s>>>(V, ldn, n, m, c, part, nbg, x, part2, nbf, st, fb);
+            k_update_gemvt<false><<<fgrid, kBlock, lds, s>>>(V, part, st, x, n, ldn, m, nbg, c, part2, fb);
         }
-        k_gemvt_reduce<<<rgrid, kBlock, 0, s>>>(part2, nbf, m, 1, nbf, c, st, rb);
+        k_gemvt_reduce<<<rgrid, kBlock, 0, s>>>(part2, st, 1, nbf, nbf, m, c, rb);
     }
-    k_update<<<ugrid, kBlock, 0, s>>>(V, ldn, n, m, c, x, npart, st, ub);
+    k_update<<<ugrid, kBlock, 0, s>>>(V, c, st, x, n, ldn, m, npart, ub);
     return nbu;
 }
 

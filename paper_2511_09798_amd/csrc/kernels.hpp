@@ -57,7 +57,7 @@ struct SymLayout {
     int64_t n, n_int;
     int32_t nb_int, nb;         // blocks of blk nodes per class, all blocks
     int32_t blk, pad;           // 128 (FP32 form), 64 or 128 (FP64 form)
-    int32_t F, Lb;              // fixed blocks per super-row, loop blocks per segment
+    int32_t F, Lb;              // fixed blocks per super-row (a power of two), loop blocks per segment
     int32_t nsr, nitems;        // super-rows, work items
     const int4* items;          // (super-row, segment, place in the partials, 0) in launch order (largest first)
     const int32_t* item_first;  // nsr + 1 entries: first item of each super-row

@@ -120,10 +120,20 @@ __device__ __forceinline__ int64_t sym_blk_end(int b, const SymLayout& L) {
     return e < lim ? e : lim;
 }
 
+// A work item, the run's state and the layout's sizes by one wait: left to itself the
+// compiler reads the layout from the arguments after the item has come.
+__device__ __forceinline__ void arrived_with_layout(int& item, int& stop, SymLayout& L) {
+    asm volatile(""
+                 : "+s"(item), "+s"(stop), "+s"(L.n), "+s"(L.n_int), "+s"(L.nb_int), "+s"(L.nb), "+s"(L.F),
+                   "+s"(L.Lb));
+}
+
+__device__ __forceinline__ int sym_shift(int F) { return __ffs(F) - 1; }
+
 // Place of block beta's column partials in ColP (in blocks): one from each
 // super-row k <= beta / F, in order of k, block after block.
 __device__ __forceinline__ int64_t sym_col_base(int beta, int F) {
-    const int64_t k = beta / F;
+    const int64_t k = beta >> sym_shift(F);
     return (int64_t)F * (k * (k + 1) / 2) + (beta - k * F) * (k + 1);
 }
 
@@ -238,18 +248,17 @@ __device__ __forceinline__ void mfs_dispatch(bool ri, bool ci, const v4u* lds_b,
 // One work item (blockIdx.x) of the SymLayout.  TRANS: y = A^T x.
 // RowP[item][(fb - kF) kMfmFixed + row], ColP[sym_col_base(c) + k][node].
 template <bool TRANS>
-__global__ __launch_bounds__(kBlock) void k_mfs(const float4* __restrict__ XS, SymLayout L,
-                                                const float4* __restrict__ frames, EntryConst c,
-                                                double* __restrict__ RowP, double* __restrict__ ColP,
-                                                const GkbState* __restrict__ st) {
+__global__ __launch_bounds__(kBlock) void k_mfs(const int4* __restrict__ items, const GkbState* __restrict__ st,
+                                                const float4* __restrict__ XS, const float4* __restrict__ frames,
+                                                double* __restrict__ RowP, double* __restrict__ ColP, SymLayout L,
+                                                EntryConst c) {
     __shared__ v4u lds_b[4 * kMfmChunk];
     __shared__ float lds_w[kMfmChunk];
     __shared__ float lds_col[2 * (kBlock / kWave)][kMfmChunk];  // per (wave, lane-group pair)
     __shared__ double colacc[kSymMaxLb * kMfmFixed];
-    int4 item = L.items[blockIdx.x];  // launch order: the largest items first
+    int4 item = items[blockIdx.x];  // launch order: the largest items first
     int stop = st != nullptr ? st->stopped : 0;
-    arrived_uniform(item.x);
-    arrived_uniform(stop);
+    arrived_with_layout(item.x, stop, L);
     if (stop) return;
     const int64_t slot = item.z;
     const int b0 = item.x * L.F;
@@ -466,18 +475,17 @@ __device__ __forceinline__ void mfs64_tiles(const double4* __restrict__ lds_p, i
 
 // One work item of the layout, blocks of B = 64 FT nodes.
 template <bool TRANS, int FT>
-__global__ __launch_bounds__(kBlock) void k_mfs64(const double4* __restrict__ XS64, SymLayout L, EntryConst c,
-                                                  double* __restrict__ RowP, double* __restrict__ ColP,
-                                                  const GkbState* __restrict__ st) {
+__global__ __launch_bounds__(kBlock) void k_mfs64(const int4* __restrict__ items, const GkbState* __restrict__ st,
+                                                  const double4* __restrict__ XS64, double* __restrict__ RowP,
+                                                  double* __restrict__ ColP, SymLayout L, EntryConst c) {
     constexpr int B = 64 * FT;
     __shared__ double4 lds_p[kMfmChunk];
     __shared__ double lds_col[2 * (kBlock / kWave)][kMfmChunk];  // per (wave, lane-group pair)
     __shared__ double colacc[kSymMaxLb * B];
     double* red = &lds_col[0][0];  // 64 rows x 17 (padded), between chunks (four workgroups fit a CU's LDS)
-    int4 item = L.items[blockIdx.x];
+    int4 item = items[blockIdx.x];
     int stop = st != nullptr ? st->stopped : 0;
-    arrived_uniform(item.x);
-    arrived_uniform(stop);
+    arrived_with_layout(item.x, stop, L);
     if (stop) return;
     const int64_t slot = item.z;
     const int b0 = item.x * L.F;
@@ -589,26 +597,26 @@ __global__ __launch_bounds__(kBlock) void k_gather_w64(const double* __restrict_
 constexpr int kSymRedThreads = 1024;
 
 template <int B>
-__global__ __launch_bounds__(kSymRedThreads) void k_mfs_reduce(SymLayout L, const double* __restrict__ RowP,
+__global__ __launch_bounds__(kSymRedThreads) void k_mfs_reduce(const int32_t* __restrict__ item_first,
+                                                               const GkbState* __restrict__ st,
+                                                               const double* __restrict__ RowP,
                                                                const double* __restrict__ ColP,
-                                                               const int32_t* __restrict__ perm,
+                                                               const int32_t* __restrict__ perm, int F, SymLayout L,
                                                                const double* __restrict__ shift_ptr, double shift_val,
-                                                               const double* __restrict__ z, double* __restrict__ y,
-                                                               const GkbState* __restrict__ st) {
+                                                               const double* __restrict__ z, double* __restrict__ y) {
     constexpr int kGroups = kSymRedThreads / B;
     __shared__ double part[kGroups][B];
-    int stop = st != nullptr ? st->stopped : 0;
     const int beta = blockIdx.x;
     const int off = threadIdx.x % B, grp = threadIdx.x / B;
-    const int k = beta / L.F;
-    const int64_t rs = (int64_t)L.F * B;
-    int i0 = L.item_first[k];
-    arrived_uniform(i0);
-    arrived_uniform(stop);
+    const int k = beta >> sym_shift(F);
+    const int64_t rs = (int64_t)F * B;
+    int i0 = item_first[k];
+    int stop = st != nullptr ? st->stopped : 0;
+    arrived_with_layout(i0, stop, L);
     if (stop) return;
-    const int nrow = (L.nb - k * L.F + L.Lb - 1) / L.Lb;
-    const double* rp = RowP + i0 * rs + (int64_t)(beta - k * L.F) * B + off;
-    const double* cp = ColP + sym_col_base(beta, L.F) * B + off;
+    const int nrow = (L.nb - k * F + L.Lb - 1) / L.Lb;
+    const double* rp = RowP + i0 * rs + (int64_t)(beta - k * F) * B + off;
+    const double* cp = ColP + sym_col_base(beta, F) * B + off;
     // the output's place and its shift term, while the partials are on their way
     const int64_t q = sym_blk_start<B>(beta, L) + off;
     const bool out = grp == 0 && q < sym_blk_end<B>(beta, L);
@@ -835,10 +843,10 @@ __device__ __forceinline__ void mfh_span(const float4* __restrict__ XS, const ui
 
 template <bool ROWS, int FT>
 __global__ __launch_bounds__(kBlock) void k_mfh_block(const float4* __restrict__ XS, const uint4* __restrict__ Vh,
-                                                      const float* __restrict__ vsc, int64_t n, int64_t n_int,
+                                                      const float4* __restrict__ frames, int64_t n, int64_t n_int,
                                                       int64_t nb_int, int64_t slice_len,
-                                                      const float4* __restrict__ frames, BlockEntry c,
-                                                      double* __restrict__ P, int64_t ldp) {
+                                                      const float* __restrict__ vsc, double* __restrict__ P,
+                                                      int64_t ldp, BlockEntry c) {
     __shared__ v4u lds_a[4 * kMfmChunk];
     __shared__ uint4 lds_v[(kMfmChunk / 4) * kBlkRhs];
     // blocks of kFix = 64 FT fixed nodes per class; the frame is that of the
@@ -981,12 +989,12 @@ __global__ __launch_bounds__(kBlock) void k_fill_hash(float* __restrict__ Vg, in
 // y_k[perm[i]] = sum_slices P[slice][k][i] - shift_k z_k[perm[i]] for right-hand
 // side k = blockIdx.y (shift_k = shift[k * sstride], z_k = z + k * ldz,
 // y_k = y + k * ldy); skipped when state k has stopped.
-__global__ __launch_bounds__(kBlock) void k_reduce_block(const double* __restrict__ P, int64_t ldp, int S, int64_t n,
-                                                         const int32_t* __restrict__ perm,
-                                                         const double* __restrict__ shift, int64_t sstride,
+__global__ __launch_bounds__(kBlock) void k_reduce_block(const double* __restrict__ P,
+                                                         const GkbState* __restrict__ st,
+                                                         const int32_t* __restrict__ perm, int64_t ldp, int64_t n,
+                                                         int S, const double* __restrict__ shift, int64_t sstride,
                                                          const double* __restrict__ z, int64_t ldz,
-                                                         double* __restrict__ y, int64_t ldy,
-                                                         const GkbState* __restrict__ st) {
+                                                         double* __restrict__ y, int64_t ldy) {
     const int k = blockIdx.y;
     if (st != nullptr && st[k].stopped) return;
     const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
@@ -1131,9 +1139,9 @@ void launch_mfs_product(int trans, const float4* XS, const float4* frames, const
                         double* RowP, double* ColP, const GkbState* st, hipStream_t s) {
     if (L.nitems <= 0) return;
     if (trans)
-        k_mfs<true><<<(unsigned)L.nitems, kBlock, 0, s>>>(XS, L, frames, c, RowP, ColP, st);
+        k_mfs<true><<<(unsigned)L.nitems, kBlock, 0, s>>>(L.items, st, XS, frames, RowP, ColP, L, c);
     else
-        k_mfs<false><<<(unsigned)L.nitems, kBlock, 0, s>>>(XS, L, frames, c, RowP, ColP, st);
+        k_mfs<false><<<(unsigned)L.nitems, kBlock, 0, s>>>(L.items, st, XS, frames, RowP, ColP, L, c);
 }
 
 void launch_gather_w64(const double* x, const int32_t* perm, int64_t n, double4* XS64, const GkbState* st,
@@ -1147,14 +1155,14 @@ void launch_mfs64_product(int trans, const double4* XS64, const SymLayout& L, co
     const unsigned g = (unsigned)L.nitems;
     if (L.blk == 64) {
         if (trans)
-            k_mfs64<true, 1><<<g, kBlock, 0, s>>>(XS64, L, c, RowP, ColP, st);
+            k_mfs64<true, 1><<<g, kBlock, 0, s>>>(L.items, st, XS64, RowP, ColP, L, c);
         else
-            k_mfs64<false, 1><<<g, kBlock, 0, s>>>(XS64, L, c, RowP, ColP, st);
+            k_mfs64<false, 1><<<g, kBlock, 0, s>>>(L.items, st, XS64, RowP, ColP, L, c);
     } else {
         if (trans)
-            k_mfs64<true, 2><<<g, kBlock, 0, s>>>(XS64, L, c, RowP, ColP, st);
+            k_mfs64<true, 2><<<g, kBlock, 0, s>>>(L.items, st, XS64, RowP, ColP, L, c);
         else
-            k_mfs64<false, 2><<<g, kBlock, 0, s>>>(XS64, L, c, RowP, ColP, st);
+            k_mfs64<false, 2><<<g, kBlock, 0, s>>>(L.items, st, XS64, RowP, ColP, L, c);
     }
 }
 
@@ -1163,10 +1171,11 @@ void launch_mfs_reduce(const SymLayout& L, const double* RowP, const double* Col
                        hipStream_t s) {
     if (L.nb <= 0) return;
     if (L.blk == 64)
-        k_mfs_reduce<64><<<(unsigned)L.nb, kSymRedThreads, 0, s>>>(L, RowP, ColP, perm, shift_ptr, shift_val, z, y, st);
+        k_mfs_reduce<64><<<(unsigned)L.nb, kSymRedThreads, 0, s>>>(L.item_first, st, RowP, ColP, perm, L.F, L,
+                                                                 shift_ptr, shift_val, z, y);
     else
-        k_mfs_reduce<128><<<(unsigned)L.nb, kSymRedThreads, 0, s>>>(L, RowP, ColP, perm, shift_ptr, shift_val, z, y,
-                                                                  st);
+        k_mfs_reduce<128><<<(unsigned)L.nb, kSymRedThreads, 0, s>>>(L.item_first, st, RowP, ColP, perm, L.F, L,
+                                                                  shift_ptr, shift_val, z, y);
 }
 
 int64_t mfh_block_blocks(int64_t n, int64_t n_int, int ft) {
@@ -1202,14 +1211,14 @@ void launch_mfh_block(int trans, int ft, const float4* XS, const float4* frames,
     dim3 grid((unsigned)mfh_block_blocks(n, n_int, ft), (unsigned)S);
     if (ft == 1) {
         if (trans)
-            k_mfh_block<false, 1><<<grid, kBlock, 0, s>>>(XS, Vh, vsc, n, n_int, nb_int, slice_len, frames, c, P, ldp);
+            k_mfh_block<false, 1><<<grid, kBlock, 0, s>>>(XS, Vh, frames, n, n_int, nb_int, slice_len, vsc, P, ldp, c);
         else
-            k_mfh_block<true, 1><<<grid, kBlock, 0, s>>>(XS, Vh, vsc, n, n_int, nb_int, slice_len, frames, c, P, ldp);
+            k_mfh_block<true, 1><<<grid, kBlock, 0, s>>>(XS, Vh, frames, n, n_int, nb_int, slice_len, vsc, P, ldp, c);
     } else {
         if (trans)
-            k_mfh_block<false, 2><<<grid, kBlock, 0, s>>>(XS, Vh, vsc, n, n_int, nb_int, slice_len, frames, c, P, ldp);
+            k_mfh_block<false, 2><<<grid, kBlock, 0, s>>>(XS, Vh, frames, n, n_int, nb_int, slice_len, vsc, P, ldp, c);
         else
-            k_mfh_block<true, 2><<<grid, kBlock, 0, s>>>(XS, Vh, vsc, n, n_int, nb_int, slice_len, frames, c, P, ldp);
+            k_mfh_block<true, 2><<<grid, kBlock, 0, s>>>(XS, Vh, frames, n, n_int, nb_int, slice_len, vsc, P, ldp, c);
     }
 }
 
@@ -1236,8 +1245,8 @@ void launch_gather_block(const double* X, int64_t ldx, int nrhs, const int32_t* 
 void launch_reduce_block(const double* P, int64_t ldp, int S, int64_t n, int nrhs, const int32_t* perm,
                          const double* shift, int64_t sstride, const double* z, int64_t ldz, double* y, int64_t ldy,
                          const GkbState* st, hipStream_t s) {
-    k_reduce_block<<<dim3((unsigned)((n + kBlock - 1) / kBlock), nrhs), kBlock, 0, s>>>(P, ldp, S, n, perm, shift,
-                                                                                       sstride, z, ldz, y, ldy, st);
+    k_reduce_block<<<dim3((unsigned)((n + kBlock - 1) / kBlock), nrhs), kBlock, 0, s>>>(P, st, perm, ldp, n, S,
+                                                                                       shift, sstride, z, ldz, y, ldy);
 }
 
 void launch_gen_rows(int prec, const void* X, int64_t n, int64_t n_int, int64_t row0, int64_t count,
