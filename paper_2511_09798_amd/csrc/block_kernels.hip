@@ -46,19 +46,37 @@ __global__ __launch_bounds__(kBlock) void k_blk_gemvt(const double* __restrict__
     const int rr = threadIdx.x & (kBt - 1), rq = threadIdx.x / kBt;  // staging: row rr, column rq + 4 q
     v4d acc = v4d{0.0, 0.0, 0.0, 0.0};
     for (int64_t rb = r0; rb < r1; rb += kBt) {
-        __syncthreads();  // the previous tile's reads are done
         const int64_t row = rb + rr;
         const bool rok = row < r1;
+        const int64_t rl = rok ? row : rb;
+        constexpr int kNv = kBt / (kBlock / kBt), kNp = kBlkRhs / (kBlock / kBt);
+        // all loads in flight together (under conditions they wait one by one: 6.8 -> 5.6 us
+        // at 20 000 rows, m = 16 .. 112)
+        double tv[kNv], tp[kNp];
 #pragma unroll
-        for (int q = 0; q < kBt / (kBlock / kBt); ++q) {
-            const int cc = rq + (kBlock / kBt) * q;
-            const int col = c0 + cc;
-            tV[rr * kBtLd + cc] = (rok && col < m) ? V[(int64_t)col * ldv + row] : 0.0;
+        for (int q = 0; q < kNv; ++q) {
+            const int col = c0 + rq + (kBlock / kBt) * q;
+            tv[q] = V[(int64_t)(col < m ? col : c0) * ldv + rl];
         }
 #pragma unroll
-        for (int q = 0; q < kBlkRhs / (kBlock / kBt); ++q) {
+        for (int q = 0; q < kNp; ++q) {
             const int k = rq + (kBlock / kBt) * q;
-            tP[rr * kPLd + k] = (rok && k < s) ? P[(int64_t)k * ldp + row] : 0.0;
+            tp[q] = P[(int64_t)(k < s ? k : 0) * ldp + rl];
+        }
+#pragma unroll
+        for (int q = 0; q < kNv; ++q) arrived(tv[q]);
+#pragma unroll
+        for (int q = 0; q < kNp; ++q) arrived(tp[q]);
+        __syncthreads();  // the previous tile's reads are done
+#pragma unroll
+        for (int q = 0; q < kNv; ++q) {
+            const int cc = rq + (kBlock / kBt) * q;
+            tV[rr * kBtLd + cc] = rok && c0 + cc < m ? tv[q] : 0.0;
+        }
+#pragma unroll
+        for (int q = 0; q < kNp; ++q) {
+            const int k = rq + (kBlock / kBt) * q;
+            tP[rr * kPLd + k] = rok && k < s ? tp[q] : 0.0;
         }
         __syncthreads();
 #pragma unroll 4
@@ -101,6 +119,9 @@ __global__ __launch_bounds__(kBlock) void k_blk_reduce(const double* __restrict_
 // s: the new values are the operands of the products as the lanes hold them, so
 // the pass of k_blk_gemvt over P and its launch are saved (6.3 + 5.6 -> 6.5 us
 // at 20 000 rows, m = s = 16).
+// Products of four columns whose loads are in flight together (a load under a
+// condition, one product at a time, waits for itself: 6.5 -> 5.7 us at 20 000 rows).
+constexpr int kUpdU = 4;
 constexpr int kGramThreads = 512;
 constexpr int64_t kGramRowsPer = 16 * (kGramThreads / kWave);  // rows of a workgroup in one turn
 
@@ -118,13 +139,29 @@ __global__ __launch_bounds__(NT) void k_blk_update(const double* V, int64_t ldv,
         const int64_t row = row0 + li;
         const bool rok = row < n;
         v4d acc = v4d{0.0, 0.0, 0.0, 0.0};
-        for (int kk = 0; kk < m; kk += 4) {
-            const int col = kk + lk;
-            const bool cok = col < m;
+        const double* vr = V + (rok ? row : row0);
+        const double* cr = c + (int64_t)(li < s ? li : 0) * ks;
+        for (int kk = 0; kk < m; kk += 4 * kUpdU) {
             // A[i][k'] = V[col kk + k'][row0 + i], B[k'][j] = c[col kk + k'][j]
-            const double a = (rok && cok) ? V[(int64_t)col * ldv + row] : 0.0;
-            const double b = (cok && li < s) ? c[(int64_t)col * cs + (int64_t)li * ks] : 0.0;
-            acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, acc, 0, 0, 0);
+            double a[kUpdU], b[kUpdU];  // the loads of kUpdU products in flight together
+#pragma unroll
+            for (int u = 0; u < kUpdU; ++u) {
+                const int64_t col = kk + 4 * u + lk < m ? kk + 4 * u + lk : m - 1;
+                a[u] = vr[col * ldv];
+                b[u] = cr[col * cs];
+            }
+#pragma unroll
+            for (int u = 0; u < kUpdU; ++u) {
+                arrived(a[u]);
+                arrived(b[u]);
+            }
+#pragma unroll
+            for (int u = 0; u < kUpdU; ++u) {
+                if (kk + 4 * u >= m) break;
+                const bool cok = kk + 4 * u + lk < m;
+                acc = __builtin_amdgcn_mfma_f64_16x16x4f64(rok && cok ? a[u] : 0.0, cok && li < s ? b[u] : 0.0, acc, 0,
+                                                           0, 0);
+            }
         }
 #pragma unroll
         for (int r = 0; r < 4; ++r) {

@@ -64,6 +64,8 @@ __device__ __forceinline__ v2d load2(const double* p) { return *reinterpret_cast
 // the compiler moves such loads behind the branch.
 __device__ __forceinline__ void arrived(double& v) { asm volatile("" : "+v"(v)); }
 __device__ __forceinline__ void arrived(int& v) { asm volatile("" : "+v"(v)); }
+__device__ __forceinline__ void arrived(float& v) { asm volatile("" : "+v"(v)); }
+__device__ __forceinline__ void arrived(float4& v) { asm volatile("" : "+v"(v.x), "+v"(v.y), "+v"(v.z), "+v"(v.w)); }
 __device__ __forceinline__ void arrived_uniform(int& v) { asm volatile("" : "+s"(v)); }
 
 // v + p[first stride] + p[(first + step) stride] + .. below count, in that order, with U

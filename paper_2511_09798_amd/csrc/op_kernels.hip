@@ -288,6 +288,23 @@ __global__ __launch_bounds__(kBlock) void k_mfs(const int4* __restrict__ items, 
             const int64_t k = sym_blk_start(cb < c1 ? cb : fb, L) + tid;
             qn = XS[k < L.n ? k : L.n - 1];
         }
+        // the lane's fixed nodes, all in flight together (rows past the block read
+        // its first): loads under a condition wait one by one, ten latencies a
+        // fixed block (1 800 nodes, one block a workgroup: 9.9 -> 9.0 us)
+        float4 qa[kMfmFt], qc[kMfmFt][4];
+#pragma unroll
+        for (int f = 0; f < kMfmFt; ++f) {
+            const int64_t base = fs + (int64_t)(wv * kMfmFt + f) * 16;
+            qa[f] = XS[base + jj < fe ? base + jj : fs];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) qc[f][r] = XS[base + 4 * g + r < fe ? base + 4 * g + r : fs];
+        }
+#pragma unroll
+        for (int f = 0; f < kMfmFt; ++f) {
+            arrived(qa[f]);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) arrived(qc[f][r]);
+        }
         v4u a[kMfmFt];
         v4f C[kMfmFt];
         float xi[kMfmFt][4];
@@ -298,10 +315,9 @@ __global__ __launch_bounds__(kBlock) void k_mfs(const int4* __restrict__ items, 
             const int64_t i = base + jj;
             float d[3] = {0.f, 0.f, 0.f};
             if (i < fe) {
-                const float4 q = XS[i];
-                d[0] = q.x - fr.x;
-                d[1] = q.y - fr.y;
-                d[2] = q.z - fr.z;
+                d[0] = qa[f].x - fr.x;
+                d[1] = qa[f].y - fr.y;
+                d[2] = qa[f].z - fr.z;
             }
             if (g < 3) {
                 a[f] = fixed_terms(-2.0f * d[g]);
@@ -317,7 +333,7 @@ __global__ __launch_bounds__(kBlock) void k_mfs(const int4* __restrict__ items, 
                 const int64_t i2 = base + 4 * g + r;
                 float d2 = 0.f, w = 0.f;
                 if (i2 < fe) {
-                    const float4 q = XS[i2];
+                    const float4 q = qc[f][r];
                     const float ex = q.x - fr.x, ey = q.y - fr.y, ez = q.z - fr.z;
                     d2 = fmaf(ez, ez, fmaf(ey, ey, ex * ex));
                     w = q.w;
@@ -919,12 +935,16 @@ __global__ __launch_bounds__(kBlock) void k_split_block(const float* __restrict_
     if (e >= nq * kBlkRhs) return;
     const int64_t q = e / kBlkRhs;
     const int k = (int)(e % kBlkRhs);
-    const float sc = vsc[k];
-    float v[4];
+    float sc = vsc[k];
+    float v[4];  // all loads in flight together
+#pragma unroll
+    for (int r = 0; r < 4; ++r) v[r] = Vg[(4 * q + r < n ? 4 * q + r : 4 * q) * kBlkRhs + k];
+    arrived(sc);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) arrived(v[r]);
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-        const int64_t j = 4 * q + r;
-        float x = j < n ? Vg[j * kBlkRhs + k] * sc : 0.f;
+        float x = 4 * q + r < n ? v[r] * sc : 0.f;
         if (__builtin_isfinite(x) && fabsf(x) > kBlkRange) x = copysignf(kBlkRange, x);
         v[r] = x;
     }
