@@ -202,8 +202,7 @@ __device__ __forceinline__ void replay_apply(double* X, int lx, int s, int r, in
         x[j] = (in && k < s) ? X + (int64_t)(r + j0 + j) * lx + k : sink;
     }
     double p = fma(vv[0], y[0], vv[1] * y[1]) + fma(vv[2], y[2], vv[3] * y[3]);
-    p += __shfl_xor(p, 16, kWave);
-    p += __shfl_xor(p, 32, kWave);
+    p = add_xor<32>(add_xor<16>(p));
     const double tw = tau * p;
 #pragma unroll
     for (int j = 0; j < 4; ++j) *x[j] = fma(-tw, vv[j], y[j]);

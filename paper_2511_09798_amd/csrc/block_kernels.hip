@@ -104,8 +104,7 @@ __global__ __launch_bounds__(kBlock) void k_blk_reduce(const double* __restrict_
     const int lane = threadIdx.x & (kWave - 1);
     double v = 0.0;
     for (int q = lane; q < chunks; q += kWave) v += part[(int64_t)q * m * kBlkRhs + e];
-#pragma unroll
-    for (int o = kWave / 2; o > 0; o >>= 1) v += __shfl_xor(v, o, kWave);
+    v = wave_sum(v);
     if (lane == 0) c[e] = v;
 }
 

@@ -104,10 +104,46 @@ __device__ __forceinline__ void wave_sync() {
 // Deterministic reductions (fixed butterfly / fixed order, no atomics)
 // ---------------------------------------------------------------------------
 
+template <int CTRL>
+__device__ __forceinline__ double row_move(double v) {
+    const int2 b = __builtin_bit_cast(int2, v);
+    return __builtin_bit_cast(double, make_int2(__builtin_amdgcn_mov_dpp(b.x, CTRL, 0xF, 0xF, true),
+                                                __builtin_amdgcn_mov_dpp(b.y, CTRL, 0xF, 0xF, true)));
+}
+
+// v + v of lane l ^ O, in registers: a lane exchange through LDS takes a latency of
+// its own, six of them a sum over the wave (1 800-node solve 3497 -> 3398 us).
+// O = 4: v is the same in lanes l and l ^ 8, as it is after O = 8.
+template <int O>
+__device__ __forceinline__ double add_xor(double v) {
+    static_assert(O == 32 || O == 16 || O == 8 || O == 4 || O == 2 || O == 1, "a power of two below the wave");
+    if constexpr (O >= 16) {
+        const uint2 b = __builtin_bit_cast(uint2, v);
+        unsigned x0, x1, y0, y1;
+        if constexpr (O == 32) {  // each half of the wave beside the other
+            const auto x = __builtin_amdgcn_permlane32_swap(b.x, b.x, false, false);
+            const auto y = __builtin_amdgcn_permlane32_swap(b.y, b.y, false, false);
+            x0 = x[0], x1 = x[1], y0 = y[0], y1 = y[1];
+        } else {  // each even row of 16 beside the odd one after it
+            const auto x = __builtin_amdgcn_permlane16_swap(b.x, b.x, false, false);
+            const auto y = __builtin_amdgcn_permlane16_swap(b.y, b.y, false, false);
+            x0 = x[0], x1 = x[1], y0 = y[0], y1 = y[1];
+        }
+        return __builtin_bit_cast(double, make_uint2(x0, y0)) + __builtin_bit_cast(double, make_uint2(x1, y1));
+    }
+    if constexpr (O == 8) return v + row_move<0x128>(v);  // row_ror:8
+    if constexpr (O == 4) return v + row_move<0x124>(v);  // row_ror:4
+    if constexpr (O == 2) return v + row_move<0x4E>(v);   // quad_perm 2 3 0 1
+    return v + row_move<0xB1>(v);                         // quad_perm 1 0 3 2
+}
+
 __device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, kWave);
-    return v;
+    v = add_xor<32>(v);
+    v = add_xor<16>(v);
+    v = add_xor<8>(v);
+    v = add_xor<4>(v);
+    v = add_xor<2>(v);
+    return add_xor<1>(v);
 }
 
 // Sum over a whole block of NT threads; every thread gets the total.

@@ -605,7 +605,7 @@ __global__ __launch_bounds__(kSmThreads) void k_cgs_small(const double* __restri
         double sum = 0.0;
 #pragma unroll
         for (int g = 0; g < kSmGroups / 2; ++g) sum += part[h * (kSmGroups / 2) + g][row];
-        sum += __shfl_xor(sum, kFuRows, kWave);
+        sum = add_xor<kFuRows>(sum);
         const int64_t i = (int64_t)b * kFuRows + row;
         double xi = 0.0;
         if (i < n) {

@@ -141,8 +141,7 @@ __device__ __forceinline__ int64_t sym_col_base(int beta, int F) {
 // 4p + 3), in a fixed order; every lane gets the sum.
 __device__ __forceinline__ double row_sum16(const double* __restrict__ row, int p) {
     double s = (row[4 * p] + row[4 * p + 1]) + (row[4 * p + 2] + row[4 * p + 3]);
-    s += __shfl_xor(s, 1, kWave);
-    s += __shfl_xor(s, 2, kWave);
+    s = add_xor<2>(add_xor<1>(s));
     return s;
 }
 

@@ -123,9 +123,8 @@ static_assert(kMaxEll <= kParThreads, "one singular value per thread in the sums
 constexpr int kParLanes = 4;  // lanes per point of the grid: 256 points (the default grid has 200) in one pass
 
 __device__ __forceinline__ double par_lanes_sum(double v) {
-#pragma unroll
-    for (int o = kParLanes / 2; o > 0; o >>= 1) v += __shfl_xor(v, o, kWave);
-    return v;
+    static_assert(kParLanes == 4, "the lanes of a quad");
+    return add_xor<1>(add_xor<2>(v));
 }
 
 // GCV numerator (without f~_{l+1}) and trace terms of one singular value.
