@@ -1340,14 +1340,23 @@ int stage_in(double* dst, const double* src, int64_t count, uint32_t flags, hipS
     return MQH_OK;
 }
 
-// p points to memory of the device itself, which its kernels may read and write.
-bool on_device(const void* ptr, int device) {
+// The `count` doubles at ptr are memory of the device itself that kernels may read and
+// write in place: at a double's address (their scalar loads drop the low address bits)
+// and within one allocation.  Anything else goes through a copy, which takes any
+// address and refuses a range that its allocation does not hold.
+bool on_device(const double* ptr, int64_t count, int device) {
+    if (reinterpret_cast<uintptr_t>(ptr) % alignof(double) != 0) return false;
     hipPointerAttribute_t a;
-    if (hipPointerGetAttributes(&a, ptr) != hipSuccess) {
+    hipDeviceptr_t base = nullptr;
+    size_t size = 0;
+    if (hipPointerGetAttributes(&a, ptr) != hipSuccess ||
+        hipMemGetAddressRange(&base, &size, const_cast<double*>(ptr)) != hipSuccess) {
         (void)hipGetLastError();
         return false;
     }
-    return a.type == hipMemoryTypeDevice && a.device == device;
+    const size_t off = reinterpret_cast<uintptr_t>(ptr) - reinterpret_cast<uintptr_t>(base);
+    return a.type == hipMemoryTypeDevice && a.device == device && off <= size &&
+           (size_t)count * sizeof(double) <= size - off;
 }
 
 int check_problem(const mqh_problem* p) {
@@ -2078,12 +2087,12 @@ int mqh_apply(mqh_problem* p, int32_t trans, const double* x, double shift, cons
     const bool overlap = z != nullptr && z != y && (uintptr_t)z < (uintptr_t)y + bytes &&
                          (uintptr_t)y < (uintptr_t)z + bytes;
     const double *xp = x, *zp = z;
-    double* out = dev && on_device(y, p->device) ? y : p->vy;
-    if (!dev || !on_device(x, p->device)) {
+    double* out = dev && on_device(y, p->n, p->device) ? y : p->vy;
+    if (!dev || !on_device(x, p->n, p->device)) {
         if ((rc = stage_in(p->vx, x, p->n, flags, p->stream))) return rc;
         xp = p->vx;
     }
-    if (z != nullptr && (!dev || overlap || !on_device(z, p->device))) {
+    if (z != nullptr && (!dev || overlap || !on_device(z, p->n, p->device))) {
         if ((rc = stage_in(p->vz, z, p->n, flags, p->stream))) return rc;
         zp = p->vz;
     }
@@ -2825,11 +2834,11 @@ int mqh_eval(mqh_problem* p, const double* coef, const double* x_eval, int64_t m
     const double* cf = coef;
     double* out = u;
     if (!dev && !all_finite(x_eval, 3 * m)) return fail(MQH_EINVAL, "non-finite evaluation point");
-    if (!dev || !on_device(coef, p->device)) {
+    if (!dev || !on_device(coef, p->n, p->device)) {
         if ((rc = stage_in(p->vx, coef, p->n, flags, s))) return rc;
         cf = p->vx;
     }
-    if (!dev || !on_device(x_eval, p->device)) {
+    if (!dev || !on_device(x_eval, 3 * m, p->device)) {
         if (3 * m > p->Exyz_cap) {
             dfree(p->Exyz);
             p->Exyz_cap = 0;
@@ -2839,7 +2848,7 @@ int mqh_eval(mqh_problem* p, const double* coef, const double* x_eval, int64_t m
         HIPCHK(hipMemcpyAsync(p->Exyz, x_eval, (size_t)(3 * m) * sizeof(double), kind_in(flags), s));
         xyz = p->Exyz;
     }
-    if (!dev || !on_device(u, p->device)) out = p->u;
+    if (!dev || !on_device(u, m, p->device)) out = p->u;
     p->eval_call = p->eval_call == INT32_MAX ? 1 : p->eval_call + 1;
     launch_eval_records(xyz, m, p->eps, p->center, p->eval_call, p->E, p->eval_flag, s);
     launch_eval(p->X64, cf, p->n, p->E, m, g, p->EP, ldm, p->eval_call, p->eval_flag, out, &p->hres->eval_bad, s);

@@ -213,6 +213,83 @@ def test_products_in_place_vectors(mq, mode, trans):
         assert np.array_equal(run(xd, zd, xd), ref)
 
 
+class _DeviceBytes:
+    """hipMalloc'ed bytes of exactly the size asked for (the page they end in is mapped whole)."""
+
+    def __init__(self, mq, size):
+        import ctypes
+
+        self.lib, self.p = mq.lib, ctypes.c_void_p()
+        self.lib.hipMalloc.argtypes = [ctypes.POINTER(ctypes.c_void_p), ctypes.c_size_t]
+        self.lib.hipMemcpy.argtypes = [ctypes.c_void_p, ctypes.c_void_p, ctypes.c_size_t, ctypes.c_int]
+        self.lib.hipFree.argtypes = [ctypes.c_void_p]
+        assert self.lib.hipMalloc(ctypes.byref(self.p), size) == 0
+        self.size = size
+
+    def put(self, a, off=0):
+        assert off + a.nbytes <= self.size
+        assert self.lib.hipMemcpy(self.p.value + off, a.ctypes.data, a.nbytes, 1) == 0
+        return self.p.value + off
+
+    def get(self, count, off=0):
+        a = np.empty(count)
+        assert self.lib.hipMemcpy(a.ctypes.data, self.p.value + off, a.nbytes, 2) == 0
+        return a
+
+    def free(self):
+        self.lib.hipFree(self.p)
+
+
+@pytest.mark.parametrize("mode", ["stored_fp64", "matfree_fp64"])
+@pytest.mark.parametrize("off", [2, 4])
+def test_device_arrays_at_any_address(mq, mode, off):
+    """Device arrays that do not start at a double's address (2 or 4 bytes past one): the bits of host arrays."""
+    n, m = 1003, 130
+    nodes, x, z, pts = I.random_nodes_cube(n, 8), I.random_vector(n, 5), I.random_vector(n, 6), I.random_nodes_cube(m, 9)
+    bufs = [_DeviceBytes(mq, 8 * k + 8) for k in (n, n, n, 3 * m, m)]
+    with mq.Problem(nodes[:700], nodes[700:], 9.0, 3.0, mode) as pr:
+        say("device arrays at any address", mode, off)
+        ref, uref = pr.apply(x, trans=True, shift=0.7, z=z), pr.eval(x, pts)
+        xp, zp, yp = bufs[0].put(x, off), bufs[1].put(z, off), bufs[2].p.value + off
+        assert mq.lib.mqh_apply(pr.h, 1, xp, 0.7, zp, yp, mq.MQH_FLAG_DEVICE_PTRS) == 0
+        assert np.array_equal(bufs[2].get(n, off), ref)
+        ep, up = bufs[3].put(pts.ravel(), off), bufs[4].p.value + off
+        assert mq.lib.mqh_eval(pr.h, xp, ep, m, up, mq.MQH_FLAG_DEVICE_PTRS) == 0
+        assert np.array_equal(bufs[4].get(m, off), uref)
+    for b in bufs:
+        b.free()
+
+
+def test_device_arrays_too_short(mq):
+    """A device array one element short of what the call takes is refused, whichever it is, and outputs that do
+    fit stay as they were.  (The missing element lies in the array's last page: nothing outside mapped memory.)"""
+    n, m = 1003, 130
+    nodes, x, z, pts = I.random_nodes_cube(n, 8), I.random_vector(n, 5), I.random_vector(n, 6), I.random_nodes_cube(m, 9)
+    mark = np.full(n, 7.0)
+    with mq.Problem(nodes[:700], nodes[700:], 9.0, 3.0, "matfree_fp64") as pr:
+        for short in range(3):
+            say("device arrays too short", "apply", short)
+            bufs = [_DeviceBytes(mq, 8 * (n - (k == short))) for k in range(3)]
+            ps = [b.put(a[: n - (k == short)]) for k, (b, a) in enumerate(zip(bufs, (x, z, mark)))]
+            assert mq.lib.mqh_apply(pr.h, 0, ps[0], 0.7, ps[1], ps[2], mq.MQH_FLAG_DEVICE_PTRS) < 0
+            left = n - (short == 2)
+            assert np.array_equal(bufs[2].get(left), mark[:left])
+            for b in bufs:
+                b.free()
+        for short in range(3):
+            say("device arrays too short", "eval", short)
+            data = (x, pts.ravel(), mark[:m])
+            bufs = [_DeviceBytes(mq, a.nbytes - 8 * (k == short)) for k, a in enumerate(data)]
+            ps = [b.put(a[: a.size - (k == short)]) for k, (b, a) in enumerate(zip(bufs, data))]
+            assert mq.lib.mqh_eval(pr.h, ps[0], ps[1], m, ps[2], mq.MQH_FLAG_DEVICE_PTRS) < 0
+            left = m - (short == 2)
+            assert np.array_equal(bufs[2].get(left), mark[:left])
+            for b in bufs:
+                b.free()
+        R = pr.matrix_rows(0, n)  # and the problem still works
+        assert np.all(np.abs(pr.apply(x) - R @ x) <= 1e-13 * (R @ np.abs(x)))
+
+
 def test_products_device_pointers(mq, orc):
     import torch
 
