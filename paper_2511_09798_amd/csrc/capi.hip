@@ -2853,10 +2853,14 @@ int mqh_eval(mqh_problem* p, const double* coef, const double* x_eval, int64_t m
     launch_eval_records(xyz, m, p->eps, p->center, p->eval_call, p->E, p->eval_flag, s);
     launch_eval(p->X64, cf, p->n, p->E, m, g, p->EP, ldm, p->eval_call, p->eval_flag, out, &p->hres->eval_bad, s);
     LAUNCHCHK("evaluation");
+    // u in other memory: host points were looked at above, so the copy need not wait for
+    // the device's verdict (a wait of its own before it: 1 000 centres from host arrays 45 -> 53 us)
+    const size_t bytes = (size_t)m * sizeof(double);
+    if (!dev) HIPCHK(hipMemcpyAsync(u, out, bytes, kind_out(flags), s));
     HIPCHK(hipStreamSynchronize(s));
     if (p->hres->eval_bad != 0) return fail(MQH_EINVAL, "non-finite evaluation point");
-    if (out != u) {
-        HIPCHK(hipMemcpyAsync(u, out, (size_t)m * sizeof(double), kind_out(flags), s));
+    if (dev && out != u) {
+        HIPCHK(hipMemcpyAsync(u, out, bytes, kind_out(flags), s));
         HIPCHK(hipStreamSynchronize(s));
     }
     return MQH_OK;
