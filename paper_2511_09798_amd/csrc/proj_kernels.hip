@@ -7,6 +7,7 @@
 #include <float.h>
 
 #include "bidiag_svd.hpp"
+#include "filter.hpp"
 #include "kernels.hpp"
 
 namespace mqh {
@@ -127,15 +128,6 @@ __device__ __forceinline__ double par_lanes_sum(double v) {
     return add_xor<1>(add_xor<2>(v));
 }
 
-// GCV numerator (without f~_{l+1}) and trace terms of one singular value.
-__device__ __forceinline__ void gcv_term(double s, double f, double l2, double& num, double& tr) {
-    const double s2 = s * s;
-    const double q = 1.0 / (s2 + l2);
-    const double x = (l2 * q) * f;
-    num = fma(x, x, num);
-    tr = fma(s2, q, tr);
-}
-
 // rho_l^2 / ((l+1) - omega sum_i phi_i)^2: eq. (30) for omega = 1, the
 // weighted GCV otherwise.
 __device__ __forceinline__ double gcv_of(double num, double tr, double flast, int l, double omega) {
@@ -147,7 +139,7 @@ __device__ __forceinline__ double gcv_of(double num, double tr, double flast, in
 __device__ inline double gcv_lanes(const double* sv, const double* ft, int l, double lam, double omega) {
     const double l2 = lam * lam;
     double a = 0.0, t = 0.0;
-    for (int i = threadIdx.x % kParLanes; i < l; i += kParLanes) gcv_term(sv[i], ft[i], l2, a, t);
+    for (int i = threadIdx.x % kParLanes; i < l; i += kParLanes) filter::gcv_term(sv[i], ft[i], l2, a, t);
     return gcv_of(par_lanes_sum(a), par_lanes_sum(t), ft[l], l, omega);
 }
 
@@ -155,26 +147,14 @@ __device__ inline double gcv_lanes(const double* sv, const double* ft, int l, do
 // d phi_i / dt = -2 phi_i psi_i) by kParLanes lanes.
 __device__ inline double lcurve_lanes(const double* sv, const double* ft, int l, double lam) {
     const double l2 = lam * lam;
-    double R = 0.0, R1 = 0.0, R2 = 0.0, E = 0.0, E1 = 0.0, E2 = 0.0;
-    for (int i = threadIdx.x % kParLanes; i < l; i += kParLanes) {
-        const double s2 = sv[i] * sv[i], f2 = ft[i] * ft[i];
-        const double q = 1.0 / (s2 + l2);
-        const double ph = s2 * q, ps = l2 * q;
-        const double r = ps * ps * f2, r1 = ph * r;
-        const double e = ph * q * f2, e1 = ps * e;  // phi^2 f2 / s2 = phi f2 / (s2 + l2)
-        R += r;
-        R1 += r1;
-        R2 = fma(r1, fma(2.0, ph, -ps), R2);
-        E += e;
-        E1 += e1;
-        E2 = fma(e1, fma(2.0, ps, -ph), E2);
-    }
-    R = fma(ft[l], ft[l], par_lanes_sum(R));
-    R1 = 4.0 * par_lanes_sum(R1);
-    R2 = 8.0 * par_lanes_sum(R2);
-    E = par_lanes_sum(E);
-    E1 = -4.0 * par_lanes_sum(E1);
-    E2 = 8.0 * par_lanes_sum(E2);
+    filter::CurveSums c;
+    for (int i = threadIdx.x % kParLanes; i < l; i += kParLanes) filter::lcurve_term(sv[i], ft[i], l2, c);
+    const double R = fma(ft[l], ft[l], par_lanes_sum(c.R));
+    const double R1 = 4.0 * par_lanes_sum(c.R1);
+    const double R2 = 8.0 * par_lanes_sum(c.R2);
+    const double E = par_lanes_sum(c.E);
+    const double E1 = -4.0 * par_lanes_sum(c.E1);
+    const double E2 = 8.0 * par_lanes_sum(c.E2);
     const double x1 = R1 / (2.0 * R), x2 = (R2 * R - R1 * R1) / (2.0 * R * R);
     const double y1 = E1 / (2.0 * E), y2 = (E2 * E - E1 * E1) / (2.0 * E * E);
     const double q = x1 * x1 + y1 * y1;
@@ -247,7 +227,7 @@ __global__ __launch_bounds__(kParThreads) void k_param_choice(const double* __re
     int nsum = 0;
     auto gcv_block = [&](double at) {
         double a = 0.0, t = 0.0;
-        if (tid < l) gcv_term(sv[tid], ft[tid], at * at, a, t);
+        if (tid < l) filter::gcv_term(sv[tid], ft[tid], at * at, a, t);
         par_block_sum2(a, t, nw, buf[nsum++ & 1]);
         return gcv_of(a, t, ft[l], l, omega);
     };
@@ -393,7 +373,7 @@ __global__ __launch_bounds__(kParThreads) void k_param_choice(const double* __re
         double gfix = 0.0;
         if (rule == 2) {  // the criterion at a given lambda: unweighted
             double a = 0.0, t = 0.0;
-            if (tid < l) gcv_term(sv[tid], ft[tid], l2, a, t);
+            if (tid < l) filter::gcv_term(sv[tid], ft[tid], l2, a, t);
             par_block_sum2(a, t, nw, buf[nsum++ & 1]);
             gfix = gcv_of(a, t, ft[l], l, 1.0);
         }

@@ -451,6 +451,25 @@ def test_projected_problem_shapes(mq, orc, kind, ell):
         assert np.max(np.abs(ch["curve"] - ref) / ref) <= (8 * ell * ell + 1024) * EPS
 
 
+@pytest.mark.parametrize("k", [-520, 508])
+def test_gcv_does_not_depend_on_the_scale(mq, k):
+    """The GCV curve of 2^k times the singular values: the same values at 2^k times the grid, also where the
+    squares are subnormal or near the largest number; a given lambda's criterion too."""
+    rng = np.random.default_rng(3)
+    s, f = np.sort(10.0 ** rng.uniform(-1, 0, 70))[::-1].copy(), rng.standard_normal(71)
+    say("gcv scale", k)
+    a = mq.mqh_param_choice(s, f, mq.MQH_METHOD_HKT, mq.MQH_RULE_GCV, n_grid=300, want_curve=True)
+    b = mq.mqh_param_choice(np.ldexp(s, k), f, mq.MQH_METHOD_HKT, mq.MQH_RULE_GCV, n_grid=300, want_curve=True)
+    # lambda as exp of a logarithm of up to 362: 362 eps of it; squares down to 2^-1047 with a step of 2^-1074
+    # (both sums are of positive terms, and at least 1 of 71 is left of the trace term)
+    tol = 71 * (8 * 362 * EPS + 2.0 ** -25)
+    assert np.all(np.abs(a["curve"] - b["curve"]) <= tol * a["curve"])
+    lam = 0.3
+    c = [mq.mqh_param_choice(np.ldexp(s, q), f, mq.MQH_METHOD_HKT, mq.MQH_RULE_FIXED, lambda_fixed=float(np.ldexp(lam, q)))
+         for q in (0, k)]
+    assert abs(c[0]["crit"] - c[1]["crit"]) <= tol * c[0]["crit"]
+
+
 def _decaying(l, seed):
     # a spectrum like that of a Golub-Kahan run on an ill-posed operator
     rng = np.random.default_rng(seed)
