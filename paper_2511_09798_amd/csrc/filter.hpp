@@ -24,11 +24,18 @@ struct Factors {
 // where the quotients do not, and they are divided out.
 constexpr double kDenMin = 0x1p-1000, kDenMax = 0x1p1000;
 
+// a / den from q = 1 / den rounded: a q and one correction by its remainder, which
+// rounds as the division does where nothing is subnormal.
+MQH_HD inline double quotient(double a, double q, double den) {
+    const double p = a * q;
+    return fma(fma(-p, den, a), q, p);
+}
+
 MQH_HD inline Factors factors(double s2, double l2, double f2) {
     const double den = s2 + l2;
     if (den >= kDenMin && den <= kDenMax) {
         const double q = 1.0 / den;
-        return Factors{s2 * q, l2 * q, f2 * q};
+        return Factors{quotient(s2, q, den), quotient(l2, q, den), quotient(f2, q, den)};
     }
     return Factors{s2 / den, l2 / den, f2 / den};
 }

@@ -47,8 +47,17 @@ def test_factors_over_the_whole_range(lib, k):
     phi, psi, _ = _factors(lib, s2, l2, np.ones_like(s2))
     den = s2 + l2
     for got, ref in ((phi, s2 / den), (psi, l2 / den)):
-        # two roundings (the reciprocal, the product) against one
-        assert np.all(np.abs(got - ref) <= 1.5 * EPS * ref)
+        assert np.all(np.abs(got - ref) <= EPS * ref)
+
+
+@pytest.mark.parametrize("k", [-900, -100, 0, 100, 900])
+def test_factors_round_as_divisions(lib, k):
+    """One rounding a quotient: bit for bit the correctly rounded divisions."""
+    s2, l2 = _spread(k, 100000)
+    f2 = np.ldexp(_spread(7, 100000)[0], k)
+    den = s2 + l2
+    for got, num in zip(_factors(lib, s2, l2, f2), (s2, l2, f2)):
+        assert np.array_equal(got, num / den)
 
 
 @pytest.mark.parametrize("k", [-520, -512, -500, 0, 500, 508])
