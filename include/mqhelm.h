@@ -60,9 +60,10 @@ extern "C" {
 /* ---- operator modes (how A enters the products) ---- */
 #define MQH_OP_STORED_FP64 0   /* A assembled once in HBM, FP64 products.  Stored in 128 x 128 tiles,
                                   one value per unordered pair of nodes (A_ij and A_ji are functions of
-                                  |X_i - X_j|: L phi for two interior nodes, phi otherwise, from which a
-                                  product forms the interior row's entry), so A takes about 4 N^2 bytes
-                                  (40 GB instead of 80 GB at N = 100 000) */
+                                  |X_i - X_j|: L phi for two interior nodes, phi for two boundary nodes,
+                                  1 + eps^2 |X_i - X_j|^2 for a mixed pair, from which a product forms
+                                  both entries), so A takes about 4 N^2 bytes (40 GB instead of 80 GB at
+                                  N = 100 000) */
 #define MQH_OP_MATFREE_FP64 1  /* entries regenerated inside every product, FP64 throughout */
 #define MQH_OP_MATFREE_FP32 2  /* entries evaluated in FP32 (the squared distances on the matrix
                                   cores, FP32-accurate), accumulated in FP64 */

@@ -18,16 +18,17 @@ namespace mqh {
 // row-major inside a tile, tile row after tile row:
 //   both interior:  L phi (= A_ij = A_ji);
 //   both boundary:  phi   (= A_ij = A_ji);
-//   mixed (R interior, C boundary): phi = A_ji; the product forms
-//                   A_ij = L phi from it (lphi_of_phi).
+//   mixed (R interior, C boundary): t = 1 + |X_i - X_j|^2, from which the product
+//                   forms A_ij = L phi and A_ji = phi as the assembly does
+//                   for the other tiles, so that every entry is rounded alike.
 // A product visits every stored tile once, as T x_C for y_R (row use) and, off
 // the diagonal, as T^T x_R for y_C (column use).  On a mixed tile A x takes L phi
 // for the rows and phi for the columns, A^T x the other way round.
 // The product is bound by HBM, and the mixed blocks' second copy was a
 // quarter of its bytes at 20% boundary nodes: 100 000 nodes 53.0 -> 40.1 GB,
 // A^T x 8.60 -> 6.46 ms (6.2 TB/s either way); 20 000 nodes 2.27 -> 1.63 GB,
-// 375 -> 268 us.  Forming L phi costs 8 FP64 instructions and one v_rcp_f64 per
-// mixed entry, under the streaming time (about 49 FP64 issue slots per value).
+// 375 -> 268 us.  Forming the two entries costs 9 FP64 instructions and one v_rsq_f64
+// per mixed value, under the streaming time (about 49 FP64 issue slots per value).
 // ---------------------------------------------------------------------------
 
 // Dense row-major A (n rows, leading dimension lda, zero columns past n), for
@@ -72,28 +73,18 @@ __device__ __forceinline__ int64_t pk_tile(const PackedLayout& L, int R, int C) 
     return (int64_t)R * L.nt - (int64_t)R * (R - 1) / 2 + (C - R);
 }
 
-// L phi from phi = sqrt(t) >= 1: s = 1 / phi from the hardware estimate e (relative
-// error below 2^-22) and one third-order step e (1 + d + d^2), d = 1 - phi e (the
-// dropped terms are below 2^-66), then the interior formula with t = phi^2.
-__device__ __forceinline__ double lphi_of_phi(double q, const EntryConst& c) {
-    const double e = __builtin_amdgcn_rcp(q);
-    const double d = fma(-q, e, 1.0);
-    const double s = fma(e, fma(d, d, d), e);
-    return fma(c.e2, s * s, fma(c.k2, q * q, c.e2x2)) * s;
-}
-
 // The stored value of pair (node R_i, node C_j) in tile (blockIdx.y = R, C = R +
 // blockIdx.x): one workgroup per stored tile, four rows at a time, two columns
 // per lane, 16-byte non-temporal stores.  Padding rows and columns hold zero,
-// in mixed tiles one (they multiply zeros of x, and lphi_of_phi stays finite).
+// in mixed tiles one (they multiply zeros of x, and the entries formed of them are finite).
 __global__ __launch_bounds__(kBlock) void k_assemble_packed(const double4* __restrict__ X, PackedLayout L,
                                                             EntryConst c, double* __restrict__ A) {
     const int R = blockIdx.y, C = R + (int)blockIdx.x;
     if (C >= L.nt) return;  // whole workgroup; no barriers in this kernel
     const int64_t r0 = pk_start(L, R), rend = pk_end(L, R);
     const int64_t c0 = pk_start(L, C), cend = pk_end(L, C);
-    const bool lphi = C < L.nti;
-    const double pad = R < L.nti && C >= L.nti ? 1.0 : 0.0;
+    const bool lphi = C < L.nti, mixed = R < L.nti && !lphi;
+    const double pad = mixed ? 1.0 : 0.0;
     const int lane2 = 2 * (threadIdx.x & (kWave - 1));
     const int64_t ja = c0 + lane2, jb = ja + 1;
     const bool va = ja < cend, vb = jb < cend;
@@ -109,8 +100,8 @@ __global__ __launch_bounds__(kBlock) void k_assemble_packed(const double4* __res
             const double4 q = X[g];
             const double ta = t_of(q.x, q.y, q.z, qa.x, qa.y, qa.z);
             const double tb = t_of(q.x, q.y, q.z, qb.x, qb.y, qb.z);
-            const double ea = lphi ? entry_interior(ta, c) : entry_boundary(ta, c);
-            const double eb = lphi ? entry_interior(tb, c) : entry_boundary(tb, c);
+            const double ea = mixed ? ta : (lphi ? entry_interior(ta, c) : entry_boundary(ta, c));
+            const double eb = mixed ? tb : (lphi ? entry_interior(tb, c) : entry_boundary(tb, c));
             v.x = va ? ea : pad;
             v.y = vb ? eb : pad;
         }
@@ -202,11 +193,12 @@ __global__ __launch_bounds__(kBlock) void k_packed_product(const double* __restr
         if (mixed) {
 #pragma unroll
             for (int r = 0; r < GR; ++r) {
-                const double l0 = lphi_of_phi(a[r].x, ec), l1 = lphi_of_phi(a[r].y, ec);
+                const double l0 = entry_interior(a[r].x, ec), l1 = entry_interior(a[r].y, ec);
+                const double f0 = entry_boundary(a[r].x, ec), f1 = entry_boundary(a[r].y, ec);
                 const double xi = xr[rbase + r];
-                cs0 = fma(TRANS ? l0 : a[r].x, xi, cs0);
-                cs1 = fma(TRANS ? l1 : a[r].y, xi, cs1);
-                rp[r] = TRANS ? fma(a[r].y, xc1, a[r].x * xc0) : fma(l1, xc1, l0 * xc0);
+                cs0 = fma(TRANS ? l0 : f0, xi, cs0);
+                cs1 = fma(TRANS ? l1 : f1, xi, cs1);
+                rp[r] = TRANS ? fma(f1, xc1, f0 * xc0) : fma(l1, xc1, l0 * xc0);
             }
         } else {
 #pragma unroll
@@ -303,7 +295,7 @@ __global__ __launch_bounds__(kRedGroups * kTile) void k_packed_reduce(PackedLayo
 
 // Rows [row0, row0 + gridDim.y) of the stored tiled matrix, row-major with
 // leading dimension n (an entry below the diagonal is read from the transposed
-// stored tile; an interior row's boundary column is formed as the products do).
+// stored tile; an entry of a mixed tile is formed as the products do).
 __global__ __launch_bounds__(kBlock) void k_packed_rows(const double* __restrict__ A, PackedLayout L, EntryConst ec,
                                                         int64_t row0, double* __restrict__ out) {
     const int64_t j = (int64_t)blockIdx.x * kBlock + threadIdx.x;
@@ -315,7 +307,7 @@ __global__ __launch_bounds__(kBlock) void k_packed_rows(const double* __restrict
     const int jc = (int)(j - pk_start(L, C));
     double v = C < R ? A[pk_tile(L, C, R) * kTileElems + (int64_t)jc * kTile + ir]
                      : A[pk_tile(L, R, C) * kTileElems + (int64_t)ir * kTile + jc];
-    if (R < L.nti && C >= L.nti) v = lphi_of_phi(v, ec);
+    if ((R < L.nti) != (C < L.nti)) v = R < L.nti ? entry_interior(v, ec) : entry_boundary(v, ec);
     out[(int64_t)blockIdx.y * L.n + j] = v;
 }
 

@@ -119,6 +119,19 @@ def test_stored_pair_values(mq, orc, n_int, n_bnd, row_scale):
         assert np.all(np.abs(y - (M @ x - 0.5 * z)) <= 1e-13 * (np.abs(M) @ np.abs(x) + np.abs(z)))
 
 
+@pytest.mark.parametrize("row_scale", [0, 1])
+@pytest.mark.parametrize("kappa,eps", [(7.0, 2.5), (0.5, 12.0), (40.0, 0.3)])
+def test_stored_entries_round_once(mq, kappa, eps, row_scale):
+    """The stored matrix holds the entries that the formula gives, bit for bit, whatever its tiles keep."""
+    nodes = I.random_nodes_cube(700, 79)
+    R = {}
+    for mode in ("stored_fp64", "matfree_fp64"):
+        with mq.Problem(nodes[:430], nodes[430:], kappa, eps, mode) as pr:
+            say("stored entries", mode, kappa, eps, row_scale)
+            R[mode] = pr.matrix_rows(0, pr.n, row_scale=row_scale)
+    assert np.array_equal(R["stored_fp64"], R["matfree_fp64"])
+
+
 @pytest.mark.parametrize("n_int,n_bnd", [(63, 1), (64, 65), (3300, 900), (15361, 4740)])
 def test_fp64_pair_product_shapes(mq, n_int, n_bnd):
     """The FP64 pair products' work shapes (blocks of 64 nodes; 1 x 2 and 1 x 4 blocks of 128) with ragged
