@@ -12,22 +12,30 @@
 // (d_{n-1}, .., d_0), (e_{n-2}, .., e_0).  A bidiagonal determines its
 // singular values to high relative accuracy, and so do these factored forms;
 // the differential qd transforms below work on them without forming B^T B:
-//  * negcount: the stationary transform L D L^T - x I = L+ D+ L+^T; the
-//    number of negative D+_i is the number of eigenvalues below x
-//    (Sylvester's law of inertia), which drives the bisection of the values;
-//  * stationary + progressive_twist: the top-down (L+ D+ L+^T) and bottom-up
+//  * negcount: the number of negative pivots of the factorisation of L D L^T - x I
+//    is the number of eigenvalues below x (Sylvester's law of inertia),
+//    which drives the bisection of the values;
+//  * chain_operands, pair_chain: the top-down (L+ D+ L+^T) and bottom-up
 //    (U- D- U-^T) factorisations of L D L^T - lambda I at an eigenvalue
-//    lambda; gamma_k = s_k + p_k + lambda is the pivot of the factorisation
-//    twisted at k, and the k of least |gamma_k| gives the eigenvector by one
-//    step of inverse iteration (twisted_solve) with z_k = 1.
-// Zero pivots (in the quotient form pivots below pivmin in magnitude) are
-// replaced by tiny negative ones (a perturbation of x within the rounding of
-// the data), so no recurrence divides by zero; in the quotient form of the
-// count a quotient that comes out NaN is taken as 1.
+//    lambda, D+_i = s_i + d_i^2, L+_i = d_i e_i / D+_i, s_{i+1} = e_i^2 s_i /
+//    D+_i - lambda from s_0 = -lambda, and D-_{i+1} = e_i^2 + p_{i+1}, U-_i =
+//    d_i e_i / D-_{i+1}, p_i = p_{i+1} d_i^2 / D-_{i+1} - lambda from
+//    p_{n-1} = d_{n-1}^2 - lambda;
+//  * twist_step, twisted_from: gamma_k = s_k + p_k + lambda is the pivot of the
+//    factorisation twisted at k, and the k of least |gamma_k| (the smallest on
+//    ties) gives the eigenvector by one step of inverse iteration with z_k = 1.
+// Zero pivots (in the quotient form of the count pivots below pivmin in
+// magnitude) are replaced by tiny negative ones (a perturbation of x within the
+// rounding of the data), so no recurrence divides by zero; in the quotient
+// form of the count a quotient that comes out NaN is taken as 1.
 #pragma once
 
 #include <math.h>
 #include <stdint.h>
+
+#ifndef __HIPCC__
+#include <vector>
+#endif
 
 #ifdef __HIPCC__
 #define MQH_HD __host__ __device__
@@ -93,6 +101,19 @@ MQH_HD inline double scale_of(uint32_t ex) {
 #endif
 }
 MQH_HD inline double pair_scale(double a, double b) { return scale_of(pair_exponent(a, b)); }
+
+// The map (u, v) -> (a u, c u + b v) up to a common factor, a, b, c >= 0, and the
+// product of two (later after earlier); positive terms only, so every entry keeps
+// its relative accuracy.
+struct QMap {
+    double a, c, b;
+};
+MQH_HD inline QMap after(const QMap& x, const QMap& y) {
+    const double a = x.a * y.a, c = fma(x.c, y.a, x.b * y.c), b = x.b * y.b;
+    const uint32_t ea = pair_exponent(a, b), ec = pair_exponent(c, 0.0);
+    const double s = scale_of(ea > ec ? ea : ec);
+    return QMap{a * s, c * s, b * s};
+}
 
 // acc with the sign of c shifted in, and the sign changes among its last m + 1 bits.
 MQH_HD inline uint32_t push_sign(uint32_t acc, double c) {
@@ -313,74 +334,45 @@ MQH_HD inline double pair_multiplier(double a, double b, double u, double de) {
     return de * c / pair_pivot(fma(u, c, a));
 }
 
-// Top-down transform at lambda: s_0 = -lambda; for i < n - 1,
-// D+_i = s_i + d_i^2, L+_i = d_i e_i / D+_i, s_{i+1} = e_i^2 s_i / D+_i - lambda.
-// Writes s[0..n-1] and lp[0..n-2].
-MQH_HD inline void stationary(const double* d, int ds, const double* e, int es, int n, double lam, double,
-                              double* lp, double* s) {
-    double w = 0.0, c = 1.0;
-    for (int i = 0; i < n; ++i) {
-        const double di = d[i * ds], ei = i + 1 < n ? e[i * es] : 0.0, b = c;
-        const double a = pair_step(w, c, di * di, ei * ei, lam);
-        if (i + 1 < n) lp[i] = pair_multiplier(a, b, di * di, di * ei);
-        s[i] = pair_quotient(a, b);
-        if (i % kRescale == kRescale - 1) {
-            const double sc = pair_scale(w, c);
-            w *= sc;
-            c *= sc;
-        }
-    }
+// The four chains of a singular triple: side 0 is B^T B on (d, e), side 1 B B^T on
+// the reversed sequences, chain c = side + 2 bottom_up at ch + 2 ld c (ld >= l).
+// Operands of step k of every chain, k < l - 1, and a chain's w0.
+MQH_HD inline void chain_operands(const double* d, const double* e, int l, int ld, int k, double* ch) {
+    const double dk = d[k], dk1 = d[k + 1], ek = e[k];
+    const int kr = l - 2 - k;  // e_k is entry kr of the reversed sequence
+    double* c0 = ch + 2 * k;
+    double* c1 = ch + 2 * ld + 2 * kr;
+    double* c2 = ch + 4 * ld + 2 * kr;
+    double* c3 = ch + 6 * ld + 2 * k;
+    c0[0] = dk * dk;
+    c0[1] = ek * ek;
+    c1[0] = dk1 * dk1;
+    c1[1] = ek * ek;
+    c2[0] = ek * ek;
+    c2[1] = dk * dk;
+    c3[0] = ek * ek;
+    c3[1] = dk1 * dk1;
+}
+MQH_HD inline double chain_start(const double* d, int l, int c) {
+    const double dn = c == 2 ? d[l - 1] : (c == 3 ? d[0] : 0.0);
+    return dn * dn;
 }
 
-// Bottom-up transform at lambda: p_{n-1} = d_{n-1}^2 - lambda; for
-// i = n-2 .. 0, D-_{i+1} = e_i^2 + p_{i+1}, U-_i = d_i e_i / D-_{i+1},
-// p_i = p_{i+1} d_i^2 / D-_{i+1} - lambda; with gamma_k = s_k + p_k + lambda
-// on the way.  Returns the twist index r = argmin |gamma_k| (the smallest k
-// on ties) and its gamma; U-_i replaces s_i in su (s_i is read first).
-MQH_HD inline int progressive_twist(const double* d, int ds, const double* e, int es, int n, double lam, double,
-                                    double* su, double* gamma_r) {
-    const double dn = d[(n - 1) * ds];
-    double w = dn * dn, b = 1.0;
-    double gbest = su[n - 1] + pair_quotient(fma(-lam, b, w), b) + lam;
-    int r = n - 1;
-    for (int i = n - 2; i >= 0; --i) {
-        const double di = d[i * ds], ei = e[i * es];
-        const double b0 = b;
-        const double um = pair_multiplier(pair_step(w, b, ei * ei, di * di, lam), b0, ei * ei, di * ei);
-        if ((n - 1 - i) % kRescale == 0) {
-            const double sc = pair_scale(w, b);
-            w *= sc;
-            b *= sc;
-        }
-        const double g = su[i] + pair_quotient(fma(-lam, b, w), b) + lam;
-        if (fabs(g) <= fabs(gbest)) {  // ties to the smaller index
-            gbest = g;
-            r = i;
-        }
-        su[i] = um;
+// |gamma_i| of a side from the pairs of its two chains; the multipliers L+_i and U-_i
+// (i < l - 1) take the place of the top-down pair.
+MQH_HD inline double twist_step(const double* d, const double* e, int l, int ld, int side, int i, double lam,
+                                double* ch) {
+    const double di = side ? d[l - 1 - i] : d[i];
+    const double ei = i + 1 < l ? (side ? e[l - 2 - i] : e[i]) : 0.0;
+    double* top = ch + 2 * ld * side + 2 * i;
+    const double* bot = ch + 2 * ld * (side + 2) + 2 * (l - 1 - i);
+    const double a = top[0], b = top[1];
+    const double g = fabs(pair_quotient(a, b) + pair_quotient(bot[0], bot[1]) + lam);
+    if (i + 1 < l) {
+        top[0] = pair_multiplier(a, b, di * di, di * ei);
+        top[1] = pair_multiplier(bot[-2], bot[-1], ei * ei, di * ei);
     }
-    *gamma_r = gbest;
-    return r;
-}
-
-// One direction of the twisted solve from z_r = 1: dir < 0 gives
-// z_i = -L+_i z_{i+1} for i = r-1 .. 0, dir > 0 gives z_{i+1} = -U-_i z_i for
-// i = r .. n-2.  z shares storage with lp (lp_i is read before z_i is
-// written, and the two directions touch disjoint entries); z_r itself is
-// set by the caller.
-MQH_HD inline void twisted_solve(double* lp_z, const double* um, int n, int r, int dir) {
-    double z = 1.0;
-    if (dir < 0) {
-        for (int i = r - 1; i >= 0; --i) {
-            z = -lp_z[i] * z;
-            lp_z[i] = z;
-        }
-    } else {
-        for (int i = r; i < n - 1; ++i) {
-            z = -um[i] * z;
-            lp_z[i + 1] = z;
-        }
-    }
+    return g;
 }
 
 // One direction of the twisted solve from z_r = 1 (z_r included, so that both may run
@@ -414,6 +406,52 @@ MQH_HD inline void twisted_from(const double* mul, int st, int n, int r, int dir
         out[0] = z;
     }
 }
+
+#ifndef __HIPCC__
+// The recurrences above on strided sequences, one transform at a time, for host
+// programs: s and L+ of the top-down transform; the twist index and its gamma with U-
+// in place of s (su); one direction of the twisted solve, z in place of L+ (z_r is the
+// caller's).
+inline void stationary(const double* d, int ds, const double* e, int es, int n, double lam, double, double* lp,
+                       double* s) {
+    std::vector<double> uv(2 * (size_t)n);
+    for (int i = 0; i + 1 < n; ++i) {
+        uv[2 * i] = d[i * ds] * d[i * ds];
+        uv[2 * i + 1] = e[i * es] * e[i * es];
+    }
+    pair_chain(uv.data(), n, 0.0, lam);
+    for (int i = 0; i < n; ++i) {
+        s[i] = pair_quotient(uv[2 * i], uv[2 * i + 1]);
+        if (i + 1 < n) lp[i] = pair_multiplier(uv[2 * i], uv[2 * i + 1], d[i * ds] * d[i * ds], d[i * ds] * e[i * es]);
+    }
+}
+inline int progressive_twist(const double* d, int ds, const double* e, int es, int n, double lam, double, double* su,
+                             double* gamma_r) {
+    std::vector<double> uv(2 * (size_t)n);  // entry k: index n - 1 - k
+    for (int k = 0; k + 1 < n; ++k) {
+        const int i = n - 2 - k;
+        uv[2 * k] = e[i * es] * e[i * es];
+        uv[2 * k + 1] = d[i * ds] * d[i * ds];
+    }
+    pair_chain(uv.data(), n, d[(n - 1) * ds] * d[(n - 1) * ds], lam);
+    int r = -1;
+    for (int i = 0; i < n; ++i) {
+        const double* bot = uv.data() + 2 * (n - 1 - i);
+        const double g = su[i] + pair_quotient(bot[0], bot[1]) + lam;
+        if (r < 0 || fabs(g) < fabs(*gamma_r)) {
+            *gamma_r = g;
+            r = i;
+        }
+        if (i + 1 < n) su[i] = pair_multiplier(bot[-2], bot[-1], e[i * es] * e[i * es], d[i * ds] * e[i * es]);
+    }
+    return r;
+}
+inline void twisted_solve(double* lp_z, const double* um, int n, int r, int dir) {
+    std::vector<double> z(n);
+    twisted_from(dir < 0 ? lp_z : um, 1, n, r, dir, z.data());
+    for (int i = r + dir; i >= 0 && i < n; i += dir) lp_z[i] = z[i];
+}
+#endif
 
 // d x + e y - s w for one row of B v - s u (or B^T u - s v) with the
 // rounding error of e y added back (two-product by fma): near a singular
@@ -476,7 +514,7 @@ constexpr double kResTol = 1e-9;
 MQH_HD inline double resid_bound(double s, double s1, int n) {
     return kResTol * s + 64.0 * (double)n * 2.220446049250313e-16 * s1;
 }
-constexpr int kSections = 256;  // multisection points per round (the device takes 64 to 256)
+constexpr int kSections = 256;  // multisection points per round at most (64 to 256 on the device, by l)
 
 }  // namespace msvd
 }  // namespace mqh

@@ -65,19 +65,6 @@ __device__ __forceinline__ double block_max(double v, double* lds) {
     return m;
 }
 
-// The map (u, v) -> (a u, c u + b v) up to a common factor, a, b, c >= 0, and the
-// product of two (later after earlier); positive terms only, so every entry keeps
-// its relative accuracy.
-struct QMap {
-    double a, c, b;
-};
-__device__ __forceinline__ QMap after(const QMap& x, const QMap& y) {
-    const double a = x.a * y.a, c = fma(x.c, y.a, x.b * y.c), b = x.b * y.b;
-    const uint32_t ea = msvd::pair_exponent(a, b), ec = msvd::pair_exponent(c, 0.0);
-    const double s = msvd::scale_of(ea > ec ? ea : ec);
-    return QMap{a * s, c * s, b * s};
-}
-
 }  // namespace
 
 // ---------------------------------------------------------------------------
@@ -131,15 +118,15 @@ __global__ __launch_bounds__(kBlock) void k_msvd_setup(const double* __restrict_
             // a chunk of steps per lane, a scan over the lanes, the chunks again
             const int per = (l - 1 + kWave - 1) / kWave;
             const int i0 = tid * per < l - 1 ? tid * per : l - 1, i1 = i0 + per < l - 1 ? i0 + per : l - 1;
-            QMap m{1.0, 0.0, 1.0};
+            msvd::QMap m{1.0, 0.0, 1.0};
             for (int i = i0; i < i1; ++i) {
                 const double a = sa[i + 1], b = sb[i + 1];
-                m = after(QMap{a * a, 1.0, b * b}, m);
+                m = msvd::after(msvd::QMap{a * a, 1.0, b * b}, m);
             }
 #pragma unroll
             for (int o = 1; o < kWave; o <<= 1) {
-                const QMap p{__shfl_up(m.a, o, kWave), __shfl_up(m.c, o, kWave), __shfl_up(m.b, o, kWave)};
-                if (tid >= o) m = after(m, p);
+                const msvd::QMap p{__shfl_up(m.a, o, kWave), __shfl_up(m.c, o, kWave), __shfl_up(m.b, o, kWave)};
+                if (tid >= o) m = msvd::after(m, p);
             }
             const double pa = __shfl_up(m.a, 1, kWave), pc = __shfl_up(m.c, 1, kWave), pb1 = __shfl_up(m.b, 1, kWave);
             double u = sa[0] * sa[0], v = 1.0;
@@ -337,27 +324,9 @@ __global__ __launch_bounds__(kWave) void k_msvd_vectors(int32_t L, const int32_t
     const double lam = ldexp(w.lam[j], -2 * shf);
     const double sig = ldexp(sv[j], -shf);
     __syncthreads();
-    for (int k = lane; k + 1 < l; k += kWave) {
-        const double dk = Ld[k], dk1 = Ld[k + 1], ek = Le[k];
-        const int kr = l - 2 - k;  // e_k is entry kr of the reversed sequence
-        double* c0 = Ch + 2 * k;
-        double* c1 = Ch + 2 * L + 2 * kr;
-        double* c2 = Ch + 4 * L + 2 * kr;
-        double* c3 = Ch + 6 * L + 2 * k;
-        c0[0] = dk * dk;
-        c0[1] = ek * ek;
-        c1[0] = dk1 * dk1;
-        c1[1] = ek * ek;
-        c2[0] = ek * ek;
-        c2[1] = dk * dk;
-        c3[0] = ek * ek;
-        c3[1] = dk1 * dk1;
-    }
+    for (int k = lane; k + 1 < l; k += kWave) msvd::chain_operands(Ld, Le, l, L, k, Ch);
     __syncthreads();
-    if (lane < 4) {
-        const double dn = lane == 2 ? Ld[l - 1] : (lane == 3 ? Ld[0] : 0.0);
-        msvd::pair_chain(Ch + 2 * L * lane, l, dn * dn, lam);
-    }
+    if (lane < 4) msvd::pair_chain(Ch + 2 * L * lane, l, msvd::chain_start(Ld, l, lane), lam);
     __syncthreads();
     int tw[2];
 #pragma unroll
@@ -365,19 +334,10 @@ __global__ __launch_bounds__(kWave) void k_msvd_vectors(int32_t L, const int32_t
         double best = INFINITY;
         int r = l - 1;
         for (int i = lane; i < l; i += kWave) {
-            const double di = side ? Ld[l - 1 - i] : Ld[i];
-            const double ei = i + 1 < l ? (side ? Le[l - 2 - i] : Le[i]) : 0.0;
-            double* top = Ch + 2 * L * side + 2 * i;
-            const double* bot = Ch + 2 * L * (side + 2) + 2 * (l - 1 - i);
-            const double a = top[0], b = top[1];
-            const double g = fabs(msvd::pair_quotient(a, b) + msvd::pair_quotient(bot[0], bot[1]) + lam);
+            const double g = msvd::twist_step(Ld, Le, l, L, side, i, lam, Ch);
             if (g < best) {  // ties to the smaller index
                 best = g;
                 r = i;
-            }
-            if (i + 1 < l) {
-                top[0] = msvd::pair_multiplier(a, b, di * di, di * ei);
-                top[1] = msvd::pair_multiplier(bot[-2], bot[-1], ei * ei, di * ei);
             }
         }
 #pragma unroll
