@@ -168,6 +168,24 @@ def test_reorthogonalisation_forms(mq, orc, n, ell):
             assert np.array_equal(g[k][key], m[key][k]), key
 
 
+@pytest.mark.parametrize("mode", ["stored_fp64", "matfree_fp64"])
+@pytest.mark.parametrize("n,nrhs,ell", [(2100, 16, 40), (4003, 9, 12), (20001, 2, 5)])
+def test_lockstep_sums_by_their_own_launch(mq, mode, n, nrhs, ell):
+    """Groups whose row blocks no longer fit one round sum the projection coefficients by a launch of their
+    own, a run alone in the kernel that needs them: the bits are the same."""
+    n_int = int(0.8 * n)
+    p = I.cube_scaled(n_int, n - n_int, kappa=12.0, eps=3.4, ell=ell)
+    F = np.stack([I.random_vector(n, 60 + k) for k in range(nrhs)])
+    with _problem(mq, p, mode) as pr:
+        say("lockstep sums", mode, n, nrhs, ell)
+        m = pr.gkb_multi(F, ell)
+        for k in (0, nrhs - 1):
+            g = pr.gkb(F[k], ell)
+            assert g["ell_done"] == ell
+            for key in ("W", "Z", "alpha", "beta"):
+                assert np.array_equal(g[key], m[key][k]), key
+
+
 @pytest.mark.parametrize("m", [1, 63, 64, 65, 1025])
 @pytest.mark.parametrize("n", [1, 48, 49, 385, 2100])
 def test_evaluation_shapes(mq, orc, n, m):
