@@ -526,7 +526,7 @@ __global__ __launch_bounds__(kBlock) void k_update_gemvt(const double* __restric
 // 512 threads per kFuRows rows.  Half the threads bring the rows of V[:, 0:m]
 // into LDS while the other half sums the projection coefficients from the nb1
 // partials p1 (layout b m + k), so the two latencies overlap and no reduction
-// is launched (RED; else it takes them from c); then x -= V c.  NORM false (first pass): out[b m + k] = the second
+// is launched; then x -= V c.  NORM false (first pass): out[b m + k] = the second
 // projection's partials; true (second pass): out[b] = the block's sum of
 // squares, and the state's snapshot for the normalisation.  These kernels are
 // bound by their launch and one memory latency: at 1 800 nodes and up to 60
@@ -537,21 +537,20 @@ constexpr int kSmMaxCols = 192;
 static_assert(kSmMaxCols * kFuLd * 8 + (kSmGroups + 1) * kFuRows * 8 + kSmMaxCols * 8 <= 65536, "LDS within 64 KB");
 static_assert(kSmThreads == 2 * kBlock && kSmGroups * kFuRows >= kBlock, "two halves; sums fit the row sums' LDS");
 
-template <bool NORM, bool RED>
+template <bool NORM>
 __global__ __launch_bounds__(kSmThreads) void k_cgs_small(const double* __restrict__ V, const double* __restrict__ p1,
                                                           GkbState* __restrict__ st, double* __restrict__ x, int64_t n,
                                                           int64_t ldn, int32_t m, int nb1, double* __restrict__ out,
-                                                          const double* __restrict__ c, int64_t cstr, Bz bz) {
+                                                          Bz bz) {
     extern __shared__ double tile[];  // [m][kFuLd]
     __shared__ double part[kSmGroups][kFuRows];
     __shared__ double xs[kFuRows];
     __shared__ double cs[kSmMaxCols];
-    // batch: V + z bz.a, p1 + z bz.b, x + z bz.c, out + z bz.d, c + z cstr, state z
+    // batch: V + z bz.a, p1 + z bz.b, x + z bz.c, out + z bz.d, state z
     const int64_t z = blockIdx.z;
     if (z != 0) {
         V += z * bz.a;
         p1 += z * bz.b;
-        c += z * cstr;
         x += z * bz.c;
         out += z * bz.d;
         st += z;
@@ -578,19 +577,15 @@ __global__ __launch_bounds__(kSmThreads) void k_cgs_small(const double* __restri
             tr[k * kFuLd] = a.x;
             tr[k * kFuLd + 1] = a.y;
         }
-    } else if (RED) {
+    } else {
         coef_group_sum(p1, nb1, m, t - kBlock, &part[0][0]);
-    } else if (t - kBlock < m) {
-        cs[t - kBlock] = c[t - kBlock];
     }
     arrived(xr);
     arrived(stop);
     if (stop) return;  // uniform over the grid
     __syncthreads();
-    if (RED) {
-        if (t < m) cs[t] = coef_of_groups(&part[0][0], m, t);
-        __syncthreads();
-    }
+    if (t < m) cs[t] = coef_of_groups(&part[0][0], m, t);
+    __syncthreads();
     double s0 = 0.0, s1 = 0.0;
     for (int k = t / kFuPairs; k < m; k += kSmGroups) {
         const double ck = cs[k];
@@ -719,12 +714,15 @@ int fused_cgs_blocks(int64_t n) { return (int)((n + kFuRows - 1) / kFuRows); }
 // The small form (k_cgs_small) up to kCgsSmallBlocks row blocks whose second
 // projection leaves at most kCgsSmallParts partials (32 loads a thread to sum
 // them).  The rule looks at n and m only, so a run's sums do not depend on the
-// runs beside it; summing in the consumer or by k_coef gives the same bits.
+// runs beside it; that is also why the line lies at 64 blocks: with 160 blocks runs alone of 2 100,
+// 3 000, 4 000 and 5 000 nodes (48 steps) gain 0.7, 0.6, 1.3 and 1.5 %, groups of 16 runs of 3 000, 4 000
+// and 5 000 lose 3.6, 1.4 and 8 %.
 constexpr int64_t kCgsSmallParts = 8192, kCgsSmallBlocks = 64;
 // A consumer's workgroups sum the partials themselves while one round of them
-// fits the GPU; with 16 runs of 20 000 nodes (10 300 workgroups) that took 39.5 us
+// fits the GPU (k_coef gives the same bits); with 16 runs of 20 000 nodes (10 300 workgroups) that took 39.5 us
 // against 26.4 + 5.1.  More than kCoefParts partials go through k_gemvt_reduce.
 constexpr int64_t kCoefParts = 8192, kCoefGrid = 1024;
+static_assert(kCgsSmallBlocks * kBlkRhs <= kCoefGrid, "every group of the small form sums them itself");
 
 bool cgs_small(int64_t n, int32_t m) {
     const int64_t nbf = fused_cgs_blocks(n);
@@ -755,15 +753,8 @@ int launch_cgs2(const double* V, int64_t ldn, int64_t n, int32_t m, double* x, d
     if (cgs_small(n, m)) {
         const dim3 grid((unsigned)nbf, 1, (unsigned)nz);
         const Bz b1{b.V, b.part, b.x, b.part}, b2{b.V, b.part, b.x, b.npart};
-        if (few) {
-            k_cgs_small<false, true><<<grid, kSmThreads, lds, s>>>(V, part, st, x, n, ldn, m, nbg, part2, c, b.c, b1);
-            k_cgs_small<true, true><<<grid, kSmThreads, lds, s>>>(V, part2, st, x, n, ldn, m, nbf, npart, c, b.c, b2);
-        } else {
-            coef(part, nbg);
-            k_cgs_small<false, false><<<grid, kSmThreads, lds, s>>>(V, part, st, x, n, ldn, m, nbg, part2, c, b.c, b1);
-            coef(part2, nbf);
-            k_cgs_small<true, false><<<grid, kSmThreads, lds, s>>>(V, part2, st, x, n, ldn, m, nbf, npart, c, b.c, b2);
-        }
+        k_cgs_small<false><<<grid, kSmThreads, lds, s>>>(V, part, st, x, n, ldn, m, nbg, part2, b1);
+        k_cgs_small<true><<<grid, kSmThreads, lds, s>>>(V, part2, st, x, n, ldn, m, nbf, npart, b2);
         return nbf;
     }
     auto reduce = [&]() {

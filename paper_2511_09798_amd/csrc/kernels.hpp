@@ -169,7 +169,7 @@ int gemvt_blocks(int64_t n);
 int update_blocks(int64_t n);
 constexpr int kFusedCgsMaxCols = 224;  // columns of the fused update and projection (its LDS tile within 64 KB)
 int fused_cgs_blocks(int64_t n);
-// Batch strides of launch_cgs2's arguments (nz slices).
+// Batch strides of launch_cgs2's arguments (nz slices, at most kBlkRhs).
 struct CgsStrides {
     int64_t V = 0, x = 0, part = 0, c = 0, npart = 0;
 };
