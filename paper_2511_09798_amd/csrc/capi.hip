@@ -233,7 +233,7 @@ struct mqh_problem {
     // the single-vector FP32 products over unordered node pairs: work items,
     // their tables, and the row / column partials of a product
     SymLayout sym{};
-    int4* sym_items = nullptr;
+    PairItem* sym_items = nullptr;
     int32_t* sym_first = nullptr;
     double* sym_row = nullptr;
     double* sym_col = nullptr;
@@ -438,65 +438,6 @@ int scale_rhs(mqh_problem* p, double* x, int nz, int64_t stride) {
     launch_scale(x, p->n_int, p->d_int, nz, stride, p->stream);
     LAUNCHCHK("row scaling of the data");
     return MQH_OK;
-}
-
-// Blocks of column partials of a pair product: one per block and super-row up
-// to its own.
-int64_t sym_col_blocks(const SymLayout& L) {
-    const int64_t k = L.nb / L.F;  // whole super-rows before the last, partial one
-    return (int64_t)L.F * (k * (k + 1) / 2) + (L.nb - k * L.F) * (k + 1);
-}
-
-// Work items of the pair products (SymLayout): blocks of blk sorted nodes per
-// class; super-rows of F fixed blocks and segments of Lb loop blocks; first[k]
-// indexes the items in (super-row, segment) order, the list itself is in
-// launch order.  A larger item writes fewer partials and sets up fewer fixed
-// blocks; too few items leave a round of resident workgroups nearly empty.
-// FP32 form: the largest shape with 1200 items (its FP32 sums follow the shape).
-// FP64 form (768 workgroups of 128-node blocks resident): the largest shape with
-// 3000 items; below that 1 x 2 blocks of 128 nodes, and with fewer of those
-// than CUs blocks of 64.  Whole products, us: 20 000 nodes 174 with (1, 4), 178
-// (2, 4), 230 (4, 8), 462 (8, 14); 70 000 nodes 1645 (4, 8), 1659 (1, 4), 1769
-// (8, 14); 1 800 nodes 32 with blocks of 64, 37 with 128.
-void sym_tables(int64_t n, int64_t n_int, bool fp64, SymLayout& L, std::vector<int4>& items,
-                std::vector<int32_t>& first) {
-    struct Shape {
-        int blk, F, Lb, want;
-    };
-    static const Shape shapes32[] = {{128, 8, 14, 1200}, {128, 4, 8, 1200}, {128, 2, 4, 1200}, {128, 1, 2, 0}};
-    static const Shape shapes64[] = {{128, 8, 14, 3000}, {128, 4, 8, 3000}, {128, 2, 8, 3000}, {128, 2, 4, 3000},
-                                     {128, 1, 4, 3000},  {128, 1, 2, 256},  {64, 1, 2, 0}};
-    for (const Shape* sh = fp64 ? shapes64 : shapes32;; ++sh) {
-        L = SymLayout{};
-        L.n = n;
-        L.n_int = n_int;
-        L.blk = sh->blk;
-        L.F = sh->F;
-        L.Lb = sh->Lb;
-        L.nb_int = (int32_t)((n_int + L.blk - 1) / L.blk);
-        L.nb = L.nb_int + (int32_t)((n - n_int + L.blk - 1) / L.blk);
-        items.clear();
-        first.clear();
-        L.nsr = (L.nb + L.F - 1) / L.F;
-        for (int k = 0; k < L.nsr; ++k) {
-            first.push_back((int32_t)items.size());
-            const int nseg = (L.nb - k * L.F + L.Lb - 1) / L.Lb;
-            for (int sg = 0; sg < nseg; ++sg) items.push_back(make_int4(k, sg, (int32_t)items.size(), 0));
-        }
-        first.push_back((int32_t)items.size());
-        L.nitems = (int32_t)items.size();
-        if (L.nitems >= sh->want) break;
-    }
-    // launch order: items by their number of block pairs, largest first
-    // (stable), so the last workgroups to start are the short ones
-    auto pairs = [&](const int4& it) {
-        const int b0 = it.x * L.F, b1 = std::min(b0 + L.F, L.nb);
-        const int c0 = b0 + it.y * L.Lb, c1 = std::min(c0 + L.Lb, L.nb);
-        int64_t cnt = 0;
-        for (int b = b0; b < b1; ++b) cnt += std::max(0, c1 - std::max(c0, b));
-        return cnt;
-    };
-    std::stable_sort(items.begin(), items.end(), [&](const int4& a, const int4& b) { return pairs(a) > pairs(b); });
 }
 
 // One product y = op(A) x - shift z on device vectors (x, z of length ldn,
@@ -2023,14 +1964,14 @@ int mqh_problem_create(const double* x_int, int64_t n_int, const double* x_bnd, 
                 return bail(hip_fail(e, "upload of the sorted layout"));
         }
         if ((e = hipStreamSynchronize(p->stream))) return bail(hip_fail(e, "upload of the sorted layout"));
-        std::vector<int4> items;
+        std::vector<PairItem> items;
         std::vector<int32_t> first;
         sym_tables(n, n_int, op_mode == MQH_OP_MATFREE_FP64, p->sym, items, first);
         if ((rc = dalloc(&p->sym_items, items.size())) || (rc = dalloc(&p->sym_first, first.size())) ||
             (rc = dalloc(&p->sym_row, items.size() * (size_t)(p->sym.F * p->sym.blk))) ||
             (rc = dalloc(&p->sym_col, (size_t)sym_col_blocks(p->sym) * (size_t)p->sym.blk)))
             return bail(rc);
-        if ((e = hipMemcpyAsync(p->sym_items, items.data(), items.size() * sizeof(int4), hipMemcpyHostToDevice,
+        if ((e = hipMemcpyAsync(p->sym_items, items.data(), items.size() * sizeof(PairItem), hipMemcpyHostToDevice,
                                 p->stream)) ||
             (e = hipMemcpyAsync(p->sym_first, first.data(), first.size() * sizeof(int32_t), hipMemcpyHostToDevice,
                                 p->stream)) ||

@@ -4,6 +4,7 @@
 #pragma once
 
 #include "common.hpp"
+#include "pair_items.hpp"
 
 namespace mqh {
 
@@ -11,6 +12,7 @@ constexpr int kMaxEll = 1024;   // largest projected problem (Golub-Kahan steps)
 constexpr int kMaxGrid = 4096;  // largest lambda grid
 constexpr int kMfmFt = 2;       // 16-node fixed tiles per wave in the FP32-evaluated products
 constexpr int kMfmFixed = (kBlock / kWave) * kMfmFt * 16;  // fixed nodes per block (128)
+static_assert(kMfmFixed == 128, "the FP32 form's blocks of the pair products' layout");
 constexpr int kMfmChunk = kBlock;  // loop nodes staged in LDS per round (one per thread)
 constexpr int kBlkRhs = 16;        // right-hand sides of a block product (lockstep Golub-Kahan runs)
 constexpr int kMaxSlices = 64;     // largest split of a product's sum over nodes
@@ -39,28 +41,6 @@ struct PackedLayout {
     int32_t nitems, pad;        // work items of a product
     const int4* items;          // nitems work items
     const int32_t* item_first;  // nt + 1 entries: first item of each tile row
-};
-
-// FP32-evaluated products over unordered node pairs (each pair's t and
-// rsqrt once, feeding y_i and y_j): nodes in the sorted order cut into
-// blocks of kMfmFixed per class (interior blocks 0 .. nb_int-1, boundary
-// blocks nb_int .. nb-1).  Work item (k, s): fixed blocks [kF, kF + F) (a
-// super-row) against loop blocks [kF + s Lb, kF + (s+1) Lb) (a segment),
-// only pairs of blocks b <= c (b == c: the block's own square, row sums
-// only).  Each item writes F x blk row partials and the column partials of its
-// loop blocks (for each block one from every super-row up to its own); a
-// node's output adds the row partials of its super-row's items and its block's
-// column partials.
-constexpr int kSymMaxF = 8;    // fixed blocks per super-row (at most)
-constexpr int kSymMaxLb = 14;  // loop blocks per segment (at most; the LDS of four workgroups per CU)
-struct SymLayout {
-    int64_t n, n_int;
-    int32_t nb_int, nb;         // blocks of blk nodes per class, all blocks
-    int32_t blk, pad;           // 128 (FP32 form), 64 or 128 (FP64 form)
-    int32_t F, Lb;              // fixed blocks per super-row (a power of two), loop blocks per segment
-    int32_t nsr, nitems;        // super-rows, work items
-    const int4* items;          // (super-row, segment, place in the partials, 0) in launch order (largest first)
-    const int32_t* item_first;  // nsr + 1 entries: first item of each super-row
 };
 
 // Result of the parameter choice, device-resident.

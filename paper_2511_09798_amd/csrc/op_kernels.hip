@@ -128,15 +128,6 @@ __device__ __forceinline__ void arrived_with_layout(int& item, int& stop, SymLay
                    "+s"(L.Lb));
 }
 
-__device__ __forceinline__ int sym_shift(int F) { return __ffs(F) - 1; }
-
-// Place of block beta's column partials in ColP (in blocks): one from each
-// super-row k <= beta / F, in order of k, block after block.
-__device__ __forceinline__ int64_t sym_col_base(int beta, int F) {
-    const int64_t k = beta >> sym_shift(F);
-    return (int64_t)F * (k * (k + 1) / 2) + (beta - k * F) * (k + 1);
-}
-
 // Sum of a row's 16 lane partials by four neighbouring lanes (part p takes 4p ..
 // 4p + 3), in a fixed order; every lane gets the sum.
 __device__ __forceinline__ double row_sum16(const double* __restrict__ row, int p) {
@@ -247,7 +238,7 @@ __device__ __forceinline__ void mfs_dispatch(bool ri, bool ci, const v4u* lds_b,
 // One work item (blockIdx.x) of the SymLayout.  TRANS: y = A^T x.
 // RowP[item][(fb - kF) kMfmFixed + row], ColP[sym_col_base(c) + k][node].
 template <bool TRANS>
-__global__ __launch_bounds__(kBlock) void k_mfs(const int4* __restrict__ items, const GkbState* __restrict__ st,
+__global__ __launch_bounds__(kBlock) void k_mfs(const PairItem* __restrict__ items, const GkbState* __restrict__ st,
                                                 const float4* __restrict__ XS, const float4* __restrict__ frames,
                                                 double* __restrict__ RowP, double* __restrict__ ColP, SymLayout L,
                                                 EntryConst c) {
@@ -255,7 +246,7 @@ __global__ __launch_bounds__(kBlock) void k_mfs(const int4* __restrict__ items, 
     __shared__ float lds_w[kMfmChunk];
     __shared__ float lds_col[2 * (kBlock / kWave)][kMfmChunk];  // per (wave, lane-group pair)
     __shared__ double colacc[kSymMaxLb * kMfmFixed];
-    int4 item = items[blockIdx.x];  // launch order: the largest items first
+    PairItem item = items[blockIdx.x];  // launch order: the largest items first
     int stop = st != nullptr ? st->stopped : 0;
     arrived_with_layout(item.x, stop, L);
     if (stop) return;
@@ -490,7 +481,7 @@ __device__ __forceinline__ void mfs64_tiles(const double4* __restrict__ lds_p, i
 
 // One work item of the layout, blocks of B = 64 FT nodes.
 template <bool TRANS, int FT>
-__global__ __launch_bounds__(kBlock) void k_mfs64(const int4* __restrict__ items, const GkbState* __restrict__ st,
+__global__ __launch_bounds__(kBlock) void k_mfs64(const PairItem* __restrict__ items, const GkbState* __restrict__ st,
                                                   const double4* __restrict__ XS64, double* __restrict__ RowP,
                                                   double* __restrict__ ColP, SymLayout L, EntryConst c) {
     constexpr int B = 64 * FT;
@@ -498,7 +489,7 @@ __global__ __launch_bounds__(kBlock) void k_mfs64(const int4* __restrict__ items
     __shared__ double lds_col[2 * (kBlock / kWave)][kMfmChunk];  // per (wave, lane-group pair)
     __shared__ double colacc[kSymMaxLb * B];
     double* red = &lds_col[0][0];  // 64 rows x 17 (padded), between chunks (four workgroups fit a CU's LDS)
-    int4 item = items[blockIdx.x];
+    PairItem item = items[blockIdx.x];
     int stop = st != nullptr ? st->stopped : 0;
     arrived_with_layout(item.x, stop, L);
     if (stop) return;

@@ -147,6 +147,21 @@ def test_fp64_pair_product_shapes(mq, n_int, n_bnd):
         assert np.all(np.abs(y - ref) <= 2e-13 * sc)  # 1e-13 for each side
 
 
+@pytest.mark.parametrize("n_int,n_bnd", [(24001, 6005), (33003, 8101), (51000, 9001), (88001, 22013)])
+def test_fp64_pair_product_super_rows(mq, n_int, n_bnd):
+    """The FP64 pair products' shapes with several fixed blocks an item (2 x 4, 2 x 8, 4 x 8 and 8 x 14 blocks of
+    128), the last super-row and segment partial, against the stored products (positive entries: |A||x| = A|x|)."""
+    nodes = I.random_nodes_cube(n_int + n_bnd, 80)
+    x = I.random_vector(n_int + n_bnd, 5)
+    ys = {}
+    for mode in ("stored_fp64", "matfree_fp64"):
+        with mq.Problem(nodes[:n_int], nodes[n_int:], 9.0, 3.0, mode) as pr:
+            say("pair product super-rows", mode, n_int, n_bnd)
+            ys[mode] = [(pr.apply(x, trans=t), pr.apply(np.abs(x), trans=t)) for t in (False, True)]
+    for (y, sc), (ref, _) in zip(ys["matfree_fp64"], ys["stored_fp64"]):
+        assert np.all(np.abs(y - ref) <= 2e-13 * sc)  # 1e-13 for each side
+
+
 @pytest.mark.parametrize("n,ell", [(70, 60), (2047, 140), (2049, 40)])
 def test_reorthogonalisation_forms(mq, orc, n, ell):
     """Runs across the small form's limits (64 blocks of 32 rows, 8192 partials): Golub-Kahan relations and
