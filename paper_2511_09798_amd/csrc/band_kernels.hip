@@ -41,21 +41,11 @@ constexpr int kChaseWaves = kChaseThreads / kWave;
 constexpr int kStageDoubles = 8192;  // reflectors staged per chunk in the replay kernels (64 KiB)
 constexpr int kMmRows = 16;          // output rows per workgroup of k_band_mm
 
-// Sums and maxima over the four lanes of a quad (data-parallel moves, no LDS).
-template <int CTRL>
-__device__ __forceinline__ double quad_move(double v) {
-    const int2 b = __builtin_bit_cast(int2, v);
-    return __builtin_bit_cast(double, make_int2(__builtin_amdgcn_mov_dpp(b.x, CTRL, 0xF, 0xF, true),
-                                                __builtin_amdgcn_mov_dpp(b.y, CTRL, 0xF, 0xF, true)));
-}
-__device__ __forceinline__ double quad_sum(double v) {
-    v += quad_move<0xB1>(v);  // lanes 1 0 3 2
-    v += quad_move<0x4E>(v);  // lanes 2 3 0 1
-    return v;
-}
+// Sums and maxima over the four lanes of a quad.
+__device__ __forceinline__ double quad_sum(double v) { return add_xor<2>(add_xor<1>(v)); }
 __device__ __forceinline__ double quad_max(double v) {
-    v = fmax(v, quad_move<0xB1>(v));
-    return fmax(v, quad_move<0x4E>(v));
+    v = fmax(v, row_move<0xB1>(v));  // lanes 1 0 3 2
+    return fmax(v, row_move<0x4E>(v));  // lanes 2 3 0 1
 }
 
 // The reflector of band.hpp for x_0 .. x_15 (0 past the reflector's length), lane
@@ -64,9 +54,7 @@ __device__ __forceinline__ double quad_max(double v) {
 // largest entry.  NaN data make tau NaN, which the acceptance test
 // downstream rejects.
 __device__ __forceinline__ double quad_reflector(const double (&x)[4], int q, double (&v)[4], double* beta) {
-    const double x0 = __builtin_bit_cast(double, make_int2(
-        __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int2, x[0]).x, 0x00, 0xF, 0xF, true),
-        __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int2, x[0]).y, 0x00, 0xF, 0xF, true)));
+    const double x0 = row_move<0x00>(x[0]);  // the quad's first lane
     double t = fmax(fmax(q == 0 ? 0.0 : fabs(x[0]), fabs(x[1])), fmax(fabs(x[2]), fabs(x[3])));
     const double tmax = quad_max(t);
     if (!(tmax > 0.0)) {

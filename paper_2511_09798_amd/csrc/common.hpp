@@ -181,12 +181,14 @@ struct EntryConst {
     float k2f, e2f, e2x2f, padf;
 };
 
-// 1/sqrt(t) for t >= 1 in FP64: the hardware estimate s (relative error
-// below 2^-24 over t in [1, 1e6], measured) refined by one third-order step.
-// With r = 1 - t s^2, 1/sqrt(t) = s (1 - r)^(-1/2) = s (1 + r/2 + 3 r^2/8 +
-// 5 r^3/16 + ...); the dropped terms are below 2^-70 relative, so the result
-// is within the final rounding (measured: the same largest error, 0.62 ulp,
-// as two Newton steps, in five instructions instead of eight).
+// 1/sqrt(t) for finite t > 0 in FP64 (the entries take t >= 1, the block QR's pivots and
+// the band's reflectors any scale): the hardware estimate s refined by one
+// third-order step.  With r = 1 - t s^2, 1/sqrt(t) = s (1 - r)^(-1/2) = s (1 + r/2 +
+// 3 r^2/8 + 5 r^3/16 + ...); the dropped terms are below 2^-70 relative, so what is left
+// is the final rounding and half of h's.  Measured over 4 million values in each of eight
+// ranges from 2^-1060 to 2^1022: the estimate within 2^-24.1 of 1/sqrt(t), the
+// result within 0.63 eps (1.00 ulp) in all of them, as two Newton steps, in five
+// instructions instead of eight.
 __device__ __forceinline__ double rsqrt_f64(double t) {
     const double s = __builtin_amdgcn_rsq(t);
     const double h = t * s;

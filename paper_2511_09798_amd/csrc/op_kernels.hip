@@ -1059,9 +1059,10 @@ __global__ __launch_bounds__(kBlock) void k_gen_rows(const typename NodeOf<R>::t
 // coefficients are scalar loads.  The kEvalWaves slices of a workgroup are added in
 // LDS in wave order, the workgroups' sums by k_eval_reduce.  Bound by the FP64 units:
 // six operations for the squared distance, the estimate of the root, five to
-// refine it and one for the sum, about 80 cycles a wave: 610 us for 20 000 points and
-// 60 000 centres, 598 measured for the call (842 with slices of a workgroup's
-// width, six refining operations and 256 partial sums a point).
+// refine it and one for the sum, by their measured issue times (5.2 cycles, 17 for the
+// estimate) 79 cycles a term and wave, 605 us at 2.4 GHz for 20 000 points and 60 000
+// centres; the call takes 598 (842 with slices of a workgroup's width, six
+// refining operations and 256 partial sums a point).
 // ---------------------------------------------------------------------------
 
 // Points as records (centred, times eps); a point that is not finite leaves the
