@@ -118,7 +118,7 @@ __global__ __launch_bounds__(kSvdThreads) void k_bidiag_svd(const double* __rest
 // ---------------------------------------------------------------------------
 
 // The sums over the spectrum are taken by groups of lanes over values staged in
-// LDS, one reciprocal a term (two divisions of global operands before).
+// LDS, one reciprocal a term (filter.hpp; two divisions of global operands before).
 constexpr int kParThreads = 1024;
 static_assert(kMaxEll <= kParThreads, "one singular value per thread in the sums over the workgroup");
 constexpr int kParLanes = 4;  // lanes per point of the grid: 256 points (the default grid has 200) in one pass
@@ -183,7 +183,8 @@ __device__ inline void par_block_sum2(double& a, double& b, int nw, double (*buf
 }
 
 // One workgroup per problem; bound by the J l terms of the grid on one compute
-// unit: 29 us for 200 points at l = 300 (73 with a thread per point).
+// unit: 34 us for 200 points of the L-curve at l = 300 (73 with a thread per point and
+// two divisions a term; 29 with factors that round twice).
 __global__ __launch_bounds__(kParThreads) void k_param_choice(const double* __restrict__ sv,
                                                                const double* __restrict__ ft, int32_t l_arg,
                                                                const int32_t* __restrict__ l_ptr, int32_t method,
