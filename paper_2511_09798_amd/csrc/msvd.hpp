@@ -466,13 +466,14 @@ MQH_HD inline double resid_row(double d, double x, double e, double y, double s,
 }
 
 // Multisection points: P points strictly inside (lo, hi), equally spaced in
-// log2 while the bracket spans more than a factor of two (from
-// max(lo, hi 2^-350); a value below that is looked for from the next round's hi
-// on), equally spaced otherwise.
+// log2 while the bracket spans more than a factor of two (from max(lo, hi 2^-350) and
+// the smallest normal number on; a value below hi 2^-350 is looked for from the next
+// round's hi on), equally spaced otherwise.
 MQH_HD inline double section_point(double lo, double hi, int t, int P) {
     const double f = (double)(t + 1) / (double)(P + 1);
     if (lo == 0.0 || hi > 2.0 * lo) {
-        const double a = log2(lo > hi * 0x1p-350 ? lo : hi * 0x1p-350);
+        const double low = hi * 0x1p-350 > 0x1p-1022 ? hi * 0x1p-350 : 0x1p-1022;
+        const double a = log2(lo > low ? lo : low);
         const double b = log2(hi);
         return exp2(a + (b - a) * f);
     }

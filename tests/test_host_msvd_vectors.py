@@ -105,6 +105,16 @@ def test_triples(lib, kind, l):
             assert (v @ Vt[j]) * (u @ U[:, j]) > 0  # u and v of one triple
 
 
+@pytest.mark.parametrize("decades", [60, 100, 107, 120, 140])
+def test_values_far_below_the_largest(lib, decades):
+    """A value many decades under the others is bracketed: of diag(1, 0.7, 10^-decades) with off-diagonal entries
+    that leave it alone, to high relative accuracy (its square down to 1e-280 of theirs)."""
+    d, e = np.array([1.0, 0.7, 10.0 ** -decades]), np.array([0.3, 10.0 ** (-2 * decades), 0.0])
+    v, u, sg = np.zeros(3), np.zeros(3), np.zeros(1)
+    lib.triple_host(_p(d), _p(e), 3, 2, 256, _p(v), _p(u), _p(sg))
+    assert abs(sg[0] / d[2] - 1.0) <= 8 * EPS
+
+
 @pytest.mark.parametrize("l", LENGTHS + [300])
 @pytest.mark.parametrize("ratio", [0.01, 0.6, 1.0])
 def test_maps_of_the_rotations(lib, l, ratio):
