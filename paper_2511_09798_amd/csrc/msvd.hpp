@@ -15,7 +15,7 @@
 //  * negcount: the number of negative pivots of the factorisation of L D L^T - x I
 //    is the number of eigenvalues below x (Sylvester's law of inertia),
 //    which drives the bisection of the values;
-//  * chain_operands, pair_chain: the top-down (L+ D+ L+^T) and bottom-up
+//  * chain_operands, chain_pairs: the top-down (L+ D+ L+^T) and bottom-up
 //    (U- D- U-^T) factorisations of L D L^T - lambda I at an eigenvalue
 //    lambda, D+_i = s_i + d_i^2, L+_i = d_i e_i / D+_i, s_{i+1} = e_i^2 s_i /
 //    D+_i - lambda from s_0 = -lambda, and D-_{i+1} = e_i^2 + p_{i+1}, U-_i =
@@ -287,9 +287,18 @@ MQH_HD inline double pair_quotient(double a, double b) { return a / pair_pivot(b
 // The pairs of a transform, in place: uv holds (u_k, v_k), k < n - 1, and receives
 // (a_k, c_k), s_k = a_k / c_k, k < n.  The top-down (stationary) transform has
 // (u, v) = (d^2, e^2) from the top and w0 = 0; the bottom-up one (e^2, d^2) from
-// the bottom and w0 = d_{n-1}^2 (then s_k is p_{n-1-k}).
-MQH_HD inline void pair_chain(double* uv, int n, double w0, double lam) {
+// the bottom and w0 = d_{n-1}^2 (then s_k is p_{n-1-k}).  False where the pairs may
+// not tell: one of them vanished (a zero pivot at a zero off-diagonal entry leaves
+// (0, 0), and nothing follows from it) or fell by 2^-400 over four steps (an end of
+// the chain may then lose range: over the six steps between two scales it falls by at
+// most 2^-800), or lam is below kChainFloor, so that what a quotient loses
+// under 2^-222 could tell beside it.  quotient_chain then takes the chain's place.
+constexpr double kChainFloor = 0x1p-170;
+constexpr uint32_t kChainMin = (1023u - 400u) << 20;
+
+MQH_HD inline bool pair_chain(double* uv, int n, double w0, double lam) {
     double w = w0, c = 1.0;
+    uint32_t lo = kPairMax, hi = kPairMin;
     double u[kRescale], v[kRescale];
     const int full = (n - 1) / kRescale * kRescale;
     for (int q = 0; q < kRescale && full > 0; ++q) {
@@ -307,7 +316,12 @@ MQH_HD inline void pair_chain(double* uv, int n, double w0, double lam) {
         for (int q = 0; q < kRescale; ++q) {
             uv[2 * q + 1] = c;
             uv[2 * q] = pair_step(w, c, u[q], v[q], lam);
-            if (q == kRescale / 2 - 1) sc = pair_scale(w, c);
+            if (q == kRescale / 2 - 1) {
+                const uint32_t ex = pair_exponent(w, c);
+                lo = ex < lo ? ex : lo;
+                hi = ex > hi ? ex : hi;
+                sc = scale_of(ex);
+            }
         }
         w *= sc;
         c *= sc;
@@ -325,6 +339,30 @@ MQH_HD inline void pair_chain(double* uv, int n, double w0, double lam) {
     }
     uv[0] = fma(-lam, c, w);
     uv[1] = c;
+    const uint32_t ex = pair_exponent(w, c);
+    lo = ex < lo ? ex : lo;
+    hi = ex > hi ? ex : hi;
+    return lam >= kChainFloor && lo > kChainMin && hi < kPairMax;
+}
+
+// The same by the quotients themselves, stored as (s_k, 1), from op(k, u, v) = (u_k, v_k):
+// s' = v s / D - lam, D = s + u, a zero pivot replaced by a tiny negative one.  Where u
+// is zero the pivot is s itself (the bottom-up transform at a zero off-diagonal entry).
+template <class Operands>
+MQH_HD inline void quotient_chain(double* uv, int n, double w0, double lam, const Operands& op) {
+    double s = w0 - lam;
+    for (int k = 0; k < n; ++k) {
+        uv[2 * k] = s;
+        uv[2 * k + 1] = 1.0;
+        if (k + 1 == n) break;
+        double u, v;
+        op(k, u, v);
+        double dp = s + u;
+        dp = fabs(dp) < 2.2250738585072014e-308 ? -2.2250738585072014e-308 : dp;
+        double t = u == 0.0 ? 1.0 : s / dp;
+        t = t == t ? t : 1.0;
+        s = t * v - lam;
+    }
 }
 
 // d e / D for the pivot D = s + u of the pair (a, b): L+_i of the top-down
@@ -336,26 +374,30 @@ MQH_HD inline double pair_multiplier(double a, double b, double u, double de) {
 
 // The four chains of a singular triple: side 0 is B^T B on (d, e), side 1 B B^T on
 // the reversed sequences, chain c = side + 2 bottom_up at ch + 2 ld c (ld >= l).
-// Operands of step k of every chain, k < l - 1, and a chain's w0.
+// Operands of step k of chain c, k < l - 1, those of every chain, and a chain's w0.
+MQH_HD inline void chain_operand(const double* d, const double* e, int l, int c, int k, double& u, double& v) {
+    const int i = c == 0 || c == 3 ? k : l - 2 - k;  // the chains 1 and 2 run from the end
+    const double di = d[c & 1 ? i + 1 : i], ei = e[i];
+    u = c < 2 ? di * di : ei * ei;
+    v = c < 2 ? ei * ei : di * di;
+}
 MQH_HD inline void chain_operands(const double* d, const double* e, int l, int ld, int k, double* ch) {
-    const double dk = d[k], dk1 = d[k + 1], ek = e[k];
-    const int kr = l - 2 - k;  // e_k is entry kr of the reversed sequence
-    double* c0 = ch + 2 * k;
-    double* c1 = ch + 2 * ld + 2 * kr;
-    double* c2 = ch + 4 * ld + 2 * kr;
-    double* c3 = ch + 6 * ld + 2 * k;
-    c0[0] = dk * dk;
-    c0[1] = ek * ek;
-    c1[0] = dk1 * dk1;
-    c1[1] = ek * ek;
-    c2[0] = ek * ek;
-    c2[1] = dk * dk;
-    c3[0] = ek * ek;
-    c3[1] = dk1 * dk1;
+    for (int c = 0; c < 4; ++c) {
+        double* uv = ch + 2 * ld * c + 2 * k;
+        chain_operand(d, e, l, c, k, uv[0], uv[1]);
+    }
 }
 MQH_HD inline double chain_start(const double* d, int l, int c) {
     const double dn = c == 2 ? d[l - 1] : (c == 3 ? d[0] : 0.0);
     return dn * dn;
+}
+
+// The pairs of chain c in place of its operands.
+MQH_HD inline void chain_pairs(const double* d, const double* e, int l, int ld, int c, double lam, double* ch) {
+    double* uv = ch + 2 * ld * c;
+    const double w0 = chain_start(d, l, c);
+    if (!pair_chain(uv, l, w0, lam))
+        quotient_chain(uv, l, w0, lam, [&](int k, double& u, double& v) { chain_operand(d, e, l, c, k, u, v); });
 }
 
 // |gamma_i| of a side from the pairs of its two chains; the multipliers L+_i and U-_i
@@ -419,7 +461,11 @@ inline void stationary(const double* d, int ds, const double* e, int es, int n, 
         uv[2 * i] = d[i * ds] * d[i * ds];
         uv[2 * i + 1] = e[i * es] * e[i * es];
     }
-    pair_chain(uv.data(), n, 0.0, lam);
+    if (!pair_chain(uv.data(), n, 0.0, lam))
+        quotient_chain(uv.data(), n, 0.0, lam, [&](int k, double& u, double& v) {
+            u = d[k * ds] * d[k * ds];
+            v = e[k * es] * e[k * es];
+        });
     for (int i = 0; i < n; ++i) {
         s[i] = pair_quotient(uv[2 * i], uv[2 * i + 1]);
         if (i + 1 < n) lp[i] = pair_multiplier(uv[2 * i], uv[2 * i + 1], d[i * ds] * d[i * ds], d[i * ds] * e[i * es]);
@@ -433,7 +479,12 @@ inline int progressive_twist(const double* d, int ds, const double* e, int es, i
         uv[2 * k] = e[i * es] * e[i * es];
         uv[2 * k + 1] = d[i * ds] * d[i * ds];
     }
-    pair_chain(uv.data(), n, d[(n - 1) * ds] * d[(n - 1) * ds], lam);
+    const double w0 = d[(n - 1) * ds] * d[(n - 1) * ds];
+    if (!pair_chain(uv.data(), n, w0, lam))
+        quotient_chain(uv.data(), n, w0, lam, [&](int k, double& u, double& v) {
+            u = e[(n - 2 - k) * es] * e[(n - 2 - k) * es];
+            v = d[(n - 2 - k) * ds] * d[(n - 2 - k) * ds];
+        });
     int r = -1;
     for (int i = 0; i < n; ++i) {
         const double* bot = uv.data() + 2 * (n - 1 - i);

@@ -326,7 +326,7 @@ __global__ __launch_bounds__(kWave) void k_msvd_vectors(int32_t L, const int32_t
     __syncthreads();
     for (int k = lane; k + 1 < l; k += kWave) msvd::chain_operands(Ld, Le, l, L, k, Ch);
     __syncthreads();
-    if (lane < 4) msvd::pair_chain(Ch + 2 * L * lane, l, msvd::chain_start(Ld, l, lane), lam);
+    if (lane < 4) msvd::chain_pairs(Ld, Le, l, L, lane, lam, Ch);
     __syncthreads();
     int tw[2];
 #pragma unroll

@@ -75,7 +75,7 @@ extern "C" double triple_host(const double* d, const double* e, int l, int j, in
     s1 = sqrt(value(0));
     const double lam = value(j), sig = sqrt(lam);
     for (int k = 0; k + 1 < l; ++k) chain_operands(D.data(), E.data(), l, l, k, ch.data());
-    for (int c = 0; c < 4; ++c) pair_chain(ch.data() + 2 * l * c, l, chain_start(D.data(), l, c), lam);
+    for (int c = 0; c < 4; ++c) chain_pairs(D.data(), E.data(), l, l, c, lam, ch.data());
     int tw[2];
     for (int side = 0; side < 2; ++side) {
         double best = INFINITY;

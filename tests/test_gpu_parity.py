@@ -516,6 +516,32 @@ def test_gcv_does_not_depend_on_the_scale(mq, k):
     assert abs(c[0]["crit"] - c[1]["crit"]) <= tol * c[0]["crit"]
 
 
+@pytest.mark.parametrize("ell", [2, 9, 30, 65, 300])
+@pytest.mark.parametrize("kind", ["zero_beta", "zero_beta_signed", "one_by_one", "graded30", "rising30"])
+def test_proj_svd_fast_path_accepts(mq, kind, ell):
+    """The fast path alone on C_l with zero beta (B then falls apart; a singular value may be a coefficient
+    itself) and with coefficients over 30 decades: accepted, with the QR iteration's values."""
+    rng = np.random.default_rng(ell)
+    a, b = rng.random(ell) + 0.1, np.concatenate([[2.0], rng.random(ell) + 0.1])
+    if kind.startswith("zero_beta"):
+        b[1:][rng.random(ell) < 0.3] = 0.0
+        a *= rng.choice([-1.0, 1.0], ell) if kind.endswith("signed") else 1.0
+    elif kind == "one_by_one":
+        a, b[1:] = 0.25 * (1 + np.arange(ell)), 0.0
+    else:
+        g = 10.0 ** -np.linspace(0, 30, ell)
+        g = g if kind == "graded30" else g[::-1]
+        a, b[1:] = a * g, b[1:] * g
+    say("fast path accepts", kind, ell)
+    sv, ft, V = mq.mqh_proj_svd(a, b, path="fast")
+    s2, f2, _ = mq.mqh_proj_svd(a, b, path="qr")
+    assert np.max(np.abs(sv / s2 - 1.0)) <= 256 * EPS
+    assert np.max(np.abs(V @ V.T - np.eye(ell))) <= 64 * ell * EPS
+    # a bidiagonal fixes a vector to eps over the relative distance of its value to the next
+    gap = np.minimum(np.abs(np.diff(s2, prepend=np.inf)), np.abs(np.diff(s2, append=-np.inf))) / s2
+    assert np.all(np.abs(np.abs(ft[:-1]) - np.abs(f2[:-1])) <= 64 * ell * EPS * b[0] / np.minimum(gap, 1.0))
+
+
 def _decaying(l, seed):
     # a spectrum like that of a Golub-Kahan run on an ill-posed operator
     rng = np.random.default_rng(seed)

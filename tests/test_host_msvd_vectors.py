@@ -83,6 +83,36 @@ def test_twisted_solve_in_both_directions(lib, n):
             assert np.array_equal(z, ref)
 
 
+def _apart(kind, l, rng):
+    """Bidiagonals with singular values that keep their distance, whose pairs vanish or lose range."""
+    d, e = 0.1 + rng.random(l), 0.1 + rng.random(l)
+    if kind == "decoupled":  # zero off-diagonal entries, 1 x 1 blocks among them
+        e[rng.random(l) < 0.4] = 0.0
+    elif kind == "diagonal":
+        e[:] = 0.0
+    elif kind == "squares":  # pivots that vanish exactly
+        d, e = 0.25 * (1 + np.arange(l)), np.where(np.arange(l) % 3 == 1, 0.25, 0.0)
+    elif kind != "random":
+        g = 10.0 ** -np.linspace(0, int(kind[6:]), l)
+        d, e = (d * g, e * g) if kind.startswith("graded") else (d * g[::-1], e * g[::-1])
+    return d, e
+
+
+@pytest.mark.parametrize("l", [1, 2, 3, 5, 8, 13, 24, 33, 60])
+@pytest.mark.parametrize("kind", ["random", "decoupled", "diagonal", "squares", "graded22", "graded30", "graded60", "rising30"])
+def test_vectors_pass_the_acceptance_test(lib, kind, l):
+    """Residuals and Gram matrices of all vectors within the bounds that the kernels accept: a zero off-diagonal entry
+    behind a vanishing pivot, and entries that fall by tens of decades, do not send a problem to the QR iteration."""
+    for seed in range(4):
+        d, e = _apart(kind, l, np.random.default_rng(100 * l + seed))
+        V, U, res = np.zeros((l, l)), np.zeros((l, l)), 0.0
+        for j in range(l):
+            res = max(res, lib.triple_host(_p(d), _p(e), l, j, 64, _p(V[j]), _p(U[j]), _p(np.zeros(1))))
+        assert res <= 1.0
+        for M in (V, U):
+            assert np.max(np.abs(M @ M.T - np.eye(l))) <= 1e-9
+
+
 @pytest.mark.parametrize("l", LENGTHS)
 @pytest.mark.parametrize("kind", ["random", "graded", "reversed", "large", "small"])
 def test_triples(lib, kind, l):
