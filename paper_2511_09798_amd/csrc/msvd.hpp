@@ -288,17 +288,19 @@ MQH_HD inline double pair_quotient(double a, double b) { return a / pair_pivot(b
 // (a_k, c_k), s_k = a_k / c_k, k < n.  The top-down (stationary) transform has
 // (u, v) = (d^2, e^2) from the top and w0 = 0; the bottom-up one (e^2, d^2) from
 // the bottom and w0 = d_{n-1}^2 (then s_k is p_{n-1-k}).  False where the pairs may
-// not tell: one of them vanished (a zero pivot at a zero off-diagonal entry leaves
-// (0, 0), and nothing follows from it) or fell by 2^-400 over four steps (an end of
-// the chain may then lose range: over the six steps between two scales it falls by at
-// most 2^-800), or lam is below kChainFloor, so that what a quotient loses
-// under 2^-222 could tell beside it.  quotient_chain then takes the chain's place.
+// not tell, and quotient_chain takes the chain's place: one of them vanished (a zero
+// pivot at a zero off-diagonal entry leaves (0, 0), and nothing follows from it) or
+// fell by 2^-400 over four steps (an end of the chain may then lose range: over the six
+// steps between two scales it falls by at most 2^-800); a pivot is zero where
+// the pair is scaled (what stands for it, pair_pivot, is of one scale); or lam is below
+// kChainFloor, so that what a quotient loses under 2^-222 could tell beside it.
 constexpr double kChainFloor = 0x1p-170;
 constexpr uint32_t kChainMin = (1023u - 400u) << 20;
 
 MQH_HD inline bool pair_chain(double* uv, int n, double w0, double lam) {
     double w = w0, c = 1.0;
     uint32_t lo = kPairMax, hi = kPairMin;
+    bool zero = false;
     double u[kRescale], v[kRescale];
     const int full = (n - 1) / kRescale * kRescale;
     for (int q = 0; q < kRescale && full > 0; ++q) {
@@ -323,6 +325,7 @@ MQH_HD inline bool pair_chain(double* uv, int n, double w0, double lam) {
                 sc = scale_of(ex);
             }
         }
+        zero = zero || c == 0.0;
         w *= sc;
         c *= sc;
         uv += 2 * kRescale;
@@ -342,12 +345,13 @@ MQH_HD inline bool pair_chain(double* uv, int n, double w0, double lam) {
     const uint32_t ex = pair_exponent(w, c);
     lo = ex < lo ? ex : lo;
     hi = ex > hi ? ex : hi;
-    return lam >= kChainFloor && lo > kChainMin && hi < kPairMax;
+    return lam >= kChainFloor && lo > kChainMin && hi < kPairMax && !zero;
 }
 
-// The same by the quotients themselves, stored as (s_k, 1), from op(k, u, v) = (u_k, v_k):
-// s' = v s / D - lam, D = s + u, a zero pivot replaced by a tiny negative one.  Where u
-// is zero the pivot is s itself (the bottom-up transform at a zero off-diagonal entry).
+// The same by the quotients themselves, from op(k, u, v) = (u_k, v_k): uv receives (s_k,
+// D_k), D = s + u, s' = v s / D - lam, a pivot below the normal numbers replaced by a
+// tiny negative one.  Where u is zero the pivot is s itself (the bottom-up transform
+// at a zero off-diagonal entry).
 template <class Operands>
 MQH_HD inline void quotient_chain(double* uv, int n, double w0, double lam, const Operands& op) {
     double s = w0 - lam;
@@ -358,18 +362,24 @@ MQH_HD inline void quotient_chain(double* uv, int n, double w0, double lam, cons
         double u, v;
         op(k, u, v);
         double dp = s + u;
-        dp = fabs(dp) < 2.2250738585072014e-308 ? -2.2250738585072014e-308 : dp;
+        dp = fabs(dp) < 0x1p-1022 ? -0x1p-1022 : dp;
+        uv[2 * k + 1] = dp;
         double t = u == 0.0 ? 1.0 : s / dp;
         t = t == t ? t : 1.0;
         s = t * v - lam;
     }
 }
 
-// d e / D for the pivot D = s + u of the pair (a, b): L+_i of the top-down
-// transform (u = d^2) and U-_i of the bottom-up one (u = e^2).
+// s_k of an entry of a chain, and d e / D for its pivot D = s + u: L+_i of the top-down
+// transform (u = d^2) and U-_i of the bottom-up one (u = e^2).  quot: the entry is
+// quotient_chain's.
+MQH_HD inline double chain_s(const double* x, bool quot) { return quot ? x[0] : pair_quotient(x[0], x[1]); }
 MQH_HD inline double pair_multiplier(double a, double b, double u, double de) {
     const double c = pair_pivot(b);
     return de * c / pair_pivot(fma(u, c, a));
+}
+MQH_HD inline double chain_multiplier(const double* x, bool quot, double u, double de) {
+    return quot ? de / x[1] : pair_multiplier(x[0], x[1], u, de);
 }
 
 // The four chains of a singular triple: side 0 is B^T B on (d, e), side 1 B B^T on
@@ -392,27 +402,29 @@ MQH_HD inline double chain_start(const double* d, int l, int c) {
     return dn * dn;
 }
 
-// The pairs of chain c in place of its operands.
-MQH_HD inline void chain_pairs(const double* d, const double* e, int l, int ld, int c, double lam, double* ch) {
+// The pairs of chain c in place of its operands; true: its quotients.
+MQH_HD inline bool chain_pairs(const double* d, const double* e, int l, int ld, int c, double lam, double* ch) {
     double* uv = ch + 2 * ld * c;
     const double w0 = chain_start(d, l, c);
-    if (!pair_chain(uv, l, w0, lam))
-        quotient_chain(uv, l, w0, lam, [&](int k, double& u, double& v) { chain_operand(d, e, l, c, k, u, v); });
+    if (pair_chain(uv, l, w0, lam)) return false;
+    quotient_chain(uv, l, w0, lam, [&](int k, double& u, double& v) { chain_operand(d, e, l, c, k, u, v); });
+    return true;
 }
 
-// |gamma_i| of a side from the pairs of its two chains; the multipliers L+_i and U-_i
-// (i < l - 1) take the place of the top-down pair.
+// |gamma_i| of a side from its two chains (bit c of quot: chain c holds quotients); the
+// multipliers L+_i and U-_i (i < l - 1) take the place of the top-down entry.
 MQH_HD inline double twist_step(const double* d, const double* e, int l, int ld, int side, int i, double lam,
-                                double* ch) {
+                                unsigned quot, double* ch) {
+    const bool qt = quot >> side & 1u, qb = quot >> (side + 2) & 1u;
     const double di = side ? d[l - 1 - i] : d[i];
     const double ei = i + 1 < l ? (side ? e[l - 2 - i] : e[i]) : 0.0;
     double* top = ch + 2 * ld * side + 2 * i;
     const double* bot = ch + 2 * ld * (side + 2) + 2 * (l - 1 - i);
-    const double a = top[0], b = top[1];
-    const double g = fabs(pair_quotient(a, b) + pair_quotient(bot[0], bot[1]) + lam);
+    const double g = fabs(chain_s(top, qt) + chain_s(bot, qb) + lam);
     if (i + 1 < l) {
-        top[0] = pair_multiplier(a, b, di * di, di * ei);
-        top[1] = pair_multiplier(bot[-2], bot[-1], ei * ei, di * ei);
+        const double lp = chain_multiplier(top, qt, di * di, di * ei);
+        top[1] = chain_multiplier(bot - 2, qb, ei * ei, di * ei);
+        top[0] = lp;
     }
     return g;
 }
@@ -454,46 +466,42 @@ MQH_HD inline void twisted_from(const double* mul, int st, int n, int r, int dir
 // programs: s and L+ of the top-down transform; the twist index and its gamma with U-
 // in place of s (su); one direction of the twisted solve, z in place of L+ (z_r is the
 // caller's).
+template <class Operands>
+inline bool host_chain(std::vector<double>& uv, int n, double w0, double lam, const Operands& op) {
+    for (int k = 0; k + 1 < n; ++k) op(k, uv[2 * k], uv[2 * k + 1]);
+    if (pair_chain(uv.data(), n, w0, lam)) return false;
+    quotient_chain(uv.data(), n, w0, lam, op);
+    return true;
+}
 inline void stationary(const double* d, int ds, const double* e, int es, int n, double lam, double, double* lp,
                        double* s) {
     std::vector<double> uv(2 * (size_t)n);
-    for (int i = 0; i + 1 < n; ++i) {
-        uv[2 * i] = d[i * ds] * d[i * ds];
-        uv[2 * i + 1] = e[i * es] * e[i * es];
-    }
-    if (!pair_chain(uv.data(), n, 0.0, lam))
-        quotient_chain(uv.data(), n, 0.0, lam, [&](int k, double& u, double& v) {
-            u = d[k * ds] * d[k * ds];
-            v = e[k * es] * e[k * es];
-        });
+    const bool q = host_chain(uv, n, 0.0, lam, [&](int k, double& u, double& v) {
+        u = d[k * ds] * d[k * ds];
+        v = e[k * es] * e[k * es];
+    });
     for (int i = 0; i < n; ++i) {
-        s[i] = pair_quotient(uv[2 * i], uv[2 * i + 1]);
-        if (i + 1 < n) lp[i] = pair_multiplier(uv[2 * i], uv[2 * i + 1], d[i * ds] * d[i * ds], d[i * ds] * e[i * es]);
+        s[i] = chain_s(&uv[2 * i], q);
+        if (i + 1 < n) lp[i] = chain_multiplier(&uv[2 * i], q, d[i * ds] * d[i * ds], d[i * ds] * e[i * es]);
     }
 }
 inline int progressive_twist(const double* d, int ds, const double* e, int es, int n, double lam, double, double* su,
                              double* gamma_r) {
     std::vector<double> uv(2 * (size_t)n);  // entry k: index n - 1 - k
-    for (int k = 0; k + 1 < n; ++k) {
-        const int i = n - 2 - k;
-        uv[2 * k] = e[i * es] * e[i * es];
-        uv[2 * k + 1] = d[i * ds] * d[i * ds];
-    }
     const double w0 = d[(n - 1) * ds] * d[(n - 1) * ds];
-    if (!pair_chain(uv.data(), n, w0, lam))
-        quotient_chain(uv.data(), n, w0, lam, [&](int k, double& u, double& v) {
-            u = e[(n - 2 - k) * es] * e[(n - 2 - k) * es];
-            v = d[(n - 2 - k) * ds] * d[(n - 2 - k) * ds];
-        });
+    const bool q = host_chain(uv, n, w0, lam, [&](int k, double& u, double& v) {
+        u = e[(n - 2 - k) * es] * e[(n - 2 - k) * es];
+        v = d[(n - 2 - k) * ds] * d[(n - 2 - k) * ds];
+    });
     int r = -1;
     for (int i = 0; i < n; ++i) {
-        const double* bot = uv.data() + 2 * (n - 1 - i);
-        const double g = su[i] + pair_quotient(bot[0], bot[1]) + lam;
+        const double* bot = &uv[2 * (n - 1 - i)];
+        const double g = su[i] + chain_s(bot, q) + lam;
         if (r < 0 || fabs(g) < fabs(*gamma_r)) {
             *gamma_r = g;
             r = i;
         }
-        if (i + 1 < n) su[i] = pair_multiplier(bot[-2], bot[-1], e[i * es] * e[i * es], d[i * ds] * e[i * es]);
+        if (i + 1 < n) su[i] = chain_multiplier(bot - 2, q, e[i * es] * e[i * es], d[i * ds] * e[i * es]);
     }
     return r;
 }

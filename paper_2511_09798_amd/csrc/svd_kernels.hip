@@ -326,7 +326,8 @@ __global__ __launch_bounds__(kWave) void k_msvd_vectors(int32_t L, const int32_t
     __syncthreads();
     for (int k = lane; k + 1 < l; k += kWave) msvd::chain_operands(Ld, Le, l, L, k, Ch);
     __syncthreads();
-    if (lane < 4) msvd::chain_pairs(Ld, Le, l, L, lane, lam, Ch);
+    const bool quot = lane < 4 && msvd::chain_pairs(Ld, Le, l, L, lane, lam, Ch);
+    const unsigned quots = (unsigned)__ballot(quot);
     __syncthreads();
     int tw[2];
 #pragma unroll
@@ -334,7 +335,7 @@ __global__ __launch_bounds__(kWave) void k_msvd_vectors(int32_t L, const int32_t
         double best = INFINITY;
         int r = l - 1;
         for (int i = lane; i < l; i += kWave) {
-            const double g = msvd::twist_step(Ld, Le, l, L, side, i, lam, Ch);
+            const double g = msvd::twist_step(Ld, Le, l, L, side, i, lam, quots, Ch);
             if (g < best) {  // ties to the smaller index
                 best = g;
                 r = i;

@@ -75,13 +75,14 @@ extern "C" double triple_host(const double* d, const double* e, int l, int j, in
     s1 = sqrt(value(0));
     const double lam = value(j), sig = sqrt(lam);
     for (int k = 0; k + 1 < l; ++k) chain_operands(D.data(), E.data(), l, l, k, ch.data());
-    for (int c = 0; c < 4; ++c) chain_pairs(D.data(), E.data(), l, l, c, lam, ch.data());
+    unsigned quot = 0;
+    for (int c = 0; c < 4; ++c) quot |= chain_pairs(D.data(), E.data(), l, l, c, lam, ch.data()) ? 1u << c : 0u;
     int tw[2];
     for (int side = 0; side < 2; ++side) {
         double best = INFINITY;
         tw[side] = l - 1;
         for (int i = 0; i < l; ++i) {
-            const double g = twist_step(D.data(), E.data(), l, l, side, i, lam, ch.data());
+            const double g = twist_step(D.data(), E.data(), l, l, side, i, lam, quot, ch.data());
             if (g < best) {
                 best = g;
                 tw[side] = i;

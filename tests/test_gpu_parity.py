@@ -542,6 +542,19 @@ def test_proj_svd_fast_path_accepts(mq, kind, ell):
     assert np.all(np.abs(np.abs(ft[:-1]) - np.abs(f2[:-1])) <= 64 * ell * EPS * b[0] / np.minimum(gap, 1.0))
 
 
+@pytest.mark.parametrize("ell", [20, 33, 49, 56, 71, 111])
+@pytest.mark.parametrize("flip", [False, True])
+def test_proj_svd_fast_path_accepts_vanishing_pivots(mq, flip, ell):
+    """alpha and beta of ones: the chains of a value meet zero pivots, also where they are scaled.  The fast path alone
+    is accepted, with the values 2 cos(k pi / (2 ell + 2)) that such a bidiagonal has."""
+    sg = np.random.default_rng(ell).choice([-1.0, 1.0], 2 * ell) if flip else np.ones(2 * ell)
+    say("vanishing pivots", ell, flip)
+    sv, ft, V = mq.mqh_proj_svd(sg[:ell], np.concatenate([[2.0], sg[ell:]]), path="fast")
+    want = 2.0 * np.cos(np.arange(1, ell + 1) * np.pi / (2 * ell + 2))
+    assert np.all(np.abs(sv - want) <= 4 * ell * EPS * want[0])
+    assert np.max(np.abs(V @ V.T - np.eye(ell))) <= 1e-9
+
+
 def _decaying(l, seed):
     # a spectrum like that of a Golub-Kahan run on an ill-posed operator
     rng = np.random.default_rng(seed)

@@ -113,6 +113,25 @@ def test_vectors_pass_the_acceptance_test(lib, kind, l):
             assert np.max(np.abs(M @ M.T - np.eye(l))) <= 1e-9
 
 
+@pytest.mark.parametrize("l", [7, 10, 12, 13, 16, 31, 33, 34, 49, 56, 64, 71, 104])
+@pytest.mark.parametrize("kind", ["ones", "ladder", "whole"])
+def test_vectors_where_a_pivot_vanishes(lib, kind, l):
+    """A zero pivot between off-diagonal entries that are not zero, also where the chain is scaled: what stands for it
+    in the pivot and in the quotient after it is one number, and the acceptance test's bounds hold."""
+    i = np.arange(l)
+    d, e = np.ones(l), np.ones(l)
+    if kind == "ladder":  # the triangular factor of the l + 1 by l bidiagonal of ones
+        d, e = np.sqrt((i + 2) / (i + 1)), np.sqrt((i + 1) / (i + 2))
+    elif kind == "whole":
+        d, e = (np.random.default_rng(l).integers(1, 4, (2, l))).astype(float)
+    V, U, res = np.zeros((l, l)), np.zeros((l, l)), 0.0
+    for j in range(l):
+        res = max(res, lib.triple_host(_p(d), _p(e), l, j, 64, _p(V[j]), _p(U[j]), _p(np.zeros(1))))
+    assert res <= 1.0
+    for M in (V, U):
+        assert np.max(np.abs(M @ M.T - np.eye(l))) <= 1e-9
+
+
 @pytest.mark.parametrize("l", LENGTHS)
 @pytest.mark.parametrize("kind", ["random", "graded", "reversed", "large", "small"])
 def test_triples(lib, kind, l):
