@@ -291,7 +291,7 @@ __global__ __launch_bounds__(kBlock) void k_msvd_values(int32_t L, const int32_t
 // 3. Vectors: one wave per (j, problem), for the sides 0 = B^T B on (d, e) and
 // 1 = B B^T on the reversed sequences.  Four lanes run the four chains (a side's
 // top-down and bottom-up transform) at once, each over operands laid out in its
-// order in LDS and overwritten by its pairs; quotients, multipliers and twist
+// order in LDS and overwritten by its pairs (or quotients); quotients, multipliers and twist
 // indices are formed by the whole wave, and four lanes again run the two
 // directions of both twisted solves.  Operands scaled by a power of two
 // (msvd::pair_shift).  Bound by the issue of the chains' instructions by one wave.
